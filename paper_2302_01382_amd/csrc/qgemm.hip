@@ -5,10 +5,9 @@
 // Both operands are K-contiguous, which is exactly what v_mfma_i32_32x32x32_i8 wants: lane l of
 // either operand holds 16 consecutive k-bytes of tile row l%32 (k-half l/32).
 //
-// Two kernels: the fast path (second half of this file; 16-byte aligned operands, K a multiple of
-// 16, or 32 for packed int4) feeds a multi-stage LDS pipeline with direct global->LDS loads; the
-// generic path right below stages tiles through registers with byte-wise loads and handles any
-// K and alignment.  Same arithmetic, same results.
+// Two kernels: the fast path (qgemm_dma.hpp; 16-byte aligned operands, K a multiple of 16, or 32
+// for packed int4) feeds a multi-stage LDS pipeline with direct global->LDS loads; qgemm_any right
+// below stages tiles through registers and handles any K and alignment.  Same arithmetic, same results.
 //
 // Packed int4 weights are expanded on their way to the matrix core: a nibble n becomes the byte
 // n << 4 (= 16 n as int8, sign included), so the accumulator holds 16 * acc exactly and is shifted
@@ -19,132 +18,153 @@ namespace mpq {
 
 __global__ void fill_u32_k(unsigned* p, unsigned v) { p[0] = v; }
 
-constexpr int BM = 128, BN = 128, BK = 64;  // block tile; BK in bytes of k
-constexpr int kGemmThreads = 256;           // 4 waves as 2 x 2, each 64 x 64 = 2 x 2 MFMA tiles
+// =====================================================================================================
+// Any K, any alignment: tiles staged through registers.
+//
+// Rows of a tensor with K % 16 != 0 start at any byte, so a tile cannot travel by global->LDS loads of
+// 16 aligned bytes.  gfx950 takes 16-byte global loads at any byte address, so a thread fetches its
+// chunks with those (load_chunk16), two k tiles ahead of their use in two register sets, and writes
+// them to a double-buffered LDS tile; one barrier per k tile of 128 bytes.  The last chunk of a row
+// is loaded so that it ENDS at the row's end (never past it: the last row may be the end of the
+// allocation) and is shifted into place when it is written to LDS.  Rows shorter than 16 bytes are
+// read byte by byte.
+//
+// What bounds it: the latency of its loads (a workgroup waits a k tile's round trip, hidden by the
+// two register sets and by the other workgroups of the CU).  Against loading every byte by itself (us):
+// 2999 x 1155 x 1021 int8 148 -> 20, 16384 x 1001 x 1000 413 -> 63, 512 x 1001 x 512 102 -> 8.7,
+// 6272 x 2302 x 256 packed int4 279 -> 20 (M x K x N); an aligned 6272 x 2304 x 256 takes 13.5 on the fast path.
+// =====================================================================================================
+constexpr int kAnyThreads = 256;  // 4 waves as 2 x 2
+constexpr int kAnyBK = 128;       // k values per tile
 
-// byte offset of 16-byte chunk `ch` (0..3) of tile row `row` in a [rows][64 B] LDS tile; the XOR makes
+// byte offset of 16-byte chunk `ch` (0..7) of tile row `row` in a [rows][128 B] LDS tile; the XOR makes
 // the 16 lanes served per clock (one chunk column of 16 rows) distinct modulo 256 B (64 banks)
-__device__ __forceinline__ int lds_off(int row, int ch) { return row * BK + ((ch ^ ((row >> 2) & 3)) << 4); }
+__device__ __forceinline__ int lds_off(int row, int ch) { return row * kAnyBK + ((ch ^ ((row >> 1) & 7)) << 4); }
 
-// ---- staging: global -> registers ------------------------------------------------------------
-// A tile (and int8 W tile): 128 rows x 64 B = 512 chunks, two per thread.
-struct Stage8 { v4i c[2]; };
-// packed W tile: 128 rows x 32 B = 256 packed chunks, one per thread (expands to two chunks)
-struct Stage4 { v4i c; };
+// One thread's share of an operand tile: CN chunks of 16 bytes, chunk j of tile row row0 + j * STEP.
+// CPR: chunks per tile row (8, or 4 of a packed-int4 tile, whose 16 bytes are 32 values).
+template <int CN, int CPR>
+struct AnyStage {
+  static constexpr int STEP = kAnyThreads / CPR;
+  const uint8_t* p[CN];  // start of the row
+  int kb;                // byte offset of the thread's chunk within a tile row
+  int row_bytes;
 
-__device__ __forceinline__ Stage8 load8(const int8_t* __restrict__ base, int64_t nrows, int64_t K,
-                                        int64_t row0, int64_t k0) {
-  Stage8 s;
+  __device__ __forceinline__ void init(const void* base, int64_t nrows, int64_t row_bytes_, int64_t r0) {
+    row_bytes = (int)row_bytes_;
+    kb = ((int)threadIdx.x % CPR) * 16;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int cid = threadIdx.x + j * kGemmThreads;
-    const int row = cid >> 2, ch = cid & 3;
-    int64_t r = row0 + row;
-    if (r >= nrows) r = nrows - 1;  // rows past the edge re-read the last row; never stored
-    const int64_t k = k0 + ch * 16;
-    const int8_t* p = base + r * K + k;
-    unsigned w[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int b = 0; b < 16; ++b)
-      if (k + b < K) w[b >> 2] |= (unsigned)(uint8_t)p[b] << (8 * (b & 3));
-    s.c[j] = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+    for (int j = 0; j < CN; ++j) {
+      int64_t r = r0 + (int)threadIdx.x / CPR + j * STEP;
+      if (r >= nrows) r = nrows - 1;  // rows past the edge re-read the last row; never stored
+      p[j] = reinterpret_cast<const uint8_t*>(base) + r * row_bytes_;
+    }
   }
-  return s;
-}
-
-__device__ __forceinline__ void store8(int8_t* lds, const Stage8& s) {
+  // k0: first byte of the tile within the row
+  __device__ __forceinline__ void load(v4i (&c)[CN], int k0) const {
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int cid = threadIdx.x + j * kGemmThreads;
-    *reinterpret_cast<v4i*>(lds + lds_off(cid >> 2, cid & 3)) = s.c[j];
+    for (int j = 0; j < CN; ++j) c[j] = load_chunk16(p[j], row_bytes, k0 + kb);
+  }
+  __device__ __forceinline__ v4i fixed(const v4i& c, int k0) const { return fix_chunk16(c, row_bytes, k0 + kb); }
+  __device__ __forceinline__ bool edge(int k0) const { return k0 + CPR * 16 > row_bytes; }  // workgroup-uniform
+};
+
+template <int CN>
+__device__ __forceinline__ void store8(int8_t* lds, const AnyStage<CN, 8>& st, const v4i (&c)[CN], int k0) {
+  const int row = (int)threadIdx.x >> 3, ch = (int)threadIdx.x & 7;
+  if (st.edge(k0)) {
+#pragma unroll
+    for (int j = 0; j < CN; ++j) *reinterpret_cast<v4i*>(lds + lds_off(row + j * 32, ch)) = st.fixed(c[j], k0);
+  } else {
+#pragma unroll
+    for (int j = 0; j < CN; ++j) *reinterpret_cast<v4i*>(lds + lds_off(row + j * 32, ch)) = c[j];
   }
 }
 
-__device__ __forceinline__ Stage4 load4(const uint8_t* __restrict__ base, int64_t nrows, int64_t K,
-                                        int64_t row0, int64_t k0) {
-  Stage4 s;
-  const int row = threadIdx.x >> 1, half = threadIdx.x & 1;
-  int64_t r = row0 + row;
-  if (r >= nrows) r = nrows - 1;
-  const int64_t k = k0 + half * 32;           // first k of this packed chunk (32 values)
-  const uint8_t* p = base + r * (K >> 1) + (k >> 1);
-  unsigned w[4] = {0, 0, 0, 0};
+template <int CN>
+__device__ __forceinline__ void store4(int8_t* lds, const AnyStage<CN, 4>& st, const v4i (&c)[CN], int k0) {
+  const int row = (int)threadIdx.x >> 2, quarter = (int)threadIdx.x & 3;
 #pragma unroll
-  for (int b = 0; b < 16; ++b)
-    if (k + 2 * b < K) w[b >> 2] |= (unsigned)p[b] << (8 * (b & 3));  // K even: pairs are whole
-  s.c = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-  return s;
+  for (int j = 0; j < CN; ++j) {
+    const v4i v = st.edge(k0) ? st.fixed(c[j], k0) : c[j];
+    unsigned b[8];
+    expand8((unsigned)v.x, b[0], b[1]);
+    expand8((unsigned)v.y, b[2], b[3]);
+    expand8((unsigned)v.z, b[4], b[5]);
+    expand8((unsigned)v.w, b[6], b[7]);
+    const int r = row + j * 64;
+    *reinterpret_cast<v4i*>(lds + lds_off(r, 2 * quarter)) = v4i{(int)b[0], (int)b[1], (int)b[2], (int)b[3]};
+    *reinterpret_cast<v4i*>(lds + lds_off(r, 2 * quarter + 1)) = v4i{(int)b[4], (int)b[5], (int)b[6], (int)b[7]};
+  }
 }
 
-__device__ __forceinline__ void store4(int8_t* lds, const Stage4& s) {
-  const int row = threadIdx.x >> 1, half = threadIdx.x & 1;
-  unsigned b[8];
-  expand8((unsigned)s.c.x, b[0], b[1]);
-  expand8((unsigned)s.c.y, b[2], b[3]);
-  expand8((unsigned)s.c.z, b[4], b[5]);
-  expand8((unsigned)s.c.w, b[6], b[7]);
-  *reinterpret_cast<v4i*>(lds + lds_off(row, 2 * half)) = v4i{(int)b[0], (int)b[1], (int)b[2], (int)b[3]};
-  *reinterpret_cast<v4i*>(lds + lds_off(row, 2 * half + 1)) = v4i{(int)b[4], (int)b[5], (int)b[6], (int)b[7]};
-}
-
-// ---- the kernel ---------------------------------------------------------------------------------
-// grid: x = N tiles (fast index, so neighbouring blocks share the A row panel), y = M tiles.
-template <bool W4>
-__global__ __launch_bounds__(kGemmThreads) void qgemm_k(const int8_t* __restrict__ A,
-                                                        const void* __restrict__ Wv, int64_t M,
-                                                        int64_t N, int64_t K,
-                                                        const float* __restrict__ a_scale,
-                                                        const float* __restrict__ w_scale,
-                                                        int w_per_row, float* __restrict__ Y,
-                                                        int32_t* __restrict__ ACC, EpiArgs epi) {
+// grid: x = N tiles (fast index, so neighbouring workgroups share the A row panel), y = M tiles.
+// TS: side of the output tile (64 or 128); a wave owns (TS / 2) x (TS / 2) of it.
+template <int TS, bool W4>
+__global__ __launch_bounds__(kAnyThreads, TS == 64 ? 4 : 2) void qgemm_any(
+    const int8_t* __restrict__ A, const void* __restrict__ Wv, int64_t M, int64_t N, int64_t K,
+    const float* __restrict__ a_scale, const float* __restrict__ w_scale, int w_per_row, float* __restrict__ Y,
+    int32_t* __restrict__ ACC, EpiArgs epi) {
+  constexpr int F = TS / 64;  // 32 x 32 matrix tiles per wave and side
+  constexpr int CA = TS / 32, CB = W4 ? TS / 64 : TS / 32;
   const float* __restrict__ YREF = epi.yref;
   double* __restrict__ PART = epi.part;
-  __shared__ __attribute__((aligned(16))) int8_t lds_a[BM * BK];
-  __shared__ __attribute__((aligned(16))) int8_t lds_b[BN * BK];
+  __shared__ __attribute__((aligned(16))) int8_t lds_a[2][TS * kAnyBK];
+  __shared__ __attribute__((aligned(16))) int8_t lds_b[2][TS * kAnyBK];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
-  const int8_t* W8 = reinterpret_cast<const int8_t*>(Wv);
-  const uint8_t* W4p = reinterpret_cast<const uint8_t*>(Wv);
+  const int64_t m0 = (int64_t)blockIdx.y * TS, n0 = (int64_t)blockIdx.x * TS;
 
-  v16i acc[2][2];
+  v16i acc[F][F];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < F; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-  Stage8 ra = load8(A, M, K, m0, 0);
-  Stage8 rb8;
-  Stage4 rb4;
-  if (W4) rb4 = load4(W4p, N, K, n0, 0);
-  else rb8 = load8(W8, N, K, n0, 0);
-
-  for (int64_t k0 = 0; k0 < K; k0 += BK) {
-    __syncthreads();  // previous step's LDS reads are done
-    store8(lds_a, ra);
-    if (W4) store4(lds_b, rb4);
-    else store8(lds_b, rb8);
-    __syncthreads();
-    if (k0 + BK < K) {  // prefetch the next tile into registers while this one is multiplied
-      ra = load8(A, M, K, m0, k0 + BK);
-      if (W4) rb4 = load4(W4p, N, K, n0, k0 + BK);
-      else rb8 = load8(W8, N, K, n0, k0 + BK);
-    }
+  AnyStage<CA, 8> sa_;
+  AnyStage<CB, W4 ? 4 : 8> sb_;
+  sa_.init(A, M, K, m0);
+  sb_.init(Wv, N, W4 ? K >> 1 : K, n0);
+  constexpr int BKB = W4 ? kAnyBK / 2 : kAnyBK;  // bytes of k per W tile row in memory
+  v4i ra[2][CA], rb[2][CB];
+  const int KT = (int)((K + kAnyBK - 1) / kAnyBK);
+  sa_.load(ra[0], 0);
+  sb_.load(rb[0], 0);
+  if (KT > 1) {
+    sa_.load(ra[1], kAnyBK);
+    sb_.load(rb[1], BKB);
+  }
+  for (int kt = 0; kt < KT; kt += 2) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int ch = 2 * s + (lane >> 5);
-      v4i fa[2], fb[2];
+    for (int u = 0; u < 2; ++u) {
+      const int t = kt + u;
+      if (t >= KT) break;  // workgroup-uniform
+      // buffer u was last read in step t - 2; every wave has passed the barrier of step t - 1 since
+      store8<CA>(lds_a[u], sa_, ra[u], t * kAnyBK);
+      if constexpr (W4) store4<CB>(lds_b[u], sb_, rb[u], t * BKB);
+      else store8<CB>(lds_b[u], sb_, rb[u], t * BKB);
+      if (t + 2 < KT) {
+        sa_.load(ra[u], (t + 2) * kAnyBK);
+        sb_.load(rb[u], (t + 2) * BKB);
+      }
+      __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const v4i*>(lds_a + lds_off(wm * 64 + i * 32 + (lane & 31), ch));
+      for (int s = 0; s < kAnyBK / 32; ++s) {
+        const int ch = 2 * s + (lane >> 5);
+        v4i fa[F], fb[F];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j] = *reinterpret_cast<const v4i*>(lds_b + lds_off(wn * 64 + j * 32 + (lane & 31), ch));
+        for (int i = 0; i < F; ++i)
+          fa[i] = *reinterpret_cast<const v4i*>(lds_a[u] + lds_off(wm * (TS / 2) + i * 32 + (lane & 31), ch));
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < F; ++j)
+          fb[j] = *reinterpret_cast<const v4i*>(lds_b[u] + lds_off(wn * (TS / 2) + j * 32 + (lane & 31), ch));
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+          for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      }
     }
   }
 
@@ -159,15 +179,15 @@ __global__ __launch_bounds__(kGemmThreads) void qgemm_k(const int8_t* __restrict
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int64_t n = n0 + wn * 64 + j * 32 + (lane & 31);
+  for (int j = 0; j < F; ++j) {
+    const int64_t n = n0 + wn * (TS / 2) + j * 32 + (lane & 31);
     if (n >= N) continue;
     const float sw = want_y ? w_scale[w_per_row ? n : 0] : 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < F; ++i) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t m = m0 + wm * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+        const int64_t m = m0 + wm * (TS / 2) + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         if (m >= M) continue;
         int a = acc[i][j][v];
         if (W4) a >>= 4;  // exact: every product carried the factor 16
@@ -186,7 +206,7 @@ __global__ __launch_bounds__(kGemmThreads) void qgemm_k(const int8_t* __restrict
   if (PART) {  // one partial per workgroup, combined in a fixed order
     const float w = wave_sum(sse);
     __syncthreads();  // the tiles in LDS are not needed any more
-    float* sm = reinterpret_cast<float*>(lds_a);
+    float* sm = reinterpret_cast<float*>(lds_a[0]);
     if (lane == 0) sm[wave] = w;
     __syncthreads();
     if (threadIdx.x == 0)
@@ -296,8 +316,8 @@ static int check_qgemm_args(const int8_t* a_q, const void* w_q, int w_storage_bi
   if (y_out && (reinterpret_cast<uintptr_t>(y_out) & 3u)) return MPQ_ERR_ALIGN;
   if (y_ref && (reinterpret_cast<uintptr_t>(y_ref) & 3u)) return MPQ_ERR_ALIGN;
   if (acc_out && (reinterpret_cast<uintptr_t>(acc_out) & 3u)) return MPQ_ERR_ALIGN;
-  const int64_t gx = (N + BN - 1) / BN, gy = (M + BM - 1) / BM;
-  if (gx > 0x7FFFFFFF || gy > 65535) return MPQ_ERR_SHAPE;           // grid of the generic kernel
+  const int64_t gx = (N + 127) / 128, gy = (M + 127) / 128;
+  if (gx > 0x7FFFFFFF || gy > 65535) return MPQ_ERR_SHAPE;           // grid of qgemm_any's larger tile
   if (((M + 63) / 64) * ((N + 63) / 64) > 0x7FFFFFFF) return MPQ_ERR_SHAPE;  // ... and of the smallest fast tile
   return MPQ_OK;
 }
@@ -316,7 +336,6 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
                      size_t ws_bytes = 0) {
   const int per_row = w_gran == MPQ_PER_ROW;
   const bool w4 = w_storage_bits == 4;
-  const int64_t gx = (N + BN - 1) / BN, gy = (M + BM - 1) / BM;
   if (fast_path(a_q, w_q, w4, M, N, K)) {
     DmaArgs d{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi, n_partials, 1, 0, false};
     const bool plain = !epi.yref && !epi.codes && !epi.act && !epi.amax;
@@ -355,9 +374,22 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
     // leave room for one workgroup per CU only) and k is long enough to have several of them
     return launch_dma_64(w4, K >= 1024 && tiles(64, 64) <= kNumCU, d);
   }
+  // 128 x 128 tiles once they fill the chip twice and k is long enough that the loop and not the output
+  // counts, else 64 x 64.  us, 128 against 64: 4000 x 2000 x 1500 33.0 / 41.0, 16384 x 1000 x 1001 62.6 / 74.3,
+  // but 4000 x 1000 x 1500 (256 tiles of 128) 27.0 / 23.6 and 12288 x 1000 x 200 32.9 / 20.7.
+  const int ts = K >= 512 && ((N + 127) / 128) * ((M + 127) / 128) >= 2 * kNumCU ? 128 : 64;
+  const int64_t gx = (N + ts - 1) / ts, gy = (M + ts - 1) / ts;
   const dim3 grid((unsigned)gx, (unsigned)gy);
-  if (w4) qgemm_k<true><<<grid, kGemmThreads, 0, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, epi);
-  else qgemm_k<false><<<grid, kGemmThreads, 0, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, epi);
+#define MPQ_ANY(TS_, W4_) \
+  qgemm_any<TS_, W4_><<<grid, kAnyThreads, 0, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, epi)
+  if (ts == 128) {
+    if (w4) MPQ_ANY(128, true);
+    else MPQ_ANY(128, false);
+  } else {
+    if (w4) MPQ_ANY(64, true);
+    else MPQ_ANY(64, false);
+  }
+#undef MPQ_ANY
   if (n_partials) *n_partials = gx * gy;
   return launch_status();
 }

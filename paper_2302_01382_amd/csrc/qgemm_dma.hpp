@@ -70,6 +70,44 @@ __device__ __forceinline__ void expand8(unsigned w, unsigned& lo, unsigned& hi) 
   hi = __builtin_amdgcn_perm(o, e, 0x07030602u);
 }
 
+// 16 bytes of a row of `row_bytes` bytes from byte k on, at any address (gfx950 loads 16 bytes from any
+// byte address; written as a copy so that the compiler knows the pointer is not aligned).  A chunk that
+// would pass the row's end is loaded so that it ends there, and fix_chunk16 moves its bytes into place
+// and zeroes the rest; chunks wholly past the end come out as zeros.  Rows shorter than 16 bytes are read
+// byte by byte.  Nothing outside the row is ever read.
+__device__ __forceinline__ v4i load_chunk16(const uint8_t* row, int row_bytes, int k) {
+  v4i v;
+  if (row_bytes >= 16) {  // uniform over the grid
+    const int kk = k <= row_bytes - 16 ? k : row_bytes - 16;
+    __builtin_memcpy(&v, row + kk, 16);
+  } else {
+    unsigned w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+      const unsigned byte = row[k + b < row_bytes ? k + b : row_bytes - 1];
+      w[b >> 2] |= (k + b < row_bytes ? byte : 0u) << (8 * (b & 3));
+    }
+    v = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+  }
+  return v;
+}
+__device__ __forceinline__ v4i fix_chunk16(const v4i& c, int row_bytes, int k) {
+  if (row_bytes < 16) return c;
+  const int s = k + 16 - row_bytes;  // bytes the load was moved back by
+  if (s <= 0) return c;
+  if (s >= 16) return v4i{0, 0, 0, 0};
+  uint64_t lo = (uint64_t)(unsigned)c.x | ((uint64_t)(unsigned)c.y << 32);
+  uint64_t hi = (uint64_t)(unsigned)c.z | ((uint64_t)(unsigned)c.w << 32);
+  if (s >= 8) {
+    lo = hi >> (8 * (s - 8));
+    hi = 0;
+  } else {
+    lo = (lo >> (8 * s)) | (hi << (64 - 8 * s));
+    hi >>= 8 * s;
+  }
+  return v4i{(int)(unsigned)lo, (int)(unsigned)(lo >> 32), (int)(unsigned)hi, (int)(unsigned)(hi >> 32)};
+}
+
 // =====================================================================================================
 // Fast path: multi-stage LDS pipeline fed by direct global->LDS loads (no register staging).
 //
