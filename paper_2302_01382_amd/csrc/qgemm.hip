@@ -235,16 +235,15 @@ __global__ __launch_bounds__(kBlock) void sum_partials_k(const double* __restric
 
 
 // ---- split along k ----------------------------------------------------------------------------------
-// A GEMM with a handful of output tiles and a long k (any layer at inference batch 1: 49 x 4608 x 512
-// is 8 tiles of 64 x 64) leaves most of the chip idle.  With a workspace the caller lets the library
-// cut k into `split` ranges: every (tile, range) pair is a workgroup that writes its raw int32
-// accumulators to a plane of the workspace, and one elementwise kernel adds the planes (integer
-// sums: exact in any order, so the accumulators stay bit-identical to the unsplit product) and
-// applies the epilogue Y = (float(acc) * s_A) * s_W[n].
+// A GEMM with a few dozen output tiles and a long k (512 x 4608 x 512 is 64 tiles of 64 x 64) leaves most of
+// the chip idle.  With a workspace the caller lets the library cut k into `split` ranges: every (tile,
+// range) pair is a workgroup that writes its raw int32 accumulators to a plane of the workspace, and
+// one elementwise kernel adds the planes (integer sums: exact in any order, so the accumulators stay
+// bit-identical to the unsplit product) and applies the epilogue Y = (float(acc) * s_A) * s_W[n].
+// Layers of at most one or two 16 x 16 tiles per CU never come here (qgemm_skinny.hip).
 // Measured on the chip: the second kernel and the planes cost about 5 us, so the split pays only
-// where the unsplit grid is tiny -- 49 x 4608 x 512 takes 13.0 us unsplit and 9.1 us in 12 ranges,
-// whereas 1568 x 4608 x 512 (200 tiles of 64 x 64: 17 us) and 6272 x 2304 x 256 (14.6 us) lose 5-9 us
-// with any split of either tile size, and stay unsplit.
+// where the unsplit grid is tiny; 1568 x 4608 x 512 (200 tiles of 64 x 64: 17 us) and 6272 x 2304 x 256
+// (14.6 us) lose 5-9 us with any split of either tile size, and stay unsplit.
 struct SplitPlan {
   int split = 1;
   int k_per_split = 0;
@@ -336,6 +335,10 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
                      size_t ws_bytes = 0) {
   const int per_row = w_gran == MPQ_PER_ROW;
   const bool w4 = w_storage_bits == 4;
+  // (the score keeps one partial per 64 x 64 tile at most: its workspace holds no more)
+  if (const int waves = epi.yref ? 0 : skinny_waves(M, N, K))
+    return launch_skinny(waves, w4, DmaArgs{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi,
+                                            n_partials, 1, 0, false});
   if (fast_path(a_q, w_q, w4, M, N, K)) {
     DmaArgs d{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi, n_partials, 1, 0, false};
     const bool plain = !epi.yref && !epi.codes && !epi.act && !epi.amax;

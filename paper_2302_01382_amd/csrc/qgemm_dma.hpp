@@ -756,4 +756,9 @@ int launch_dma_192(bool w4, bool three_stages, const DmaArgs& a);
 int launch_dma_128(bool w4, bool three_stages, const DmaArgs& a);
 int launch_dma_64(bool w4, bool long_k, const DmaArgs& a);
 
+// Layers with few output tiles (qgemm_skinny.hip): how many waves split k, 0 where the layer is better
+// off with the tiled kernels.
+int skinny_waves(int64_t M, int64_t N, int64_t K);
+int launch_skinny(int waves, bool w4, const DmaArgs& d);
+
 }  // namespace mpq

@@ -44,3 +44,34 @@ def test_the_128_tile(K, wbits):
     _, acc = mpq.qgemm(dev(a), dev(ws), None, None, wbits, want_y=False, want_acc=True)
     np.testing.assert_array_equal(host(acc)[rows], acc_o)
     np.testing.assert_array_equal(host(acc).astype(np.int64).sum(0), a.astype(np.int64).sum(0) @ w.astype(np.int64).T)
+
+
+# one 16 x 16 tile per CU at most, 4 waves (K < 2048) and 8; two per CU; K around the step of 128, fewer
+# steps than waves, more steps than one round of loads; ragged M and N; any alignment
+@pytest.mark.parametrize("mnk", [(1, 1, 128), (7, 250, 96), (16, 16, 129), (49, 512, 640), (64, 256, 256), (33, 31, 2047),
+                                 (17, 65, 2048), (250, 250, 2050), (5, 100, 8320), (256, 512, 2304), (500, 250, 130)])
+@pytest.mark.parametrize("wbits,by", [(8, 0), (8, 5), (4, 0), (4, 1)])
+def test_layers_of_few_tiles(mnk, wbits, by):
+    import torch
+    M, N, K = mnk
+    K += K & 1 if wbits == 4 else 0
+    a, w = rand_codes((M, K), 127, 74), rand_codes((N, K), 127 if wbits == 8 else 7, 75)
+    ws = w if wbits == 8 else oracle.pack4(w)
+    sa = np.array([0.013], np.float32)
+    sw = (np.random.Generator(np.random.PCG64(76)).random(N).astype(np.float32) + 0.5) * np.float32(1e-2)
+    y_o, acc_o = oracle.qgemm(a, ws, sa, sw, wbits, oracle.PER_ROW)
+    da, dw = misaligned(a, by), misaligned(ws, by)
+    y, acc = mpq.qgemm(da, dw, dev(sa), dev(sw), wbits, mpq.PER_ROW, want_acc=True)
+    np.testing.assert_array_equal(host(acc), acc_o)
+    np.testing.assert_array_equal(host(y), y_o)          # two fp32 products in a fixed order
+    # activation, running maximum and codes in the epilogue
+    r, m = mpq.qgemm_act(da, dw, dev(sa), dev(sw), mpq.ACT_RELU, wbits, mpq.PER_ROW)
+    np.testing.assert_array_equal(host(r), np.maximum(y_o, 0))
+    assert host(m)[0] == np.maximum(y_o, 0).max()
+    codes = mpq.qgemm_act_codes(da, dw, dev(sa), dev(sw), mpq.ACT_RELU, m, 5, wbits, mpq.PER_ROW)
+    _, c_o, _ = oracle.fake_quant(np.maximum(y_o, 0), host(m), 5)
+    np.testing.assert_array_equal(host(codes), c_o)
+    # an output that is only 4-byte aligned takes the scalar stores
+    buf = torch.zeros(M * N + 4, dtype=torch.float32, device="cuda")[1:1 + M * N].view(M, N)
+    mpq.qgemm(da, dw, dev(sa), dev(sw), wbits, mpq.PER_ROW, y=buf)
+    np.testing.assert_array_equal(host(buf), y_o)
