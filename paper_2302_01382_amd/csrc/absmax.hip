@@ -16,23 +16,17 @@ __global__ void fill_u32(unsigned* p, int64_t n, unsigned v) {
   if (i < n) p[i] = v;
 }
 
-// flat tensor: contiguous 16 KiB tiles dealt round-robin when VEC, scalar grid-stride otherwise
+// flat tensor: contiguous 16 KiB tiles dealt round-robin, the last n % 4 elements one by one
 // partials: float [gridDim.x]
-template <bool VEC>
 __global__ __launch_bounds__(kBlock) void absmax_flat(const float* __restrict__ x, int64_t n,
                                                       float* __restrict__ partials) {
-  const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t nthr = (int64_t)gridDim.x * kBlock;
   float m = 0.0f;
-  if (VEC) {
-    const int64_t n4 = n >> 2;
-    for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 a, int64_t) {
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-    });
-    for (int64_t j = (n4 << 2) + tid; j < n; j += nthr) m = fmaxf(m, fabsf(x[j]));
-  } else {
-    for (int64_t j = tid; j < n; j += nthr) m = fmaxf(m, fabsf(x[j]));
-  }
+  const int64_t n4 = n >> 2;
+  for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 a, int64_t) {
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
+  });
+  const int64_t j = (n4 << 2) + threadIdx.x;
+  if (blockIdx.x == 0 && j < n) m = fmaxf(m, fabsf(x[j]));
   m = wave_max(m);
   __shared__ float sm[kBlock / kWave];
   if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = m;
@@ -60,7 +54,7 @@ __global__ __launch_bounds__(kBlock) void absmax_finish(const float* __restrict_
 constexpr int64_t kSeg = 16384;
 
 // DIRECT: one segment per row and no running maximum -> plain store, no clearing pass needed
-template <bool VEC, bool DIRECT>
+template <bool DIRECT>
 __global__ __launch_bounds__(kBlock) void absmax_rows(const float* __restrict__ x, int64_t rows,
                                                       int64_t cols, int64_t nseg,
                                                       unsigned* __restrict__ out) {
@@ -72,25 +66,21 @@ __global__ __launch_bounds__(kBlock) void absmax_rows(const float* __restrict__ 
   const int64_t c1 = (c0 + kSeg < cols) ? c0 + kSeg : cols;
   const float* row = x + r * cols;
   float m = 0.0f;
-  if (VEC) {  // cols % 4 == 0 and x 16-byte aligned: every row start is aligned
-    const float4* r4 = reinterpret_cast<const float4*>(row);
-    int64_t i = (c0 >> 2) + lane;
-    const int64_t end = c1 >> 2;
-    for (; i + 3 * kWave < end; i += 4 * kWave) {  // four loads in flight per lane
-      const float4 a = load_stream(r4 + i), b = load_stream(r4 + i + kWave), c = load_stream(r4 + i + 2 * kWave),
-                   d = load_stream(r4 + i + 3 * kWave);
-      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))),
-                         fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w)))));
-      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(c.x), fabsf(c.y)), fmaxf(fabsf(c.z), fabsf(c.w))),
-                         fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fmaxf(fabsf(d.z), fabsf(d.w)))));
-    }
-    for (; i < end; i += kWave) {
-      const float4 a = load_stream(r4 + i);
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-    }
-  } else {
-    for (int64_t c = c0 + lane; c < c1; c += kWave) m = fmaxf(m, fabsf(row[c]));
+  int64_t i = c0 + 4 * lane;
+  constexpr int64_t kStep = 4 * kWave;  // columns a wave covers per load
+  for (; i + 3 * kStep + 4 <= c1; i += 4 * kStep) {  // four loads in flight per lane
+    const float4 a = load_stream(row + i), b = load_stream(row + i + kStep), c = load_stream(row + i + 2 * kStep),
+                 d = load_stream(row + i + 3 * kStep);
+    m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))),
+                       fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w)))));
+    m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(c.x), fabsf(c.y)), fmaxf(fabsf(c.z), fabsf(c.w))),
+                       fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fmaxf(fabsf(d.z), fabsf(d.w)))));
   }
+  for (; i + 4 <= c1; i += kStep) {
+    const float4 a = load_stream(row + i);
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
+  }
+  if (lane < (int)(c1 & 3)) m = fmaxf(m, fabsf(row[(c1 & ~(int64_t)3) + lane]));  // c0 is a multiple of 4
   m = wave_max(m);
   if (lane == 0) {
     if (DIRECT) out[r] = abs_key(m);
@@ -98,32 +88,47 @@ __global__ __launch_bounds__(kBlock) void absmax_rows(const float* __restrict__ 
   }
 }
 
-// per column: a lane owns 4 adjacent columns (VEC) or one column; waves of a block take
-// interleaved rows; blockIdx.y strides over row chunks.
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void absmax_cols(const float* __restrict__ x, int64_t rows,
-                                                      int64_t cols, unsigned* __restrict__ out) {
+// per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4), the 16 waves of a workgroup
+// take interleaved rows and meet in LDS; blockIdx.y strides over row chunks, which meet in an atomic
+// maximum per column and workgroup.  Those atomics are what bounds a kernel that has one per WAVE and
+// many short row chunks: 12288 x 768 took 65 us with 4-wave workgroups of 64 rows; two of these
+// workgroups per CU and one atomic per column and workgroup: 10.6 (16384 x 64: 82 -> 8.7;
+// 1024 x 4096: 12.2 -> 6.2).
+constexpr int kColWaves = 16;
+__global__ __launch_bounds__(kColWaves * kWave) void absmax_cols(const float* __restrict__ x, int64_t rows,
+                                                                 int64_t cols, unsigned* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
-  const int64_t r_first = (int64_t)blockIdx.y * (kBlock / kWave) + wave;
-  if (VEC) {
-    const int64_t c = ((int64_t)blockIdx.x * kWave + lane) * 4;
-    if (c >= cols) return;
-    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int64_t row_step = (int64_t)gridDim.y * kColWaves;
+  const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
+  const int64_t c = ((int64_t)blockIdx.x * kWave + lane) * 4;
+  float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c + 4 <= cols) {
+#pragma unroll 4
     for (int64_t r = r_first; r < rows; r += row_step) {
-      const float4 a = *reinterpret_cast<const float4*>(x + r * cols + c);
+      const float4 a = load_stream(x + r * cols + c);
       m.x = fmaxf(m.x, fabsf(a.x)); m.y = fmaxf(m.y, fabsf(a.y));
       m.z = fmaxf(m.z, fabsf(a.z)); m.w = fmaxf(m.w, fabsf(a.w));
     }
-    atomicMax(out + c + 0, abs_key(m.x)); atomicMax(out + c + 1, abs_key(m.y));
-    atomicMax(out + c + 2, abs_key(m.z)); atomicMax(out + c + 3, abs_key(m.w));
-  } else {
-    const int64_t c = (int64_t)blockIdx.x * kWave + lane;
-    if (c >= cols) return;
-    float m = 0.0f;
-    for (int64_t r = r_first; r < rows; r += row_step) m = fmaxf(m, fabsf(x[r * cols + c]));
-    atomicMax(out + c, abs_key(m));
+  } else if (c < cols) {
+    const int live = (int)(cols - c);  // 1 .. 3
+#pragma unroll 4
+    for (int64_t r = r_first; r < rows; r += row_step) {
+      const float* p = x + r * cols + c;
+      m.x = fmaxf(m.x, fabsf(p[0]));
+      m.y = fmaxf(m.y, fabsf(p[live > 1 ? 1 : 0]));
+      m.z = fmaxf(m.z, fabsf(p[live > 2 ? 2 : 0]));
+    }
+  }
+  __shared__ float4 sm[kColWaves][kWave];
+  sm[wave][lane] = m;
+  __syncthreads();
+  const int64_t col = (int64_t)blockIdx.x * (kWave * 4) + threadIdx.x;
+  if (threadIdx.x < kWave * 4 && col < cols) {
+    float t = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kColWaves; ++w) t = fmaxf(t, reinterpret_cast<const float*>(sm[w])[threadIdx.x]);
+    atomicMax(out + col, abs_key(t));
   }
 }
 
@@ -140,13 +145,12 @@ __global__ void scale_from_absmax_k(const float* __restrict__ absmax, int64_t co
 
 using namespace mpq;
 
-static unsigned absmax_flat_grid(int64_t n, bool vec) {
-  return vec ? flat_grid(n >> 2, kBlock * kTileVec) : flat_grid(n, kBlock * 4);
-}
+static unsigned absmax_flat_grid(int64_t n) { return flat_grid(n >> 2, kBlock * kTileVec); }
 
 extern "C" size_t mpq_calibrate_absmax_workspace_bytes(int64_t rows, int64_t cols, int gran) {
   if (rows <= 0 || cols <= 0 || mul_overflows(rows, cols) || gran != MPQ_PER_TENSOR) return 0;
-  const unsigned a = absmax_flat_grid(rows * cols, true), b = absmax_flat_grid(rows * cols, false);
+  // (the larger of the grids of 4-element and 1-element work items)
+  const unsigned a = absmax_flat_grid(rows * cols), b = flat_grid(rows * cols, kBlock * 4);
   return (size_t)(a > b ? a : b) * sizeof(float);
 }
 
@@ -166,11 +170,9 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
   const int64_t n = rows * cols;
   const int64_t nseg = (cols + kSeg - 1) / kSeg;
   const bool direct = gran == MPQ_PER_ROW && nseg == 1 && !accumulate;
-  const bool a16 = aligned16(x);
-  const bool vec = a16 && (cols & 3) == 0;
   // grid limits are part of the argument check: nothing is enqueued before they have passed
   const int64_t row_blocks = (rows * nseg + kBlock / kWave - 1) / (kBlock / kWave);
-  const int64_t cols_per_block = vec ? kWave * 4 : kWave;
+  const int64_t cols_per_block = kWave * 4;
   const int64_t col_gx = (cols + cols_per_block - 1) / cols_per_block;
   if (gran == MPQ_PER_ROW && row_blocks > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
   if (gran == MPQ_PER_COL && col_gx > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
@@ -179,28 +181,22 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
     fill_u32<<<(unsigned)((nch + 255) / 256), 256, 0, st>>>(out, nch, 0u);
   }
   if (gran == MPQ_PER_TENSOR) {
-    const unsigned g = absmax_flat_grid(n, a16);
+    const unsigned g = absmax_flat_grid(n);
     float* partials = reinterpret_cast<float*>(ws);
-    if (a16) absmax_flat<true><<<g, kBlock, 0, st>>>(x, n, partials);
-    else absmax_flat<false><<<g, kBlock, 0, st>>>(x, n, partials);
+    absmax_flat<<<g, kBlock, 0, st>>>(x, n, partials);
     absmax_finish<<<1, kBlock, 0, st>>>(partials, (int)g, accumulate, absmax_out);
   } else if (gran == MPQ_PER_ROW) {
     const unsigned g = (unsigned)row_blocks;
-    if (vec && direct) absmax_rows<true, true><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
-    else if (vec) absmax_rows<true, false><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
-    else if (direct) absmax_rows<false, true><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
-    else absmax_rows<false, false><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
+    if (direct) absmax_rows<true><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
+    else absmax_rows<false><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
   } else {
     const int64_t gx = col_gx;
-    // enough row chunks to give the chip ~8 blocks per CU, at least 16 rows per wave
-    int64_t gy = ((int64_t)kNumCU * 8 + gx - 1) / gx;
-    const int64_t max_gy = (rows + 4 * 16 - 1) / (4 * 16);
+    // two workgroups per CU, at least 4 rows per wave
+    int64_t gy = ((int64_t)kNumCU * 2 + gx - 1) / gx;
+    const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
     if (gy > max_gy) gy = max_gy;
-    if (gy < 1) gy = 1;
-    if (gy > 65535) gy = 65535;
     dim3 grid((unsigned)gx, (unsigned)gy);
-    if (vec) absmax_cols<true><<<grid, kBlock, 0, st>>>(x, rows, cols, out);
-    else absmax_cols<false><<<grid, kBlock, 0, st>>>(x, rows, cols, out);
+    absmax_cols<<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, out);
   }
   return launch_status();
 }

@@ -149,10 +149,22 @@ __device__ __forceinline__ float code_f(float x, float inv, float qmax) {
 // and 5.7 TB/s without, the error sweep 5.8-6.0 against 5.2-5.4.  The address-space cast also tells
 // the compiler that the pointer is a global one where it cannot see that (pointers read from a
 // table in memory would otherwise become flat loads).
+// The pointer need only be 4-byte aligned: gfx950 loads and stores 16 bytes at any byte address, and the
+// vector types below say so to the compiler, so a tensor with an odd number of columns, or a view into
+// one, takes the same 16-byte accesses as an aligned one.
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ float4 load_stream(const float4* p) {
-  typedef float v4f __attribute__((ext_vector_type(4)));
-  const v4f v = __builtin_nontemporal_load((const __attribute__((address_space(1))) v4f*)p);
+  const f4_any v = __builtin_nontemporal_load((const __attribute__((address_space(1))) f4_any*)p);
   return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 load_stream(const float* p) { return load_stream(reinterpret_cast<const float4*>(p)); }
+// plain (cached) 16-byte accesses at 4-byte alignment
+__device__ __forceinline__ float4 load4(const float* p) {
+  const f4_any v = *reinterpret_cast<const f4_any*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store4(float* p, const float4& v) {
+  *reinterpret_cast<f4_any*>(p) = f4_any{v.x, v.y, v.z, v.w};
 }
 
 // Visits every float4 of x4[0, n4) that the tile round-robin deals to this block: f(value, index).

@@ -40,13 +40,41 @@ __device__ __forceinline__ unsigned pack_nibbles(float t0, float t1, float t2, f
   return a | (b << 4) | (c << 8) | (d << 12);
 }
 
-// one float4 of x with one constant set for all four columns
-__device__ __forceinline__ void emit4(const float4 v, const QConst& c, int64_t i4, float* y,
-                                      int8_t* codes, uint8_t* packed) {
-  const float t0 = magic_t(v.x, c), t1 = magic_t(v.y, c), t2 = magic_t(v.z, c), t3 = magic_t(v.w, c);
-  if (y) reinterpret_cast<float4*>(y)[i4] = make_float4(dequant_t(t0, c), dequant_t(t1, c), dequant_t(t2, c), dequant_t(t3, c));
-  if (codes) reinterpret_cast<unsigned*>(codes)[i4] = pack_bytes(t0, t1, t2, t3);
-  if (packed) reinterpret_cast<unsigned short*>(packed)[i4] = (unsigned short)pack_nibbles(t0, t1, t2, t3);
+// Outputs of four consecutive elements from flat element e on.  Any of the three pointers may lie at any
+// address of its element type: the stores are 16, 4 and 2 bytes wide whatever the alignment (gfx950 stores
+// to any byte address; the vector types say so to the compiler).
+typedef unsigned u32_any __attribute__((aligned(1)));
+typedef unsigned short u16_any __attribute__((aligned(1)));
+
+__device__ __forceinline__ void emit4(const float4 v, const QConst& k0, const QConst& k1, const QConst& k2,
+                                      const QConst& k3, int64_t e, float* y, int8_t* codes, uint8_t* packed) {
+  const float t0 = magic_t(v.x, k0), t1 = magic_t(v.y, k1), t2 = magic_t(v.z, k2), t3 = magic_t(v.w, k3);
+  if (y) store4(y + e, make_float4(dequant_t(t0, k0), dequant_t(t1, k1), dequant_t(t2, k2), dequant_t(t3, k3)));
+  if (codes) *reinterpret_cast<u32_any*>(codes + e) = pack_bytes(t0, t1, t2, t3);
+  if (packed) *reinterpret_cast<u16_any*>(packed + (e >> 1)) = (unsigned short)pack_nibbles(t0, t1, t2, t3);
+}
+// ... with one constant set for all four
+__device__ __forceinline__ void emit4(const float4 v, const QConst& c, int64_t e, float* y, int8_t* codes,
+                                      uint8_t* packed) {
+  emit4(v, c, c, c, c, e, y, codes, packed);
+}
+
+// One to three elements from flat element e on (the end of a tensor or row), one lane; packed: e is a
+// multiple of 4 or of an even row, and there are two of them.  All are read before the first is written.
+__device__ __forceinline__ void emit_tail(const float* x, const QConst& k0, const QConst& k1, const QConst& k2,
+                                          int64_t e, int count, float* y, int8_t* codes, uint8_t* packed) {
+  const float t0 = magic_t(x[e], k0), t1 = magic_t(x[count > 1 ? e + 1 : e], k1), t2 = magic_t(x[count > 2 ? e + 2 : e], k2);
+  if (y) {
+    y[e] = dequant_t(t0, k0);
+    if (count > 1) y[e + 1] = dequant_t(t1, k1);
+    if (count > 2) y[e + 2] = dequant_t(t2, k2);
+  }
+  if (codes) {
+    codes[e] = (int8_t)(bits_from_f(t0) & 0xFF);
+    if (count > 1) codes[e + 1] = (int8_t)(bits_from_f(t1) & 0xFF);
+    if (count > 2) codes[e + 2] = (int8_t)(bits_from_f(t2) & 0xFF);
+  }
+  if (packed) packed[e >> 1] = (uint8_t)(pack_nibbles(t0, t1, 0.0f, 0.0f) & 0xFFu);
 }
 
 // ---- per tensor, flat, 128-bit loads; n4 = n / 4 vectors, tail of n % 4 scalars ------------
@@ -59,22 +87,12 @@ __global__ __launch_bounds__(kBlock) void fq_flat(const float* __restrict__ x, i
   if (step_out && tid == 0) step_out[0] = c.scale;  // the step size the codes dequantize with
   const int64_t n4 = n >> 2;
   for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4,
-                      [&](const float4 v, int64_t i) { emit4(v, c, i, y, codes, packed); });
+                      [&](const float4 v, int64_t i) { emit4(v, c, i << 2, y, codes, packed); });
   // tail: at most 3 elements, pairs stay together (n even whenever packed != null)
-  if (tid == 0) {
-    for (int64_t j = n4 << 2; j < n; ++j) {
-      const float t = magic_t(x[j], c);
-      if (y) y[j] = dequant_t(t, c);
-      if (codes) codes[j] = (int8_t)(bits_from_f(t) & 0xFF);
-      if (packed && !(j & 1)) {
-        const float t1 = magic_t(x[j + 1], c);
-        packed[j >> 1] = (uint8_t)(((unsigned)bits_from_f(t) & 0xFu) | (((unsigned)bits_from_f(t1) & 0xFu) << 4));
-      }
-    }
-  }
+  if (tid == 0 && (n & 3)) emit_tail(x, c, c, c, n4 << 2, (int)(n & 3), y, codes, packed);
 }
 
-// ---- per row: one wave per (row, segment); cols % 4 == 0 -------------------------------------
+// ---- per row: one wave per (row, segment) -------------------------------------
 constexpr int64_t kSeg = 16384;
 
 __global__ __launch_bounds__(kBlock) void fq_rows(const float* __restrict__ x, int64_t rows,
@@ -89,22 +107,24 @@ __global__ __launch_bounds__(kBlock) void fq_rows(const float* __restrict__ x, i
   const int64_t c0 = seg * kSeg;
   const int64_t c1 = (c0 + kSeg < cols) ? c0 + kSeg : cols;
   const QConst c = make_qconst(absmax[r], bits);
-  const int64_t base4 = (r * cols) >> 2;
-  const float4* x4 = reinterpret_cast<const float4*>(x);
-  int64_t i = (c0 >> 2) + lane;
-  const int64_t end = c1 >> 2;
-  for (; i + 3 * kWave < end; i += 4 * kWave) {  // four loads in flight per lane
-    const float4 v0 = load_stream(x4 + base4 + i), v1 = load_stream(x4 + base4 + i + kWave),
-                 v2 = load_stream(x4 + base4 + i + 2 * kWave), v3 = load_stream(x4 + base4 + i + 3 * kWave);
-    emit4(v0, c, base4 + i, y, codes, packed);
-    emit4(v1, c, base4 + i + kWave, y, codes, packed);
-    emit4(v2, c, base4 + i + 2 * kWave, y, codes, packed);
-    emit4(v3, c, base4 + i + 3 * kWave, y, codes, packed);
+  const int64_t base = r * cols;
+  int64_t i = base + c0 + 4 * lane;
+  const int64_t end = base + c1;
+  constexpr int64_t kStep = 4 * kWave;  // columns a wave covers per load
+  for (; i + 3 * kStep + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
+    const float4 v0 = load_stream(x + i), v1 = load_stream(x + i + kStep), v2 = load_stream(x + i + 2 * kStep),
+                 v3 = load_stream(x + i + 3 * kStep);
+    emit4(v0, c, i, y, codes, packed);
+    emit4(v1, c, i + kStep, y, codes, packed);
+    emit4(v2, c, i + 2 * kStep, y, codes, packed);
+    emit4(v3, c, i + 3 * kStep, y, codes, packed);
   }
-  for (; i < end; i += kWave) emit4(load_stream(x4 + base4 + i), c, base4 + i, y, codes, packed);
+  for (; i + 4 <= end; i += kStep) emit4(load_stream(x + i), c, i, y, codes, packed);
+  // the last cols % 4 elements of the row (an even number, starting on an even one, whenever packed != null)
+  if (lane == 0 && (c1 & 3)) emit_tail(x, c, c, c, end - (c1 & 3), (int)(c1 & 3), y, codes, packed);
 }
 
-// ---- per column: a lane owns 4 adjacent columns; cols % 4 == 0 --------------------------------
+// ---- per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4) ----------------
 __global__ __launch_bounds__(kBlock) void fq_cols(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, const float* __restrict__ absmax,
                                                   int bits, float* __restrict__ y,
@@ -114,43 +134,16 @@ __global__ __launch_bounds__(kBlock) void fq_cols(const float* __restrict__ x, i
   const int wave = threadIdx.x / kWave;
   const int64_t c = ((int64_t)blockIdx.x * kWave + lane) * 4;
   if (c >= cols) return;
-  const float4 m = *reinterpret_cast<const float4*>(absmax + c);
-  const QConst k0 = make_qconst(m.x, bits), k1 = make_qconst(m.y, bits), k2 = make_qconst(m.z, bits),
-               k3 = make_qconst(m.w, bits);
+  const int live = c + 4 <= cols ? 4 : (int)(cols - c);
+  const QConst k0 = make_qconst(absmax[c], bits), k1 = make_qconst(absmax[live > 1 ? c + 1 : c], bits),
+               k2 = make_qconst(absmax[live > 2 ? c + 2 : c], bits), k3 = make_qconst(absmax[live > 3 ? c + 3 : c], bits);
   const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
-  for (int64_t r = (int64_t)blockIdx.y * (kBlock / kWave) + wave; r < rows; r += row_step) {
-    const int64_t i4 = (r * cols + c) >> 2;
-    const float4 v = reinterpret_cast<const float4*>(x)[i4];
-    const float t0 = magic_t(v.x, k0), t1 = magic_t(v.y, k1), t2 = magic_t(v.z, k2), t3 = magic_t(v.w, k3);
-    if (y) reinterpret_cast<float4*>(y)[i4] = make_float4(dequant_t(t0, k0), dequant_t(t1, k1), dequant_t(t2, k2), dequant_t(t3, k3));
-    if (codes) reinterpret_cast<unsigned*>(codes)[i4] = pack_bytes(t0, t1, t2, t3);
-    if (packed) reinterpret_cast<unsigned short*>(packed)[i4] = (unsigned short)pack_nibbles(t0, t1, t2, t3);
-  }
-}
-
-// ---- generic: any shape / alignment / granularity; a thread owns one pair of flat elements ----
-__global__ __launch_bounds__(kBlock) void fq_generic(const float* __restrict__ x, int64_t rows,
-                                                     int64_t cols, int gran,
-                                                     const float* __restrict__ absmax, int bits,
-                                                     float* __restrict__ y, int8_t* __restrict__ codes,
-                                                     uint8_t* __restrict__ packed, float* __restrict__ step_out) {
-  const int64_t n = rows * cols;
-  const int64_t npairs = (n + 1) >> 1;
-  if (step_out && blockIdx.x == 0 && threadIdx.x == 0) step_out[0] = make_qconst(absmax[0], bits).scale;  // per tensor only
-  for (int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x; p < npairs; p += (int64_t)gridDim.x * kBlock) {
-    unsigned nib = 0;
-    for (int e = 0; e < 2; ++e) {
-      const int64_t j = 2 * p + e;
-      if (j >= n) break;
-      const int64_t r = j / cols, cc = j - r * cols;
-      const int64_t ch = gran == MPQ_PER_ROW ? r : gran == MPQ_PER_COL ? cc : 0;
-      const QConst c = make_qconst(absmax[ch], bits);
-      const float t = magic_t(x[j], c);
-      if (y) y[j] = dequant_t(t, c);
-      if (codes) codes[j] = (int8_t)(bits_from_f(t) & 0xFF);
-      nib |= ((unsigned)bits_from_f(t) & 0xFu) << (4 * e);
-    }
-    if (packed) packed[p] = (uint8_t)nib;  // cols even: the pair shares a row
+  const int64_t r0 = (int64_t)blockIdx.y * (kBlock / kWave) + wave;
+  if (live == 4) {
+#pragma unroll 4
+    for (int64_t r = r0; r < rows; r += row_step) emit4(load4(x + r * cols + c), k0, k1, k2, k3, r * cols + c, y, codes, packed);
+  } else {
+    for (int64_t r = r0; r < rows; r += row_step) emit_tail(x, k0, k1, k2, r * cols + c, live, y, codes, packed);
   }
 }
 
@@ -168,27 +161,27 @@ int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, cons
   if (packed4_out && (cols & 1)) return MPQ_ERR_SHAPE;
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = rows * cols;
-  const bool vec_ok = aligned16(x) && (!y_out || aligned16(y_out)) &&
-                      (!codes_out || (reinterpret_cast<uintptr_t>(codes_out) & 3u) == 0) &&
-                      (!packed4_out || (reinterpret_cast<uintptr_t>(packed4_out) & 1u) == 0);
-  if (vec_ok && gran == MPQ_PER_TENSOR) {
+  if (gran == MPQ_PER_TENSOR) {
     fq_flat<<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n, absmax, bits, y_out, codes_out, packed4_out, step_out);
-  } else if (vec_ok && gran == MPQ_PER_ROW && (cols & 3) == 0) {
+  } else if (gran == MPQ_PER_ROW) {
     const int64_t nseg = (cols + kSeg - 1) / kSeg;
     const int64_t blocks = (rows * nseg + kBlock / kWave - 1) / (kBlock / kWave);
     if (blocks > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
     fq_rows<<<(unsigned)blocks, kBlock, 0, st>>>(x, rows, cols, nseg, absmax, bits, y_out, codes_out, packed4_out);
-  } else if (vec_ok && gran == MPQ_PER_COL && (cols & 3) == 0 && aligned16(absmax)) {
+  } else {
     const int64_t gx = (cols + kWave * 4 - 1) / (kWave * 4);
     if (gx > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
     int64_t gy = ((int64_t)kNumCU * 8 + gx - 1) / gx;
-    const int64_t max_gy = (rows + 4 * 8 - 1) / (4 * 8);
+    // at least 8 rows per wave, 2 where that would leave CUs without a workgroup
+    int64_t max_gy = (rows + 4 * 8 - 1) / (4 * 8);
+    if (max_gy * gx < kNumCU) {
+      max_gy = (kNumCU + gx - 1) / gx;
+      if (max_gy > (rows + 4 * 2 - 1) / (4 * 2)) max_gy = (rows + 4 * 2 - 1) / (4 * 2);
+    }
     if (gy > max_gy) gy = max_gy;
     if (gy < 1) gy = 1;
     if (gy > 65535) gy = 65535;
     fq_cols<<<dim3((unsigned)gx, (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
-  } else {
-    fq_generic<<<flat_grid((n + 1) >> 1, kBlock * 4), kBlock, 0, st>>>(x, rows, cols, gran, absmax, bits, y_out, codes_out, packed4_out, step_out);
   }
   return launch_status();
 }

@@ -25,21 +25,16 @@ constexpr int64_t kSeg = 16384;  // columns per wave item in the per-row kernels
 
 // ---- per tensor ----------------------------------------------------------------------------
 // partials: double [gridDim.x][NB]
-template <int NB, bool VEC>
+template <int NB>
 __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, int64_t n,
                                                   const float* __restrict__ absmax, int b_lo,
                                                   double* __restrict__ partials) {
   Sweep<NB> s;
   s.init(absmax[0], b_lo);
-  const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t nthr = (int64_t)gridDim.x * kBlock;
-  if (VEC) {
-    const int64_t n4 = n >> 2;
-    for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
-    for (int64_t j = (n4 << 2) + tid; j < n; j += nthr) s.add(x[j]);
-  } else {
-    for (int64_t j = tid; j < n; j += nthr) s.add(x[j]);
-  }
+  const int64_t n4 = n >> 2;
+  for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
+  const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
+  if (blockIdx.x == 0 && j < n) s.add(x[j]);
   __shared__ float sm[kBlock / kWave][NB];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
@@ -81,22 +76,31 @@ __global__ __launch_bounds__(kBlock) void qe_finish_tree(const double* __restric
   if (threadIdx.x < NB) out[threadIdx.x] = sm[0][threadIdx.x];
 }
 
-// partials laid out [np][nch][nb] (per-column kernels) or [nch][np][nb] (per-row kernels)
-__global__ void qe_finish_serial(const double* __restrict__ partials, int64_t nch, int64_t np,
-                                 int nb, int64_t stride_ch, int64_t stride_p,
-                                 double* __restrict__ out) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nch * nb) return;
-  const int64_t ch = k / nb;
-  const int b = (int)(k - ch * nb);
+// out[k] = sum_p partials[k + p * stride] (per-column kernels: planes of nch * nb sums) or, rows cut into
+// segments, with the nb sums of a row's segments next to each other: k / nb * stride_ch + k % nb + p * stride.
+// 64 outputs per workgroup; wave w adds the partials p = w, w + 4, ... and the four meet in a fixed order.
+__global__ __launch_bounds__(kBlock) void qe_finish_planes(const double* __restrict__ partials, int64_t nch, int64_t np,
+                                                           int nb, int64_t stride_ch, int64_t stride_p,
+                                                           double* __restrict__ out) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t k = (int64_t)blockIdx.x * kWave + lane;
+  const bool live = k < nch * nb;
   double a = 0.0;
-  for (int64_t p = 0; p < np; ++p) a += partials[ch * stride_ch + p * stride_p + b];
-  out[k] = a;
+  if (live) {
+    const int64_t ch = k / nb;
+    const double* src = partials + ch * stride_ch + (k - ch * nb);
+#pragma unroll 8
+    for (int64_t p = wave; p < np; p += kBlock / kWave) a += src[p * stride_p];
+  }
+  __shared__ double sm[kBlock / kWave][kWave];
+  sm[wave][lane] = a;
+  __syncthreads();
+  if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
 }
 
 // ---- per row: one wave per (row, segment) ------------------------------------------------------
 // dst: nseg == 1 -> out [rows][NB]; else partials [rows][nseg][NB]; same indexing item*NB
-template <int NB, bool VEC>
+template <int NB>
 __global__ __launch_bounds__(kBlock) void qe_rows(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, int64_t nseg,
                                                   const float* __restrict__ absmax, int b_lo,
@@ -110,19 +114,16 @@ __global__ __launch_bounds__(kBlock) void qe_rows(const float* __restrict__ x, i
   Sweep<NB> s;
   s.init(absmax[r], b_lo);
   const float* row = x + r * cols;
-  if (VEC) {
-    const float4* r4 = reinterpret_cast<const float4*>(row);
-    int64_t i = (c0 >> 2) + lane;
-    const int64_t e4 = c1 >> 2;
-    for (; i + 3 * kWave < e4; i += 4 * kWave) {
-      const float4 a = load_stream(r4 + i), b = load_stream(r4 + i + kWave), c = load_stream(r4 + i + 2 * kWave),
-                   d = load_stream(r4 + i + 3 * kWave);
-      s.add4(a); s.add4(b); s.add4(c); s.add4(d);
-    }
-    for (; i < e4; i += kWave) s.add4(load_stream(r4 + i));
-  } else {
-    for (int64_t c = c0 + lane; c < c1; c += kWave) s.add(row[c]);
+  const float4* r4 = reinterpret_cast<const float4*>(row);  // 4-byte aligned: see load_stream
+  int64_t i = (c0 >> 2) + lane;
+  const int64_t e4 = c1 >> 2;
+  for (; i + 3 * kWave < e4; i += 4 * kWave) {
+    const float4 a = load_stream(r4 + i), b = load_stream(r4 + i + kWave), c = load_stream(r4 + i + 2 * kWave),
+                 d = load_stream(r4 + i + 3 * kWave);
+    s.add4(a); s.add4(b); s.add4(c); s.add4(d);
   }
+  for (; i < e4; i += kWave) s.add4(load_stream(r4 + i));
+  if (lane < (int)(c1 & 3)) s.add(row[(e4 << 2) + lane]);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const float w = wave_sum(s.acc[b]);
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(kBlock) void qe_rows(const float* __restrict__ x, i
 // ---- per row, short rows: LPR lanes per row (16 or 64), 64 / LPR rows per wave ---------------------
 // The 2 NB per-row constants cost a division each; here lane j of a row group computes constant j
 // only and the group shares them through the cross-lane network, and the final sums need 4 DPP
-// steps instead of a full wave reduction.  cols % 4 == 0, x 16-byte aligned, cols <= kSeg.
+// steps instead of a full wave reduction.  cols <= kSeg.
 template <int NB, int LPR>
 __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ x, int64_t rows,
                                                       int64_t cols, const float* __restrict__ absmax,
@@ -170,6 +171,7 @@ __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ 
     s.add4(a); s.add4(b); s.add4(c); s.add4(d);
   }
   for (; i < e4; i += LPR) s.add4(load_stream(r4 + i));
+  if (lr < (int)(cols & 3)) s.add(x[r * cols + (e4 << 2) + lr]);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const float w = LPR == 16 ? row16_sum(s.acc[b]) : wave_sum(s.acc[b]);
@@ -177,68 +179,95 @@ __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ 
   }
 }
 
-// ---- per column: a lane owns CPL adjacent columns; the block's 4 waves take interleaved rows ----
+// ---- per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4); the workgroup's 8
+// waves take interleaved rows and meet in LDS ----
+// Two workgroups per CU, so that there are few partials to fold; 12288 x 768 with the
+// finishing kernel: 117 -> 27 us (16384 x 64: 128 -> 16).
 // partials: double [gridDim.y][cols][NB]
-template <int NB, int CPL>
-__global__ __launch_bounds__(kBlock) void qe_cols(const float* __restrict__ x, int64_t rows,
+constexpr int kColWaves = 8;
+template <int NB>
+__global__ __launch_bounds__(kColWaves * kWave, 4) void qe_cols(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, const float* __restrict__ absmax,
                                                   int b_lo, double* __restrict__ partials) {
+  constexpr int CPL = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int64_t c = ((int64_t)blockIdx.x * kWave + lane) * CPL;
-  const bool live = c < cols;
+  const int live = c + CPL <= cols ? CPL : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
+  // The 2 NB constants of a column cost a division each: the workgroup shares the divisions of its 256
+  // columns through LDS instead of every wave forming those of its four (56 divisions per lane).
+  __shared__ float lds[kColWaves * kWave * (CPL * NB + 1)];
+  constexpr int CST = 2 * NB + 1;  // constants of a column: 2 NB, padded to an odd pitch
+  static_assert(kWave * CPL * CST <= kColWaves * kWave * (CPL * NB + 1), "the constants fit where the sums go");
+  for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
+    const int cl = i / NB, b = i - cl * NB;
+    const int64_t cc = (int64_t)blockIdx.x * (kWave * CPL) + cl;
+    float sc = 0.0f, inv = 0.0f;
+    if (cc < cols) bit_constants(absmax[cc], b_lo + b, sc, inv);
+    lds[cl * CST + b] = inv;
+    lds[cl * CST + NB + b] = sc;
+  }
+  __syncthreads();
   Sweep<NB> s[CPL];
 #pragma unroll
-  for (int k = 0; k < CPL; ++k) s[k].init(live ? absmax[c + k] : 0.0f, b_lo);
-  if (live) {
-    const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
-    for (int64_t r = (int64_t)blockIdx.y * (kBlock / kWave) + wave; r < rows; r += row_step) {
-      if (CPL == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(x + r * cols + c);
-        s[0].add(v.x); s[1 % CPL].add(v.y); s[2 % CPL].add(v.z); s[3 % CPL].add(v.w);
-      } else {
-        s[0].add(x[r * cols + c]);
-      }
+  for (int k = 0; k < CPL; ++k) {
+    s[k].m = k < live ? absmax[c + k] : 0.0f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      s[k].inv[b] = lds[(lane * CPL + k) * CST + b];
+      s[k].sc[b] = lds[(lane * CPL + k) * CST + NB + b];
+      s[k].acc[b] = 0.0f;
     }
   }
-  __shared__ float sm[kBlock / kWave][kWave][CPL * NB + 1];
+  __syncthreads();  // the sums go where the constants were
+  const int64_t row_step = (int64_t)gridDim.y * kColWaves;
+  const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
+  if (live == CPL) {
+#pragma unroll 2
+    for (int64_t r = r_first; r < rows; r += row_step) {
+      const float4 v = load_stream(x + r * cols + c);
+      s[0].add(v.x); s[1].add(v.y); s[2].add(v.z); s[3].add(v.w);
+    }
+  } else if (live > 0) {
+#pragma unroll 2
+    for (int64_t r = r_first; r < rows; r += row_step) {
+      const float* p = x + r * cols + c;
+      const float v0 = p[0], v1 = live > 1 ? p[1] : 0.0f, v2 = live > 2 ? p[2] : 0.0f;
+      s[0].add(v0); s[1].add(v1); s[2].add(v2);
+    }
+  }
+  float (*sm)[kWave][CPL * NB + 1] = reinterpret_cast<float (*)[kWave][CPL * NB + 1]>(lds);
 #pragma unroll
   for (int k = 0; k < CPL; ++k)
 #pragma unroll
     for (int b = 0; b < NB; ++b) sm[wave][lane][k * NB + b] = s[k].acc[b];
   __syncthreads();
-  if (wave == 0 && live) {
+  // the workgroup's 256 columns x NB sums are consecutive in the plane of partials
+  const int64_t left = (cols - (int64_t)blockIdx.x * (kWave * CPL)) * NB;
+  double* dst = partials + ((int64_t)blockIdx.y * cols + (int64_t)blockIdx.x * (kWave * CPL)) * NB;
+  for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
+    if (i >= left) break;
+    const int l = i / (CPL * NB), j = i - l * (CPL * NB);
+    double v = 0.0;
 #pragma unroll
-    for (int k = 0; k < CPL; ++k)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int j = k * NB + b;
-        const double v = ((double)sm[0][lane][j] + (double)sm[1][lane][j]) +
-                         ((double)sm[2][lane][j] + (double)sm[3][lane][j]);
-        partials[((int64_t)blockIdx.y * cols + c + k) * NB + b] = v;
-      }
+    for (int w = 0; w < kColWaves; ++w) v += (double)sm[w][l][j];
+    dst[i] = v;
   }
 }
 
 // ---- two-tensor squared distance -----------------------------------------------------------------
-template <bool VEC>
 __global__ __launch_bounds__(kBlock) void sse_pair_k(const float* __restrict__ y,
                                                      const float* __restrict__ yr, int64_t n,
                                                      double* __restrict__ partials) {
-  const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t nthr = (int64_t)gridDim.x * kBlock;
   float acc = 0.0f;
   auto add = [&](float a, float b) { const float e = a - b; acc = __builtin_fmaf(e, e, acc); };
-  if (VEC) {
-    const int64_t n4 = n >> 2;
-    for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
-                             [&](const float4 a, const float4 b) {
-                               add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
-                             });
-    for (int64_t j = (n4 << 2) + tid; j < n; j += nthr) add(y[j], yr[j]);
-  } else {
-    for (int64_t j = tid; j < n; j += nthr) add(y[j], yr[j]);
-  }
+  const int64_t n4 = n >> 2;
+  for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
+                           [&](const float4 a, const float4 b) {
+                             add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
+                           });
+  const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
+  if (blockIdx.x == 0 && j < n) add(y[j], yr[j]);
   __shared__ float sm[kBlock / kWave];
   const float w = wave_sum(acc);
   if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = w;
@@ -252,33 +281,27 @@ struct QeGeom {
   unsigned gx = 1, gy = 1;
   int64_t nseg = 1;
   int64_t partial_doubles = 0;  // doubles of workspace
-  bool vec = false;
 };
 
-static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb, bool aligned) {
+static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb) {
   QeGeom g;
   const int64_t n = rows * cols;
   if (gran == MPQ_PER_TENSOR) {
-    g.vec = aligned;
     // 4 blocks per CU: the full sweep needs ~65 VGPRs (7 waves per SIMD), so 8 blocks per CU
     // would not be co-resident and the late blocks would trail the rest
-    const unsigned gv = flat_grid(n >> 2, kBlock * kTileVec, 4), gs = flat_grid(n, kBlock * 4, 4);
-    g.gx = g.vec ? gv : gs;
-    // the query cannot see the pointer: reserve for the larger of the two grids
-    const unsigned worst = gv > gs ? gv : gs;
-    g.partial_doubles = (int64_t)worst * nb;
+    g.gx = flat_grid(n >> 2, kBlock * kTileVec, 4);
+    const unsigned gs = flat_grid(n, kBlock * 4, 4);  // the query reserves for single-element work items
+    g.partial_doubles = (int64_t)(g.gx > gs ? g.gx : gs) * nb;
   } else if (gran == MPQ_PER_ROW) {
-    g.vec = aligned && (cols & 3) == 0;
     g.nseg = (cols + kSeg - 1) / kSeg;
     const int64_t blocks = (rows * g.nseg + kBlock / kWave - 1) / (kBlock / kWave);
     g.gx = (unsigned)blocks;
     g.partial_doubles = g.nseg > 1 ? rows * g.nseg * nb : 0;
   } else {
-    g.vec = aligned && (cols & 3) == 0;
-    const int64_t worst_gx = (cols + kWave - 1) / kWave;          // scalar columns
-    const int64_t gx = g.vec ? (cols + kWave * 4 - 1) / (kWave * 4) : worst_gx;
-    // row chunks: fill the chip ~8 blocks per CU, at least 8 rows per wave
-    auto rows_chunks = [&](int64_t gxx) {
+    const int64_t gx = (cols + kWave * 4 - 1) / (kWave * 4);
+    // what the query has always reserved: row chunks for ~8 workgroups of 4 waves per CU, at least 8 rows
+    // per wave, with 4 columns or 1 column per lane
+    auto reserved = [&](int64_t gxx) {
       int64_t gy = ((int64_t)kNumCU * 8 + gxx - 1) / gxx;
       const int64_t max_gy = (rows + 4 * 8 - 1) / (4 * 8);
       if (gy > max_gy) gy = max_gy;
@@ -286,11 +309,15 @@ static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb, bool ali
       if (gy > 65535) gy = 65535;
       return gy;
     };
+    const int64_t r4 = reserved(gx), r1 = reserved((cols + kWave - 1) / kWave);
+    g.partial_doubles = (r4 > r1 ? r4 : r1) * cols * nb;
+    // what the kernel takes of it: two workgroups per CU, at least 4 rows per wave (never more than r4)
+    int64_t gy = ((int64_t)kNumCU * 2 + gx - 1) / gx;
+    const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
+    if (gy > max_gy) gy = max_gy;
+    if (gy > r4) gy = r4;
     g.gx = (unsigned)gx;
-    g.gy = (unsigned)rows_chunks(gx);
-    const int64_t worst_gy = rows_chunks(worst_gx) > rows_chunks((cols + kWave * 4 - 1) / (kWave * 4))
-                                 ? rows_chunks(worst_gx) : rows_chunks((cols + kWave * 4 - 1) / (kWave * 4));
-    g.partial_doubles = worst_gy * cols * nb;
+    g.gy = (unsigned)gy;
   }
   return g;
 }
@@ -300,12 +327,10 @@ static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t col
                       const float* absmax, int b_lo, double* out, double* ws, hipStream_t st) {
   const int64_t n = rows * cols;
   if (gran == MPQ_PER_TENSOR) {
-    if (g.vec) qe_flat<NB, true><<<g.gx, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
-    else qe_flat<NB, false><<<g.gx, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+    qe_flat<NB><<<g.gx, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
     qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)g.gx, out);
   } else if (gran == MPQ_PER_ROW) {
-    double* dst = g.nseg == 1 ? out : ws;
-    if (g.vec && g.nseg == 1) {
+    if (g.nseg == 1) {
       // 16 lanes per row up to 2048 columns (>= 4 vectors per lane from 256 columns on), else a wave
       if (cols <= 2048) {
         const int64_t blocks = (rows + 15) / 16;
@@ -314,18 +339,16 @@ static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t col
         const int64_t blocks = (rows + 3) / 4;
         qe_rows_sub<NB, 64><<<(unsigned)blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
       }
-    } else if (g.vec) qe_rows<NB, true><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, dst);
-    else qe_rows<NB, false><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, dst);
-    if (g.nseg > 1) {
+    } else {
+      qe_rows<NB><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, ws);
       const int64_t k = rows * NB;
-      qe_finish_serial<<<(unsigned)((k + 255) / 256), 256, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
+      qe_finish_planes<<<(unsigned)((k + kWave - 1) / kWave), kBlock, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
     }
   } else {
     dim3 grid(g.gx, g.gy);
-    if (g.vec) qe_cols<NB, 4><<<grid, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, ws);
-    else qe_cols<NB, 1><<<grid, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, ws);
+    qe_cols<NB><<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, ws);
     const int64_t k = cols * NB;
-    qe_finish_serial<<<(unsigned)((k + 255) / 256), 256, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
+    qe_finish_planes<<<(unsigned)((k + kWave - 1) / kWave), kBlock, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
   }
 }
 
@@ -345,7 +368,7 @@ using namespace mpq;
 extern "C" size_t mpq_quant_error_workspace_bytes(int64_t rows, int64_t cols, int gran, int b_lo,
                                                   int b_hi) {
   if (check_qe_args(rows, cols, gran, b_lo, b_hi) != MPQ_OK) return 0;
-  const QeGeom g = qe_geometry(rows, cols, gran, b_hi - b_lo + 1, true);
+  const QeGeom g = qe_geometry(rows, cols, gran, b_hi - b_lo + 1);
   return (size_t)g.partial_doubles * sizeof(double);
 }
 
@@ -356,7 +379,7 @@ static int run_quant_error(const float* x, int64_t rows, int64_t cols, int gran,
   const int rc = check_qe_args(rows, cols, gran, b_lo, b_hi);
   if (rc != MPQ_OK) return rc;
   const int nb = b_hi - b_lo + 1;
-  const QeGeom g = qe_geometry(rows, cols, gran, nb, aligned16(x));
+  const QeGeom g = qe_geometry(rows, cols, gran, nb);
   const size_t need = (size_t)g.partial_doubles * sizeof(double);
   if (need > 0 && (!ws || ws_bytes < need)) return builtin_scratch ? MPQ_ERR_TOO_LARGE : MPQ_ERR_WORKSPACE;
   if (need > 0 && !aligned16(ws)) return MPQ_ERR_ALIGN;
@@ -443,14 +466,12 @@ extern "C" int mpq_sse_pair(const float* y, const float* y_ref, int64_t n, doubl
                             void* ws, size_t ws_bytes, void* stream) {
   if (!y || !y_ref || !sse_out) return MPQ_ERR_NULL;
   if (n <= 0 || n > ((int64_t)1 << 46)) return MPQ_ERR_SHAPE;
-  const bool vec = aligned16(y) && aligned16(y_ref);
-  const unsigned grid = vec ? flat_grid(n >> 2, kBlock * 2) : flat_grid(n, kBlock * 4);
+  const unsigned grid = flat_grid(n >> 2, kBlock * 2);
   if (!ws || ws_bytes < mpq_sse_pair_workspace_bytes(n)) return MPQ_ERR_WORKSPACE;
   if (!aligned16(ws) || (reinterpret_cast<uintptr_t>(sse_out) & 7u) != 0) return MPQ_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
   double* wsd = reinterpret_cast<double*>(ws);
-  if (vec) sse_pair_k<true><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
-  else sse_pair_k<false><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  sse_pair_k<<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
   qe_finish_tree<1><<<1, kBlock, 0, st>>>(wsd, (int64_t)grid, sse_out);
   return launch_status();
 }

@@ -1,0 +1,59 @@
+"""The streaming calls at odd sizes and alignments: 16-byte accesses at any element, the last cols % 4 (or
+n % 4) elements by themselves, columns in groups of four with a ragged last group, several row chunks."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_parity import data, dev, host, mpq
+
+pytestmark = pytest.mark.gpu
+
+# rows, cols: remainders 0..3 of the vector, short rows, more than one wave / workgroup of columns, several
+# trips of four loads, more row chunks than waves; 16390 columns are two segments of a row
+SHAPES = [(1, 1), (3, 2), (5, 3), (2, 5), (67, 7), (130, 66), (33, 255), (33, 257), (40, 1023), (70, 1030), (1500, 5),
+          (2100, 70), (9, 2049), (3, 16390)]
+
+
+def at(a, off):
+    """a on the device, `off` elements behind a 16-byte boundary."""
+    import torch
+    t = torch.from_numpy(np.ascontiguousarray(a))
+    buf = torch.zeros(t.numel() + 4, dtype=t.dtype, device="cuda")
+    buf[off:off + t.numel()] = t.reshape(-1).cuda()
+    return buf[off:off + t.numel()].view(t.shape)
+
+
+@pytest.mark.parametrize("gran", [mpq.PER_TENSOR, mpq.PER_ROW, mpq.PER_COL])
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("off", [0, 1, 3])
+def test_streaming_calls(shape, off, gran):
+    import torch
+    x = data(shape, 90 + off)
+    dx = at(x, off)
+    m_o = oracle.absmax(x, gran)
+    m = mpq.calibrate_absmax(dx, gran)
+    np.testing.assert_array_equal(host(m), m_o)
+    run = dev(np.full_like(m_o, m_o.max() / 2))       # running maximum
+    mpq.calibrate_absmax(dx, gran, out=run, accumulate=True)
+    np.testing.assert_array_equal(host(run), np.maximum(m_o, m_o.max() / 2))
+    for lo, hi in ((2, 8), (5, 5)):
+        sse = host(mpq.quant_error(dx, m, lo, hi, gran))
+        want = oracle.quant_error(x, m_o, lo, hi, gran)
+        # fp32 partial sums: 1e-4 relative; an element on the grid (its channel's maximum) has an error of
+        # one rounding of its product, hence the floor at (2^-24 max)^2 per element of a channel
+        np.testing.assert_allclose(sse, want, rtol=1e-4, atol=(2.0 ** -24 * float(m_o.max())) ** 2 * x.size)
+    for bits in (8, 3):
+        packed = bits == 3 and shape[1] % 2 == 0
+        y = at(np.zeros(shape, np.float32), off)
+        codes = torch.zeros(x.size + 8, dtype=torch.int8, device="cuda")[off:off + x.size].view(shape)
+        p4 = torch.zeros(x.size // 2 + 8, dtype=torch.uint8, device="cuda")[off:off + x.size // 2].view(shape[0], -1) if packed else None
+        mpq.fake_quant(dx, m, bits, gran, y=y, codes=codes, packed4=p4)
+        y_o, c_o, p_o = oracle.fake_quant(x, m_o, bits, gran, want_packed4=packed)
+        np.testing.assert_array_equal(host(codes), c_o)
+        np.testing.assert_array_equal(host(y), y_o)
+        if packed:
+            np.testing.assert_array_equal(host(p4), p_o)
+    if gran == mpq.PER_TENSOR:
+        ref = data(shape, 95)
+        got = host(mpq.sse_pair(dx, at(ref, (off + 2) % 4)))[0]
+        assert got == pytest.approx(oracle.sse_pair(x, ref), rel=1e-4)
