@@ -50,6 +50,31 @@ __global__ __launch_bounds__(kBlock) void absmax_finish(const float* __restrict_
   }
 }
 
+// Up to kOneMax elements: one workgroup, one launch.  Device time, two launches against this: 16 x 16
+// 3.3 / 1.6 us, 64 x 256 3.8 / 2.1, 128 x 256 3.8 / 2.3.
+constexpr int64_t kOneMax = 32768;
+__global__ __launch_bounds__(kOneBlock) void absmax_one(const float* __restrict__ x, int n, int accumulate,
+                                                        float* __restrict__ out) {
+  float m = 0.0f;
+  const int n4 = n >> 2;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n4; i += kOneBlock) {
+    const float4 a = load4(x + 4 * i);
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
+  }
+  if ((int)threadIdx.x < (n & 3)) m = fmaxf(m, fabsf(x[(n & ~3) + threadIdx.x]));
+  m = wave_max(m);
+  __shared__ float sm[kOneBlock / kWave];
+  if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = accumulate ? out[0] : 0.0f;
+#pragma unroll
+    for (int w = 0; w < kOneBlock / kWave; ++w) t = fmaxf(t, sm[w]);
+    out[0] = t;
+  }
+}
+
 // per row: one wave per (row, segment of kSeg columns)
 constexpr int64_t kSeg = 16384;
 
@@ -180,7 +205,9 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
   if (!accumulate && !direct && gran != MPQ_PER_TENSOR) {
     fill_u32<<<(unsigned)((nch + 255) / 256), 256, 0, st>>>(out, nch, 0u);
   }
-  if (gran == MPQ_PER_TENSOR) {
+  if (gran == MPQ_PER_TENSOR && n <= kOneMax) {
+    absmax_one<<<1, kOneBlock, 0, st>>>(x, (int)n, accumulate, absmax_out);
+  } else if (gran == MPQ_PER_TENSOR) {
     const unsigned g = absmax_flat_grid(n);
     float* partials = reinterpret_cast<float*>(ws);
     absmax_flat<<<g, kBlock, 0, st>>>(x, n, partials);

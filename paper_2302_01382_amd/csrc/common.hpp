@@ -70,6 +70,11 @@ inline unsigned flat_grid(int64_t units, int64_t units_per_trip, int blocks_per_
   return (unsigned)((trips + r - 1) / r);
 }
 
+// A tensor this small is reduced by ONE workgroup of kOneBlock threads that writes the result itself: a second
+// launch costs the host 4.3 us and the GPU 2.5-3, more than one CU needs for these reads.  (n: elements;
+// the limits are where one CU still beats the two launches, measured at each kernel.)
+constexpr int kOneBlock = 1024;
+
 // ---- device side ---------------------------------------------------------------------------
 #if defined(__HIPCC__)
 

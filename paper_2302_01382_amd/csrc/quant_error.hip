@@ -49,6 +49,36 @@ __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, i
         ((double)sm[2][threadIdx.x] + (double)sm[3][threadIdx.x]);
 }
 
+// Up to kOneLimit / NB elements: one workgroup, one launch.  Device time for b = 2..8, two launches against
+// this: 16 x 16 5.2 / 3.3 us, 64 x 128 6.3 / 4.5, 64 x 256 6.5 / 6.0; for one width 128 x 256 4.4 / 2.8.
+constexpr int64_t kOneLimit = 7 * 16384;
+template <int NB>
+__global__ __launch_bounds__(kOneBlock) void qe_one(const float* __restrict__ x, int n,
+                                                    const float* __restrict__ absmax, int b_lo,
+                                                    double* __restrict__ out) {
+  constexpr int NW = kOneBlock / kWave;
+  Sweep<NB> s;
+  s.init(absmax[0], b_lo);
+  const int n4 = n >> 2;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n4; i += kOneBlock) s.add4(load4(x + 4 * i));
+  if ((int)threadIdx.x < (n & 3)) s.add(x[(n & ~3) + threadIdx.x]);
+  __shared__ float sm[NW][NB];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const float w = wave_sum(s.acc[b]);
+    if (lane == 0) sm[wave][b] = w;
+  }
+  __syncthreads();
+  if (threadIdx.x < NB) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += (double)sm[w][threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+}
+
 // out[b] = sum_p partials[p][b], p < np, in a fixed order: thread t adds p = t, t + 256, ...
 // (independent loads, unrolled), then a fixed LDS tree over the 256 threads.
 template <int NB>
@@ -276,6 +306,33 @@ __global__ __launch_bounds__(kBlock) void sse_pair_k(const float* __restrict__ y
     partials[blockIdx.x] = ((double)sm[0] + (double)sm[1]) + ((double)sm[2] + (double)sm[3]);
 }
 
+// Up to kOnePair elements: one workgroup, one launch.  Device time, two launches against this: 64 x 256
+// 4.2 / 2.3 us, 128 x 256 4.2 / 3.2.
+constexpr int64_t kOnePair = 32768;
+__global__ __launch_bounds__(kOneBlock) void sse_pair_one(const float* __restrict__ y, const float* __restrict__ yr,
+                                                          int n, double* __restrict__ out) {
+  constexpr int NW = kOneBlock / kWave;
+  float acc = 0.0f;
+  auto add = [&](float a, float b) { const float e = a - b; acc = __builtin_fmaf(e, e, acc); };
+  const int n4 = n >> 2;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n4; i += kOneBlock) {
+    const float4 a = load4(y + 4 * i), b = load4(yr + 4 * i);
+    add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
+  }
+  if ((int)threadIdx.x < (n & 3)) add(y[(n & ~3) + threadIdx.x], yr[(n & ~3) + threadIdx.x]);
+  __shared__ float sm[NW];
+  const float w = wave_sum(acc);
+  if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = w;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) t += (double)sm[v];
+    out[0] = t;
+  }
+}
+
 // ---- launch geometry, shared by the workspace queries and the launchers --------------------------
 struct QeGeom {
   unsigned gx = 1, gy = 1;
@@ -326,7 +383,9 @@ template <int NB>
 static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t cols, int gran,
                       const float* absmax, int b_lo, double* out, double* ws, hipStream_t st) {
   const int64_t n = rows * cols;
-  if (gran == MPQ_PER_TENSOR) {
+  if (gran == MPQ_PER_TENSOR && n * NB <= kOneLimit) {
+    qe_one<NB><<<1, kOneBlock, 0, st>>>(x, (int)n, absmax, b_lo, out);
+  } else if (gran == MPQ_PER_TENSOR) {
     qe_flat<NB><<<g.gx, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
     qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)g.gx, out);
   } else if (gran == MPQ_PER_ROW) {
@@ -470,6 +529,10 @@ extern "C" int mpq_sse_pair(const float* y, const float* y_ref, int64_t n, doubl
   if (!ws || ws_bytes < mpq_sse_pair_workspace_bytes(n)) return MPQ_ERR_WORKSPACE;
   if (!aligned16(ws) || (reinterpret_cast<uintptr_t>(sse_out) & 7u) != 0) return MPQ_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
+  if (n <= kOnePair) {
+    sse_pair_one<<<1, kOneBlock, 0, st>>>(y, y_ref, (int)n, sse_out);
+    return launch_status();
+  }
   double* wsd = reinterpret_cast<double*>(ws);
   sse_pair_k<<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
   qe_finish_tree<1><<<1, kBlock, 0, st>>>(wsd, (int64_t)grid, sse_out);

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 # rows, cols: remainders 0..3 of the vector, short rows, more than one wave / workgroup of columns, several
 # trips of four loads, more row chunks than waves; 16390 columns are two segments of a row
 SHAPES = [(1, 1), (3, 2), (5, 3), (2, 5), (67, 7), (130, 66), (33, 255), (33, 257), (40, 1023), (70, 1030), (1500, 5),
-          (2100, 70), (9, 2049), (3, 16390)]
+          (2100, 70), (9, 2049), (3, 16390),
+          # around the sizes up to which one workgroup reduces a whole tensor (16384 and 32768 elements)
+          (128, 128), (5, 3277), (128, 256), (2731, 12)]
 
 
 def at(a, off):
