@@ -43,34 +43,30 @@ struct GradAcc {
     if (r == q) s_x = __builtin_fmaf(g, x, s_x);  // the clamp was inactive
     s_loss = __builtin_fmaf(e, e, s_loss);
   }
+  template <bool HAS_G>
+  __device__ __forceinline__ void add4(const TwoScales& t, const float4& v, const float4& g) {
+    add<HAS_G>(t, v.x, g.x); add<HAS_G>(t, v.y, g.y); add<HAS_G>(t, v.z, g.z); add<HAS_G>(t, v.w, g.w);
+  }
 };
 
 // ---- per tensor: tiles dealt round-robin, one partial triple per workgroup ---------------------
-template <bool HAS_G, bool VEC>
+template <bool HAS_G>
 __global__ __launch_bounds__(kBlock) void sg_flat(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t n, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
                                                   double* __restrict__ partials) {
   const TwoScales t(inv[0], scale[0], bits);
   GradAcc a;
-  if (VEC) {
-    const int64_t n4 = n >> 2;
-    if (HAS_G) {
-      for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
-                               [&](const float4 v, const float4 u) {
-                                 a.add<true>(t, v.x, u.x); a.add<true>(t, v.y, u.y);
-                                 a.add<true>(t, v.z, u.z); a.add<true>(t, v.w, u.w);
-                               });
-    } else {
-      for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) {
-        a.add<false>(t, v.x, 0.0f); a.add<false>(t, v.y, 0.0f);
-        a.add<false>(t, v.z, 0.0f); a.add<false>(t, v.w, 0.0f);
-      });
-    }
+  const int64_t n4 = n >> 2;
+  if (HAS_G) {
+    for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
+                             [&](const float4 v, const float4 u) { a.add4<true>(t, v, u); });
   } else {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-      a.add<HAS_G>(t, x[i], HAS_G ? g[i] : 0.0f);
+    for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4,
+                        [&](const float4 v, int64_t) { a.add4<false>(t, v, v); });
   }
+  const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
+  if (blockIdx.x == 0 && j < n) a.add<HAS_G>(t, x[j], HAS_G ? g[j] : 0.0f);
   __shared__ float sm[3][kBlock / kWave];
   const float w0 = wave_sum(a.s_code), w1 = wave_sum(a.s_x), w2 = wave_sum(a.s_loss);
   if ((threadIdx.x & (kWave - 1)) == 0) {
@@ -112,34 +108,47 @@ __global__ __launch_bounds__(kBlock) void sg_finish(const double* __restrict__ p
   }
 }
 
-// ---- per row: one wave per row, results written directly ---------------------------------------
-template <bool HAS_G, bool VEC>
+// ---- per row: LPR lanes per row (16 or 64), results written directly ------------------------------
+// Four 16-byte loads per tensor in flight per lane before the first use: a wave per row with one in flight
+// took 9.8 us on 12288 x 768 (13.7 with a gradient), 49 (95) on 16384 x 4096; this 8.9 (12.7) and 43 (85).
+template <bool HAS_G, int LPR>
 __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t rows, int64_t cols, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
                                                   double* __restrict__ dinv, double* __restrict__ dscale,
                                                   double* __restrict__ loss) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t r = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (r >= rows) return;  // the whole wave leaves together
+  const int lr = threadIdx.x % LPR;
+  int64_t r = (int64_t)blockIdx.x * (kBlock / LPR) + threadIdx.x / LPR;
+  const bool live = r < rows;
+  if (!live) r = rows - 1;  // every lane stays active for the cross-lane sums; result discarded
   const TwoScales t(inv[r], scale[r], bits);
   GradAcc a;
   const float* xr = x + r * cols;
   const float* gr = HAS_G ? g + r * cols : nullptr;
-  if (VEC) {  // cols % 4 == 0 and 16-byte aligned tensors: rows start aligned
-    const float4* x4 = reinterpret_cast<const float4*>(xr);
-    const float4* g4 = reinterpret_cast<const float4*>(gr);
-    for (int64_t c = lane; c < (cols >> 2); c += kWave) {
-      const float4 v = x4[c];
-      const float4 u = HAS_G ? g4[c] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      a.add<HAS_G>(t, v.x, u.x); a.add<HAS_G>(t, v.y, u.y);
-      a.add<HAS_G>(t, v.z, u.z); a.add<HAS_G>(t, v.w, u.w);
+  constexpr int U = 4;
+  constexpr int64_t kStep = 4 * LPR;
+  for (int64_t c0 = 0; c0 + 4 <= cols; c0 += U * kStep) {  // the same trips for every lane of the row
+    // pieces past the row's end stay zero, in x and in g: they add nothing to any of the three sums
+    float4 v[U], u[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t c = c0 + k * kStep + 4 * lr;
+      v[k] = c + 4 <= cols ? load_stream(xr + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (HAS_G) u[k] = c + 4 <= cols ? load_stream(gr + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      else u[k] = v[k];
     }
-  } else {
-    for (int64_t c = lane; c < cols; c += kWave) a.add<HAS_G>(t, xr[c], HAS_G ? gr[c] : 0.0f);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (c0 + k * kStep + 4 <= cols) a.add4<HAS_G>(t, v[k], u[k]);  // skips pieces that no lane has
   }
-  const float w0 = wave_sum(a.s_code), w1 = wave_sum(a.s_x), w2 = wave_sum(a.s_loss);
-  if (lane == 0) {
+  if (lr < (int)(cols & 3)) {
+    const int64_t e = (cols & ~(int64_t)3) + lr;
+    a.add<HAS_G>(t, xr[e], HAS_G ? gr[e] : 0.0f);
+  }
+  const float w0 = LPR == 16 ? row16_sum(a.s_code) : wave_sum(a.s_code);
+  const float w1 = LPR == 16 ? row16_sum(a.s_x) : wave_sum(a.s_x);
+  const float w2 = LPR == 16 ? row16_sum(a.s_loss) : wave_sum(a.s_loss);
+  if (lr == 0 && live) {
     dscale[r] = (double)w0;
     dinv[r] = (double)t.scale * (double)w1;
     if (loss) loss[r] = (double)w2;
@@ -147,17 +156,63 @@ __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, c
 }
 
 // ---- forward with explicit scales ----------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void fq_scales_k(const float* __restrict__ x, int64_t n, int64_t cols,
-                                                      int per_row, const float* __restrict__ inv,
-                                                      const float* __restrict__ scale, int bits,
-                                                      float* __restrict__ y, int8_t* __restrict__ codes) {
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-    const int64_t ch = per_row ? i / cols : 0;
-    const TwoScales t(inv[ch], scale[ch], bits);
-    const float q = __builtin_amdgcn_fmed3f(t.rounded(x[i]), -t.qmax, t.qmax);
-    if (y) y[i] = q * t.scale;
-    if (codes) codes[i] = (int8_t)(int)q;
+// One thread per element with a division per element for its row and another for the clamp's limit
+// took 28 us on 12288 x 768 and 185 on 16384 x 4096; sixteen bytes at a time, the limit once per lane and row,
+// 14.5 and 81.
+__device__ __forceinline__ float q_of(const TwoScales& t, float x) {
+  return __builtin_amdgcn_fmed3f(t.rounded(x), -t.qmax, t.qmax);
+}
+typedef unsigned u32_any __attribute__((aligned(1)));  // codes may start at any byte
+
+// four outputs from flat element e on
+__device__ __forceinline__ void fqs_emit4(const TwoScales& t, const float4& v, int64_t e, float* y, int8_t* codes) {
+  const float q0 = q_of(t, v.x), q1 = q_of(t, v.y), q2 = q_of(t, v.z), q3 = q_of(t, v.w);
+  if (y) store4(y + e, make_float4(q0 * t.scale, q1 * t.scale, q2 * t.scale, q3 * t.scale));
+  if (codes)
+    *reinterpret_cast<u32_any*>(codes + e) = ((unsigned)(int)q0 & 0xFFu) | (((unsigned)(int)q1 & 0xFFu) << 8) |
+                                             (((unsigned)(int)q2 & 0xFFu) << 16) | ((unsigned)(int)q3 << 24);
+}
+__device__ __forceinline__ void fqs_emit1(const TwoScales& t, float v, int64_t e, float* y, int8_t* codes) {
+  const float q = q_of(t, v);
+  if (y) y[e] = q * t.scale;
+  if (codes) codes[e] = (int8_t)(int)q;
+}
+
+__global__ __launch_bounds__(kBlock) void fqs_flat(const float* __restrict__ x, int64_t n, const float* __restrict__ inv,
+                                                   const float* __restrict__ scale, int bits, float* __restrict__ y,
+                                                   int8_t* __restrict__ codes) {
+  const TwoScales t(inv[0], scale[0], bits);
+  const int64_t n4 = n >> 2;
+  for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4,
+                      [&](const float4 v, int64_t i) { fqs_emit4(t, v, i << 2, y, codes); });
+  const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
+  if (blockIdx.x == 0 && j < n) fqs_emit1(t, x[j], j, y, codes);
+}
+
+// LPR lanes per row (16 or 64); blockIdx.y: segments of seg columns (a multiple of 4)
+template <int LPR>
+__global__ __launch_bounds__(kBlock) void fqs_rows(const float* __restrict__ x, int64_t rows, int64_t cols,
+                                                   const float* __restrict__ inv, const float* __restrict__ scale,
+                                                   int bits, int64_t seg, float* __restrict__ y,
+                                                   int8_t* __restrict__ codes) {
+  const int lr = threadIdx.x % LPR;
+  const int64_t r = (int64_t)blockIdx.x * (kBlock / LPR) + threadIdx.x / LPR;
+  if (r >= rows) return;
+  const TwoScales t(inv[r], scale[r], bits);
+  const int64_t c0 = (int64_t)blockIdx.y * seg, c1 = c0 + seg < cols ? c0 + seg : cols;
+  const int64_t end = r * cols + c1;
+  constexpr int64_t kStep = 4 * LPR;
+  for (int64_t i = r * cols + c0 + 4 * lr; i + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
+    float4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * kStep + 4 <= end) v[k] = load_stream(x + i + k * kStep);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * kStep + 4 <= end) fqs_emit4(t, v[k], i + k * kStep, y, codes);
   }
+  const int64_t e = end - (c1 & 3) + lr;
+  if (e < end) fqs_emit1(t, x[e], e, y, codes);
 }
 
 // ---- p <- fl32(p - lr * dL/dp), in double, rounded once -----------------------------------------
@@ -177,10 +232,11 @@ static int check_sa(int64_t rows, int64_t cols, int gran, int bits) {
   return MPQ_OK;
 }
 
-static unsigned sg_grid(int64_t n, bool vec, bool has_g) {
-  if (!vec) return flat_grid(n, kBlock * 4);
-  return flat_grid(n >> 2, kBlock * (has_g ? 2 : kTileVec));
-}
+static unsigned sg_grid(int64_t n, bool has_g) { return flat_grid(n >> 2, kBlock * (has_g ? 2 : kTileVec)); }
+
+// Rows of up to kShortRow columns are walked by 16 lanes each, longer ones by a wave: 16 against 64 lanes,
+// gradients of 5000 x 400 5.1 / 3.9 us, forward of 3001 x 1147 9.8 / 7.5.
+constexpr int64_t kShortRow = 256;
 
 }  // namespace mpq
 
@@ -192,18 +248,28 @@ extern "C" int mpq_fake_quant_scales(const float* x, int64_t rows, int64_t cols,
   if (!x || !inv || !scale || (!y_out && !codes_out)) return MPQ_ERR_NULL;
   const int rc = check_sa(rows, cols, gran, bits);
   if (rc != MPQ_OK) return rc;
-  const int64_t n = rows * cols;
-  fq_scales_k<<<flat_grid(n, kBlock * 4), kBlock, 0, (hipStream_t)stream>>>(x, n, cols, gran == MPQ_PER_ROW, inv, scale,
-                                                                           bits, y_out, codes_out);
+  hipStream_t st = (hipStream_t)stream;
+  if (gran == MPQ_PER_TENSOR)
+    fqs_flat<<<flat_grid((rows * cols) >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, rows * cols, inv, scale, bits, y_out, codes_out);
+  else if (cols <= kShortRow)
+    fqs_rows<16><<<(unsigned)((rows + 15) / 16), kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, cols, y_out, codes_out);
+  else {
+    // few long rows: cut into segments of whole trips (1024 columns a wave) until the chip has its waves
+    int64_t nseg = (2048 + rows - 1) / rows;
+    if (nseg > (cols + 1023) / 1024) nseg = (cols + 1023) / 1024;
+    const int64_t seg = ((cols + nseg - 1) / nseg + 1023) / 1024 * 1024;
+    const dim3 grid((unsigned)((rows + 3) / 4), (unsigned)((cols + seg - 1) / seg));
+    fqs_rows<64><<<grid, kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, seg, y_out, codes_out);
+  }
   return launch_status();
 }
 
 extern "C" size_t mpq_scale_grad_workspace_bytes(int64_t rows, int64_t cols, int gran) {
   if (check_sa(rows, cols, gran, 8) != MPQ_OK || gran != MPQ_PER_TENSOR) return 0;
   const int64_t n = rows * cols;
-  unsigned g = sg_grid(n, false, false);
-  for (int v = 0; v < 2; ++v) {  // the largest grid any variant may use
-    const unsigned c = sg_grid(n, true, v != 0);
+  unsigned g = flat_grid(n, kBlock * 4);  // the query reserves for single-element work items
+  for (int v = 0; v < 2; ++v) {           // ... and for the largest grid any variant may use
+    const unsigned c = sg_grid(n, v != 0);
     g = c > g ? c : g;
   }
   return (size_t)g * 3 * sizeof(double);
@@ -220,31 +286,27 @@ extern "C" int mpq_scale_grad(const float* x, int64_t rows, int64_t cols, int gr
     return MPQ_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = rows * cols;
-  const bool vec = aligned16(x) && (!g || aligned16(g));
   if (gran == MPQ_PER_TENSOR) {
     if (!ws || ws_bytes < mpq_scale_grad_workspace_bytes(rows, cols, gran)) return MPQ_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(ws) & 7u) return MPQ_ERR_ALIGN;
     double* partials = reinterpret_cast<double*>(ws);
-    const bool v = vec && (n & 3) == 0;
-    const unsigned grid = sg_grid(n, v, g != nullptr);
-    if (g) {
-      if (v) sg_flat<true, true><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
-      else sg_flat<true, false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
-    } else {
-      if (v) sg_flat<false, true><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
-      else sg_flat<false, false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
-    }
+    const unsigned grid = sg_grid(n, g != nullptr);
+    if (g) sg_flat<true><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
+    else sg_flat<false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
     sg_finish<<<1, kBlock, 0, st>>>(partials, (int64_t)grid, scale, dinv_out, dscale_out, loss_out);
   } else {
-    const bool v = vec && (cols & 3) == 0;
-    const unsigned grid = (unsigned)((rows + 3) / 4);
-    if (g) {
-      if (v) sg_rows<true, true><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out);
-      else sg_rows<true, false><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out);
+    const bool short_rows = cols <= kShortRow;
+    const unsigned grid = (unsigned)(short_rows ? (rows + 15) / 16 : (rows + 3) / 4);
+#define MPQ_SG(G_, LPR_) \
+  sg_rows<G_, LPR_><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out)
+    if (short_rows) {
+      if (g) MPQ_SG(true, 16);
+      else MPQ_SG(false, 16);
     } else {
-      if (v) sg_rows<false, true><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out);
-      else sg_rows<false, false><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out);
+      if (g) MPQ_SG(true, 64);
+      else MPQ_SG(false, 64);
     }
+#undef MPQ_SG
   }
   return launch_status();
 }

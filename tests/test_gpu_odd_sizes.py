@@ -59,3 +59,25 @@ def test_streaming_calls(shape, off, gran):
         ref = data(shape, 95)
         got = host(mpq.sse_pair(dx, at(ref, (off + 2) % 4)))[0]
         assert got == pytest.approx(oracle.sse_pair(x, ref), rel=1e-4)
+
+
+@pytest.mark.parametrize("gran", [mpq.PER_TENSOR, mpq.PER_ROW])
+@pytest.mark.parametrize("shape", [(1, 1), (5, 3), (67, 7), (33, 255), (20, 256), (9, 257), (70, 1030), (6, 4099), (2, 9001), (300, 64)])
+@pytest.mark.parametrize("off", [0, 3])
+def test_scale_adjustment(shape, off, gran):
+    """16 lanes (up to 256 columns) or a wave per row, pieces past the row's end, rows cut into segments."""
+    x, g = data(shape, 96), data(shape, 97)
+    m = oracle.absmax(x, gran)
+    for bits in (3, 8):
+        qmax = np.float32(2 ** (bits - 1) - 1)
+        inv, scale = (qmax / m * np.float32(1.3)).astype(np.float32), (m / qmax).astype(np.float32)
+        y, codes = mpq.fake_quant_scales(at(x, off), dev(inv), dev(scale), bits, gran, want_codes=True)
+        y_o, c_o = oracle.fake_quant_scales(x, inv, scale, bits, gran)
+        np.testing.assert_array_equal(host(codes), c_o)
+        np.testing.assert_array_equal(host(y), y_o)
+        for up in (None, g):
+            got = mpq.scale_grad(at(x, off), dev(inv), dev(scale), bits, None if up is None else at(up, (off + 1) % 4), gran)
+            want = oracle.scale_grad(x, inv, scale, bits, up, gran)
+            # fp32 partial sums of terms of either sign: 1e-4 of the sum of their absolute values
+            for a, key, lim in zip(got, ("dinv", "dscale", "loss"), ("abs_dinv", "abs_dscale", "loss")):
+                assert np.all(np.abs(host(a) - want[key]) <= 1e-4 * want[lim] + 1e-12)
