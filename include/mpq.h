@@ -59,8 +59,8 @@ int mpq_last_hip_error(void);
 /* Library version, major*100 + minor. */
 int mpq_version(void);
 /* Optional.  Configures, on the caller's current device, every kernel variant of the quantized-layer
- * calls that needs more than the default amount of on-chip memory (a per-kernel runtime attribute,
- * not a stream operation).  Without it the first call that selects a variant does the same for
+ * calls and of mpq_hutchinson_quad_signs that needs more than the default amount of on-chip memory (a
+ * per-kernel runtime attribute, not a stream operation).  Without it the first call that selects a variant does the same for
  * that variant; code that records the calls into a HIP graph calls mpq_init() before the capture
  * begins, or runs each call once eagerly first.  Thread safe, idempotent, allocates nothing. */
 int mpq_init(void);

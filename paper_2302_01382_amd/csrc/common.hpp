@@ -29,6 +29,9 @@ inline int launch_status() {
 int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, const float* absmax, int bits,
                       float* y_out, int8_t* codes_out, uint8_t* packed4_out, float* step_out, void* stream);
 
+// defined in hutchinson.hip: allows its kernels the LDS they need on the current device (mpq_init)
+int prepare_hutchinson();
+
 // defined in qgemm.hip: the host-side argument checks of mpq_qgemm_act / mpq_qgemm_score, for callers
 // that must validate several layers before their first launch
 int check_qgemm_act_args(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N, int64_t K,

@@ -10,19 +10,22 @@
 //                        mpq_rademacher would store): no probe matrix is read at all
 //
 // The second is a dense contraction X [M x K] times V' [K x P] followed by a column-wise sum of
-// squares, so it runs on the fp32 matrix cores (v_mfma_f32_32x32x2_f32; products with +-1 are
+// squares, so it runs on the matrix cores: the third on the bf16 ones (products with signs are exact
+// there too, see hutch_signs_k), the second on the fp32 matrix cores (v_mfma_f32_32x32x2_f32; products with +-1 are
 // exact, the sums over k round in fp32).  X is read once per group of up to 64 probes; with 32
 // probes the kernel is bound by that read (4 bytes per element of X against 64 flops), with 64
 // the fp32 matrix rate is level with it.  V (P x K floats, at most a few MB) stays in L2.
 //
 // A workgroup of eight waves owns 32 rows of X at a time; the waves split k between them (a
-// contiguous eighth each) and walk it in chunks of 32 (lane l: row l % 32, sixteen consecutive k in half l / 32 of the chunk, loaded as four
-// 16-byte pieces that feed four K = 2 matrix steps each), add their 32 x 32 partial products
+// contiguous eighth each) and walk it in chunks of 32 (lane l: row l % 32, sixteen consecutive k in
+// half l / 32 of the chunk, loaded as four 16-byte pieces that feed four K = 2 matrix steps each), add their 32 x 32 partial products
 // through LDS, and wave 0 squares and accumulates.  Lane l of a product tile holds column
 // p = l % 32 and sixteen of the rows m, so the column sums of squares need no cross-lane work
 // until the very end.
 #include "common.hpp"
 #include "philox.hpp"
+
+#include <atomic>
 
 namespace mpq {
 
@@ -71,50 +74,26 @@ struct Operands {
   float4 v[PB][CH];
 };
 
-// Where the probes come from: a matrix in memory, or (SIGNS) the sign stream of mpq_rademacher
-// drawn on the spot: with K a multiple of 16 the sixteen signs a lane needs for a chunk are one
-// half of a 32-bit Philox word (one Philox call per lane and chunk, about 80 vector operations
-// next to the chunk's 16 matrix steps of 64 clocks each).  Chunks of 64 k (a whole word per lane)
-// were slower: a lane's run of 128 bytes puts 64 different lines under every load instruction.
-struct Probes {
-  const float* V;
-  unsigned long long seed, sid, first;  // first: index of probe row 0 of this pass in the sign matrix
-};
-
-// the sixteen signs starting at element `base` (a multiple of 16) of the sign matrix, in the low bits
-__device__ __forceinline__ unsigned sign_word(const Probes& pr, unsigned long long base) {
-  const unsigned long long g = base >> 7;
-  const U4 w = philox4x32_10((unsigned)g, (unsigned)(g >> 32), (unsigned)pr.sid, (unsigned)(pr.sid >> 32),
-                             (unsigned)pr.seed, (unsigned)(pr.seed >> 32) ^ 0x5241444Du);
-  const unsigned sel = (unsigned)(base >> 5) & 3u;
-  const unsigned word = sel == 0 ? w.a : sel == 1 ? w.b : sel == 2 ? w.c : w.d;
-  return word >> ((unsigned)base & 16u);
-}
-
-__device__ __forceinline__ float sign_f(unsigned bits, int t) {  // +1.0f, or -1.0f if bit t is set
-  return f_from_bits((int)(0x3F800000u | (((bits >> t) & 1u) << 31)));
-}
-
-// piece e (four k) of the chunk that starts at kb for this lane: X always, V when it is in memory
-template <int PB, int CH, bool VEC, bool SIGNS>
+// piece e (four k) of the chunk that starts at kb for this lane
+template <int PB, int CH, bool VEC>
 __device__ __forceinline__ void load_piece(Operands<PB, CH>& o, int e, const float* __restrict__ xr, bool m_ok,
-                                           const Probes& pr, int64_t P, int64_t K, int64_t kb, int row, bool live) {
+                                           const float* __restrict__ V, int64_t P, int64_t K, int64_t kb, int row,
+                                           bool live) {
   const int64_t k = kb + 4 * e;
   o.x[e] = load4f<VEC>(xr + k, K - k, live && m_ok);
-  if (!SIGNS) {
 #pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      const int64_t p = pb * 32 + row;
-      const bool p_ok = live && p < P;
-      o.v[pb][e] = load4f<VEC>(pr.V + (p_ok ? p : 0) * K + k, K - k, p_ok);
-    }
+  for (int pb = 0; pb < PB; ++pb) {
+    const int64_t p = pb * 32 + row;
+    const bool p_ok = live && p < P;
+    o.v[pb][e] = load4f<VEC>(V + (p_ok ? p : 0) * K + k, K - k, p_ok);
   }
 }
 
 // part: float [gridDim.x][PB * 32], this workgroup's share of sum_m (X V')[m][p]^2
-template <int PB, bool VEC, bool SIGNS>
+template <int PB, bool VEC>
 __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__ X, int64_t M, int64_t K,
-                                                       Probes pr, int64_t P, float* __restrict__ part) {
+                                                       const float* __restrict__ V, int64_t P,
+                                                       float* __restrict__ part) {
   constexpr int CH = 4;               // pieces per chunk and lane
   constexpr int CK = 8 * CH;          // k per chunk
   __shared__ float red[kHW - 1][PB][16][64];
@@ -141,35 +120,21 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[pb][v] = 0.0f;
 
-    // first element of the sign matrix this lane needs from chunk c of probe block pb (columns
-    // past P get signs too; their sums are never read)
-    auto sign_base = [&](int pb, int64_t c) {
-      return (pr.first + (unsigned long long)(pb * 32 + row)) * (unsigned long long)K +
-             (unsigned long long)(c * CK + half * (CK / 2));
-    };
     // A piece's registers are refilled with the same piece of the wave's next chunk as soon as
     // the matrix steps that read them have been issued: loads run most of a chunk ahead of their
     // use without a second set of registers.
     Operands<PB, CH> o;
-    unsigned bits[PB], bits_next[PB];
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) bits[pb] = SIGNS ? sign_word(pr, sign_base(pb, c_lo)) : 0u;
 #pragma unroll
     for (int e = 0; e < CH; ++e)
-      load_piece<PB, CH, VEC, SIGNS>(o, e, xr, m_ok, pr, P, K, c_lo * CK + half * (CK / 2), row, c_lo < c_hi);
+      load_piece<PB, CH, VEC>(o, e, xr, m_ok, V, P, K, c_lo * CK + half * (CK / 2), row, c_lo < c_hi);
     for (int64_t c = c_lo; c < c_hi; ++c) {
       const int64_t kn = (c + 1) * CK + half * (CK / 2);
       const bool more = c + 1 < c_hi;
 #pragma unroll
-      for (int pb = 0; pb < PB; ++pb) bits_next[pb] = SIGNS ? sign_word(pr, sign_base(pb, c + 1)) : 0u;
-#pragma unroll
       for (int e = 0; e < CH; ++e) {
         float4 v[PB];
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb)
-          v[pb] = SIGNS ? make_float4(sign_f(bits[pb], 4 * e), sign_f(bits[pb], 4 * e + 1), sign_f(bits[pb], 4 * e + 2),
-                                      sign_f(bits[pb], 4 * e + 3))
-                        : o.v[pb][e];
+        for (int pb = 0; pb < PB; ++pb) v[pb] = o.v[pb][e];
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) acc[pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.x[e].x, v[pb].x, acc[pb], 0, 0, 0);
 #pragma unroll
@@ -178,10 +143,8 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
         for (int pb = 0; pb < PB; ++pb) acc[pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.x[e].z, v[pb].z, acc[pb], 0, 0, 0);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) acc[pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.x[e].w, v[pb].w, acc[pb], 0, 0, 0);
-        load_piece<PB, CH, VEC, SIGNS>(o, e, xr, m_ok, pr, P, K, kn, row, more);
+        load_piece<PB, CH, VEC>(o, e, xr, m_ok, V, P, K, kn, row, more);
       }
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb) bits[pb] = bits_next[pb];
     }
 
     // the k shares of the 32 x 32 products meet in wave 0, in a fixed order
@@ -214,6 +177,248 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
   }
 }
 
+// =====================================================================================================
+// The sign probes drawn in the kernel.
+//
+// Products with +-1 need no fp32 multiplier: x is split exactly into three bf16 numbers (the 24 bits of its
+// significand, eight at a time: hi = the top of x, mid = the top of x - hi, lo = the rest; all three
+// differences are exact), the signs are bf16, and v_mfma_f32_32x32x16_bf16 adds the exact products in
+// fp32.  Three such steps take 96 clocks where sixteen k took 512 on v_mfma_f32_32x32x2_f32, with an eighth
+// of the roundings of the sum, so what bounds the kernel is the read of X: 67 M elements x 4 bytes.
+//
+// X travels global -> LDS in tiles of 32 rows x 32 k by direct loads of whole 128-byte lines (a lane that
+// reads its own row, as the operand layout wants it, touches 64 lines per load instruction and keeps the
+// memory at 4.4 TB/s), four tiles deep per wave.  Every wave has a ring of its own, so there is no
+// barrier in the k loop: a wave waits for its own loads only.  Waves split k in shares of whole 128-k blocks;
+// a block is what one Philox call per lane serves (four words, each half of a lane pair takes 16 bits of
+// each), or two where K is no multiple of 128 and a probe's blocks straddle Philox blocks.
+//
+// us with the finishing kernel, fp32 steps against this: 16384 x 4096 32 probes 77 -> 55 (4.9 TB/s), 64 probes
+// 110 -> 64; 16384 x 2048 42 -> 30; 70000 x 512 51 -> 34; 9000 x 2064 46 -> 35; 1000 x 4096 31 -> 19.  Below about
+// 100 K elements both are launch and latency (64 x 128 6.3 -> 7.2).  Error against 64 bits 5e-9 (was 7e-9).
+// =====================================================================================================
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+struct Signs {
+  unsigned long long seed, sid, first;  // first: index of probe row 0 of this pass in the sign matrix
+};
+
+// the Philox block that holds element `base` of the sign matrix
+__device__ __forceinline__ U4 sign_block(const Signs& sg, unsigned long long base) {
+  const unsigned long long g = base >> 7;
+  return philox4x32_10((unsigned)g, (unsigned)(g >> 32), (unsigned)sg.sid, (unsigned)(sg.sid >> 32),
+                       (unsigned)sg.seed, (unsigned)(sg.seed >> 32) ^ 0x5241444Du);
+}
+// eight signs (bits 0..7 of `bits`) as bf16 +1 / -1, lowest bit first
+__device__ __forceinline__ v8bf sign_operand(unsigned bits) {
+  unsigned d[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    d[j] = 0x3F803F80u | ((bits << (15 - 2 * j)) & 0x8000u) | ((bits << (30 - 2 * j)) & 0x80000000u);
+  return __builtin_bit_cast(v8bf, d);
+}
+
+// x = hi + mid + lo, exactly, for eight x
+__device__ __forceinline__ void split3(const float (&x)[8], v8bf& hi, v8bf& mid, v8bf& lo) {
+  unsigned h[4], m[4], l[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float a = x[2 * j], b = x[2 * j + 1];
+    const unsigned ua = (unsigned)bits_from_f(a), ub = (unsigned)bits_from_f(b);
+    h[j] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    const float ra = a - f_from_bits((int)(ua & 0xFFFF0000u)), rb = b - f_from_bits((int)(ub & 0xFFFF0000u));
+    const unsigned va = (unsigned)bits_from_f(ra), vb = (unsigned)bits_from_f(rb);
+    m[j] = __builtin_amdgcn_perm(vb, va, 0x07060302u);
+    const float la = ra - f_from_bits((int)(va & 0xFFFF0000u)), lb = rb - f_from_bits((int)(vb & 0xFFFF0000u));
+    l[j] = __builtin_amdgcn_perm((unsigned)bits_from_f(lb), (unsigned)bits_from_f(la), 0x07060302u);
+  }
+  hi = __builtin_bit_cast(v8bf, h);
+  mid = __builtin_bit_cast(v8bf, m);
+  lo = __builtin_bit_cast(v8bf, l);
+}
+
+constexpr int kSW = 8;                   // most waves of a workgroup
+constexpr int kRing = 4;                 // tiles of a wave's ring
+constexpr int kTileBytes = 32 * 128;     // 32 rows x 32 floats
+// LDS of a workgroup of ks * groups waves: the rings, the partial products of all but the first wave of a
+// group, and the last step's sums
+constexpr int signs_lds(int ks, int groups) {
+  return ks * groups * kRing * kTileBytes + (ks - 1) * groups * 16 * 64 * (int)sizeof(float) + kSW * 2 * 32 * (int)sizeof(float);
+}
+
+static __device__ __attribute__((aligned(16))) int g_zeros16[4];  // never written: rows and k past the edge
+
+// ks: waves that split k (1, 2, 4 or 8); the workgroup's ks * groups waves work on `groups` blocks of 32 rows
+// at a time
+// part: float [gridDim.x][PB * 32], this workgroup's share of sum_m (X V')[m][p]^2
+template <int PB>
+__global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restrict__ X, int64_t M, int64_t K,
+                                                          Signs sg, int ks, int groups, int iters,
+                                                          float* __restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* red = reinterpret_cast<float*>(lds + ks * groups * kRing * kTileBytes);  // [(ks - 1) * groups][16][64]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int row = lane & 31, half = lane >> 5;
+  const int group = wave / ks, kshare = wave % ks;
+  const int nblock = (int)((K + 127) >> 7);             // 128-k blocks
+  const int per = (nblock + ks - 1) / ks;               // of a wave: kshare, kshare + ks, ...; those past K read zeros
+  const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (unsigned)(wave * kRing * kTileBytes);
+  const char* my = lds + wave * kRing * kTileBytes;
+  const char* zero = reinterpret_cast<const char*>(g_zeros16);
+
+  // Requests run kRing tiles ahead of the work, across row blocks.  Load i of a tile brings rows
+  // 8 i .. 8 i + 7: lane l row 8 i + l / 8, and to keep the operand reads free of bank conflicts slot s of
+  // row r holds the 16-byte chunk s ^ ((r >> 1) & 7) of its 128 bytes.
+  // Rows past the edge re-read the last row (their products are dropped below); the lane's four addresses
+  // move along with the tiles, so that a request costs two additions per load.
+  int rq_b = 0;  // number of the wave's 128-k block
+  int64_t rq_blk = (int64_t)blockIdx.x * groups + group;
+  const char* src[4];
+  auto start_block = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int64_t m = rq_blk * 32 + 8 * i + (lane >> 3);
+      if (m >= M) m = M - 1;
+      const int c = (lane & 7) ^ ((4 * i + (lane >> 4)) & 7);
+      src[i] = reinterpret_cast<const char*>(X + m * K + (int64_t)kshare * 128 + 4 * c);
+    }
+  };
+  start_block();
+  const int last_k = (int)K - 32;  // K % 16 == 0 and a chunk of four is whole or absent
+  auto request = [&](unsigned slot) {  // tile `slot` of the block
+    const int k0 = ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
+    const bool edge = k0 > last_k;  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const char* p = src[i];
+      if (edge && k0 + 4 * (int)((lane & 7) ^ ((4 * i + (lane >> 4)) & 7)) >= (int)K) p = zero;
+      // M0 holds the LDS address of lane 0; the wait state is the one the ISA asks for after its write
+      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p),
+                   "s"(ring + slot * kTileBytes + i * 1024u)
+                   : "memory");
+      src[i] += 128;
+    }
+    if (slot == kRing - 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) src[i] += (ks - 1) * 512;
+      if (++rq_b == per) {
+        rq_b = 0;
+        rq_blk += (int64_t)gridDim.x * groups;
+        start_block();
+      }
+    }
+  };
+  static_assert(kRing == 4, "tile t of a 128-k block lives in ring slot t");
+#pragma unroll 1
+  for (unsigned t = 0; t < kRing; ++t) request(t);
+
+  float s[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) s[pb] = 0.0f;
+  const bool whole_blocks = (K & 127) == 0;
+  const unsigned sw = (unsigned)(row >> 1) & 7u;
+  // the lane's four chunks of a tile: k = 16 half + 4 e
+  unsigned off[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) off[e] = (unsigned)row * 128u + ((((unsigned)half * 4u + e) ^ sw) << 4);
+
+  for (int it = 0; it < iters; ++it) {
+    v16f acc[PB];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[pb][v] = 0.0f;
+    for (int b = kshare; b < per * ks; b += ks) {
+      U4 words[PB];
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        const unsigned long long base = (sg.first + (unsigned long long)(pb * 32 + row)) * (unsigned long long)K +
+                                        (unsigned long long)b * 128u;
+        if (whole_blocks) {
+          words[pb] = sign_block(sg, base);
+        } else {  // the 128 signs start at any multiple of 16 elements: cut out of two blocks
+          const U4 p0 = sign_block(sg, base), p1 = sign_block(sg, base + 128u);
+          unsigned w[8] = {p0.a, p0.b, p0.c, p0.d, p1.a, p1.b, p1.c, p1.d};
+          const unsigned at = (unsigned)base & 127u;
+#pragma unroll
+          for (int i = 0; i < 7; ++i) w[i] = (at & 16u) ? (w[i] >> 16) | (w[i + 1] << 16) : w[i];
+#pragma unroll
+          for (int i = 0; i < 6; ++i) w[i] = (at & 32u) ? w[i + 1] : w[i];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w[i] = (at & 64u) ? w[i + 2] : w[i];
+          words[pb] = U4{w[0], w[1], w[2], w[3]};
+        }
+      }
+#pragma unroll 1
+      for (int t = 0; t < 4; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kRing - 1) * 4) : "memory");  // all but the youngest three tiles
+        float x[2][8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float4 v = *reinterpret_cast<const float4*>(my + t * kTileBytes + off[e]);
+          x[e >> 1][(e & 1) * 4 + 0] = v.x;
+          x[e >> 1][(e & 1) * 4 + 1] = v.y;
+          x[e >> 1][(e & 1) * 4 + 2] = v.z;
+          x[e >> 1][(e & 1) * 4 + 3] = v.w;
+        }
+        // the tile is in registers: its slot can be filled again
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        request((unsigned)t);
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          v8bf hi, mid, lo;
+          split3(x[st], hi, mid, lo);
+#pragma unroll
+          for (int pb = 0; pb < PB; ++pb) {
+            const v8bf v = sign_operand((half ? words[pb].a >> 16 : words[pb].a) >> (8 * st));
+            acc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, v, acc[pb], 0, 0, 0);
+            acc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, v, acc[pb], 0, 0, 0);
+            acc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, v, acc[pb], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) words[pb] = U4{words[pb].b, words[pb].c, words[pb].d, 0u};
+      }
+    }
+    // the k shares of a row block's 32 x 32 products meet in its first wave, in a fixed order
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      float* mine = red + (int64_t)(group * (ks - 1) + kshare - 1) * (16 * 64) + lane;
+      if (kshare > 0) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mine[v * 64] = acc[pb][v];
+      }
+      __syncthreads();
+      if (kshare == 0) {
+        // the lane's row of register v is m_lo + 8 (v / 4) + v % 4
+        const int64_t m_lo = (((int64_t)it * gridDim.x + blockIdx.x) * groups + group) * 32 + 4 * half;
+        const float* others = red + (int64_t)group * (ks - 1) * (16 * 64) + lane;
+        for (int w = 0; w < ks - 1; ++w)  // sixteen independent reads per share
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[pb][v] += others[(w * 16 + v) * 64];
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (m_lo + (v >> 2) * 8 + (v & 3) < M) s[pb] = __builtin_fmaf(acc[pb][v], acc[pb][v], s[pb]);
+      }
+      __syncthreads();  // red is free again
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // requests past the last tile land before the LDS is given back
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const float t = s[pb] + __shfl_xor(s[pb], 32);  // the two halves hold different rows of the same column
+    if (kshare == 0 && lane < 32) red[(group * PB + pb) * 32 + lane] = t;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < PB * 32) {
+    float t = 0.0f;
+    for (int g = 0; g < groups; ++g) t += red[g * PB * 32 + threadIdx.x];
+    part[(int64_t)blockIdx.x * (PB * 32) + threadIdx.x] = t;
+  }
+}
+
 // quad[p] = sum over workgroups of part[b][p], in double, fixed order; one workgroup per probe
 __global__ __launch_bounds__(kBlock) void hutch_finish(const float* __restrict__ part, int nblocks, int width,
                                                        double* __restrict__ quad) {
@@ -242,9 +447,61 @@ static int64_t hutch_grid(int64_t M, int pb) {
   return g > need ? g : need;
 }
 
+// How a pass is laid out: ks waves per row block, `groups` row blocks per workgroup, `grid` workgroups
+// (one per CU at a time, what the LDS allows) that make `iters` trips.  grid never exceeds hutch_grid, which
+// the workspace is sized for, and no lane accumulates more than 256 row blocks in fp32.
+// The layout with the least estimated time is taken: a trip costs the 128-k blocks of a wave times what one
+// takes, 1.4 us (its own latencies) plus 0.7 us for every wave of the CU (the memory rate they share) -- from
+// 16384 x 4096 in four and in eight waves per CU, 67 and 55 us -- and 1 us for adding the shares.
+struct SignsPlan {
+  int ks = 1, groups = 1, iters = 1;
+  int64_t grid = 1;
+};
+static SignsPlan plan_signs(int64_t M, int64_t K) {
+  const int64_t nblk = (M + 31) >> 5, nb = (K + 127) >> 7;
+  SignsPlan best;
+  double least = 0.0;
+  for (int ks = 1; ks <= kSW; ks *= 2)
+    for (int groups = 1; groups * ks <= kSW; groups *= 2) {
+      SignsPlan p;
+      p.ks = ks;
+      p.groups = groups;
+      const int64_t items = (nblk + groups - 1) / groups;
+      p.grid = items < kNumCU ? items : kNumCU;
+      if (p.grid < (items + 255) / 256) p.grid = (items + 255) / 256;
+      p.iters = (int)((items + p.grid - 1) / p.grid);
+      const double rounds = (double)((p.grid + kNumCU - 1) / kNumCU) * p.iters;
+      const double per = (double)((nb + ks - 1) / ks);
+      const double cost = rounds * (per * (1.4 + 0.7 * ks * groups) + 1.0);
+      if (least == 0.0 || cost < least) {
+        least = cost;
+        best = p;
+      }
+    }
+  return best;
+}
+
+// Dynamic LDS above 64 KiB has to be allowed once per kernel and device.
+static int signs_allow_lds() {
+  static std::atomic<unsigned> done[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+  if (done[dev].load(std::memory_order_relaxed)) return MPQ_OK;
+  for (const void* k : {reinterpret_cast<const void*>(&hutch_signs_k<1>), reinterpret_cast<const void*>(&hutch_signs_k<2>)}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, signs_lds(kSW, 1));
+    if (e != hipSuccess) { set_last_hip_error((int)e); return MPQ_ERR_HIP; }
+  }
+  done[dev].store(1, std::memory_order_relaxed);
+  return MPQ_OK;
+}
+
 }  // namespace mpq
 
 using namespace mpq;
+
+namespace mpq {
+int prepare_hutchinson() { return signs_allow_lds(); }
+}  // namespace mpq
 
 extern "C" int mpq_rademacher(uint64_t seed, uint64_t stream_id, int64_t rows, int64_t cols, float* v_out,
                               void* stream) {
@@ -270,19 +527,32 @@ extern "C" size_t mpq_hutchinson_quad_workspace_bytes(int64_t M, int64_t K, int6
 static int run_hutchinson(const float* x, int64_t M, int64_t K, const float* v, uint64_t seed, uint64_t stream_id,
                           int64_t P, double* quad_out, float* part, hipStream_t st) {
   const bool signs = v == nullptr;
-  const bool vec = aligned16(x) && (signs || aligned16(v)) && (K & 3) == 0;
+  if (signs) {
+    const int rc = signs_allow_lds();
+    if (rc != MPQ_OK) return rc;
+  }
+  const bool vec = !signs && aligned16(x) && aligned16(v) && (K & 3) == 0;
   for (int64_t p0 = 0; p0 < P; p0 += kProbeGroup) {
     const int64_t pg = P - p0 < kProbeGroup ? P - p0 : kProbeGroup;
     const int pb = probe_blocks(pg);
-    const unsigned g = (unsigned)hutch_grid(M, pb);
-    const Probes pr = {signs ? nullptr : v + p0 * K, seed, stream_id, (unsigned long long)p0};
-#define MPQ_HUTCH(PB_)                                                                                  \
-  (signs ? hutch_k<PB_, true, true><<<g, kHW * 64, 0, st>>>(x, M, K, pr, pg, part)                       \
-   : vec ? hutch_k<PB_, true, false><<<g, kHW * 64, 0, st>>>(x, M, K, pr, pg, part)                      \
-         : hutch_k<PB_, false, false><<<g, kHW * 64, 0, st>>>(x, M, K, pr, pg, part))
-    if (pb == 1) MPQ_HUTCH(1);
-    else MPQ_HUTCH(2);
+    unsigned g;
+    if (signs) {
+      const SignsPlan pl = plan_signs(M, K);
+      g = (unsigned)pl.grid;
+      const Signs sg = {seed, stream_id, (unsigned long long)p0};
+      const int threads = pl.ks * pl.groups * 64, lds = signs_lds(pl.ks, pl.groups);
+      if (pb == 1) hutch_signs_k<1><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, part);
+      else hutch_signs_k<2><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, part);
+    } else {
+      g = (unsigned)hutch_grid(M, pb);
+      const float* vp = v + p0 * K;
+#define MPQ_HUTCH(PB_)                                                                     \
+  (vec ? hutch_k<PB_, true><<<g, kHW * 64, 0, st>>>(x, M, K, vp, pg, part)                 \
+       : hutch_k<PB_, false><<<g, kHW * 64, 0, st>>>(x, M, K, vp, pg, part))
+      if (pb == 1) MPQ_HUTCH(1);
+      else MPQ_HUTCH(2);
 #undef MPQ_HUTCH
+    }
     hutch_finish<<<(unsigned)pg, kBlock, 0, st>>>(part, (int)g, pb * 32, quad_out + p0);
   }
   return launch_status();

@@ -416,7 +416,7 @@ extern "C" int mpq_init(void) {
     if (rc == MPQ_OK) rc = launch_dma_64(w4 != 0, true, d);
     if (rc != MPQ_OK) return rc;
   }
-  return MPQ_OK;
+  return prepare_hutchinson();
 }
 
 extern "C" size_t mpq_qgemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int w_storage_bits) {

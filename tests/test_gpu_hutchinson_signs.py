@@ -1,0 +1,52 @@
+"""mpq_hutchinson_quad_signs where its layout changes: rows around the 32-row block, k around the 128-k block and
+no multiple of it (sign words cut out of two Philox blocks), 1 to 8 waves sharing k, several trips per
+workgroup, both probe widths and several passes; and the exactness of the three-way split."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import data, dev, host, mpq
+
+pytestmark = pytest.mark.gpu
+
+
+def want(x, v):
+    return ((x.astype(np.float64) @ v.astype(np.float64).T) ** 2).sum(0)
+
+
+@pytest.mark.parametrize("mkp", [(1, 16, 1), (31, 48, 3), (32, 128, 32), (33, 144, 33), (65, 256, 64), (40, 272, 65),
+                                 (300, 1040, 5), (70, 2064, 130), (9000, 256, 4), (20000, 80, 7)])
+def test_layouts(mkp):
+    M, K, P = mkp
+    x = data((M, K), 110)
+    v = host(mpq.rademacher(7, 3, P, K))
+    got = host(mpq.hutchinson_quad_signs(dev(x), 7, 3, P))
+    # exact products; sums of K terms and of M squares in fp32: far below 1e-5 of a sum of squares
+    np.testing.assert_allclose(got, want(x, v), rtol=1e-5)
+
+
+def test_the_split_is_exact_over_the_exponent_range():
+    """One column per row: a row's product is +-x itself, so the quadratic form is the sum of exact squares."""
+    M, K = 64, 16
+    r = np.random.Generator(np.random.PCG64(111))
+    for scale in (-18, -6, 0, 6, 18):       # squares stay in the range of fp32
+        x = np.zeros((M, K), np.float32)
+        x[np.arange(M), r.integers(0, K, M)] = (r.standard_normal(M) * 10.0 ** scale).astype(np.float32)
+        got = host(mpq.hutchinson_quad_signs(dev(x), 5, 0, 4))
+        np.testing.assert_allclose(got, np.full(4, (x.astype(np.float64) ** 2).sum()), rtol=2e-6)  # fp32 squares and their sum
+
+
+def test_replay_in_a_graph():
+    import torch
+    x = dev(data((500, 272), 112))
+    ws, out = mpq.Workspace(), torch.empty(9, dtype=torch.float64, device="cuda")
+    mpq.init()
+    eager = host(mpq.hutchinson_quad_signs(x, 1, 2, 9, ws=ws)).copy()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        mpq.hutchinson_quad_signs(x, 1, 2, 9, out=out, ws=ws)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(host(out), eager)
