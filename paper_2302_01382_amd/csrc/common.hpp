@@ -29,6 +29,17 @@ inline int launch_status() {
 int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, const float* absmax, int bits,
                       float* y_out, int8_t* codes_out, uint8_t* packed4_out, float* step_out, void* stream);
 
+// ... on a tensor whose maximum is still one value per workgroup of the kernel that wrote it: max over
+// part[0 .. parts) is folded by every workgroup and left in absmax_out; int8 codes only
+constexpr int kMaxParts = 1024;
+int fake_quant_codes_from_parts(const float* x, int64_t n, const float* part, int parts, float* absmax_out, int bits,
+                                int8_t* codes_out, float* step_out, hipStream_t st);
+
+// defined in qgemm.hip, for mpq_stack_evaluate
+int qgemm_act_partials(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N, int64_t K,
+                       const float* a_scale, const float* w_scale, int w_gran, int act, float* y_out,
+                       float* absmax_out, float* part, int64_t room, int* parts, hipStream_t st);
+
 // defined in hutchinson.hip: allows its kernels the LDS they need on the current device (mpq_init)
 int prepare_hutchinson();
 

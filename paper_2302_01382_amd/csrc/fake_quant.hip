@@ -92,6 +92,50 @@ __global__ __launch_bounds__(kBlock) void fq_flat(const float* __restrict__ x, i
   if (tid == 0 && (n & 3)) emit_tail(x, c, c, c, n4 << 2, (int)(n & 3), y, codes, packed);
 }
 
+// ---- per tensor, codes only, the maximum still in parts (at most kMaxParts) --------------------
+// Every workgroup folds the parts for itself (a few KB out of the L2) while its first tile is on its way.
+__global__ __launch_bounds__(kBlock) void fq_parts(const float* __restrict__ x, int64_t n, const float* __restrict__ part,
+                                                   int parts, float* __restrict__ absmax_out, int bits,
+                                                   int8_t* __restrict__ codes, float* __restrict__ step_out) {
+  constexpr int64_t tile = (int64_t)kBlock * kTileVec;
+  const int64_t n4 = n >> 2, ntiles = (n4 + tile - 1) / tile;
+  int64_t t = blockIdx.x;
+  float4 v[kTileVec];
+  auto fetch = [&]() {
+#pragma unroll
+    for (int u = 0; u < kTileVec; ++u) {
+      const int64_t i = t * tile + threadIdx.x + u * kBlock;
+      if (i < n4) v[u] = load_stream(x + 4 * i);
+    }
+  };
+  if (t < ntiles) fetch();
+  float m = 0.0f;
+#pragma unroll
+  for (int u = 0; u < kMaxParts / kBlock; ++u) {
+    const int p = threadIdx.x + u * kBlock;
+    if (p < parts) m = fmaxf(m, part[p]);
+  }
+  m = wave_max(m);
+  __shared__ float sm[kBlock / kWave];
+  if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = m;
+  __syncthreads();
+  const QConst c = make_qconst(fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3])), bits);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    absmax_out[0] = c.m;
+    step_out[0] = c.scale;
+    if (n & 3) emit_tail(x, c, c, c, n4 << 2, (int)(n & 3), nullptr, codes, nullptr);
+  }
+  while (t < ntiles) {
+#pragma unroll
+    for (int u = 0; u < kTileVec; ++u) {
+      const int64_t i = t * tile + threadIdx.x + u * kBlock;
+      if (i < n4) emit4(v[u], c, i << 2, nullptr, codes, nullptr);
+    }
+    t += gridDim.x;
+    if (t < ntiles) fetch();
+  }
+}
+
 // ---- per row: one wave per (row, segment) -------------------------------------
 constexpr int64_t kSeg = 16384;
 
@@ -183,6 +227,12 @@ int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, cons
     if (gy > 65535) gy = 65535;
     fq_cols<<<dim3((unsigned)gx, (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
   }
+  return launch_status();
+}
+
+int fake_quant_codes_from_parts(const float* x, int64_t n, const float* part, int parts, float* absmax_out, int bits,
+                                int8_t* codes_out, float* step_out, hipStream_t st) {
+  fq_parts<<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n, part, parts, absmax_out, bits, codes_out, step_out);
   return launch_status();
 }
 

@@ -461,6 +461,24 @@ int check_qgemm_score_args(const int8_t* a_q, const void* w_q, int w_storage_bit
 }
 }  // namespace mpq
 
+// mpq_qgemm_act for mpq_stack_evaluate, arguments already checked: the running maximum goes to `part` as one
+// value per workgroup, their number to *parts, where the layer takes the tiled kernels and there are at most
+// `room` of them; else *parts = 0 and the maximum is merged into absmax_out as usual.
+namespace mpq {
+int qgemm_act_partials(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N, int64_t K,
+                       const float* a_scale, const float* w_scale, int w_gran, int act, float* y_out,
+                       float* absmax_out, float* part, int64_t room, int* parts, hipStream_t st) {
+  EpiArgs epi{nullptr, nullptr, act, reinterpret_cast<unsigned*>(absmax_out), nullptr, 0, nullptr};
+  *parts = 0;
+  const bool tiled = !skinny_waves(M, N, K) && fast_path(a_q, w_q, w_storage_bits == 4, M, N, K);
+  int64_t count = 0;
+  if (tiled && max_partials(M, N) <= room) epi.amax_part = part;
+  const int rc = run_qgemm(a_q, w_q, w_storage_bits, M, N, K, a_scale, w_scale, w_gran, y_out, nullptr, epi, &count, st);
+  if (epi.amax_part) *parts = (int)count;
+  return rc;
+}
+}  // namespace mpq
+
 extern "C" int mpq_qgemm_act(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N,
                              int64_t K, const float* a_scale, const float* w_scale, int w_gran, int act,
                              float* y_out, float* absmax_out, int accumulate, void* stream) {

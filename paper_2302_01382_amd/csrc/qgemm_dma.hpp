@@ -18,7 +18,9 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 //  - score: accumulate sum (Y - yref)^2, one double partial per workgroup in `part`;
 //  - activation: Y <- act(Y) before it is stored (1 = ReLU, 2 = GELU), and the largest |Y| after
 //    the activation merged into amax[0] (an integer atomic max over the bit patterns of the
-//    non-negative floats: exact and independent of the order);
+//    non-negative floats: exact and independent of the order), or one maximum per workgroup in
+//    amax_part for a consumer that folds them (256 workgroups that end together wait 2.7 us for
+//    each other's atomics on one address);
 //  - codes: the activated output quantized on the spot (Eq. 1 with the absmax in q_absmax[0], which
 //    an earlier pass over the same product found) and stored as int8 codes, so that the fp32 layer
 //    output never travels to HBM and back on its way into the next layer's GEMM.
@@ -30,6 +32,7 @@ struct EpiArgs {
   const float* q_absmax;
   int q_bits;
   int8_t* codes;
+  float* amax_part = nullptr;  // not null: a workgroup leaves its largest |Y| here, at its number, and not in amax
 };
 constexpr EpiArgs kNoEpi = {nullptr, nullptr, 0, nullptr, nullptr, 0, nullptr};
 
@@ -681,7 +684,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
     if (threadIdx.x == 0) {
       float t = 0.0f;
       for (int i = 0; i < C::NW; ++i) t = fmaxf(t, sm[i]);
-      atomicMax(epi.amax, abs_key(t));
+      if (epi.amax_part) epi.amax_part[blockIdx.x] = t;
+      else atomicMax(epi.amax, abs_key(t));
     }
   }
 }

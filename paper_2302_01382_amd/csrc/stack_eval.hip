@@ -54,19 +54,30 @@ extern "C" int mpq_stack_evaluate(const mpq_stack_layer* layers, int n_layers, i
   // the running maxima of the inputs of layers 1.. start at zero (the activation's output is what
   // they are taken of; layer 0's input was calibrated by the caller)
   if (n_layers > 1) clear_f32<<<(unsigned)((n_layers - 1 + 255) / 256), 256, 0, st>>>(a_absmax + 1, n_layers - 1);
+  // Until the last layer's score needs it the workspace holds the maxima of a layer's workgroups: the quantizer
+  // of the next layer folds them, which spares the workgroups an atomic on one address that they all reach
+  // at the same time: 4096 x 1024 x 1024 with ReLU 12.8 us without a maximum, 15.4 with the atomics, 13.0 so.
+  float* part = reinterpret_cast<float*>(ws);
+  int64_t room = (int64_t)(ws_bytes / sizeof(float));
+  if (room > mpq::kMaxParts) room = mpq::kMaxParts;
+  int parts = 0;  // maxima that the layer before left there; 0: its maximum is in a_absmax
   for (int l = 0; l < n_layers; ++l) {
     const mpq_stack_layer& L = layers[l];
     const int w = width_index[l];
     int rc;
-    if (l > 0) {
+    if (l > 0 && parts > 0) {
+      rc = mpq::fake_quant_codes_from_parts(layers[l - 1].h, M * L.K, part, parts, a_absmax + l, act_bits, L.a_codes,
+                                            a_scale + l, st);
+      if (rc != MPQ_OK) return rc;
+    } else if (l > 0) {
       // the quantizer kernel also leaves the step size: no launch of its own for one division
       rc = mpq::fake_quant_launch(layers[l - 1].h, M, L.K, MPQ_PER_TENSOR, a_absmax + l, act_bits, nullptr, L.a_codes,
                                   nullptr, a_scale + l, stream);
       if (rc != MPQ_OK) return rc;
     }
     if (l + 1 < n_layers) {
-      rc = mpq_qgemm_act(L.a_codes, L.w_q[w], L.w_storage_bits[w], M, L.N, L.K, a_scale + l, L.w_scale[w], w_gran, act,
-                         L.h, a_absmax + l + 1, 1, stream);
+      rc = mpq::qgemm_act_partials(L.a_codes, L.w_q[w], L.w_storage_bits[w], M, L.N, L.K, a_scale + l, L.w_scale[w], w_gran,
+                                   act, L.h, a_absmax + l + 1, part, room, &parts, st);
     } else {
       rc = mpq_qgemm_score(L.a_codes, L.w_q[w], L.w_storage_bits[w], M, L.N, L.K, a_scale + l, L.w_scale[w], w_gran,
                            y_ref, sse_out, nullptr, ws, ws_bytes, stream);

@@ -178,3 +178,25 @@ def test_the_end_to_end_demo_runs():
     assert r.returncode == 0, r.stdout
     for needle in ("order by E_QE", "order by E_N", "order by Hessian", "bisection", "greedy", "rel.size"):
         assert needle in r.stdout, r.stdout
+
+
+@pytest.mark.parametrize("M,shapes", [(700, [(512, 512), (512, 512), (96, 512)]), (601, [(1021, 512), (640, 1021), (64, 640)]),
+                                      (2100, [(1024, 96), (1024, 1024), (1024, 1024)])])
+def test_native_evaluation_with_maxima_per_workgroup(M, shapes):
+    """Layers large enough for the tiled kernels leave one maximum per workgroup, which the next layer's quantizer
+    folds (and an odd number of elements, and a layer whose K no tile fits): the same maxima, steps, codes and
+    score as the calls one by one."""
+    import torch
+    r = np.random.Generator(np.random.PCG64(200))
+    x = torch.from_numpy(r.standard_normal((M, shapes[0][1]), dtype=np.float32)).cuda()
+    ws = [torch.from_numpy((r.standard_normal(s, dtype=np.float32) * np.float32(np.sqrt(2.0 / s[1])))).cuda() for s in shapes]
+    st = QuantStack(x, ws, [8, 4])
+    for bits in ([8, 8, 8], [4, 8, 4]):
+        st.a_absmax_all[1:].fill_(-1.0)
+        a = st.evaluate(bits)
+        keep = [t.clone() for t in (st.a_absmax_all, st.a_scale_all, *st.a_codes)]
+        st.a_absmax_all[1:].fill_(-1.0)
+        b = st.evaluate_by_calls(bits)
+        assert a == b
+        for u, v in zip(keep, (st.a_absmax_all, st.a_scale_all, *st.a_codes)):
+            assert torch.equal(u, v)
