@@ -784,7 +784,7 @@ struct DmaArgs {
 int launch_dma_256(bool w4, const DmaArgs& a);
 int launch_dma_192(bool w4, bool three_stages, const DmaArgs& a);
 int launch_dma_128(bool w4, bool three_stages, const DmaArgs& a);
-int launch_dma_64(bool w4, bool long_k, const DmaArgs& a);
+int launch_dma_64(bool w4, bool long_k, bool two_stages, const DmaArgs& a);
 
 // Layers with few output tiles (qgemm_skinny.hip): how many waves split k, 0 where the layer is better
 // off with the tiled kernels.

@@ -75,3 +75,24 @@ def test_layers_of_few_tiles(mnk, wbits, by):
     buf = torch.zeros(M * N + 4, dtype=torch.float32, device="cuda")[1:1 + M * N].view(M, N)
     mpq.qgemm(da, dw, dev(sa), dev(sw), wbits, mpq.PER_ROW, y=buf)
     np.testing.assert_array_equal(host(buf), y_o)
+
+
+# a k of two and of four k tiles takes two LDS stages: 64 x 64 tiles with k tiles of 128 and of 256 bytes, 128 x 128
+# tiles; last tile whole and ragged; the counts on either side take three
+@pytest.mark.parametrize("mnk", [(1000, 520, 256), (1000, 520, 224), (1000, 520, 512), (1000, 520, 416), (1000, 520, 128), (1000, 520, 384),
+                                 (1000, 520, 640), (1001, 530, 1024), (1001, 530, 1008), (2100, 1030, 256), (2100, 1030, 512),
+                                 (2100, 1030, 448)])
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_short_k_in_two_stages(mnk, wbits):
+    M, N, K = mnk
+    K = (K + 31) // 32 * 32 if wbits == 4 else K
+    a, w = rand_codes((M, K), 127, 77), rand_codes((N, K), 127 if wbits == 8 else 7, 78)
+    ws = w if wbits == 8 else oracle.pack4(w)
+    _, acc = mpq.qgemm(dev(a), dev(ws), None, None, wbits, want_y=False, want_acc=True)
+    # products of codes are whole numbers below 2^31: exact in double
+    np.testing.assert_array_equal(host(acc), (a.astype(np.float64) @ w.astype(np.float64).T).astype(np.int64))
+    sa, sw = np.array([0.01], np.float32), np.array([0.02], np.float32)
+    r, m = mpq.qgemm_act(dev(a), dev(ws), dev(sa), dev(sw), mpq.ACT_RELU, wbits)   # one scale for all channels
+    y = np.maximum((host(acc).astype(np.float32) * sa) * sw, 0)
+    np.testing.assert_array_equal(host(r), y)
+    assert host(m)[0] == y.max()
