@@ -226,13 +226,14 @@ int mpq_noise_inject_sweep(const float* x, int64_t rows, int64_t cols, int gran,
  * y_out      nullable fp32 [M x N]; acc_out nullable int32 [M x N]; at least one is required.
  * K*127*127 must stay below 2^31 (K <= 133143), else MPQ_ERR_SHAPE.
  * 16-byte aligned a_q / w_q with K a multiple of 16 (32 for packed int4) take the fast path;
- * anything else is computed by a slower byte-wise loader with identical results.
- * Workspace: optional.  Shapes with a handful of output tiles and a long K (at most 64 tiles of
- * 64 x 64, K >= 1024: any layer at inference batch 1) are cut along K when the caller passes
- * the workspace the query asks for (16-byte aligned): partial int32 accumulators go to the
- * workspace and are added by a second kernel -- integer sums, so acc_out and y_out are bit-identical
- * to the unsplit product.  With ws == NULL (or too small) the same results are computed without
- * the split, only slower on those shapes; the query returns 0 for shapes that are not split. */
+ * anything else goes through registers in 16-byte chunks at any alignment, with identical results.
+ * Workspace: optional.  Shapes with few output tiles and a long K (at most 64 tiles of 64 x 64,
+ * K >= 1024) may be cut along K when the caller passes the workspace the query asks for (16-byte
+ * aligned): partial int32 accumulators go to the workspace and are added by a second kernel --
+ * integer sums, so acc_out and y_out are bit-identical to the unsplit product.  With ws == NULL (or
+ * too small) the same results are computed without the split; layers of very few tiles (inference
+ * batch 1) split K inside one kernel and do not touch the workspace; the query returns 0 for shapes
+ * that are never cut. */
 size_t mpq_qgemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int w_storage_bits);
 int mpq_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N,
               int64_t K, const float* a_scale, const float* w_scale, int w_gran, float* y_out,
