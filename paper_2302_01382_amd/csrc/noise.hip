@@ -91,29 +91,56 @@ __device__ __forceinline__ float sigma_of(float absmax, int bits, float lambda) 
   return lambda * scale;
 }
 
-// ---- one sigma for the whole group of four: per tensor, or per row with cols % 4 == 0 -------
-// ROWS = false: flat; ROWS = true: group g lies in row g / (cols/4)
-// Both kernels write nb outputs, one per bit-width b_lo .. b_lo + nb - 1, `stride` elements apart:
-// z does not depend on b, so a sweep over bit-widths draws it once per element.
-template <bool ROWS>
-__global__ __launch_bounds__(kBlock) void noise_vec(const float* __restrict__ x, int64_t n4,
-                                                    int64_t cols4, const float* __restrict__ absmax,
-                                                    int b_lo, int nb, float lambda, unsigned long long seed,
-                                                    unsigned long long sid, float* __restrict__ y,
-                                                    int64_t stride4) {
+// ---- per tensor and per row: a group of four elements at a time, at any alignment ---------------
+// Both kernels of this file write nb outputs, one per bit-width b_lo .. b_lo + nb - 1, `stride` elements
+// apart: z does not depend on b, so a sweep over bit-widths draws it once per element.
+// MODE 0: one scale; 1: scales per row, cols a multiple of 4 (a group lies in one row); 2: scales per row,
+// any cols >= 4 (a group lies in one row or two).  Bound by its HBM traffic, 4 + 4 nb bytes per element; one
+// element at a time with a 64-bit division for its row and a division per width (noise_generic), 4096 x 1023 per
+// row took 84 us at seven widths and 13.3 at one, so 21.4 and 10.6 (4096 x 1024: 21.4 and 9.7); 1000 x 1001
+// 14.6 -> 9.9.
+template <int MODE>
+__global__ __launch_bounds__(kBlock) void noise_vec(const float* __restrict__ x, int64_t n, int64_t cols,
+                                                    const float* __restrict__ absmax, int b_lo, int nb, float lambda,
+                                                    unsigned long long seed, unsigned long long sid,
+                                                    float* __restrict__ y, int64_t stride) {
+  const bool narrow = n < ((int64_t)1 << 32);  // rows from a 32-bit division
+  auto row_of = [&](int64_t e) {
+    return narrow ? (int64_t)((unsigned)e / (unsigned)cols) : e / cols;
+  };
+  const int64_t n4 = n >> 2;
   for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t g) {
-    const float m = absmax[ROWS ? g / cols4 : 0];
     const float4 z = gauss4(seed, sid, (unsigned long long)g);
-    for (int k = 0; k < nb; ++k) {
-      const float sig = sigma_of(m, b_lo + k, lambda);
-      reinterpret_cast<float4*>(y)[g + k * stride4] =
-          make_float4(__builtin_fmaf(sig, z.x, v.x), __builtin_fmaf(sig, z.y, v.y),
-                      __builtin_fmaf(sig, z.z, v.z), __builtin_fmaf(sig, z.w, v.w));
+    if (MODE == 2) {
+      const int64_t r = row_of(4 * g);
+      const int left = (int)((r + 1) * cols - 4 * g < 4 ? (r + 1) * cols - 4 * g : 4);  // of the group in row r: 1 .. 4
+      const float m0 = absmax[r], m1 = absmax[left < 4 ? r + 1 : r];
+      for (int k = 0; k < nb; ++k) {
+        const float s0 = sigma_of(m0, b_lo + k, lambda), s1 = sigma_of(m1, b_lo + k, lambda);
+        store4(y + 4 * g + k * stride,
+               make_float4(__builtin_fmaf(s0, z.x, v.x), __builtin_fmaf(left > 1 ? s0 : s1, z.y, v.y),
+                           __builtin_fmaf(left > 2 ? s0 : s1, z.z, v.z), __builtin_fmaf(left > 3 ? s0 : s1, z.w, v.w)));
+      }
+    } else {
+      const float m = absmax[MODE == 1 ? row_of(4 * g) : 0];
+      for (int k = 0; k < nb; ++k) {
+        const float sig = sigma_of(m, b_lo + k, lambda);
+        store4(y + 4 * g + k * stride,
+               make_float4(__builtin_fmaf(sig, z.x, v.x), __builtin_fmaf(sig, z.y, v.y),
+                           __builtin_fmaf(sig, z.z, v.z), __builtin_fmaf(sig, z.w, v.w)));
+      }
     }
   });
+  if (blockIdx.x == 0 && (int)threadIdx.x < (int)(n & 3)) {  // the last n % 4 elements, a lane each
+    const float4 z = gauss4(seed, sid, (unsigned long long)n4);
+    const int e = (int)threadIdx.x;
+    const int64_t i = (n4 << 2) + e;
+    const float m = absmax[MODE == 0 ? 0 : row_of(i)], xi = x[i], zi = e == 0 ? z.x : e == 1 ? z.y : z.z;
+    for (int k = 0; k < nb; ++k) y[i + k * stride] = __builtin_fmaf(sigma_of(m, b_lo + k, lambda), zi, xi);
+  }
 }
 
-// ---- generic: any shape, alignment, granularity; a lane still owns one group of four ----------
+// ---- per column, and rows of fewer than four elements; a lane still owns one group of four ----------
 __global__ __launch_bounds__(kBlock) void noise_generic(const float* __restrict__ x, int64_t rows,
                                                         int64_t cols, int gran,
                                                         const float* __restrict__ absmax, int b_lo, int nb,
@@ -142,14 +169,19 @@ static int launch_noise(const float* x, int64_t rows, int64_t cols, int gran, co
                         int nb, float lambda, uint64_t seed, uint64_t stream_id, float* y_out, int64_t stride,
                         hipStream_t st) {
   const int64_t n = rows * cols;
-  const bool vec = aligned16(x) && aligned16(y_out) && (n & 3) == 0 && (stride & 3) == 0;
-  if (vec && gran == MPQ_PER_TENSOR) {
-    noise_vec<false><<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n >> 2, 0, absmax, b_lo, nb, lambda, seed, stream_id, y_out, stride >> 2);
-  } else if (vec && gran == MPQ_PER_ROW && (cols & 3) == 0) {
-    noise_vec<true><<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n >> 2, cols >> 2, absmax, b_lo, nb, lambda, seed, stream_id, y_out, stride >> 2);
+#define MPQ_NOISE(MODE_)                                                                                             \
+  noise_vec<MODE_><<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n, cols, absmax, b_lo, nb, lambda, seed, \
+                                                                           stream_id, y_out, stride)
+  if (gran == MPQ_PER_TENSOR) {
+    MPQ_NOISE(0);
+  } else if (gran == MPQ_PER_ROW && (cols & 3) == 0) {
+    MPQ_NOISE(1);
+  } else if (gran == MPQ_PER_ROW && cols >= 4) {
+    MPQ_NOISE(2);
   } else {
     noise_generic<<<flat_grid((n + 3) >> 2, kBlock * 2), kBlock, 0, st>>>(x, rows, cols, gran, absmax, b_lo, nb, lambda, seed, stream_id, y_out, stride);
   }
+#undef MPQ_NOISE
   return launch_status();
 }
 

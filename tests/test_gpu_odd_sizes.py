@@ -81,3 +81,27 @@ def test_scale_adjustment(shape, off, gran):
             # fp32 partial sums of terms of either sign: 1e-4 of the sum of their absolute values
             for a, key, lim in zip(got, ("dinv", "dscale", "loss"), ("abs_dinv", "abs_dscale", "loss")):
                 assert np.all(np.abs(host(a) - want[key]) <= 1e-4 * want[lim] + 1e-12)
+
+
+@pytest.mark.parametrize("gran", [mpq.PER_TENSOR, mpq.PER_ROW, mpq.PER_COL])
+@pytest.mark.parametrize("shape", [(1, 1), (5, 3), (7, 4), (9, 5), (67, 7), (33, 255), (20, 256), (70, 1030), (3, 4099)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_noise(shape, off, gran):
+    """Groups of four elements in one row, in two rows and (rows of three elements) in more; the last n % 4; planes
+    that start at any element.  Bit for bit."""
+    import torch
+    x = data(shape, 98)
+    m = oracle.absmax(x, gran)
+    want = {b: oracle.noise_inject(x, m, b, 0.3, 9, 2, gran) for b in (2, 5, 8)}
+    got = at(np.zeros(shape, np.float32), off)
+    mpq.noise_inject(at(x, off), dev(m), 5, 0.3, 9, 2, gran, out=got)
+    np.testing.assert_array_equal(host(got), want[5])
+    n, stride = x.size, x.size + 3
+    buf = torch.zeros(7 * stride + 4, dtype=torch.float32, device="cuda")
+    out = buf[off:off + 7 * stride].view(7, stride)[:, :n].unflatten(1, shape)
+    mpq.noise_inject_sweep(at(x, off), dev(m), 2, 8, 0.3, 9, 2, gran, out=out)
+    for b in want:
+        np.testing.assert_array_equal(host(out[b - 2]), want[b])
+    inplace = at(x, off)
+    mpq.noise_inject(inplace, dev(m), 8, 0.3, 9, 2, gran, out=inplace)
+    np.testing.assert_array_equal(host(inplace), want[8])
