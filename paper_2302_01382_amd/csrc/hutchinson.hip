@@ -261,8 +261,8 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row = lane & 31, half = lane >> 5;
   const int group = wave / ks, kshare = wave % ks;
-  const int nblock = (int)((K + 127) >> 7);             // 128-k blocks
-  const int per = (nblock + ks - 1) / ks;               // of a wave: kshare, kshare + ks, ...; those past K read zeros
+  const int64_t nblock = (K + 127) >> 7;                // 128-k blocks
+  const int64_t per = (nblock + ks - 1) / ks;           // of a wave: kshare, kshare + ks, ...; those past K read zeros
   const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (unsigned)(wave * kRing * kTileBytes);
   const char* my = lds + wave * kRing * kTileBytes;
   const char* zero = reinterpret_cast<const char*>(g_zeros16);
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
   // row r holds the 16-byte chunk s ^ ((r >> 1) & 7) of its 128 bytes.
   // Rows past the edge re-read the last row (their products are dropped below); the lane's four addresses
   // move along with the tiles, so that a request costs two additions per load.
-  int rq_b = 0;  // number of the wave's 128-k block
+  int64_t rq_b = 0;  // number of the wave's 128-k block
   int64_t rq_blk = (int64_t)blockIdx.x * groups + group;
   const char* src[4];
   auto start_block = [&]() {
@@ -285,14 +285,14 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     }
   };
   start_block();
-  const int last_k = (int)K - 32;  // K % 16 == 0 and a chunk of four is whole or absent
+  const int64_t last_k = K - 32;  // K % 16 == 0 and a chunk of four is whole or absent
   auto request = [&](unsigned slot) {  // tile `slot` of the block
-    const int k0 = ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
+    const int64_t k0 = ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
     const bool edge = k0 > last_k;  // wave-uniform
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const char* p = src[i];
-      if (edge && k0 + 4 * (int)((lane & 7) ^ ((4 * i + (lane >> 4)) & 7)) >= (int)K) p = zero;
+      if (edge && k0 + 4 * (int)((lane & 7) ^ ((4 * i + (lane >> 4)) & 7)) >= K) p = zero;
       // M0 holds the LDS address of lane 0; the wait state is the one the ISA asks for after its write
       asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(p),
                    "s"(ring + slot * kTileBytes + i * 1024u)
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[pb][v] = 0.0f;
-    for (int b = kshare; b < per * ks; b += ks) {
+    for (int64_t b = kshare; b < per * ks; b += ks) {
       U4 words[PB];
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
