@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_shapes.hpp"
 #include "mpq.h"
 
 namespace mpq {

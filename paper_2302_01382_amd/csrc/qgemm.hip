@@ -316,7 +316,7 @@ static int check_qgemm_args(const int8_t* a_q, const void* w_q, int w_storage_bi
   if (y_ref && (reinterpret_cast<uintptr_t>(y_ref) & 3u)) return MPQ_ERR_ALIGN;
   if (acc_out && (reinterpret_cast<uintptr_t>(acc_out) & 3u)) return MPQ_ERR_ALIGN;
   const int64_t gx = (N + 127) / 128, gy = (M + 127) / 128;
-  if (gx > 0x7FFFFFFF || gy > 65535) return MPQ_ERR_SHAPE;           // grid of qgemm_any's larger tile
+  if (gx > 0x7FFFFFFF || gy > kMaxGridY) return MPQ_ERR_SHAPE;       // grid of qgemm_any (see any_tile)
   if (((M + 63) / 64) * ((N + 63) / 64) > 0x7FFFFFFF) return MPQ_ERR_SHAPE;  // ... and of the smallest fast tile
   return MPQ_OK;
 }
@@ -384,10 +384,7 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
     const bool long_k = K >= 1024 && tiles(64, 64) <= kNumCU;
     return launch_dma_64(w4, long_k, two(long_k ? 256 : 128), d);
   }
-  // 128 x 128 tiles once they fill the chip twice and k is long enough that the loop and not the output
-  // counts, else 64 x 64.  us, 128 against 64: 4000 x 2000 x 1500 33.0 / 41.0, 16384 x 1000 x 1001 62.6 / 74.3,
-  // but 4000 x 1000 x 1500 (256 tiles of 128) 27.0 / 23.6 and 12288 x 1000 x 200 32.9 / 20.7.
-  const int ts = K >= 512 && ((N + 127) / 128) * ((M + 127) / 128) >= 2 * kNumCU ? 128 : 64;
+  const int ts = any_tile(M, N, K, kNumCU);
   const int64_t gx = (N + ts - 1) / ts, gy = (M + ts - 1) / ts;
   const dim3 grid((unsigned)gx, (unsigned)gy);
 #define MPQ_ANY(TS_, W4_) \

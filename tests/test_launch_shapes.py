@@ -1,0 +1,50 @@
+"""The host-side rules for launch shapes (csrc/launch_shapes.hpp), compiled into a plain C++ program: a launch
+counts its work items in x in 32 bits and its workgroups in y in 16, whatever the sizes."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "launch_shapes.hpp"
+using namespace mpq;
+int main() {
+  int bad = 0;
+  // row tiles of the quantized layer for any K and alignment: every M that the argument check admits (its
+  // 128-row tiles number at most kMaxGridY), next to the edges where the tile changes
+  const int64_t ms[] = {1, 64, 4096, 64 * 65535 - 1, 64 * 65535, 64 * 65535 + 1, 5000000, 128 * 65535 - 1, 128 * 65535};
+  const int64_t ns[] = {1, 3, 130, 4096}, ks[] = {1, 17, 147, 511, 512, 4607};
+  for (int64_t M : ms)
+    for (int64_t N : ns)
+      for (int64_t K : ks) {
+        const int ts = any_tile(M, N, K, 256);
+        const int64_t gy = (M + ts - 1) / ts;
+        if (gy > kMaxGridY || (ts != 64 && ts != 128)) { std::printf("tile %d for %lld x %lld x %lld\n", ts, (long long)M, (long long)N, (long long)K); bad = 1; }
+      }
+  const int64_t wants[] = {1, 2, 1 << 20, 1 << 21, 1 << 22, 1 << 23, 1 << 24, (int64_t)1 << 33, (int64_t)1 << 46};
+  for (int threads : {64, 256, 512, 1024})
+    for (int64_t w : wants) {
+      const int64_t g = blocks_x(w, threads);
+      if (g < 1 || g > w || g * threads > 0xFFFFFFFFll || (w * threads <= ((int64_t)1 << 31) && g != w)) { std::printf("grid %lld of %d for %lld\n", (long long)g, threads, (long long)w); bad = 1; }
+    }
+  if (!bad) std::puts("shapes ok");
+  return bad;
+}
+"""
+
+
+def test_no_launch_is_larger_than_the_runtime_takes(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no C++ compiler")
+    src, exe = tmp_path / "shapes.cpp", tmp_path / "shapes"
+    src.write_text(PROGRAM)
+    r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2302_01382_amd", "csrc"),
+                        str(src), "-o", str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    r = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    assert r.returncode == 0 and "shapes ok" in r.stdout, r.stdout
