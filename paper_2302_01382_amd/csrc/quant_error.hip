@@ -113,19 +113,22 @@ __global__ __launch_bounds__(kBlock) void qe_finish_planes(const double* __restr
                                                            int nb, int64_t stride_ch, int64_t stride_p,
                                                            double* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t k = (int64_t)blockIdx.x * kWave + lane;
-  const bool live = k < nch * nb;
-  double a = 0.0;
-  if (live) {
-    const int64_t ch = k / nb;
-    const double* src = partials + ch * stride_ch + (k - ch * nb);
-#pragma unroll 8
-    for (int64_t p = wave; p < np; p += kBlock / kWave) a += src[p * stride_p];
-  }
   __shared__ double sm[kBlock / kWave][kWave];
-  sm[wave][lane] = a;
-  __syncthreads();
-  if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
+  for (int64_t k0 = (int64_t)blockIdx.x * kWave; k0 < nch * nb; k0 += (int64_t)gridDim.x * kWave) {
+    const int64_t k = k0 + lane;
+    const bool live = k < nch * nb;
+    double a = 0.0;
+    if (live) {
+      const int64_t ch = k / nb;
+      const double* src = partials + ch * stride_ch + (k - ch * nb);
+#pragma unroll 8
+      for (int64_t p = wave; p < np; p += kBlock / kWave) a += src[p * stride_p];
+    }
+    sm[wave][lane] = a;
+    __syncthreads();
+    if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
+    __syncthreads();  // sm is free again
+  }
 }
 
 // ---- per row: one wave per (row, segment) ------------------------------------------------------
@@ -222,66 +225,69 @@ __global__ __launch_bounds__(kColWaves * kWave, 4) void qe_cols(const float* __r
   constexpr int CPL = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  const int64_t c = ((int64_t)blockIdx.x * kWave + lane) * CPL;
-  const int live = c + CPL <= cols ? CPL : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
-  // The 2 NB constants of a column cost a division each: the workgroup shares the divisions of its 256
-  // columns through LDS instead of every wave forming those of its four (56 divisions per lane).
   __shared__ float lds[kColWaves * kWave * (CPL * NB + 1)];
-  constexpr int CST = 2 * NB + 1;  // constants of a column: 2 NB, padded to an odd pitch
-  static_assert(kWave * CPL * CST <= kColWaves * kWave * (CPL * NB + 1), "the constants fit where the sums go");
-  for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
-    const int cl = i / NB, b = i - cl * NB;
-    const int64_t cc = (int64_t)blockIdx.x * (kWave * CPL) + cl;
-    float sc = 0.0f, inv = 0.0f;
-    if (cc < cols) bit_constants(absmax[cc], b_lo + b, sc, inv);
-    lds[cl * CST + b] = inv;
-    lds[cl * CST + NB + b] = sc;
-  }
-  __syncthreads();
-  Sweep<NB> s[CPL];
-#pragma unroll
-  for (int k = 0; k < CPL; ++k) {
-    s[k].m = k < live ? absmax[c + k] : 0.0f;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      s[k].inv[b] = lds[(lane * CPL + k) * CST + b];
-      s[k].sc[b] = lds[(lane * CPL + k) * CST + NB + b];
-      s[k].acc[b] = 0.0f;
+  for (int64_t group = blockIdx.x; group * (kWave * CPL) < cols; group += gridDim.x) {
+    const int64_t c = (group * kWave + lane) * CPL;
+    const int live = c + CPL <= cols ? CPL : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
+    // The 2 NB constants of a column cost a division each: the workgroup shares the divisions of its 256
+    // columns through LDS instead of every wave forming those of its four (56 divisions per lane).
+    constexpr int CST = 2 * NB + 1;  // constants of a column: 2 NB, padded to an odd pitch
+    static_assert(kWave * CPL * CST <= kColWaves * kWave * (CPL * NB + 1), "the constants fit where the sums go");
+    for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
+      const int cl = i / NB, b = i - cl * NB;
+      const int64_t cc = group * (kWave * CPL) + cl;
+      float sc = 0.0f, inv = 0.0f;
+      if (cc < cols) bit_constants(absmax[cc], b_lo + b, sc, inv);
+      lds[cl * CST + b] = inv;
+      lds[cl * CST + NB + b] = sc;
     }
-  }
-  __syncthreads();  // the sums go where the constants were
-  const int64_t row_step = (int64_t)gridDim.y * kColWaves;
-  const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
-  if (live == CPL) {
+    __syncthreads();
+    Sweep<NB> s[CPL];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      s[k].m = k < live ? absmax[c + k] : 0.0f;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        s[k].inv[b] = lds[(lane * CPL + k) * CST + b];
+        s[k].sc[b] = lds[(lane * CPL + k) * CST + NB + b];
+        s[k].acc[b] = 0.0f;
+      }
+    }
+    __syncthreads();  // the sums go where the constants were
+    const int64_t row_step = (int64_t)gridDim.y * kColWaves;
+    const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
+    if (live == CPL) {
 #pragma unroll 2
-    for (int64_t r = r_first; r < rows; r += row_step) {
-      const float4 v = load_stream(x + r * cols + c);
-      s[0].add(v.x); s[1].add(v.y); s[2].add(v.z); s[3].add(v.w);
-    }
-  } else if (live > 0) {
+      for (int64_t r = r_first; r < rows; r += row_step) {
+        const float4 v = load_stream(x + r * cols + c);
+        s[0].add(v.x); s[1].add(v.y); s[2].add(v.z); s[3].add(v.w);
+      }
+    } else if (live > 0) {
 #pragma unroll 2
-    for (int64_t r = r_first; r < rows; r += row_step) {
-      const float* p = x + r * cols + c;
-      const float v0 = p[0], v1 = live > 1 ? p[1] : 0.0f, v2 = live > 2 ? p[2] : 0.0f;
-      s[0].add(v0); s[1].add(v1); s[2].add(v2);
+      for (int64_t r = r_first; r < rows; r += row_step) {
+        const float* p = x + r * cols + c;
+        const float v0 = p[0], v1 = live > 1 ? p[1] : 0.0f, v2 = live > 2 ? p[2] : 0.0f;
+        s[0].add(v0); s[1].add(v1); s[2].add(v2);
+      }
     }
-  }
-  float (*sm)[kWave][CPL * NB + 1] = reinterpret_cast<float (*)[kWave][CPL * NB + 1]>(lds);
+    float (*sm)[kWave][CPL * NB + 1] = reinterpret_cast<float (*)[kWave][CPL * NB + 1]>(lds);
 #pragma unroll
-  for (int k = 0; k < CPL; ++k)
+    for (int k = 0; k < CPL; ++k)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) sm[wave][lane][k * NB + b] = s[k].acc[b];
-  __syncthreads();
-  // the workgroup's 256 columns x NB sums are consecutive in the plane of partials
-  const int64_t left = (cols - (int64_t)blockIdx.x * (kWave * CPL)) * NB;
-  double* dst = partials + ((int64_t)blockIdx.y * cols + (int64_t)blockIdx.x * (kWave * CPL)) * NB;
-  for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
-    if (i >= left) break;
-    const int l = i / (CPL * NB), j = i - l * (CPL * NB);
-    double v = 0.0;
+      for (int b = 0; b < NB; ++b) sm[wave][lane][k * NB + b] = s[k].acc[b];
+    __syncthreads();
+    // the workgroup's 256 columns x NB sums are consecutive in the plane of partials
+    const int64_t left = (cols - group * (kWave * CPL)) * NB;
+    double* dst = partials + ((int64_t)blockIdx.y * cols + group * (kWave * CPL)) * NB;
+    for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
+      if (i >= left) break;
+      const int l = i / (CPL * NB), j = i - l * (CPL * NB);
+      double v = 0.0;
 #pragma unroll
-    for (int w = 0; w < kColWaves; ++w) v += (double)sm[w][l][j];
-    dst[i] = v;
+      for (int w = 0; w < kColWaves; ++w) v += (double)sm[w][l][j];
+      dst[i] = v;
+    }
+    __syncthreads();  // the sums are read: the next columns' constants may overwrite them
   }
 }
 
@@ -373,7 +379,7 @@ static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb) {
     const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
     if (gy > max_gy) gy = max_gy;
     if (gy > r4) gy = r4;
-    g.gx = (unsigned)gx;
+    g.gx = blocks_x(gx, kColWaves * kWave);
     g.gy = (unsigned)gy;
   }
   return g;
@@ -405,13 +411,13 @@ static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t col
     } else {
       qe_rows<NB><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, ws);
       const int64_t k = rows * NB;
-      qe_finish_planes<<<(unsigned)((k + kWave - 1) / kWave), kBlock, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
+      qe_finish_planes<<<blocks_x((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
     }
   } else {
     dim3 grid(g.gx, g.gy);
     qe_cols<NB><<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, ws);
     const int64_t k = cols * NB;
-    qe_finish_planes<<<(unsigned)((k + kWave - 1) / kWave), kBlock, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
+    qe_finish_planes<<<blocks_x((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
   }
 }
 
