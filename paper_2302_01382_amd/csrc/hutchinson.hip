@@ -240,20 +240,23 @@ __device__ __forceinline__ void split3(const float (&x)[8], v8bf& hi, v8bf& mid,
 constexpr int kSW = 8;                   // most waves of a workgroup
 constexpr int kRing = 4;                 // tiles of a wave's ring
 constexpr int kTileBytes = 32 * 128;     // 32 rows x 32 floats
-// LDS of a workgroup of ks * groups waves: the rings, the partial products of all but the first wave of a
-// group, and the last step's sums
+// LDS of a workgroup of ks * groups waves: the rings, and the partial products of all but the first wave of a
+// group or, in their place, the last step's sums
 constexpr int signs_lds(int ks, int groups) {
-  return ks * groups * kRing * kTileBytes + (ks - 1) * groups * 16 * 64 * (int)sizeof(float) + kSW * 2 * 32 * (int)sizeof(float);
+  const int shares = (ks - 1) * groups * 16 * 64 * (int)sizeof(float), sums = groups * 2 * 32 * (int)sizeof(double);
+  return ks * groups * kRing * kTileBytes + (shares > sums ? shares : sums);
 }
 
 static __device__ __attribute__((aligned(16))) int g_zeros16[4];  // never written: rows and k past the edge
 
 // ks: waves that split k (1, 2, 4 or 8); the workgroup's ks * groups waves work on `groups` blocks of 32 rows
 // at a time
-// part: float [gridDim.x][PB * 32], this workgroup's share of sum_m (X V')[m][p]^2
+// part: the sums of squares of 32 rows are fp32, everything above them is double: with per_block float
+// [row blocks][PB * 32], one such sum each (what the workspace has room for up to kBlockSums of them), else
+// float [gridDim.x][2][PB * 32], the workgroup's share as the nearest float and what is left of it
 template <int PB>
 __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restrict__ X, int64_t M, int64_t K,
-                                                          Signs sg, int ks, int groups, int iters,
+                                                          Signs sg, int ks, int groups, int iters, int per_block,
                                                           float* __restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   float* red = reinterpret_cast<float*>(lds + ks * groups * kRing * kTileBytes);  // [(ks - 1) * groups][16][64]
@@ -272,7 +275,9 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
   // row r holds the 16-byte chunk s ^ ((r >> 1) & 7) of its 128 bytes.
   // Rows past the edge re-read the last row (their products are dropped below); the lane's four addresses
   // move along with the tiles, so that a request costs two additions per load.
-  int64_t rq_b = 0;  // number of the wave's 128-k block
+  // Nothing is requested past the last row block: at the end the kernel would wait for it.
+  int64_t rq_b = 0;                       // number of the wave's 128-k block
+  int64_t rq_left = (int64_t)iters * per;  // blocks still to be requested in whole
   int64_t rq_blk = (int64_t)blockIdx.x * groups + group;
   const char* src[4];
   auto start_block = [&]() {
@@ -287,6 +292,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
   start_block();
   const int64_t last_k = K - 32;  // K % 16 == 0 and a chunk of four is whole or absent
   auto request = [&](unsigned slot) {  // tile `slot` of the block
+    if (rq_left == 0) return;
     const int64_t k0 = ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
     const bool edge = k0 > last_k;  // wave-uniform
 #pragma unroll
@@ -302,6 +308,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     if (slot == kRing - 1) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) src[i] += (ks - 1) * 512;
+      --rq_left;
       if (++rq_b == per) {
         rq_b = 0;
         rq_blk += (int64_t)gridDim.x * groups;
@@ -313,9 +320,9 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
 #pragma unroll 1
   for (unsigned t = 0; t < kRing; ++t) request(t);
 
-  float s[PB];
+  double sum[PB];
 #pragma unroll
-  for (int pb = 0; pb < PB; ++pb) s[pb] = 0.0f;
+  for (int pb = 0; pb < PB; ++pb) sum[pb] = 0.0;
   const bool whole_blocks = (K & 127) == 0;
   const unsigned sw = (unsigned)(row >> 1) & 7u;
   // the lane's four chunks of a tile: k = 16 half + 4 e
@@ -352,7 +359,9 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
       }
 #pragma unroll 1
       for (int t = 0; t < 4; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kRing - 1) * 4) : "memory");  // all but the youngest three tiles
+        // all but the youngest three tiles; in the wave's last block no younger ones follow
+        if (rq_left > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kRing - 1) * 4) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         float x[2][8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -393,29 +402,40 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
       __syncthreads();
       if (kshare == 0) {
         // the lane's row of register v is m_lo + 8 (v / 4) + v % 4
-        const int64_t m_lo = (((int64_t)it * gridDim.x + blockIdx.x) * groups + group) * 32 + 4 * half;
+        const int64_t block = ((int64_t)it * gridDim.x + blockIdx.x) * groups + group;
+        const int64_t m_lo = block * 32 + 4 * half;
         const float* others = red + (int64_t)group * (ks - 1) * (16 * 64) + lane;
         for (int w = 0; w < ks - 1; ++w)  // sixteen independent reads per share
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[pb][v] += others[(w * 16 + v) * 64];
+        float s = 0.0f;
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          if (m_lo + (v >> 2) * 8 + (v & 3) < M) s[pb] = __builtin_fmaf(acc[pb][v], acc[pb][v], s[pb]);
+          if (m_lo + (v >> 2) * 8 + (v & 3) < M) s = __builtin_fmaf(acc[pb][v], acc[pb][v], s);
+        if (per_block) {
+          s += __shfl_xor(s, 32);  // the two halves hold different rows of the same column
+          if (lane < 32 && block * 32 < M) part[block * (PB * 32) + pb * 32 + lane] = s;
+        } else {
+          sum[pb] += (double)s;
+        }
       }
       __syncthreads();  // red is free again
     }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // requests past the last tile land before the LDS is given back
+  if (per_block) return;  // uniform over the grid; no request is in flight
+  double* sums = reinterpret_cast<double*>(red);
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
-    const float t = s[pb] + __shfl_xor(s[pb], 32);  // the two halves hold different rows of the same column
-    if (kshare == 0 && lane < 32) red[(group * PB + pb) * 32 + lane] = t;
+    const double t = sum[pb] + __shfl_xor(sum[pb], 32);
+    if (kshare == 0 && lane < 32) sums[(group * PB + pb) * 32 + lane] = t;
   }
   __syncthreads();
   if ((int)threadIdx.x < PB * 32) {
-    float t = 0.0f;
-    for (int g = 0; g < groups; ++g) t += red[g * PB * 32 + threadIdx.x];
-    part[(int64_t)blockIdx.x * (PB * 32) + threadIdx.x] = t;
+    double t = 0.0;
+    for (int g = 0; g < groups; ++g) t += sums[g * PB * 32 + threadIdx.x];
+    float* dst = part + (int64_t)blockIdx.x * 2 * (PB * 32) + threadIdx.x;
+    dst[0] = (float)t;
+    dst[PB * 32] = (float)(t - (double)(float)t);
   }
 }
 
@@ -437,19 +457,22 @@ __global__ __launch_bounds__(kBlock) void hutch_finish(const float* __restrict__
 
 static int probe_blocks(int64_t pg) { return pg <= 32 ? 1 : 2; }
 
+constexpr int64_t kBlockSums = (int64_t)kNumCU * 4;
+
 // workgroups of one pass: a few per CU, every lane accumulating at most 256 row blocks in fp32
 static int64_t hutch_grid(int64_t M, int pb) {
   const int64_t nblk = (M + 31) >> 5;
   (void)pb;
-  int64_t g = (int64_t)kNumCU * 4;
+  int64_t g = kBlockSums;
   if (g > nblk) g = nblk;
   const int64_t need = (nblk + 255) / 256;
   return g > need ? g : need;
 }
 
 // How a pass is laid out: ks waves per row block, `groups` row blocks per workgroup, `grid` workgroups
-// (one per CU at a time, what the LDS allows) that make `iters` trips.  grid never exceeds hutch_grid, which
-// the workspace is sized for, and no lane accumulates more than 256 row blocks in fp32.
+// (one per CU at a time, what the LDS allows) that make `iters` trips.
+// The workspace holds hutch_grid rows of 64 floats: up to kBlockSums row blocks it has one for each of them, above
+// that at least kBlockSums, two for each of the kNumCU workgroups.
 // The layout with the least estimated time is taken: a trip costs the 128-k blocks of a wave times what one
 // takes, 1.4 us (its own latencies) plus 0.7 us for every wave of the CU (the memory rate they share) -- from
 // 16384 x 4096 in four and in eight waves per CU, 67 and 55 us -- and 1 us for adding the shares.
@@ -468,11 +491,9 @@ static SignsPlan plan_signs(int64_t M, int64_t K) {
       p.groups = groups;
       const int64_t items = (nblk + groups - 1) / groups;
       p.grid = items < kNumCU ? items : kNumCU;
-      if (p.grid < (items + 255) / 256) p.grid = (items + 255) / 256;
       p.iters = (int)((items + p.grid - 1) / p.grid);
-      const double rounds = (double)((p.grid + kNumCU - 1) / kNumCU) * p.iters;
       const double per = (double)((nb + ks - 1) / ks);
-      const double cost = rounds * (per * (1.4 + 0.7 * ks * groups) + 1.0);
+      const double cost = p.iters * (per * (1.4 + 0.7 * ks * groups) + 1.0);
       if (least == 0.0 || cost < least) {
         least = cost;
         best = p;
@@ -535,16 +556,20 @@ static int run_hutchinson(const float* x, int64_t M, int64_t K, const float* v, 
   for (int64_t p0 = 0; p0 < P; p0 += kProbeGroup) {
     const int64_t pg = P - p0 < kProbeGroup ? P - p0 : kProbeGroup;
     const int pb = probe_blocks(pg);
-    unsigned g;
+    int64_t sums;  // rows of part
     if (signs) {
       const SignsPlan pl = plan_signs(M, K);
-      g = (unsigned)pl.grid;
+      const int64_t nblk = (M + 31) >> 5;
+      const int per_block = nblk <= kBlockSums;
+      sums = per_block ? nblk : 2 * pl.grid;
       const Signs sg = {seed, stream_id, (unsigned long long)p0};
+      const unsigned g = (unsigned)pl.grid;
       const int threads = pl.ks * pl.groups * 64, lds = signs_lds(pl.ks, pl.groups);
-      if (pb == 1) hutch_signs_k<1><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, part);
-      else hutch_signs_k<2><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, part);
+      if (pb == 1) hutch_signs_k<1><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, per_block, part);
+      else hutch_signs_k<2><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, per_block, part);
     } else {
-      g = (unsigned)hutch_grid(M, pb);
+      const unsigned g = (unsigned)hutch_grid(M, pb);
+      sums = g;
       const float* vp = v + p0 * K;
 #define MPQ_HUTCH(PB_)                                                                     \
   (vec ? hutch_k<PB_, true><<<g, kHW * 64, 0, st>>>(x, M, K, vp, pg, part)                 \
@@ -553,7 +578,7 @@ static int run_hutchinson(const float* x, int64_t M, int64_t K, const float* v, 
       else MPQ_HUTCH(2);
 #undef MPQ_HUTCH
     }
-    hutch_finish<<<(unsigned)pg, kBlock, 0, st>>>(part, (int)g, pb * 32, quad_out + p0);
+    hutch_finish<<<(unsigned)pg, kBlock, 0, st>>>(part, (int)sums, pb * 32, quad_out + p0);
   }
   return launch_status();
 }

@@ -1,6 +1,7 @@
 """mpq_hutchinson_quad_signs where its layout changes: rows around the 32-row block, k around the 128-k block and
 no multiple of it (sign words cut out of two Philox blocks), 1 to 8 waves sharing k, several trips per
-workgroup, both probe widths and several passes; and the exactness of the three-way split."""
+workgroup with a ragged last one, both probe widths and several passes; the exactness of the three-way split;
+and sums over the rows in double."""
 import numpy as np
 import pytest
 
@@ -22,6 +23,32 @@ def test_layouts(mkp):
     got = host(mpq.hutchinson_quad_signs(dev(x), 7, 3, P))
     # exact products; sums of K terms and of M squares in fp32: far below 1e-5 of a sum of squares
     np.testing.assert_allclose(got, want(x, v), rtol=1e-5)
+
+
+# grid times row blocks per workgroup is 2048 at most, so these take two trips or more whatever the layout, the
+# last one partly past M: k in whole 128-k blocks and not, one probe block and two; a K long enough for 8 waves each
+@pytest.mark.parametrize("mkp", [(70001, 512, 33), (70001, 80, 5), (66000, 208, 64), (35003, 4096, 3)])
+def test_several_trips(mkp):
+    import torch
+    M, K, P = mkp
+    x = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(113), device="cuda")
+    v = mpq.rademacher(7, 3, P, K).double().t().contiguous()
+    exact = torch.zeros(P, dtype=torch.float64, device="cuda")
+    for r in range(0, M, 8192):
+        exact += (x[r:r + 8192].double() @ v).square().sum(0)
+    got = mpq.hutchinson_quad_signs(x, 7, 3, P)
+    # products exact, sums over k of one row in fp32: relative 2^-24 sqrt(K) of a row's, far less of their sum
+    np.testing.assert_allclose(host(got), host(exact), rtol=1e-7)
+
+
+@pytest.mark.parametrize("M", [16384, 9001, 40007])
+def test_row_blocks_are_added_in_double(M):
+    """2^24 in the first 32 rows, 1 in each 32 after them: whole numbers that an fp32 running sum would drop."""
+    x = np.zeros((M, 16), np.float32)
+    x[::32, 3] = 1.0
+    x[0, 3] = 4096.0
+    blocks = (M + 31) // 32
+    np.testing.assert_array_equal(host(mpq.hutchinson_quad_signs(dev(x), 5, 0, 40)), np.full(40, 2.0 ** 24 + blocks - 1))
 
 
 def test_the_split_is_exact_over_the_exponent_range():
