@@ -193,9 +193,10 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
 // a block is what one Philox call per lane serves (four words, each half of a lane pair takes 16 bits of
 // each), or two where K is no multiple of 128 and a probe's blocks straddle Philox blocks.
 //
-// us with the finishing kernel, fp32 steps against this: 16384 x 4096 32 probes 77 -> 55 (4.9 TB/s), 64 probes
-// 110 -> 64; 16384 x 2048 42 -> 30; 70000 x 512 51 -> 34; 9000 x 2064 46 -> 35; 1000 x 4096 31 -> 19.  Below about
-// 100 K elements both are launch and latency (64 x 128 6.3 -> 7.2).  Error against 64 bits 5e-9 (was 7e-9).
+// us with the finishing kernel, fp32 steps against this: 16384 x 4096 32 probes 77 -> 54 (5.0 TB/s), 64 probes
+// 110 -> 63; 16384 x 2048 42 -> 28; 70000 x 512 44 -> 31; 9000 x 2064 36 -> 33; 1000 x 4096 30 -> 19; 16384 x 64
+// 7.7 -> 7.0.  Below about 100 K elements both are launch and latency: 64 x 512 8.8 -> 7.7, 64 x 64 6.2 -> 6.3, and
+// 64 x 128, whose four tiles are one wave's, 6.3 -> 7.0.
 // =====================================================================================================
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
@@ -317,8 +318,12 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     }
   };
   static_assert(kRing == 4, "tile t of a 128-k block lives in ring slot t");
+  // (a wave whose only block is cut off by K requests and multiplies the tiles in front of K alone: there the
+  // kernel is latency from end to end: 64 x 64 7.5 -> 6.4 us with the finishing kernel's shorter reduction)
+  const int cut = rq_left == 1 && K < ((int64_t)kshare + 1) * 128 ? (int)((K - (int64_t)kshare * 128 + 31) >> 5) : 4;
 #pragma unroll 1
-  for (unsigned t = 0; t < kRing; ++t) request(t);
+  for (int t = 0; t < cut; ++t) request((unsigned)t);
+  if (cut < 4) rq_left = 0;
 
   double sum[PB];
 #pragma unroll
@@ -358,7 +363,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
         }
       }
 #pragma unroll 1
-      for (int t = 0; t < 4; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
+      for (int t = 0; t < cut; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
         // all but the youngest three tiles; in the wave's last block no younger ones follow
         if (rq_left > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kRing - 1) * 4) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -444,15 +449,13 @@ __global__ __launch_bounds__(kBlock) void hutch_finish(const float* __restrict__
                                                        double* __restrict__ quad) {
   const int p = blockIdx.x;
   double t = 0.0;
+#pragma unroll 4
   for (int b = threadIdx.x; b < nblocks; b += kBlock) t += (double)part[(int64_t)b * width + p];
-  __shared__ double sm[kBlock];
-  sm[threadIdx.x] = t;
+  t = wave_sum(t);
+  __shared__ double sm[kBlock / kWave];
+  if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = t;
   __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sm[threadIdx.x] += sm[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) quad[p] = sm[0];
+  if (threadIdx.x == 0) quad[p] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
 }
 
 static int probe_blocks(int64_t pg) { return pg <= 32 ? 1 : 2; }
