@@ -126,37 +126,36 @@ __global__ __launch_bounds__(kColWaves * kWave) void absmax_cols(const float* __
   const int wave = threadIdx.x / kWave;
   const int64_t row_step = (int64_t)gridDim.y * kColWaves;
   const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
-  for (int64_t group = blockIdx.x; group * (kWave * 4) < cols; group += gridDim.x) {
-    const int64_t c = (group * kWave + lane) * 4;
-    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c + 4 <= cols) {
+  const int64_t group = block_index();
+  if (group * (kWave * 4) >= cols) return;  // the whole workgroup
+  const int64_t c = (group * kWave + lane) * 4;
+  float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c + 4 <= cols) {
 #pragma unroll 4
-      for (int64_t r = r_first; r < rows; r += row_step) {
-        const float4 a = load_stream(x + r * cols + c);
-        m.x = fmaxf(m.x, fabsf(a.x)); m.y = fmaxf(m.y, fabsf(a.y));
-        m.z = fmaxf(m.z, fabsf(a.z)); m.w = fmaxf(m.w, fabsf(a.w));
-      }
-    } else if (c < cols) {
-      const int live = (int)(cols - c);  // 1 .. 3
-#pragma unroll 4
-      for (int64_t r = r_first; r < rows; r += row_step) {
-        const float* p = x + r * cols + c;
-        m.x = fmaxf(m.x, fabsf(p[0]));
-        m.y = fmaxf(m.y, fabsf(p[live > 1 ? 1 : 0]));
-        m.z = fmaxf(m.z, fabsf(p[live > 2 ? 2 : 0]));
-      }
+    for (int64_t r = r_first; r < rows; r += row_step) {
+      const float4 a = load_stream(x + r * cols + c);
+      m.x = fmaxf(m.x, fabsf(a.x)); m.y = fmaxf(m.y, fabsf(a.y));
+      m.z = fmaxf(m.z, fabsf(a.z)); m.w = fmaxf(m.w, fabsf(a.w));
     }
-    __shared__ float4 sm[kColWaves][kWave];
-    sm[wave][lane] = m;
-    __syncthreads();
-    const int64_t col = group * (kWave * 4) + threadIdx.x;
-    if (threadIdx.x < kWave * 4 && col < cols) {
-      float t = 0.0f;
+  } else if (c < cols) {
+    const int live = (int)(cols - c);  // 1 .. 3
+#pragma unroll 4
+    for (int64_t r = r_first; r < rows; r += row_step) {
+      const float* p = x + r * cols + c;
+      m.x = fmaxf(m.x, fabsf(p[0]));
+      m.y = fmaxf(m.y, fabsf(p[live > 1 ? 1 : 0]));
+      m.z = fmaxf(m.z, fabsf(p[live > 2 ? 2 : 0]));
+    }
+  }
+  __shared__ float4 sm[kColWaves][kWave];
+  sm[wave][lane] = m;
+  __syncthreads();
+  const int64_t col = group * (kWave * 4) + threadIdx.x;
+  if (threadIdx.x < kWave * 4 && col < cols) {
+    float t = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kColWaves; ++w) t = fmaxf(t, reinterpret_cast<const float*>(sm[w])[threadIdx.x]);
-      atomicMax(out + col, abs_key(t));
-    }
-    __syncthreads();  // sm is free again
+    for (int w = 0; w < kColWaves; ++w) t = fmaxf(t, reinterpret_cast<const float*>(sm[w])[threadIdx.x]);
+    atomicMax(out + col, abs_key(t));
   }
 }
 
@@ -225,7 +224,7 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
     int64_t gy = ((int64_t)kNumCU * 2 + gx - 1) / gx;
     const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
     if (gy > max_gy) gy = max_gy;
-    const dim3 grid(blocks_x(gx, kColWaves * kWave), (unsigned)gy);
+    const dim3 grid = wide_grid(gx, kColWaves * kWave, (unsigned)gy);
     absmax_cols<<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, out);
   }
   return launch_status();

@@ -85,6 +85,11 @@ inline unsigned flat_grid(int64_t units, int64_t units_per_trip, int blocks_per_
   return (unsigned)((trips + r - 1) / r);
 }
 
+// Grid of `want` workgroups of `threads`, in x and, past what x can count, in z (block_index, launch_shapes.hpp).
+inline dim3 wide_grid(int64_t want, int threads, unsigned y = 1) {
+  return dim3(blocks_x(want, threads), y, blocks_z(want, threads));
+}
+
 // A tensor this small is reduced by ONE workgroup of kOneBlock threads that writes the result itself: a second
 // launch costs the host 4.3 us and the GPU 2.5-3, more than one CU needs for these reads.  (n: elements;
 // the limits are where one CU still beats the two launches, measured at each kernel.)
@@ -92,6 +97,9 @@ constexpr int kOneBlock = 1024;
 
 // ---- device side ---------------------------------------------------------------------------
 #if defined(__HIPCC__)
+
+// number of this workgroup in a wide_grid (may exceed what was wanted)
+__device__ __forceinline__ int64_t block_index() { return (int64_t)blockIdx.z * gridDim.x + blockIdx.x; }
 
 __device__ __forceinline__ float f_from_bits(int v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ int bits_from_f(float v) { return __builtin_bit_cast(int, v); }

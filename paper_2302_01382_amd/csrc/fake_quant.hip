@@ -145,28 +145,27 @@ __global__ __launch_bounds__(kBlock) void fq_rows(const float* __restrict__ x, i
                                                   float* __restrict__ y, int8_t* __restrict__ codes,
                                                   uint8_t* __restrict__ packed) {
   const int lane = threadIdx.x & (kWave - 1);
-  for (int64_t item = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; item < rows * nseg;
-       item += (int64_t)gridDim.x * (kBlock / kWave)) {
-    const int64_t r = item / nseg, seg = item - r * nseg;
-    const int64_t c0 = seg * kSeg;
-    const int64_t c1 = (c0 + kSeg < cols) ? c0 + kSeg : cols;
-    const QConst c = make_qconst(absmax[r], bits);
-    const int64_t base = r * cols;
-    int64_t i = base + c0 + 4 * lane;
-    const int64_t end = base + c1;
-    constexpr int64_t kStep = 4 * kWave;  // columns a wave covers per load
-    for (; i + 3 * kStep + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
-      const float4 v0 = load_stream(x + i), v1 = load_stream(x + i + kStep), v2 = load_stream(x + i + 2 * kStep),
-                   v3 = load_stream(x + i + 3 * kStep);
-      emit4(v0, c, i, y, codes, packed);
-      emit4(v1, c, i + kStep, y, codes, packed);
-      emit4(v2, c, i + 2 * kStep, y, codes, packed);
-      emit4(v3, c, i + 3 * kStep, y, codes, packed);
-    }
-    for (; i + 4 <= end; i += kStep) emit4(load_stream(x + i), c, i, y, codes, packed);
-    // the last cols % 4 elements of the row (an even number, starting on an even one, whenever packed != null)
-    if (lane == 0 && (c1 & 3)) emit_tail(x, c, c, c, end - (c1 & 3), (int)(c1 & 3), y, codes, packed);
+  const int64_t item = block_index() * (kBlock / kWave) + threadIdx.x / kWave;
+  if (item >= rows * nseg) return;
+  const int64_t r = item / nseg, seg = item - r * nseg;
+  const int64_t c0 = seg * kSeg;
+  const int64_t c1 = (c0 + kSeg < cols) ? c0 + kSeg : cols;
+  const QConst c = make_qconst(absmax[r], bits);
+  const int64_t base = r * cols;
+  int64_t i = base + c0 + 4 * lane;
+  const int64_t end = base + c1;
+  constexpr int64_t kStep = 4 * kWave;  // columns a wave covers per load
+  for (; i + 3 * kStep + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
+    const float4 v0 = load_stream(x + i), v1 = load_stream(x + i + kStep), v2 = load_stream(x + i + 2 * kStep),
+                 v3 = load_stream(x + i + 3 * kStep);
+    emit4(v0, c, i, y, codes, packed);
+    emit4(v1, c, i + kStep, y, codes, packed);
+    emit4(v2, c, i + 2 * kStep, y, codes, packed);
+    emit4(v3, c, i + 3 * kStep, y, codes, packed);
   }
+  for (; i + 4 <= end; i += kStep) emit4(load_stream(x + i), c, i, y, codes, packed);
+  // the last cols % 4 elements of the row (an even number, starting on an even one, whenever packed != null)
+  if (lane == 0 && (c1 & 3)) emit_tail(x, c, c, c, end - (c1 & 3), (int)(c1 & 3), y, codes, packed);
 }
 
 // ---- per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4) ----------------
@@ -177,18 +176,18 @@ __global__ __launch_bounds__(kBlock) void fq_cols(const float* __restrict__ x, i
                                                   uint8_t* __restrict__ packed) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  for (int64_t c = ((int64_t)blockIdx.x * kWave + lane) * 4; c < cols; c += (int64_t)gridDim.x * (kWave * 4)) {
-    const int live = c + 4 <= cols ? 4 : (int)(cols - c);
-    const QConst k0 = make_qconst(absmax[c], bits), k1 = make_qconst(absmax[live > 1 ? c + 1 : c], bits),
-                 k2 = make_qconst(absmax[live > 2 ? c + 2 : c], bits), k3 = make_qconst(absmax[live > 3 ? c + 3 : c], bits);
-    const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
-    const int64_t r0 = (int64_t)blockIdx.y * (kBlock / kWave) + wave;
-    if (live == 4) {
+  const int64_t c = (block_index() * kWave + lane) * 4;
+  if (c >= cols) return;
+  const int live = c + 4 <= cols ? 4 : (int)(cols - c);
+  const QConst k0 = make_qconst(absmax[c], bits), k1 = make_qconst(absmax[live > 1 ? c + 1 : c], bits),
+               k2 = make_qconst(absmax[live > 2 ? c + 2 : c], bits), k3 = make_qconst(absmax[live > 3 ? c + 3 : c], bits);
+  const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
+  const int64_t r0 = (int64_t)blockIdx.y * (kBlock / kWave) + wave;
+  if (live == 4) {
 #pragma unroll 4
-      for (int64_t r = r0; r < rows; r += row_step) emit4(load4(x + r * cols + c), k0, k1, k2, k3, r * cols + c, y, codes, packed);
-    } else {
-      for (int64_t r = r0; r < rows; r += row_step) emit_tail(x, k0, k1, k2, r * cols + c, live, y, codes, packed);
-    }
+    for (int64_t r = r0; r < rows; r += row_step) emit4(load4(x + r * cols + c), k0, k1, k2, k3, r * cols + c, y, codes, packed);
+  } else {
+    for (int64_t r = r0; r < rows; r += row_step) emit_tail(x, k0, k1, k2, r * cols + c, live, y, codes, packed);
   }
 }
 
@@ -212,7 +211,7 @@ int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, cons
     const int64_t nseg = (cols + kSeg - 1) / kSeg;
     const int64_t blocks = (rows * nseg + kBlock / kWave - 1) / (kBlock / kWave);
     if (blocks > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-    fq_rows<<<blocks_x(blocks, kBlock), kBlock, 0, st>>>(x, rows, cols, nseg, absmax, bits, y_out, codes_out, packed4_out);
+    fq_rows<<<wide_grid(blocks, kBlock), kBlock, 0, st>>>(x, rows, cols, nseg, absmax, bits, y_out, codes_out, packed4_out);
   } else {
     const int64_t gx = (cols + kWave * 4 - 1) / (kWave * 4);
     if (gx > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
@@ -226,7 +225,7 @@ int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, cons
     if (gy > max_gy) gy = max_gy;
     if (gy < 1) gy = 1;
     if (gy > 65535) gy = 65535;
-    fq_cols<<<dim3(blocks_x(gx, kBlock), (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
+    fq_cols<<<wide_grid(gx, kBlock, (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
   }
   return launch_status();
 }

@@ -6,12 +6,17 @@
 
 namespace mpq {
 
-// A launch counts its work items per dimension in 32 bits and its workgroups in y in 16.  Kernels whose
-// grid grows with the tensor take at most this many workgroups in x and loop over what is left.
+// A launch counts its work items per dimension in 32 bits and its workgroups in y and z in 16.  A kernel whose
+// grid grows with the tensor takes at most blocks_x workgroups in x and the rest of the `want` in z; the
+// last layer of z may hold more than are left.
 constexpr int64_t kMaxGridY = 65535;
 inline unsigned blocks_x(int64_t want, int threads) {
   const int64_t most = ((int64_t)1 << 31) / threads;
   return (unsigned)(want < most ? want : most);
+}
+inline unsigned blocks_z(int64_t want, int threads) {
+  const int64_t x = blocks_x(want, threads);
+  return (unsigned)((want + x - 1) / x);
 }
 
 // Side of the output tile of qgemm_any: 128 once such tiles fill the chip twice and k is long enough that the loop

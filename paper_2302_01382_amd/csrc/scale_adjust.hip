@@ -196,23 +196,23 @@ __global__ __launch_bounds__(kBlock) void fqs_rows(const float* __restrict__ x, 
                                                    int bits, int64_t seg, float* __restrict__ y,
                                                    int8_t* __restrict__ codes) {
   const int lr = threadIdx.x % LPR;
-  for (int64_t r = (int64_t)blockIdx.x * (kBlock / LPR) + threadIdx.x / LPR; r < rows; r += (int64_t)gridDim.x * (kBlock / LPR)) {
-    const TwoScales t(inv[r], scale[r], bits);
-    const int64_t c0 = (int64_t)blockIdx.y * seg, c1 = c0 + seg < cols ? c0 + seg : cols;
-    const int64_t end = r * cols + c1;
-    constexpr int64_t kStep = 4 * LPR;
-    for (int64_t i = r * cols + c0 + 4 * lr; i + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
-      float4 v[4];
+  const int64_t r = block_index() * (kBlock / LPR) + threadIdx.x / LPR;
+  if (r >= rows) return;
+  const TwoScales t(inv[r], scale[r], bits);
+  const int64_t c0 = (int64_t)blockIdx.y * seg, c1 = c0 + seg < cols ? c0 + seg : cols;
+  const int64_t end = r * cols + c1;
+  constexpr int64_t kStep = 4 * LPR;
+  for (int64_t i = r * cols + c0 + 4 * lr; i + 4 <= end; i += 4 * kStep) {  // four loads in flight per lane
+    float4 v[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i + k * kStep + 4 <= end) v[k] = load_stream(x + i + k * kStep);
+    for (int k = 0; k < 4; ++k)
+      if (i + k * kStep + 4 <= end) v[k] = load_stream(x + i + k * kStep);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i + k * kStep + 4 <= end) fqs_emit4(t, v[k], i + k * kStep, y, codes);
-    }
-    const int64_t e = end - (c1 & 3) + lr;
-    if (e < end) fqs_emit1(t, x[e], e, y, codes);
+    for (int k = 0; k < 4; ++k)
+      if (i + k * kStep + 4 <= end) fqs_emit4(t, v[k], i + k * kStep, y, codes);
   }
+  const int64_t e = end - (c1 & 3) + lr;
+  if (e < end) fqs_emit1(t, x[e], e, y, codes);
 }
 
 // ---- p <- fl32(p - lr * dL/dp), in double, rounded once -----------------------------------------
@@ -252,13 +252,13 @@ extern "C" int mpq_fake_quant_scales(const float* x, int64_t rows, int64_t cols,
   if (gran == MPQ_PER_TENSOR)
     fqs_flat<<<flat_grid((rows * cols) >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, rows * cols, inv, scale, bits, y_out, codes_out);
   else if (cols <= kShortRow)
-    fqs_rows<16><<<blocks_x((rows + 15) / 16, kBlock), kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, cols, y_out, codes_out);
+    fqs_rows<16><<<wide_grid((rows + 15) / 16, kBlock), kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, cols, y_out, codes_out);
   else {
     // few long rows: cut into segments of whole trips (1024 columns a wave) until the chip has its waves
     int64_t nseg = (2048 + rows - 1) / rows;
     if (nseg > (cols + 1023) / 1024) nseg = (cols + 1023) / 1024;
     const int64_t seg = ((cols + nseg - 1) / nseg + 1023) / 1024 * 1024;
-    const dim3 grid(blocks_x((rows + 3) / 4, kBlock), (unsigned)((cols + seg - 1) / seg));
+    const dim3 grid = wide_grid((rows + 3) / 4, kBlock, (unsigned)((cols + seg - 1) / seg));
     fqs_rows<64><<<grid, kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, seg, y_out, codes_out);
   }
   return launch_status();
