@@ -114,21 +114,18 @@ __global__ __launch_bounds__(kBlock) void qe_finish_planes(const double* __restr
                                                            double* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   __shared__ double sm[kBlock / kWave][kWave];
-  for (int64_t k0 = (int64_t)blockIdx.x * kWave; k0 < nch * nb; k0 += (int64_t)gridDim.x * kWave) {
-    const int64_t k = k0 + lane;
-    const bool live = k < nch * nb;
-    double a = 0.0;
-    if (live) {
-      const int64_t ch = k / nb;
-      const double* src = partials + ch * stride_ch + (k - ch * nb);
+  const int64_t k = block_index() * kWave + lane;
+  const bool live = k < nch * nb;
+  double a = 0.0;
+  if (live) {
+    const int64_t ch = k / nb;
+    const double* src = partials + ch * stride_ch + (k - ch * nb);
 #pragma unroll 8
-      for (int64_t p = wave; p < np; p += kBlock / kWave) a += src[p * stride_p];
-    }
-    sm[wave][lane] = a;
-    __syncthreads();
-    if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
-    __syncthreads();  // sm is free again
+    for (int64_t p = wave; p < np; p += kBlock / kWave) a += src[p * stride_p];
   }
+  sm[wave][lane] = a;
+  __syncthreads();
+  if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
 }
 
 // ---- per row: one wave per (row, segment) ------------------------------------------------------
@@ -215,79 +212,190 @@ __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ 
 // ---- per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4); the workgroup's 8
 // waves take interleaved rows and meet in LDS ----
 // Two workgroups per CU, so that there are few partials to fold; 12288 x 768 with the
-// finishing kernel: 117 -> 27 us (16384 x 64: 128 -> 16).
+// finishing kernel: 117 -> 27 us (16384 x 64: 128 -> 16).  half: rows a lane adds in fp32 before its sums
+// go to double, at least half of its rows (the second part's way through LDS costs 12288 x 768 2.8 us of 30).
 // partials: double [gridDim.y][cols][NB]
 constexpr int kColWaves = 8;
 template <int NB>
 __global__ __launch_bounds__(kColWaves * kWave, 4) void qe_cols(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, const float* __restrict__ absmax,
-                                                  int b_lo, double* __restrict__ partials) {
+                                                  int b_lo, int64_t half, double* __restrict__ partials) {
   constexpr int CPL = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
+  const int64_t group = block_index();
+  if (group * (kWave * CPL) >= cols) return;  // the whole workgroup
   __shared__ float lds[kColWaves * kWave * (CPL * NB + 1)];
-  for (int64_t group = blockIdx.x; group * (kWave * CPL) < cols; group += gridDim.x) {
-    const int64_t c = (group * kWave + lane) * CPL;
-    const int live = c + CPL <= cols ? CPL : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
-    // The 2 NB constants of a column cost a division each: the workgroup shares the divisions of its 256
-    // columns through LDS instead of every wave forming those of its four (56 divisions per lane).
-    constexpr int CST = 2 * NB + 1;  // constants of a column: 2 NB, padded to an odd pitch
-    static_assert(kWave * CPL * CST <= kColWaves * kWave * (CPL * NB + 1), "the constants fit where the sums go");
-    for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
-      const int cl = i / NB, b = i - cl * NB;
-      const int64_t cc = group * (kWave * CPL) + cl;
-      float sc = 0.0f, inv = 0.0f;
-      if (cc < cols) bit_constants(absmax[cc], b_lo + b, sc, inv);
-      lds[cl * CST + b] = inv;
-      lds[cl * CST + NB + b] = sc;
-    }
-    __syncthreads();
-    Sweep<NB> s[CPL];
+  const int64_t c = (group * kWave + lane) * CPL;
+  const int live = c + CPL <= cols ? CPL : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
+  // The 2 NB constants of a column cost a division each: the workgroup shares the divisions of its 256
+  // columns through LDS instead of every wave forming those of its four (56 divisions per lane).
+  constexpr int CST = 2 * NB + 1;  // constants of a column: 2 NB, padded to an odd pitch
+  static_assert(kWave * CPL * CST <= kColWaves * kWave * (CPL * NB + 1), "the constants fit where the sums go");
+  for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
+    const int cl = i / NB, b = i - cl * NB;
+    const int64_t cc = group * (kWave * CPL) + cl;
+    float sc = 0.0f, inv = 0.0f;
+    if (cc < cols) bit_constants(absmax[cc], b_lo + b, sc, inv);
+    lds[cl * CST + b] = inv;
+    lds[cl * CST + NB + b] = sc;
+  }
+  __syncthreads();
+  Sweep<NB> s[CPL];
 #pragma unroll
-    for (int k = 0; k < CPL; ++k) {
-      s[k].m = k < live ? absmax[c + k] : 0.0f;
+  for (int k = 0; k < CPL; ++k) {
+    s[k].m = k < live ? absmax[c + k] : 0.0f;
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        s[k].inv[b] = lds[(lane * CPL + k) * CST + b];
-        s[k].sc[b] = lds[(lane * CPL + k) * CST + NB + b];
-        s[k].acc[b] = 0.0f;
-      }
+    for (int b = 0; b < NB; ++b) {
+      s[k].inv[b] = lds[(lane * CPL + k) * CST + b];
+      s[k].sc[b] = lds[(lane * CPL + k) * CST + NB + b];
+      s[k].acc[b] = 0.0f;
     }
-    __syncthreads();  // the sums go where the constants were
-    const int64_t row_step = (int64_t)gridDim.y * kColWaves;
-    const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
+  }
+  __syncthreads();  // the sums go where the constants were
+  const int64_t row_step = (int64_t)gridDim.y * kColWaves;
+  const int64_t r_first = (int64_t)blockIdx.y * kColWaves + wave;
+  // two parts: the first one's sums wait in LDS, each lane's in its own place, until the second is done
+  const bool two_parts = rows > half * row_step;
+  float (*sm)[kWave][CPL * NB + 1] = reinterpret_cast<float (*)[kWave][CPL * NB + 1]>(lds);
+  auto add_rows = [&](int64_t r, int64_t r_end) {
     if (live == CPL) {
 #pragma unroll 2
-      for (int64_t r = r_first; r < rows; r += row_step) {
-        const float4 v = load_stream(x + r * cols + c);
-        s[0].add(v.x); s[1].add(v.y); s[2].add(v.z); s[3].add(v.w);
+      for (; r < r_end; r += row_step) {
+        const float4 u = load_stream(x + r * cols + c);
+        s[0].add(u.x); s[1].add(u.y); s[2].add(u.z); s[3].add(u.w);
       }
     } else if (live > 0) {
 #pragma unroll 2
-      for (int64_t r = r_first; r < rows; r += row_step) {
+      for (; r < r_end; r += row_step) {
         const float* p = x + r * cols + c;
         const float v0 = p[0], v1 = live > 1 ? p[1] : 0.0f, v2 = live > 2 ? p[2] : 0.0f;
         s[0].add(v0); s[1].add(v1); s[2].add(v2);
       }
     }
-    float (*sm)[kWave][CPL * NB + 1] = reinterpret_cast<float (*)[kWave][CPL * NB + 1]>(lds);
+  };
+  auto put_sums = [&]() {
 #pragma unroll
     for (int k = 0; k < CPL; ++k)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) sm[wave][lane][k * NB + b] = s[k].acc[b];
+      for (int b = 0; b < NB; ++b) {
+        sm[wave][lane][k * NB + b] = s[k].acc[b];
+        s[k].acc[b] = 0.0f;
+      }
+  };
+  if (two_parts) {
+    add_rows(r_first, r_first + half * row_step < rows ? r_first + half * row_step : rows);
+    put_sums();
+    add_rows(r_first + half * row_step, rows);
+  } else {
+    add_rows(r_first, rows);
+  }
+  constexpr int VO = (kWave * CPL * NB + kColWaves * kWave - 1) / (kColWaves * kWave);  // sums a thread adds up
+  double v[VO] = {};
+  auto add_waves = [&]() {
     __syncthreads();
-    // the workgroup's 256 columns x NB sums are consecutive in the plane of partials
-    const int64_t left = (cols - group * (kWave * CPL)) * NB;
-    double* dst = partials + ((int64_t)blockIdx.y * cols + group * (kWave * CPL)) * NB;
-    for (int i = threadIdx.x; i < kWave * CPL * NB; i += kColWaves * kWave) {
-      if (i >= left) break;
-      const int l = i / (CPL * NB), j = i - l * (CPL * NB);
-      double v = 0.0;
 #pragma unroll
-      for (int w = 0; w < kColWaves; ++w) v += (double)sm[w][l][j];
-      dst[i] = v;
+    for (int o = 0; o < VO; ++o) {
+      const int i = threadIdx.x + o * (kColWaves * kWave);
+      if (i < kWave * CPL * NB) {
+        const int l = i / (CPL * NB), j = i - l * (CPL * NB);
+#pragma unroll
+        for (int w = 0; w < kColWaves; ++w) v[o] += (double)sm[w][l][j];
+      }
     }
-    __syncthreads();  // the sums are read: the next columns' constants may overwrite them
+  };
+  if (two_parts) {
+    add_waves();
+    __syncthreads();  // read: the second part's sums may overwrite them
+  }
+  put_sums();
+  add_waves();
+  // the workgroup's 256 columns x NB sums are consecutive in the plane of partials
+  const int64_t here = (cols - group * (kWave * CPL)) * NB;
+  double* dst = partials + ((int64_t)blockIdx.y * cols + group * (kWave * CPL)) * NB;
+#pragma unroll
+  for (int o = 0; o < VO; ++o) {
+    const int i = threadIdx.x + o * (kColWaves * kWave);
+    if (i < kWave * CPL * NB && i < here) dst[i] = v[o];
+  }
+}
+
+// ---- per column, few rows: one launch, results written directly ------------------------------------
+// A lane owns a column, the NW waves of a workgroup take interleaved rows and meet in LDS in double.  kOneRows
+// rows of a wave are in flight together; their fp32 sums go to double as a whole, or two by two where one wave
+// has all rows.
+constexpr int kOneRows = 8;
+template <int NB, int NW>
+__global__ __launch_bounds__(NW * kWave) void qe_cols_one(const float* __restrict__ x, int64_t rows, int64_t cols,
+                                                          const float* __restrict__ absmax, int b_lo,
+                                                          double* __restrict__ out) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  __shared__ double sm[NW][kWave * NB];
+  const int64_t c0 = block_index() * kWave;
+  if (c0 >= cols) return;  // the whole workgroup
+  const int64_t c = c0 + lane < cols ? c0 + lane : cols - 1;  // lanes past the edge: result discarded
+  const float* xc = x + c;
+  float v[kOneRows];
+  auto fetch = [&](int64_t r) {
+#pragma unroll
+    for (int u = 0; u < kOneRows; ++u)
+      if (r + u * NW < rows) v[u] = xc[(r + u * NW) * cols];  // wave-uniform
+  };
+  fetch(wave);
+  Sweep<NB> s;
+  if (NW == 1) {
+    s.init(absmax[c], b_lo);
+  } else {  // the workgroup shares the divisions of its 64 columns
+    float* k = reinterpret_cast<float*>(sm[0]);
+    for (int i = threadIdx.x; i < kWave * NB; i += NW * kWave) {
+      const int cl = i / NB;
+      float sc = 0.0f, inv = 0.0f;
+      if (c0 + cl < cols) bit_constants(absmax[c0 + cl], b_lo + i - cl * NB, sc, inv);
+      k[2 * i] = inv;
+      k[2 * i + 1] = sc;
+    }
+    __syncthreads();
+    s.m = absmax[c];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      s.inv[b] = k[2 * (lane * NB + b)];
+      s.sc[b] = k[2 * (lane * NB + b) + 1];
+      s.acc[b] = 0.0f;
+    }
+    __syncthreads();  // the sums go where the constants were
+  }
+  double a[NB] = {};
+  auto flush = [&]() {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      a[b] += (double)s.acc[b];
+      s.acc[b] = 0.0f;
+    }
+  };
+  for (int64_t r = wave; r < rows; r += kOneRows * NW) {
+#pragma unroll
+    for (int u = 0; u < kOneRows; ++u) {
+      if (r + u * NW < rows) s.add(v[u]);
+      if (u == kOneRows - 1 || (NW == 1 && (u & 1))) flush();
+    }
+    fetch(r + kOneRows * NW);
+  }
+  if (NW == 1) {
+    if (c0 + lane < cols) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) out[c * NB + b] = a[b];
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) sm[wave][lane * NB + b] = a[b];
+    __syncthreads();
+    const int64_t here = (cols - c0) * NB;
+    for (int i = threadIdx.x; i < kWave * NB && i < here; i += NW * kWave) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) t += sm[w][i];
+      out[c0 * NB + i] = t;
+    }
   }
 }
 
@@ -342,6 +450,8 @@ __global__ __launch_bounds__(kOneBlock) void sse_pair_one(const float* __restric
 // ---- launch geometry, shared by the workspace queries and the launchers --------------------------
 struct QeGeom {
   unsigned gx = 1, gy = 1;
+  int64_t cols_x = 1;  // per column: workgroups along the columns
+  int64_t half = 1;  // per column: rows a lane adds in fp32
   int64_t nseg = 1;
   int64_t partial_doubles = 0;  // doubles of workspace
 };
@@ -379,10 +489,24 @@ static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb) {
     const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
     if (gy > max_gy) gy = max_gy;
     if (gy > r4) gy = r4;
-    g.gx = blocks_x(gx, kColWaves * kWave);
+    g.cols_x = gx;
     g.gy = (unsigned)gy;
+    const int64_t lane_rows = (rows + gy * kColWaves - 1) / (gy * kColWaves);
+    // ... added in fp32 by a lane: no more than with one of the reserved row chunks per four waves
+    const int64_t waves = 4 * ((cols & 3) == 0 ? r4 : r1), most = (rows + waves - 1) / waves;
+    g.half = lane_rows <= most ? most : (lane_rows + 1) / 2;
   }
   return g;
+}
+
+// Waves of a workgroup of qe_cols_one, 0 where qe_cols and its finishing kernel are faster (groups: of 64 columns).
+// us for seven widths, 1 | 4 | 16 waves / two launches: 8 x 4096 3.2 | 3.5 | 3.6 / 7.1, 32 x 4096 5.7 | 3.8 | 4.0 / 8.5,
+// 64 x 300001 25.9 | 30.3 | 61 / 60, 64 x 65536 11.6 | 8.0 | 14.5 / 18, 256 x 101 28.8 | 9.5 | 5.9 / 7.3, 512 x 16384
+// 59 | 20 | 10.4 / 20, 512 x 64 - | 16 | 8.8 / 9, 1000 x 64 - | 30 | 14.5 / 8, 1000 x 4096 - | 31 | 15.3 / 16.
+static int qe_cols_waves(int64_t rows, int64_t groups) {
+  if (rows <= 8 || (rows <= 64 && groups >= 2048)) return 1;
+  if (rows <= 32 || (rows <= 512 && groups >= 512)) return 4;
+  return rows <= 512 ? 16 : 0;
 }
 
 template <int NB>
@@ -411,13 +535,26 @@ static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t col
     } else {
       qe_rows<NB><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, ws);
       const int64_t k = rows * NB;
-      qe_finish_planes<<<blocks_x((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
+      qe_finish_planes<<<wide_grid((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, rows, g.nseg, NB, g.nseg * NB, NB, out);
     }
   } else {
-    dim3 grid(g.gx, g.gy);
-    qe_cols<NB><<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, ws);
+    const int64_t groups = (cols + kWave - 1) / kWave;
+    const int nw = qe_cols_waves(rows, groups);
+    if (nw == 16) {
+      qe_cols_one<NB, 16><<<wide_grid(groups, 16 * kWave), 16 * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      return;
+    }
+    if (nw == 4) {
+      qe_cols_one<NB, 4><<<wide_grid(groups, 4 * kWave), 4 * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      return;
+    }
+    if (nw == 1) {
+      qe_cols_one<NB, 1><<<wide_grid(groups, kWave), kWave, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      return;
+    }
+    qe_cols<NB><<<wide_grid(g.cols_x, kColWaves * kWave, g.gy), kColWaves * kWave, 0, st>>>(x, rows, cols, absmax, b_lo, g.half, ws);
     const int64_t k = cols * NB;
-    qe_finish_planes<<<blocks_x((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
+    qe_finish_planes<<<wide_grid((k + kWave - 1) / kWave, kBlock), kBlock, 0, st>>>(ws, cols, (int64_t)g.gy, NB, NB, cols * NB, out);
   }
 }
 

@@ -105,3 +105,27 @@ def test_noise(shape, off, gran):
     inplace = at(x, off)
     mpq.noise_inject(inplace, dev(m), 8, 0.3, 9, 2, gran, out=inplace)
     np.testing.assert_array_equal(host(inplace), want[8])
+
+
+# per column: up to 8, 32 and 512 rows a workgroup of 1, 4 and 16 waves writes the result itself (1 up to 64 rows from
+# 2048 groups of 64 columns on, 4 up to 512 rows from 512 groups on); above, two launches
+@pytest.mark.parametrize("shape", [(1, 65), (8, 130), (9, 63), (32, 129), (33, 64), (512, 70), (513, 70), (64, 131073), (65, 131009),
+                                   (100, 32769), (600, 9)])
+@pytest.mark.parametrize("widths", [(2, 8), (4, 4), (3, 5)])
+def test_sweep_per_column_of_few_rows(shape, widths):
+    x = data(shape, 99)
+    m = oracle.absmax(x, oracle.PER_COL) * np.float32(1.25)     # off the grid: no element's error is a rounding alone
+    for off in (0, 1):
+        got = host(mpq.quant_error(at(x, off), dev(m), *widths, mpq.PER_COL))
+        np.testing.assert_allclose(got, oracle.quant_error(x, m, *widths, oracle.PER_COL), rtol=1e-5)
+
+
+def test_per_column_fp32_sums_stay_short():
+    """Errors of 1/4 in the first rows, of 1/4 2^-13 below: an fp32 sum that holds one of the former drops the
+    squares of the latter.  A lane adds at most max(8, rows * groups of 256 columns / 8192) rows in fp32."""
+    rows, cols = 2 ** 17, 4
+    x = np.full((rows, cols), 0.25 * 2.0 ** -13, np.float32)
+    x[:4096] = 0.25
+    got = host(mpq.quant_error(dev(x), dev(np.ones(cols, np.float32)), 2, 2, mpq.PER_COL))
+    want = oracle.quant_error(x, np.ones(cols, np.float32), 2, 2, oracle.PER_COL)
+    assert np.all(np.abs(got / want - 1) <= (rows / 8192) * 2.0 ** -26)
