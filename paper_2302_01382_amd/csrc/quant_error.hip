@@ -18,6 +18,7 @@
 #include "sweep.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 namespace mpq {
 
@@ -128,8 +129,8 @@ __global__ __launch_bounds__(kBlock) void qe_finish_planes(const double* __restr
   if (wave == 0 && live) out[k] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
 }
 
-// ---- per row: one wave per (row, segment) ------------------------------------------------------
-// dst: nseg == 1 -> out [rows][NB]; else partials [rows][nseg][NB]; same indexing item*NB
+// ---- per row, rows of several segments: one wave per (row, segment) -----------------------------
+// dst: partials [rows][nseg][NB]
 template <int NB>
 __global__ __launch_bounds__(kBlock) void qe_rows(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, int64_t nseg,
@@ -165,7 +166,11 @@ __global__ __launch_bounds__(kBlock) void qe_rows(const float* __restrict__ x, i
 // The 2 NB per-row constants cost a division each; here lane j of a row group computes constant j
 // only and the group shares them through the cross-lane network, and the final sums need 4 DPP
 // steps instead of a full wave reduction.  cols <= kSeg.
-template <int NB, int LPR>
+// PLAN: a tensor that a sweep plan can hold: the sums are formed as the batched kernels form them, so that the two
+// calls agree bit for bit.  Any other: rows start anywhere, so neighbouring vectors share lines, and cached loads
+// beat streaming ones (16384 x 255, 16 lanes: 7.5 / 7.4 us, 300 x 1023, 64 lanes: 4.5 / 3.7, one width of 4000 x 101
+// 2.9 / 2.4); and a lane has a sum per element of a vector, which keeps its fp32 chains at cols / (4 LPR).
+template <int NB, int LPR, bool PLAN>
 __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ x, int64_t rows,
                                                       int64_t cols, const float* __restrict__ absmax,
                                                       int b_lo, double* __restrict__ out) {
@@ -176,35 +181,52 @@ __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ 
   const bool live = r < rows;
   if (!live) r = rows - 1;  // keep every lane active for the cross-lane steps; result discarded
   const float m = absmax[r];
-  // lane j < 7: inv of bit-width b_lo + j; lane 7 + j: scale of bit-width b_lo + j
-  float mine = 0.0f;
-  {
+  const float4* r4 = reinterpret_cast<const float4*>(x + r * cols);
+  const int64_t e4 = cols >> 2;
+  float4 v[4];  // four vectors in flight per lane; those past the row's end are zeros, which add nothing
+  auto load = [&](int64_t i) { return PLAN ? load_stream(r4 + i) : load4(reinterpret_cast<const float*>(r4 + i)); };
+  auto fetch = [&](int64_t i0) {
+    if (i0 + 4 * LPR <= e4) {  // the same for all lanes of the wave
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = load(i0 + k * LPR + lr);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t i = i0 + k * LPR + lr;
+        v[k] = i < e4 ? load(i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
+    }
+  };
+  fetch(0);
+  const float last = lr < (int)(cols & 3) ? x[r * cols + (e4 << 2) + lr] : 0.0f;
+  std::conditional_t<PLAN, Sweep<NB>, Sweep4<NB>> s;
+  if (NB == 1) {
+    s.init(m, b_lo);
+    s.clear();
+  } else {
+    // lane j < 7: inv of bit-width b_lo + j; lane 7 + j: scale of bit-width b_lo + j
     const int j = lr < 7 ? lr : lr - 7;
     float sc, inv;
     bit_constants(m, b_lo + (j < NB ? j : 0), sc, inv);
-    mine = lr < 7 ? inv : sc;
+    const float mine = lr < 7 ? inv : sc;
+    s.m = m;
+    s.clear();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      s.inv[b] = __shfl(mine, b, LPR);
+      s.sc[b] = __shfl(mine, 7 + b, LPR);
+    }
   }
-  Sweep<NB> s;
-  s.m = m;
+  for (int64_t i0 = 0; i0 < e4; i0 += 4 * LPR) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i0 + k * LPR < e4) s.add4(v[k]);
+    if (i0 + 4 * LPR < e4) fetch(i0 + 4 * LPR);
+  }
+  s.add(last);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    s.inv[b] = __shfl(mine, b, LPR);
-    s.sc[b] = __shfl(mine, 7 + b, LPR);
-    s.acc[b] = 0.0f;
-  }
-  const float4* r4 = reinterpret_cast<const float4*>(x + r * cols);
-  const int64_t e4 = cols >> 2;
-  int64_t i = lr;
-  for (; i + 3 * LPR < e4; i += 4 * LPR) {
-    const float4 a = load_stream(r4 + i), b = load_stream(r4 + i + LPR), c = load_stream(r4 + i + 2 * LPR),
-                 d = load_stream(r4 + i + 3 * LPR);
-    s.add4(a); s.add4(b); s.add4(c); s.add4(d);
-  }
-  for (; i < e4; i += LPR) s.add4(load_stream(r4 + i));
-  if (lr < (int)(cols & 3)) s.add(x[r * cols + (e4 << 2) + lr]);
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const float w = LPR == 16 ? row16_sum(s.acc[b]) : wave_sum(s.acc[b]);
+    const float w = LPR == 16 ? row16_sum(s.total(b)) : wave_sum(s.total(b));
     if (lr == 0 && live) out[r * NB + b] = (double)w;
   }
 }
@@ -499,6 +521,14 @@ static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb) {
   return g;
 }
 
+// Rows that no plan holds: 16 lanes per row or a wave?  us, 16 | 64 lanes: 300 x 511 4.4 | 3.2, 1000 x 101 3.1 | 3.1,
+// 1000 x 511 4.5 | 3.3, 4000 x 257 3.6 | 4.6, 4000 x 767 7.1 | 6.8, 16384 x 1023 16.2 | 20.2, 16384 x 2047 26.8 | 28.1; one
+// width 4000 x 257 2.6 | 2.9, 4000 x 511 3.9 | 3.7, 16384 x 511 6.4 | 8.0, 16384 x 1023 12.9 | 12.1.
+static bool qe_rows_short(int64_t rows, int64_t cols, int nb) {
+  if (rows >= 8192) return cols <= (nb < 3 ? 768 : 2048);
+  return cols <= 64 || cols <= rows / 8;
+}
+
 // Waves of a workgroup of qe_cols_one, 0 where qe_cols and its finishing kernel are faster (groups: of 64 columns).
 // us for seven widths, 1 | 4 | 16 waves / two launches: 8 x 4096 3.2 | 3.5 | 3.6 / 7.1, 32 x 4096 5.7 | 3.8 | 4.0 / 8.5,
 // 64 x 300001 25.9 | 30.3 | 61 / 60, 64 x 65536 11.6 | 8.0 | 14.5 / 18, 256 x 101 28.8 | 9.5 | 5.9 / 7.3, 512 x 16384
@@ -520,18 +550,15 @@ static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t col
     qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)g.gx, out);
   } else if (gran == MPQ_PER_ROW) {
     if (g.nseg == 1) {
-      // 16 lanes per row up to 2048 columns (>= 4 vectors per lane from 256 columns on), else a wave.
-      // With fewer than 8192 rows (two waves per SIMD of 16-lane rows) a wave per row is faster from 512
-      // columns on: 3001 x 1147 9.6 -> 6.4 us, 1000 x 1999 14.9 -> 7.6, 300 x 700 6.8 -> 4.4, but 16384 x 1023
-      // 22.2 -> 25.5.  Only for tensors a sweep plan cannot hold: for the others the two calls agree bit for bit.
       const bool plan_holds = (cols & 3) == 0 && aligned16(x);
-      if (cols <= 512 || (cols <= 2048 && (plan_holds || rows >= 8192))) {
-        const int64_t blocks = (rows + 15) / 16;
-        qe_rows_sub<NB, 16><<<(unsigned)blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
-      } else {
-        const int64_t blocks = (rows + 3) / 4;
-        qe_rows_sub<NB, 64><<<(unsigned)blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
-      }
+      // (the batched kernels': 16 lanes per row up to 2048 columns, else a wave)
+      const bool sixteen = plan_holds ? cols <= 2048 : qe_rows_short(rows, cols, NB);
+      const int64_t per = sixteen ? kBlock / 16 : kBlock / kWave;
+      const unsigned blocks = (unsigned)((rows + per - 1) / per);
+      if (plan_holds && sixteen) qe_rows_sub<NB, 16, true><<<blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      else if (plan_holds) qe_rows_sub<NB, 64, true><<<blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      else if (sixteen) qe_rows_sub<NB, 16, false><<<blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
+      else qe_rows_sub<NB, 64, false><<<blocks, kBlock, 0, st>>>(x, rows, cols, absmax, b_lo, out);
     } else {
       qe_rows<NB><<<g.gx, kBlock, 0, st>>>(x, rows, cols, g.nseg, absmax, b_lo, ws);
       const int64_t k = rows * NB;

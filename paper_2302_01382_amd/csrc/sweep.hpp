@@ -28,22 +28,51 @@ struct Sweep {
       acc[b] = 0.0f;
     }
   }
-  __device__ __forceinline__ void add(float v) {
+  __device__ __forceinline__ void add(float v) { add_to(v, acc); }
+  __device__ __forceinline__ void add_to(float v, float (&sum)[NB]) const {
     const float vc = __builtin_amdgcn_fmed3f(v, -m, m);
     if (NB == 7) {
       const float a = __builtin_fabsf(v);
       const float e = __builtin_amdgcn_fmed3f(a, __builtin_fabsf(a - m), 0.0f);  // min of two non-negatives
-      acc[0] = __builtin_fmaf(e, e, acc[0]);
+      sum[0] = __builtin_fmaf(e, e, sum[0]);
     }
 #pragma unroll
     for (int b = (NB == 7 ? 1 : 0); b < NB; ++b) {
       const float t = __builtin_fmaf(vc, inv[b], kMagic);
       const float q = t - kMagic;
       const float e = __builtin_fmaf(q, sc[b], -v);
-      acc[b] = __builtin_fmaf(e, e, acc[b]);
+      sum[b] = __builtin_fmaf(e, e, sum[b]);
     }
   }
   __device__ __forceinline__ void add4(const float4 v) { add(v.x); add(v.y); add(v.z); add(v.w); }
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = 0.0f;
+  }
+  __device__ __forceinline__ float total(int b) const { return acc[b]; }
+};
+
+// With a sum for each of the four elements of a vector: a lane's fp32 chains are as short as with one element
+// per lane and load.
+template <int NB>
+struct Sweep4 : Sweep<NB> {
+  float rest[3][NB];
+  __device__ __forceinline__ void clear() {
+    Sweep<NB>::clear();
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) rest[k][b] = 0.0f;
+  }
+  __device__ __forceinline__ void add4(const float4 v) {
+    this->add(v.x);
+    this->add_to(v.y, rest[0]);
+    this->add_to(v.z, rest[1]);
+    this->add_to(v.w, rest[2]);
+  }
+  __device__ __forceinline__ float total(int b) const {
+    return (this->acc[b] + rest[0][b]) + (rest[1][b] + rest[2][b]);
+  }
 };
 
 }  // namespace mpq

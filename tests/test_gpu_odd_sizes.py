@@ -129,3 +129,34 @@ def test_per_column_fp32_sums_stay_short():
     got = host(mpq.quant_error(dev(x), dev(np.ones(cols, np.float32)), 2, 2, mpq.PER_COL))
     want = oracle.quant_error(x, np.ones(cols, np.float32), 2, 2, oracle.PER_COL)
     assert np.all(np.abs(got / want - 1) <= (rows / 8192) * 2.0 ** -26)
+
+
+# rows that no sweep plan holds: 16 lanes or a wave per row; whole trips of four vectors and every way to fall short
+@pytest.mark.parametrize("shape", [(3, 5), (5, 64), (9, 65), (40, 127), (40, 255), (33, 257), (17, 1021), (17, 1026), (3, 2500), (600, 75),
+                                   (600, 76), (8192, 131), (8191, 1025), (8200, 771), (8200, 2047), (8200, 2050)])
+@pytest.mark.parametrize("widths", [(2, 8), (4, 4), (3, 5)])
+def test_sweep_per_row_at_any_size(shape, widths):
+    """As close to the sums in 64 bits as fp32 sums of 64 lanes, each over every 64th column, that meet in a
+    tree: the random part of the roundings of such sums, with 15 % for the spread of the estimate."""
+    x = data(shape, 100)
+    m = oracle.absmax(x, oracle.PER_ROW) * np.float32(1.25)
+    off = 1 if shape[1] % 4 == 0 else 0
+    got = host(mpq.quant_error(at(x, off), dev(m), *widths, mpq.PER_ROW))
+    want = oracle.quant_error(x, m, *widths, oracle.PER_ROW)
+    np.testing.assert_allclose(got, want, rtol=1e-5)
+    if shape[0] < 2000:
+        return
+    b = widths[1]
+    qmax = np.float32(2 ** (b - 1) - 1)
+    inv, sc = (qmax / m)[:, None], (m / qmax)[:, None]
+    q = np.rint(x.astype(np.float64) * inv)
+    e = (q * sc.astype(np.float64) - x).astype(np.float32)          # one fused multiply-add
+    lanes = np.zeros((shape[0], 64), np.float32)
+    exact = (e.astype(np.float64) ** 2).sum(1)
+    for c in range(0, shape[1], 64):
+        p = e[:, c:c + 64]
+        lanes[:, :p.shape[1]] = (p.astype(np.float64) ** 2 + lanes[:, :p.shape[1]]).astype(np.float32)
+    while lanes.shape[1] > 1:
+        lanes = lanes[:, 0::2] + lanes[:, 1::2]
+    rms = np.sqrt(np.mean((lanes[:, 0] / exact - 1) ** 2))
+    assert np.sqrt(np.mean((got[:, -1] / exact - 1) ** 2)) <= 1.15 * rms
