@@ -160,6 +160,16 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Sum over the wave of which only the sixteen lanes of a row are added in fp32 (a tree), the four rows in double.
+__device__ __forceinline__ double wave_sum_rows(float v) {
+  v = row16_sum(v);
+  const float r0 = f_from_bits(__builtin_amdgcn_readlane(bits_from_f(v), 0));
+  const float r1 = f_from_bits(__builtin_amdgcn_readlane(bits_from_f(v), 16));
+  const float r2 = f_from_bits(__builtin_amdgcn_readlane(bits_from_f(v), 32));
+  const float r3 = f_from_bits(__builtin_amdgcn_readlane(bits_from_f(v), 48));
+  return ((double)r0 + (double)r1) + ((double)r2 + (double)r3);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp<kQuadSwap1>(v));
   v = fmaxf(v, dpp<kQuadSwap2>(v));
@@ -262,6 +272,33 @@ __device__ __forceinline__ void for_each_vec4_pair_tiled(const float4* __restric
       }
     }
   }
+}
+
+// The same over tensors that start anywhere, where neighbouring vectors share lines and cached loads beat
+// streaming ones, or that are too small to give every CU a tile: one vector per thread and trip, four trips'
+// loads in flight.  Grid: flat_grid(n, 4 * kBlock).
+template <typename F>
+__device__ __forceinline__ void for_each_vec4_strided(const float* __restrict__ x, int64_t n4, F&& f) {
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  for (; i + 3 * step < n4; i += 4 * step) {
+    const float4 a = load4(x + 4 * i), b = load4(x + 4 * (i + step)), c = load4(x + 4 * (i + 2 * step)),
+                 d = load4(x + 4 * (i + 3 * step));
+    f(a); f(b); f(c); f(d);
+  }
+  for (; i < n4; i += step) f(load4(x + 4 * i));
+}
+template <typename F>
+__device__ __forceinline__ void for_each_vec4_pair_strided(const float* __restrict__ a, const float* __restrict__ b,
+                                                           int64_t n4, F&& f) {
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  for (; i + step < n4; i += 2 * step) {
+    const float4 a0 = load4(a + 4 * i), b0 = load4(b + 4 * i), a1 = load4(a + 4 * (i + step)), b1 = load4(b + 4 * (i + step));
+    f(a0, b0);
+    f(a1, b1);
+  }
+  if (i < n4) f(load4(a + 4 * i), load4(b + 4 * i));
 }
 
 // |x| as an unsigned key: for non-negative floats the bit pattern orders like the value, so an

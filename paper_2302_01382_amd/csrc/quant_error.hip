@@ -26,21 +26,24 @@ constexpr int64_t kSeg = 16384;  // columns per wave item in the per-row kernels
 
 // ---- per tensor ----------------------------------------------------------------------------
 // partials: double [gridDim.x][NB]
-template <int NB>
+// PLAN: a tensor that a sweep plan can hold, summed as the batched kernels do (bit for bit)
+template <int NB, bool PLAN>
 __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, int64_t n,
                                                   const float* __restrict__ absmax, int b_lo,
                                                   double* __restrict__ partials) {
-  Sweep<NB> s;
+  std::conditional_t<PLAN, Sweep<NB>, Sweep4<NB>> s;
   s.init(absmax[0], b_lo);
+  s.clear();
   const int64_t n4 = n >> 2;
-  for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
+  if (PLAN) for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
+  else for_each_vec4_strided(x, n4, [&](const float4 v) { s.add4(v); });
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
   if (blockIdx.x == 0 && j < n) s.add(x[j]);
   __shared__ float sm[kBlock / kWave][NB];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const float w = wave_sum(s.acc[b]);
+    const float w = wave_sum(s.total(b));
     if (lane == 0) sm[wave][b] = w;
   }
   __syncthreads();
@@ -50,32 +53,35 @@ __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, i
         ((double)sm[2][threadIdx.x] + (double)sm[3][threadIdx.x]);
 }
 
-// Up to kOneLimit / NB elements: one workgroup, one launch.  Device time for b = 2..8, two launches against
-// this: 16 x 16 5.2 / 3.3 us, 64 x 128 6.3 / 4.5, 64 x 256 6.5 / 6.0; for one width 128 x 256 4.4 / 2.8.
-constexpr int64_t kOneLimit = 7 * 16384;
+// Up to kOneLimit / NB elements and kOneMost: one workgroup, one launch; a lane has an fp32 sum per element of a
+// vector, and double takes over from rows of sixteen lanes on.  Device time for b = 2..8, two launches against this: 64 x 64 5.7 / 4.6 us, 64 x 128
+// 6.0 / 5.3, 64 x 256 6.1 / 6.2 (and a launch, 4.3 us of the host's time, less); for one width 128 x 256 4.3 / 2.8,
+// 256 x 256 4.3 / 3.7, from 80000 elements on two launches are faster.
+constexpr int64_t kOneLimit = 7 * 16384, kOneMost = 65536;
 template <int NB>
 __global__ __launch_bounds__(kOneBlock) void qe_one(const float* __restrict__ x, int n,
                                                     const float* __restrict__ absmax, int b_lo,
                                                     double* __restrict__ out) {
   constexpr int NW = kOneBlock / kWave;
-  Sweep<NB> s;
+  Sweep4<NB> s;
   s.init(absmax[0], b_lo);
+  s.clear();
   const int n4 = n >> 2;
 #pragma unroll 4
   for (int i = threadIdx.x; i < n4; i += kOneBlock) s.add4(load4(x + 4 * i));
   if ((int)threadIdx.x < (n & 3)) s.add(x[(n & ~3) + threadIdx.x]);
-  __shared__ float sm[NW][NB];
+  __shared__ double sm[NW][NB];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const float w = wave_sum(s.acc[b]);
+    const double w = wave_sum_rows(s.total(b));
     if (lane == 0) sm[wave][b] = w;
   }
   __syncthreads();
   if (threadIdx.x < NB) {
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) t += (double)sm[w][threadIdx.x];
+    for (int w = 0; w < NW; ++w) t += sm[w][threadIdx.x];
     out[threadIdx.x] = t;
   }
 }
@@ -422,49 +428,53 @@ __global__ __launch_bounds__(NW * kWave) void qe_cols_one(const float* __restric
 }
 
 // ---- two-tensor squared distance -----------------------------------------------------------------
+// a lane has a sum per element of a vector
+struct PairSum {
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  __device__ __forceinline__ void add(float a, float b, int k = 0) { const float e = a - b; acc[k] = __builtin_fmaf(e, e, acc[k]); }
+  __device__ __forceinline__ void add4(const float4& a, const float4& b) {
+    add(a.x, b.x, 0); add(a.y, b.y, 1); add(a.z, b.z, 2); add(a.w, b.w, 3);
+  }
+};
+template <bool ALIGNED>
 __global__ __launch_bounds__(kBlock) void sse_pair_k(const float* __restrict__ y,
                                                      const float* __restrict__ yr, int64_t n,
                                                      double* __restrict__ partials) {
-  float acc = 0.0f;
-  auto add = [&](float a, float b) { const float e = a - b; acc = __builtin_fmaf(e, e, acc); };
+  PairSum s;
   const int64_t n4 = n >> 2;
-  for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
-                           [&](const float4 a, const float4 b) {
-                             add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
-                           });
+  if (ALIGNED)
+    for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
+                             [&](const float4 a, const float4 b) { s.add4(a, b); });
+  else for_each_vec4_pair_strided(y, yr, n4, [&](const float4 a, const float4 b) { s.add4(a, b); });
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
-  if (blockIdx.x == 0 && j < n) add(y[j], yr[j]);
+  if (blockIdx.x == 0 && j < n) s.add(y[j], yr[j]);
   __shared__ float sm[kBlock / kWave];
-  const float w = wave_sum(acc);
+  const float w = wave_sum((s.acc[0] + s.acc[1]) + (s.acc[2] + s.acc[3]));
   if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = w;
   __syncthreads();
   if (threadIdx.x == 0)
     partials[blockIdx.x] = ((double)sm[0] + (double)sm[1]) + ((double)sm[2] + (double)sm[3]);
 }
 
-// Up to kOnePair elements: one workgroup, one launch.  Device time, two launches against this: 64 x 256
-// 4.2 / 2.3 us, 128 x 256 4.2 / 3.2.
+// Up to kOnePair elements: one workgroup, one launch, lanes meet in double.  Device time, two launches against
+// this: 64 x 256 4.1 / 2.4 us, 128 x 256 4.1 / 3.3.
 constexpr int64_t kOnePair = 32768;
 __global__ __launch_bounds__(kOneBlock) void sse_pair_one(const float* __restrict__ y, const float* __restrict__ yr,
                                                           int n, double* __restrict__ out) {
   constexpr int NW = kOneBlock / kWave;
-  float acc = 0.0f;
-  auto add = [&](float a, float b) { const float e = a - b; acc = __builtin_fmaf(e, e, acc); };
+  PairSum s;
   const int n4 = n >> 2;
 #pragma unroll 4
-  for (int i = threadIdx.x; i < n4; i += kOneBlock) {
-    const float4 a = load4(y + 4 * i), b = load4(yr + 4 * i);
-    add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
-  }
-  if ((int)threadIdx.x < (n & 3)) add(y[(n & ~3) + threadIdx.x], yr[(n & ~3) + threadIdx.x]);
-  __shared__ float sm[NW];
-  const float w = wave_sum(acc);
+  for (int i = threadIdx.x; i < n4; i += kOneBlock) s.add4(load4(y + 4 * i), load4(yr + 4 * i));
+  if ((int)threadIdx.x < (n & 3)) s.add(y[(n & ~3) + threadIdx.x], yr[(n & ~3) + threadIdx.x]);
+  __shared__ double sm[NW];
+  const double w = wave_sum(((double)s.acc[0] + (double)s.acc[1]) + ((double)s.acc[2] + (double)s.acc[3]));
   if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = w;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0.0;
 #pragma unroll
-    for (int v = 0; v < NW; ++v) t += (double)sm[v];
+    for (int v = 0; v < NW; ++v) t += sm[v];
     out[0] = t;
   }
 }
@@ -485,7 +495,7 @@ static QeGeom qe_geometry(int64_t rows, int64_t cols, int gran, int nb) {
     // 4 blocks per CU: the full sweep needs ~65 VGPRs (7 waves per SIMD), so 8 blocks per CU
     // would not be co-resident and the late blocks would trail the rest
     g.gx = flat_grid(n >> 2, kBlock * kTileVec, 4);
-    const unsigned gs = flat_grid(n, kBlock * 4, 4);  // the query reserves for single-element work items
+    const unsigned gs = flat_grid(n, kBlock * 4, 4);  // of an unaligned tensor
     g.partial_doubles = (int64_t)(g.gx > gs ? g.gx : gs) * nb;
   } else if (gran == MPQ_PER_ROW) {
     g.nseg = (cols + kSeg - 1) / kSeg;
@@ -543,11 +553,17 @@ template <int NB>
 static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t cols, int gran,
                       const float* absmax, int b_lo, double* out, double* ws, hipStream_t st) {
   const int64_t n = rows * cols;
-  if (gran == MPQ_PER_TENSOR && n * NB <= kOneLimit) {
+  if (gran == MPQ_PER_TENSOR && n * NB <= kOneLimit && n <= kOneMost) {
     qe_one<NB><<<1, kOneBlock, 0, st>>>(x, (int)n, absmax, b_lo, out);
   } else if (gran == MPQ_PER_TENSOR) {
-    qe_flat<NB><<<g.gx, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
-    qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)g.gx, out);
+    unsigned parts = g.gx;
+    if (aligned16(x)) {
+      qe_flat<NB, true><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+    } else {
+      parts = flat_grid(n, kBlock * 4, 4);
+      qe_flat<NB, false><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+    }
+    qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)parts, out);
   } else if (gran == MPQ_PER_ROW) {
     if (g.nseg == 1) {
       const bool plan_holds = (cols & 3) == 0 && aligned16(x);
@@ -699,7 +715,6 @@ extern "C" int mpq_sse_pair(const float* y, const float* y_ref, int64_t n, doubl
                             void* ws, size_t ws_bytes, void* stream) {
   if (!y || !y_ref || !sse_out) return MPQ_ERR_NULL;
   if (n <= 0 || n > ((int64_t)1 << 46)) return MPQ_ERR_SHAPE;
-  const unsigned grid = flat_grid(n >> 2, kBlock * 2);
   if (!ws || ws_bytes < mpq_sse_pair_workspace_bytes(n)) return MPQ_ERR_WORKSPACE;
   if (!aligned16(ws) || (reinterpret_cast<uintptr_t>(sse_out) & 7u) != 0) return MPQ_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
@@ -708,7 +723,10 @@ extern "C" int mpq_sse_pair(const float* y, const float* y_ref, int64_t n, doubl
     return launch_status();
   }
   double* wsd = reinterpret_cast<double*>(ws);
-  sse_pair_k<<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  const bool aligned = aligned16(y) && aligned16(y_ref);
+  const unsigned grid = aligned ? flat_grid(n >> 2, kBlock * 2) : flat_grid(n, kBlock * 4);
+  if (aligned) sse_pair_k<true><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  else sse_pair_k<false><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
   qe_finish_tree<1><<<1, kBlock, 0, st>>>(wsd, (int64_t)grid, sse_out);
   return launch_status();
 }

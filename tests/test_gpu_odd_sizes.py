@@ -160,3 +160,36 @@ def test_sweep_per_row_at_any_size(shape, widths):
         lanes = lanes[:, 0::2] + lanes[:, 1::2]
     rms = np.sqrt(np.mean((lanes[:, 0] / exact - 1) ** 2))
     assert np.sqrt(np.mean((got[:, -1] / exact - 1) ** 2)) <= 1.15 * rms
+
+
+def lane_sums(e):
+    """Sums of squares as 64-lane waves of fp32 sums of four vectors a lane form them, the waves in double."""
+    n = e.size // 4096 * 4096
+    v = e[:n].reshape(-1, 4, 64, 4)                                  # tile of a wave, vector, lane, element
+    acc = np.zeros((v.shape[0], 64), np.float32)
+    for k in range(4):
+        for c in range(4):
+            acc = (v[:, k, :, c].astype(np.float64) ** 2 + acc).astype(np.float32)
+    while acc.shape[1] > 1:
+        acc = acc[:, 0::2] + acc[:, 1::2]
+    return acc.astype(np.float64).sum() + (e[n:].astype(np.float64) ** 2).sum()
+
+
+@pytest.mark.parametrize("n", [4096, 16384, 32768, 65536, 69632])
+@pytest.mark.parametrize("off", [0, 1])
+def test_small_tensors_are_summed_as_closely_as_larger_ones(n, off):
+    """One workgroup up to 65536 elements (one width) and 32768 (squared distance), any alignment: rms error over 24
+    inputs no larger than that of lane_sums, with 25 % for the spread of either estimate."""
+    err = np.zeros((24, 4))
+    for i in range(24):
+        x, ref = data((1, n), 300 + i), data((1, n), 400 + i)
+        d = (x - ref).reshape(-1)
+        m = oracle.absmax(x) * np.float32(1.25)
+        inv, sc = np.float32(7) / m, m / np.float32(7)
+        e = (np.rint(x.astype(np.float64) * inv) * sc.astype(np.float64) - x).astype(np.float32).reshape(-1)
+        for k, (v, got) in enumerate(((d, host(mpq.sse_pair(at(x, off), at(ref, off)))[0]),
+                                      (e, host(mpq.quant_error(at(x, off), dev(m), 4, 4))[0, 0]))):
+            exact = (v.astype(np.float64) ** 2).sum()
+            err[i, 2 * k:2 * k + 2] = got / exact - 1, lane_sums(v) / exact - 1
+    rms = np.sqrt((err ** 2).mean(0))
+    assert rms[0] <= 1.25 * rms[1] and rms[2] <= 1.25 * rms[3], rms
