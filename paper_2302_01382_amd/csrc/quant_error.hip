@@ -448,12 +448,11 @@ __global__ __launch_bounds__(kBlock) void sse_pair_k(const float* __restrict__ y
   else for_each_vec4_pair_strided(y, yr, n4, [&](const float4 a, const float4 b) { s.add4(a, b); });
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
   if (blockIdx.x == 0 && j < n) s.add(y[j], yr[j]);
-  __shared__ float sm[kBlock / kWave];
-  const float w = wave_sum((s.acc[0] + s.acc[1]) + (s.acc[2] + s.acc[3]));
+  __shared__ double sm[kBlock / kWave];
+  const double w = wave_sum_rows((s.acc[0] + s.acc[1]) + (s.acc[2] + s.acc[3]));
   if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = w;
   __syncthreads();
-  if (threadIdx.x == 0)
-    partials[blockIdx.x] = ((double)sm[0] + (double)sm[1]) + ((double)sm[2] + (double)sm[3]);
+  if (threadIdx.x == 0) partials[blockIdx.x] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
 }
 
 // Up to kOnePair elements: one workgroup, one launch, lanes meet in double.  Device time, two launches against

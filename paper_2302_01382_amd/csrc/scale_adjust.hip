@@ -43,32 +43,48 @@ struct GradAcc {
     if (r == q) s_x = __builtin_fmaf(g, x, s_x);  // the clamp was inactive
     s_loss = __builtin_fmaf(e, e, s_loss);
   }
-  template <bool HAS_G>
-  __device__ __forceinline__ void add4(const TwoScales& t, const float4& v, const float4& g) {
-    add<HAS_G>(t, v.x, g.x); add<HAS_G>(t, v.y, g.y); add<HAS_G>(t, v.z, g.z); add<HAS_G>(t, v.w, g.w);
-  }
 };
 
-// ---- per tensor: tiles dealt round-robin, one partial triple per workgroup ---------------------
+// One for each of the four elements of a vector, which keeps the fp32 chains short.
 template <bool HAS_G>
+struct GradAcc4 {
+  GradAcc k[4];
+  __device__ __forceinline__ void add(const TwoScales& t, float x, float g) { k[0].template add<HAS_G>(t, x, g); }
+  __device__ __forceinline__ void add4(const TwoScales& t, const float4& v, const float4& g) {
+    k[0].template add<HAS_G>(t, v.x, g.x);
+    k[1].template add<HAS_G>(t, v.y, g.y);
+    k[2].template add<HAS_G>(t, v.z, g.z);
+    k[3].template add<HAS_G>(t, v.w, g.w);
+  }
+  __device__ __forceinline__ float code() const { return (k[0].s_code + k[1].s_code) + (k[2].s_code + k[3].s_code); }
+  __device__ __forceinline__ float x() const { return (k[0].s_x + k[1].s_x) + (k[2].s_x + k[3].s_x); }
+  __device__ __forceinline__ float loss() const { return (k[0].s_loss + k[1].s_loss) + (k[2].s_loss + k[3].s_loss); }
+};
+
+// ---- per tensor: one partial triple per workgroup ----------------------------------------------
+// TILED: tiles dealt round-robin, else (small or unaligned tensors) one vector a trip
+template <bool HAS_G, bool TILED>
 __global__ __launch_bounds__(kBlock) void sg_flat(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t n, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
                                                   double* __restrict__ partials) {
   const TwoScales t(inv[0], scale[0], bits);
-  GradAcc a;
+  GradAcc4<HAS_G> a;
   const int64_t n4 = n >> 2;
-  if (HAS_G) {
-    for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
-                             [&](const float4 v, const float4 u) { a.add4<true>(t, v, u); });
+  if (TILED) {
+    if (HAS_G)
+      for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
+                               [&](const float4 v, const float4 u) { a.add4(t, v, u); });
+    else
+      for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { a.add4(t, v, v); });
   } else {
-    for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4,
-                        [&](const float4 v, int64_t) { a.add4<false>(t, v, v); });
+    if (HAS_G) for_each_vec4_pair_strided(x, g, n4, [&](const float4 v, const float4 u) { a.add4(t, v, u); });
+    else for_each_vec4_strided(x, n4, [&](const float4 v) { a.add4(t, v, v); });
   }
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
-  if (blockIdx.x == 0 && j < n) a.add<HAS_G>(t, x[j], HAS_G ? g[j] : 0.0f);
-  __shared__ float sm[3][kBlock / kWave];
-  const float w0 = wave_sum(a.s_code), w1 = wave_sum(a.s_x), w2 = wave_sum(a.s_loss);
+  if (blockIdx.x == 0 && j < n) a.add(t, x[j], HAS_G ? g[j] : 0.0f);
+  __shared__ double sm[3][kBlock / kWave];
+  const double w0 = wave_sum_rows(a.code()), w1 = wave_sum_rows(a.x()), w2 = wave_sum_rows(a.loss());
   if ((threadIdx.x & (kWave - 1)) == 0) {
     sm[0][threadIdx.x / kWave] = w0;
     sm[1][threadIdx.x / kWave] = w1;
@@ -76,8 +92,8 @@ __global__ __launch_bounds__(kBlock) void sg_flat(const float* __restrict__ x, c
   }
   __syncthreads();
   if (threadIdx.x < 3) {
-    const float* s = sm[threadIdx.x];
-    partials[(int64_t)blockIdx.x * 3 + threadIdx.x] = ((double)s[0] + (double)s[1]) + ((double)s[2] + (double)s[3]);
+    const double* s = sm[threadIdx.x];
+    partials[(int64_t)blockIdx.x * 3 + threadIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
   }
 }
 
@@ -109,9 +125,10 @@ __global__ __launch_bounds__(kBlock) void sg_finish(const double* __restrict__ p
 }
 
 // ---- per row: LPR lanes per row (16 or 64), results written directly ------------------------------
-// Four 16-byte loads per tensor in flight per lane before the first use: a wave per row with one in flight
-// took 9.8 us on 12288 x 768 (13.7 with a gradient), 49 (95) on 16384 x 4096; this 8.9 (12.7) and 43 (85).
-template <bool HAS_G, int LPR>
+// U 16-byte loads per tensor in flight per lane, the first ones in front of the scales: four where a row has
+// several trips for them (12288 x 768 9.8 -> 8.9 us, with a gradient 13.7 -> 12.5), one where the code's length
+// counts, as it is fetched cold (300 x 256 2.9 -> 2.4).
+template <bool HAS_G, int LPR, int U, bool STREAM>
 __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t rows, int64_t cols, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
@@ -121,33 +138,37 @@ __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, c
   int64_t r = (int64_t)blockIdx.x * (kBlock / LPR) + threadIdx.x / LPR;
   const bool live = r < rows;
   if (!live) r = rows - 1;  // every lane stays active for the cross-lane sums; result discarded
-  const TwoScales t(inv[r], scale[r], bits);
-  GradAcc a;
   const float* xr = x + r * cols;
   const float* gr = HAS_G ? g + r * cols : nullptr;
-  constexpr int U = 4;
   constexpr int64_t kStep = 4 * LPR;
-  for (int64_t c0 = 0; c0 + 4 <= cols; c0 += U * kStep) {  // the same trips for every lane of the row
-    // pieces past the row's end stay zero, in x and in g: they add nothing to any of the three sums
-    float4 v[U], u[U];
+  float4 v[U], u[U];
+  auto fetch = [&](int64_t c0) {
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int64_t c = c0 + k * kStep + 4 * lr;
-      v[k] = c + 4 <= cols ? load_stream(xr + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (HAS_G) u[k] = c + 4 <= cols ? load_stream(gr + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      else u[k] = v[k];
+      if (c + 4 <= cols) {
+        v[k] = STREAM ? load_stream(xr + c) : load4(xr + c);
+        if (HAS_G) u[k] = STREAM ? load_stream(gr + c) : load4(gr + c);
+      }
     }
+  };
+  fetch(0);
+  const bool tail = lr < (int)(cols & 3);
+  const int64_t e = (cols & ~(int64_t)3) + lr;
+  const float xe = tail ? xr[e] : 0.0f, ge = HAS_G && tail ? gr[e] : 0.0f;
+  const TwoScales t(inv[r], scale[r], bits);
+  GradAcc4<HAS_G> a;
+#pragma unroll 1
+  for (int64_t c0 = 0; c0 + 4 <= cols; c0 += U * kStep) {  // the same trips for every lane of the row
 #pragma unroll
     for (int k = 0; k < U; ++k)
-      if (c0 + k * kStep + 4 <= cols) a.add4<HAS_G>(t, v[k], u[k]);  // skips pieces that no lane has
+      if (c0 + k * kStep + 4 * lr + 4 <= cols) a.add4(t, v[k], HAS_G ? u[k] : v[k]);
+    fetch(c0 + U * kStep);
   }
-  if (lr < (int)(cols & 3)) {
-    const int64_t e = (cols & ~(int64_t)3) + lr;
-    a.add<HAS_G>(t, xr[e], HAS_G ? gr[e] : 0.0f);
-  }
-  const float w0 = LPR == 16 ? row16_sum(a.s_code) : wave_sum(a.s_code);
-  const float w1 = LPR == 16 ? row16_sum(a.s_x) : wave_sum(a.s_x);
-  const float w2 = LPR == 16 ? row16_sum(a.s_loss) : wave_sum(a.s_loss);
+  if (tail) a.add(t, xe, ge);
+  const float w0 = LPR == 16 ? row16_sum(a.code()) : wave_sum(a.code());
+  const float w1 = LPR == 16 ? row16_sum(a.x()) : wave_sum(a.x());
+  const float w2 = LPR == 16 ? row16_sum(a.loss()) : wave_sum(a.loss());
   if (lr == 0 && live) {
     dscale[r] = (double)w0;
     dinv[r] = (double)t.scale * (double)w1;
@@ -234,8 +255,14 @@ static int check_sa(int64_t rows, int64_t cols, int gran, int bits) {
 
 static unsigned sg_grid(int64_t n, bool has_g) { return flat_grid(n >> 2, kBlock * (has_g ? 2 : kTileVec)); }
 
-// Rows of up to kShortRow columns are walked by 16 lanes each, longer ones by a wave: 16 against 64 lanes,
-// gradients of 5000 x 400 5.1 / 3.9 us, forward of 3001 x 1147 9.8 / 7.5.
+// Gradients per row: 16 lanes per row or a wave?  us with an upstream gradient, 16 | 64 lanes: 1000 x 101 2.6 | 2.5,
+// 5000 x 101 2.9 | 3.2, 5000 x 255 4.3 | 4.1, 16384 x 384 9.9 | 10.5, 16384 x 511 13.7 | 12.3, 40000 x 384 20.2 | 20.6.
+static bool sg_sixteen(int64_t rows, int64_t cols) { return cols <= 64 || cols <= rows / 32; }
+// Tensors beyond the caches are streamed: 16384 x 768 with a gradient 18.5 -> 16.9 us, but 1000 x 4096 9.3 -> 11.8.
+constexpr int64_t kStreamFrom = 5ll << 20;
+
+// Forward: rows of up to kShortRow columns are walked by 16 lanes each, longer ones by a wave: 16 against 64
+// lanes, 3001 x 1147 9.8 / 7.5 us.
 constexpr int64_t kShortRow = 256;
 
 }  // namespace mpq
@@ -267,7 +294,7 @@ extern "C" int mpq_fake_quant_scales(const float* x, int64_t rows, int64_t cols,
 extern "C" size_t mpq_scale_grad_workspace_bytes(int64_t rows, int64_t cols, int gran) {
   if (check_sa(rows, cols, gran, 8) != MPQ_OK || gran != MPQ_PER_TENSOR) return 0;
   const int64_t n = rows * cols;
-  unsigned g = flat_grid(n, kBlock * 4);  // the query reserves for single-element work items
+  unsigned g = flat_grid(n, kBlock * 4);  // the grid of small and unaligned tensors
   for (int v = 0; v < 2; ++v) {           // ... and for the largest grid any variant may use
     const unsigned c = sg_grid(n, v != 0);
     g = c > g ? c : g;
@@ -290,22 +317,36 @@ extern "C" int mpq_scale_grad(const float* x, int64_t rows, int64_t cols, int gr
     if (!ws || ws_bytes < mpq_scale_grad_workspace_bytes(rows, cols, gran)) return MPQ_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(ws) & 7u) return MPQ_ERR_ALIGN;
     double* partials = reinterpret_cast<double*>(ws);
-    const unsigned grid = sg_grid(n, g != nullptr);
-    if (g) sg_flat<true><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
-    else sg_flat<false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials);
+    // below 2^19 elements tiles give too few CUs a workgroup: 255000 4.7 us against 5.4, but 1000001 6.2 against 5.8
+    const bool tiled = aligned16(x) && (!g || aligned16(g)) && n > ((int64_t)1 << 19);
+    const unsigned grid = tiled ? sg_grid(n, g != nullptr) : flat_grid(n, kBlock * 4);
+#define MPQ_SG(G_, T_) sg_flat<G_, T_><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials)
+    if (g) {
+      if (tiled) MPQ_SG(true, true);
+      else MPQ_SG(true, false);
+    } else {
+      if (tiled) MPQ_SG(false, true);
+      else MPQ_SG(false, false);
+    }
+#undef MPQ_SG
     sg_finish<<<1, kBlock, 0, st>>>(partials, (int64_t)grid, scale, dinv_out, dscale_out, loss_out);
   } else {
-    const bool short_rows = cols <= kShortRow;
-    const unsigned grid = (unsigned)(short_rows ? (rows + 15) / 16 : (rows + 3) / 4);
-#define MPQ_SG(G_, LPR_) \
-  sg_rows<G_, LPR_><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out)
-    if (short_rows) {
-      if (g) MPQ_SG(true, 16);
-      else MPQ_SG(false, 16);
+    const bool sixteen = sg_sixteen(rows, cols), short_code = cols <= (sixteen ? 256 : 768), stream = rows * cols > kStreamFrom;
+    const unsigned grid = (unsigned)(sixteen ? (rows + 15) / 16 : (rows + 3) / 4);
+#define MPQ_SG(G_, LPR_, U_, S_) \
+  sg_rows<G_, LPR_, U_, S_><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out)
+#define MPQ_SG_U(G_, LPR_)                         \
+  if (stream) MPQ_SG(G_, LPR_, 4, true);           \
+  else if (short_code) MPQ_SG(G_, LPR_, 1, false); \
+  else MPQ_SG(G_, LPR_, 4, false)
+    if (sixteen) {
+      if (g) { MPQ_SG_U(true, 16); }
+      else { MPQ_SG_U(false, 16); }
     } else {
-      if (g) MPQ_SG(true, 64);
-      else MPQ_SG(false, 64);
+      if (g) { MPQ_SG_U(true, 64); }
+      else { MPQ_SG_U(false, 64); }
     }
+#undef MPQ_SG_U
 #undef MPQ_SG
   }
   return launch_status();

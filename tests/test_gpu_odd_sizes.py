@@ -193,3 +193,37 @@ def test_small_tensors_are_summed_as_closely_as_larger_ones(n, off):
             err[i, 2 * k:2 * k + 2] = got / exact - 1, lane_sums(v) / exact - 1
     rms = np.sqrt((err ** 2).mean(0))
     assert rms[0] <= 1.25 * rms[1] and rms[2] <= 1.25 * rms[3], rms
+
+
+# 16 lanes or a wave per row, one load in flight or four, streamed or cached; per tensor in tiles or one vector a trip
+@pytest.mark.parametrize("gran,shape", [(mpq.PER_ROW, s) for s in [(5, 64), (5, 65), (3, 768), (3, 769), (2100, 64), (2100, 66), (8200, 256),
+                                                                  (8210, 257), (3, 1800001), (5300, 1000), (42000, 130)]] +
+                         [(mpq.PER_TENSOR, s) for s in [(1, 524288), (1, 524293), (7, 100001)]])
+def test_scale_gradients_where_the_layout_changes(gran, shape):
+    x, g = data(shape, 101), data(shape, 102)
+    m = oracle.absmax(x, gran)
+    inv, scale = (np.float32(7) / m * np.float32(1.3)).astype(np.float32), (m / np.float32(7)).astype(np.float32)
+    for off in (0, 1):
+        for up in (None, g):
+            got = mpq.scale_grad(at(x, off), dev(inv), dev(scale), 4, None if up is None else at(up, (off + 1) % 4), gran)
+            want = oracle.scale_grad(x, inv, scale, 4, up, gran)
+            for a, key, lim in zip(got, ("dinv", "dscale", "loss"), ("abs_dinv", "abs_dscale", "loss")):
+                # rms of a million random roundings of fp32 sums, far below 1e-6 of the sum of absolute values
+                assert np.all(np.abs(host(a) - want[key]) <= 1e-6 * want[lim] + 1e-12)
+
+
+@pytest.mark.parametrize("shape", [(4000, 256), (4000, 255), (8200, 250)])
+def test_scale_gradients_are_summed_as_closely_as_by_64_lanes(shape):
+    x, g = data(shape, 103), data(shape, 104)
+    m = oracle.absmax(x, oracle.PER_ROW)
+    inv, scale = (np.float32(7) / m).astype(np.float32), (m / np.float32(7)).astype(np.float32)
+    dscale = host(mpq.scale_grad(dev(x), dev(inv), dev(scale), 4, dev(g), mpq.PER_ROW)[1])
+    gq = g.astype(np.float64) * np.clip(np.rint(x.astype(np.float64) * inv[:, None]), -7, 7)
+    lanes = np.zeros((shape[0], 64), np.float32)
+    for c in range(0, shape[1], 64):
+        p = gq[:, c:c + 64]
+        lanes[:, :p.shape[1]] = (p + lanes[:, :p.shape[1]]).astype(np.float32)
+    while lanes.shape[1] > 1:
+        lanes = lanes[:, 0::2] + lanes[:, 1::2]
+    rms = [np.sqrt(np.mean(((v - gq.sum(1)) / np.abs(gq).sum(1)) ** 2)) for v in (dscale, lanes[:, 0])]
+    assert rms[0] <= 1.06 * rms[1], rms     # thousands of rows: either estimate is good to 2 %
