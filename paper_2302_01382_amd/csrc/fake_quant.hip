@@ -60,10 +60,10 @@ __device__ __forceinline__ void emit4(const float4 v, const QConst& c, int64_t e
 }
 
 // One to three elements from flat element e on (the end of a tensor or row), one lane; packed: e is a
-// multiple of 4 or of an even row, and there are two of them.  All are read before the first is written.
-__device__ __forceinline__ void emit_tail(const float* x, const QConst& k0, const QConst& k1, const QConst& k2,
+// multiple of 4 or of an even row, and there are two of them.
+__device__ __forceinline__ void emit_some(const float4 v, const QConst& k0, const QConst& k1, const QConst& k2,
                                           int64_t e, int count, float* y, int8_t* codes, uint8_t* packed) {
-  const float t0 = magic_t(x[e], k0), t1 = magic_t(x[count > 1 ? e + 1 : e], k1), t2 = magic_t(x[count > 2 ? e + 2 : e], k2);
+  const float t0 = magic_t(v.x, k0), t1 = magic_t(v.y, k1), t2 = magic_t(v.z, k2);
   if (y) {
     y[e] = dequant_t(t0, k0);
     if (count > 1) y[e + 1] = dequant_t(t1, k1);
@@ -75,6 +75,14 @@ __device__ __forceinline__ void emit_tail(const float* x, const QConst& k0, cons
     if (count > 2) codes[e + 2] = (int8_t)(bits_from_f(t2) & 0xFF);
   }
   if (packed) packed[e >> 1] = (uint8_t)(pack_nibbles(t0, t1, 0.0f, 0.0f) & 0xFFu);
+}
+// those elements (past the last one: the first again); all are read before the first is written
+__device__ __forceinline__ float4 load_some(const float* x, int count) {
+  return make_float4(x[0], x[count > 1 ? 1 : 0], x[count > 2 ? 2 : 0], 0.0f);
+}
+__device__ __forceinline__ void emit_tail(const float* x, const QConst& c, int64_t e, int count, float* y, int8_t* codes,
+                                          uint8_t* packed) {
+  emit_some(load_some(x + e, count), c, c, c, e, count, y, codes, packed);
 }
 
 // ---- per tensor, flat, 128-bit loads; n4 = n / 4 vectors, tail of n % 4 scalars ------------
@@ -89,7 +97,7 @@ __global__ __launch_bounds__(kBlock) void fq_flat(const float* __restrict__ x, i
   for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4,
                       [&](const float4 v, int64_t i) { emit4(v, c, i << 2, y, codes, packed); });
   // tail: at most 3 elements, pairs stay together (n even whenever packed != null)
-  if (tid == 0 && (n & 3)) emit_tail(x, c, c, c, n4 << 2, (int)(n & 3), y, codes, packed);
+  if (tid == 0 && (n & 3)) emit_tail(x, c, n4 << 2, (int)(n & 3), y, codes, packed);
 }
 
 // ---- per tensor, codes only, the maximum still in parts (at most kMaxParts) --------------------
@@ -123,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void fq_parts(const float* __restrict__ x, 
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     absmax_out[0] = c.m;
     step_out[0] = c.scale;
-    if (n & 3) emit_tail(x, c, c, c, n4 << 2, (int)(n & 3), nullptr, codes, nullptr);
+    if (n & 3) emit_tail(x, c, n4 << 2, (int)(n & 3), nullptr, codes, nullptr);
   }
   while (t < ntiles) {
 #pragma unroll
@@ -136,20 +144,19 @@ __global__ __launch_bounds__(kBlock) void fq_parts(const float* __restrict__ x, 
   }
 }
 
-// ---- per row: one wave per (row, segment) -------------------------------------
-constexpr int64_t kSeg = 16384;
+// ---- per row: one wave per (row, segment of seg columns, a multiple of 4) ------------------------
+constexpr int64_t kSeg = 16384;  // the longest segment
 
 __global__ __launch_bounds__(kBlock) void fq_rows(const float* __restrict__ x, int64_t rows,
-                                                  int64_t cols, int64_t nseg,
+                                                  int64_t cols, int64_t nseg, int64_t seg,
                                                   const float* __restrict__ absmax, int bits,
                                                   float* __restrict__ y, int8_t* __restrict__ codes,
                                                   uint8_t* __restrict__ packed) {
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t item = block_index() * (kBlock / kWave) + threadIdx.x / kWave;
   if (item >= rows * nseg) return;
-  const int64_t r = item / nseg, seg = item - r * nseg;
-  const int64_t c0 = seg * kSeg;
-  const int64_t c1 = (c0 + kSeg < cols) ? c0 + kSeg : cols;
+  const int64_t r = item / nseg, c0 = (item - r * nseg) * seg;
+  const int64_t c1 = (c0 + seg < cols) ? c0 + seg : cols;
   const QConst c = make_qconst(absmax[r], bits);
   const int64_t base = r * cols;
   int64_t i = base + c0 + 4 * lane;
@@ -165,30 +172,72 @@ __global__ __launch_bounds__(kBlock) void fq_rows(const float* __restrict__ x, i
   }
   for (; i + 4 <= end; i += kStep) emit4(load_stream(x + i), c, i, y, codes, packed);
   // the last cols % 4 elements of the row (an even number, starting on an even one, whenever packed != null)
-  if (lane == 0 && (c1 & 3)) emit_tail(x, c, c, c, end - (c1 & 3), (int)(c1 & 3), y, codes, packed);
+  if (lane == 0 && (c1 & 3)) emit_tail(x, c, end - (c1 & 3), (int)(c1 & 3), y, codes, packed);
+}
+
+// ---- per row, short rows: LPR lanes per row (4 or 16) --------------------------------------------
+// A wave per row: 100000 x 16 28 us at any alignment, 16384 x 101 8.6; 4 and 16 lanes 4.2 and 4.7.
+template <int LPR>
+__global__ __launch_bounds__(kBlock) void fq_rows_sub(const float* __restrict__ x, int64_t rows, int64_t cols,
+                                                      const float* __restrict__ absmax, int bits,
+                                                      float* __restrict__ y, int8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ packed) {
+  const int lr = threadIdx.x % LPR;
+  const int64_t r = block_index() * (kBlock / LPR) + threadIdx.x / LPR;
+  if (r >= rows) return;
+  const int64_t base = r * cols;
+  const int last = (int)(cols & 3);
+  const QConst c = make_qconst(absmax[r], bits);
+#pragma unroll 2
+  for (int64_t i = 4 * lr; i + 4 <= cols; i += 4 * LPR) emit4(load4(x + base + i), c, base + i, y, codes, packed);
+  // the last cols % 4 elements of the row (an even number, starting on an even one, whenever packed != null)
+  if (lr == LPR - 1 && last) emit_tail(x, c, base + cols - last, last, y, codes, packed);
 }
 
 // ---- per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4) ----------------
+// Narrow tensors: RW rows share a wave's 64 lanes (100000 x 16 12.5 -> 5.8 us).
+template <int RW>
 __global__ __launch_bounds__(kBlock) void fq_cols(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, const float* __restrict__ absmax,
                                                   int bits, float* __restrict__ y,
                                                   int8_t* __restrict__ codes,
                                                   uint8_t* __restrict__ packed) {
+  constexpr int L = kWave / RW;  // lanes of a row
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  const int64_t c = (block_index() * kWave + lane) * 4;
+  const int64_t c = (block_index() * L + lane % L) * 4;
   if (c >= cols) return;
   const int live = c + 4 <= cols ? 4 : (int)(cols - c);
-  const QConst k0 = make_qconst(absmax[c], bits), k1 = make_qconst(absmax[live > 1 ? c + 1 : c], bits),
-               k2 = make_qconst(absmax[live > 2 ? c + 2 : c], bits), k3 = make_qconst(absmax[live > 3 ? c + 3 : c], bits);
-  const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave);
-  const int64_t r0 = (int64_t)blockIdx.y * (kBlock / kWave) + wave;
-  if (live == 4) {
-#pragma unroll 4
-    for (int64_t r = r0; r < rows; r += row_step) emit4(load4(x + r * cols + c), k0, k1, k2, k3, r * cols + c, y, codes, packed);
-  } else {
-    for (int64_t r = r0; r < rows; r += row_step) emit_tail(x, k0, k1, k2, r * cols + c, live, y, codes, packed);
+  const int64_t row_step = (int64_t)gridDim.y * (kBlock / kWave) * RW;
+  const int64_t r0 = ((int64_t)blockIdx.y * (kBlock / kWave) + wave) * RW + lane / L;
+  float4 m;  // loaded as one: constant by constant, each load waits for the division before it
+  if (live == 4) m = load4(absmax + c);
+  else m = load_some(absmax + c, live);
+  const QConst k0 = make_qconst(m.x, bits), k1 = make_qconst(m.y, bits), k2 = make_qconst(m.z, bits), k3 = make_qconst(m.w, bits);
+  for (int64_t r = r0; r < rows; r += row_step) {  // one wait for both kinds of lanes
+    const int64_t e = r * cols + c;
+    float4 v;
+    if (live == 4) v = load4(x + e);
+    else v = load_some(x + e, live);
+    if (live == 4) emit4(v, k0, k1, k2, k3, e, y, codes, packed);
+    else emit_some(v, k0, k1, k2, e, live, y, codes, packed);
   }
+}
+
+template <int RW>
+static void launch_fq_cols(const float* x, int64_t rows, int64_t cols, const float* absmax, int bits, float* y,
+                           int8_t* codes, uint8_t* packed, hipStream_t st) {
+  constexpr int64_t width = kWave / RW * 4, pass = kBlock / kWave * RW;  // columns and rows of a workgroup
+  const int64_t gx = (cols + width - 1) / width;
+  int64_t gy = ((int64_t)kNumCU * 8 + gx - 1) / gx;
+  // at least 8 rows per lane, 2 where that would leave CUs without a workgroup
+  int64_t max_gy = (rows + pass * 8 - 1) / (pass * 8);
+  if (max_gy * gx < kNumCU) {
+    max_gy = (kNumCU + gx - 1) / gx;
+    if (max_gy > (rows + pass * 2 - 1) / (pass * 2)) max_gy = (rows + pass * 2 - 1) / (pass * 2);
+  }
+  if (gy > max_gy) gy = max_gy;
+  fq_cols<RW><<<wide_grid(gx, kBlock, (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y, codes, packed);
 }
 
 // mpq_fake_quant with one more output: for per-tensor granularity the kernel also leaves the step
@@ -207,25 +256,27 @@ int fake_quant_launch(const float* x, int64_t rows, int64_t cols, int gran, cons
   const int64_t n = rows * cols;
   if (gran == MPQ_PER_TENSOR) {
     fq_flat<<<flat_grid(n >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, n, absmax, bits, y_out, codes_out, packed4_out, step_out);
+  } else if (gran == MPQ_PER_ROW && cols <= 32) {
+    fq_rows_sub<4><<<wide_grid((rows + 63) / 64, kBlock), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
+  } else if (gran == MPQ_PER_ROW && cols <= 256) {
+    fq_rows_sub<16><<<wide_grid((rows + 15) / 16, kBlock), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
   } else if (gran == MPQ_PER_ROW) {
-    const int64_t nseg = (cols + kSeg - 1) / kSeg;
+    // few long rows: cut into segments of whole trips (1024 columns) until the chip has its waves: 4 x 300001
+    // 23 -> 5.4 us, 64 x 30000 24 -> 5.1
+    int64_t nseg = (2048 + rows - 1) / rows;
+    if (nseg > (cols + 1023) / 1024) nseg = (cols + 1023) / 1024;
+    int64_t seg = ((cols + nseg - 1) / nseg + 1023) / 1024 * 1024;
+    if (seg > kSeg) seg = kSeg;
+    nseg = (cols + seg - 1) / seg;
     const int64_t blocks = (rows * nseg + kBlock / kWave - 1) / (kBlock / kWave);
     if (blocks > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-    fq_rows<<<wide_grid(blocks, kBlock), kBlock, 0, st>>>(x, rows, cols, nseg, absmax, bits, y_out, codes_out, packed4_out);
+    fq_rows<<<wide_grid(blocks, kBlock), kBlock, 0, st>>>(x, rows, cols, nseg, seg, absmax, bits, y_out, codes_out, packed4_out);
   } else {
-    const int64_t gx = (cols + kWave * 4 - 1) / (kWave * 4);
-    if (gx > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-    int64_t gy = ((int64_t)kNumCU * 8 + gx - 1) / gx;
-    // at least 8 rows per wave, 2 where that would leave CUs without a workgroup
-    int64_t max_gy = (rows + 4 * 8 - 1) / (4 * 8);
-    if (max_gy * gx < kNumCU) {
-      max_gy = (kNumCU + gx - 1) / gx;
-      if (max_gy > (rows + 4 * 2 - 1) / (4 * 2)) max_gy = (rows + 4 * 2 - 1) / (4 * 2);
-    }
-    if (gy > max_gy) gy = max_gy;
-    if (gy < 1) gy = 1;
-    if (gy > 65535) gy = 65535;
-    fq_cols<<<wide_grid(gx, kBlock, (unsigned)gy), kBlock, 0, st>>>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out);
+    if ((cols + kWave * 4 - 1) / (kWave * 4) > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
+    if (cols <= 16) launch_fq_cols<16>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out, st);
+    else if (cols <= 64) launch_fq_cols<4>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out, st);
+    else if (cols <= 128) launch_fq_cols<2>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out, st);
+    else launch_fq_cols<1>(x, rows, cols, absmax, bits, y_out, codes_out, packed4_out, st);
   }
   return launch_status();
 }

@@ -227,3 +227,13 @@ def test_scale_gradients_are_summed_as_closely_as_by_64_lanes(shape):
         lanes = lanes[:, 0::2] + lanes[:, 1::2]
     rms = [np.sqrt(np.mean(((v - gq.sum(1)) / np.abs(gq).sum(1)) ** 2)) for v in (dscale, lanes[:, 0])]
     assert rms[0] <= 1.06 * rms[1], rms     # thousands of rows: either estimate is good to 2 %
+
+
+# lanes per row (4 up to 32 columns, 16 up to 256), rows per wave of a narrow tensor's columns (16, 64 and 128 columns),
+# one row chunk of column maxima (64 and 128 rows), long rows in segments of 1024 columns and of 16384
+@pytest.mark.parametrize("gran", [mpq.PER_ROW, mpq.PER_COL])
+@pytest.mark.parametrize("shape", [(70, 32), (70, 33), (300, 16), (300, 17), (64, 64), (65, 65), (128, 128), (129, 129), (130, 256), (70, 258),
+                                   (129, 3), (3, 70001), (2, 70002), (1, 5), (1100, 2050), (2060, 1030), (4000, 20), (1, 36866)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_streaming_calls_where_the_layout_changes(shape, off, gran):
+    test_streaming_calls(shape, off, gran)
