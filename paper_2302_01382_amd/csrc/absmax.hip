@@ -113,15 +113,46 @@ __global__ __launch_bounds__(kBlock) void absmax_rows(const float* __restrict__ 
   }
 }
 
+// per row, short rows: LPR lanes per row (4 or 16) of up to 256 columns, every row's result written by its own
+// lanes.  A wave per row: 16384 x 101 5.2 us, 100000 x 16 17.5; this 3.1 and 2.6.
+template <int LPR>
+__global__ __launch_bounds__(kBlock) void absmax_rows_sub(const float* __restrict__ x, int64_t rows, int64_t cols,
+                                                          int accumulate, float* __restrict__ out) {
+  const int lr = threadIdx.x % LPR;
+  int64_t r = block_index() * (kBlock / LPR) + threadIdx.x / LPR;
+  const bool live = r < rows;
+  if (!live) r = rows - 1;  // every lane stays active for the cross-lane steps
+  const float* row = x + r * cols;
+  const float before = lr == 0 && accumulate ? out[r] : 0.0f;
+  float m = lr < (int)(cols & 3) ? fabsf(row[(cols & ~(int64_t)3) + lr]) : 0.0f;
+#pragma unroll 2
+  for (int64_t i = 4 * lr; i + 4 <= cols; i += 4 * LPR) {
+    const float4 a = load4(row + i);
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
+  }
+  m = fmaxf(m, dpp<kQuadSwap1>(m));
+  m = fmaxf(m, dpp<kQuadSwap2>(m));
+  if (LPR == 16) {
+    m = fmaxf(m, dpp<kRowHalfMirror>(m));
+    m = fmaxf(m, dpp<kRowMirror>(m));
+  }
+  if (lr == 0 && live) out[r] = fmaxf(m, before);
+}
+
 // per column: a lane owns 4 adjacent columns (the last lane of a row 1 to 4), the 16 waves of a workgroup
 // take interleaved rows and meet in LDS; blockIdx.y strides over row chunks, which meet in an atomic
 // maximum per column and workgroup.  Those atomics are what bounds a kernel that has one per WAVE and
 // many short row chunks: 12288 x 768 took 65 us with 4-wave workgroups of 64 rows; two of these
 // workgroups per CU and one atomic per column and workgroup: 10.6 (16384 x 64: 82 -> 8.7;
 // 1024 x 4096: 12.2 -> 6.2).
+// DIRECT: one row chunk: its maxima are the result, and the clearing launch is spared (16 x 4096 4.3 -> 2.6 us,
+// 100 x 101 5.4 -> 3.3; from 200 x 1000 on several chunks are faster).
 constexpr int kColWaves = 16;
+constexpr int64_t kColDirect = 128;
+template <bool DIRECT>
 __global__ __launch_bounds__(kColWaves * kWave) void absmax_cols(const float* __restrict__ x, int64_t rows,
-                                                                 int64_t cols, unsigned* __restrict__ out) {
+                                                                 int64_t cols, int accumulate,
+                                                                 unsigned* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int64_t row_step = (int64_t)gridDim.y * kColWaves;
@@ -130,18 +161,22 @@ __global__ __launch_bounds__(kColWaves * kWave) void absmax_cols(const float* __
   if (group * (kWave * 4) >= cols) return;  // the whole workgroup
   const int64_t c = (group * kWave + lane) * 4;
   float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (c + 4 <= cols) {
+  const int live = c + 4 <= cols ? 4 : c < cols ? (int)(cols - c) : 0;  // columns this lane owns
+  if (cols >= 4) {
+    // the last lane of a row loads the row's last four columns, so that no lane takes a path of its own
+    const float* p = x + (live == 4 ? c : cols - 4);
 #pragma unroll 4
     for (int64_t r = r_first; r < rows; r += row_step) {
-      const float4 a = load_stream(x + r * cols + c);
+      const float4 a = load_stream(p + r * cols);
       m.x = fmaxf(m.x, fabsf(a.x)); m.y = fmaxf(m.y, fabsf(a.y));
       m.z = fmaxf(m.z, fabsf(a.z)); m.w = fmaxf(m.w, fabsf(a.w));
     }
-  } else if (c < cols) {
-    const int live = (int)(cols - c);  // 1 .. 3
-#pragma unroll 4
+    if (live == 3) m = make_float4(m.y, m.z, m.w, 0.0f);
+    if (live == 2) m = make_float4(m.z, m.w, 0.0f, 0.0f);
+    if (live == 1) m = make_float4(m.w, 0.0f, 0.0f, 0.0f);
+  } else if (live > 0) {
     for (int64_t r = r_first; r < rows; r += row_step) {
-      const float* p = x + r * cols + c;
+      const float* p = x + r * cols;
       m.x = fmaxf(m.x, fabsf(p[0]));
       m.y = fmaxf(m.y, fabsf(p[live > 1 ? 1 : 0]));
       m.z = fmaxf(m.z, fabsf(p[live > 2 ? 2 : 0]));
@@ -155,7 +190,8 @@ __global__ __launch_bounds__(kColWaves * kWave) void absmax_cols(const float* __
     float t = 0.0f;
 #pragma unroll
     for (int w = 0; w < kColWaves; ++w) t = fmaxf(t, reinterpret_cast<const float*>(sm[w])[threadIdx.x]);
-    atomicMax(out + col, abs_key(t));
+    if (DIRECT) out[col] = abs_key(accumulate ? fmaxf(t, f_from_bits((int)out[col])) : t);
+    else atomicMax(out + col, abs_key(t));
   }
 }
 
@@ -204,7 +240,15 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
   if (gran == MPQ_PER_ROW && row_blocks > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
   if (gran == MPQ_PER_COL && col_gx > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
   if (gran != MPQ_PER_TENSOR && (nch + 255) / 256 > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-  if (!accumulate && !direct && gran != MPQ_PER_TENSOR) {
+  const bool short_rows = gran == MPQ_PER_ROW && cols <= 256;
+  // row chunks: one up to kColDirect rows (half of that where a running maximum spares the clearing anyway), else
+  // two workgroups per CU, at least 4 rows per wave
+  const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
+  int64_t col_gy = ((int64_t)kNumCU * 2 + col_gx - 1) / col_gx;
+  if (col_gy > max_gy) col_gy = max_gy;
+  if (rows <= (accumulate ? kColDirect / 2 : kColDirect)) col_gy = 1;
+  const bool cleared = gran == MPQ_PER_ROW ? !direct && !short_rows : gran == MPQ_PER_COL && col_gy > 1;
+  if (!accumulate && cleared) {
     fill_u32<<<(unsigned)((nch + 255) / 256), 256, 0, st>>>(out, nch, 0u);
   }
   if (gran == MPQ_PER_TENSOR && n <= kOneMax) {
@@ -214,18 +258,18 @@ extern "C" int mpq_calibrate_absmax(const float* x, int64_t rows, int64_t cols, 
     float* partials = reinterpret_cast<float*>(ws);
     absmax_flat<<<g, kBlock, 0, st>>>(x, n, partials);
     absmax_finish<<<1, kBlock, 0, st>>>(partials, (int)g, accumulate, absmax_out);
+  } else if (short_rows && cols <= 32) {
+    absmax_rows_sub<4><<<wide_grid((rows + 63) / 64, kBlock), kBlock, 0, st>>>(x, rows, cols, accumulate, absmax_out);
+  } else if (short_rows) {
+    absmax_rows_sub<16><<<wide_grid((rows + 15) / 16, kBlock), kBlock, 0, st>>>(x, rows, cols, accumulate, absmax_out);
   } else if (gran == MPQ_PER_ROW) {
     const unsigned g = (unsigned)row_blocks;
     if (direct) absmax_rows<true><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
     else absmax_rows<false><<<g, kBlock, 0, st>>>(x, rows, cols, nseg, out);
   } else {
-    const int64_t gx = col_gx;
-    // two workgroups per CU, at least 4 rows per wave
-    int64_t gy = ((int64_t)kNumCU * 2 + gx - 1) / gx;
-    const int64_t max_gy = (rows + kColWaves * 4 - 1) / (kColWaves * 4);
-    if (gy > max_gy) gy = max_gy;
-    const dim3 grid = wide_grid(gx, kColWaves * kWave, (unsigned)gy);
-    absmax_cols<<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, out);
+    const dim3 grid = wide_grid(col_gx, kColWaves * kWave, (unsigned)col_gy);
+    if (col_gy == 1) absmax_cols<true><<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, accumulate, out);
+    else absmax_cols<false><<<grid, kColWaves * kWave, 0, st>>>(x, rows, cols, accumulate, out);
   }
   return launch_status();
 }
