@@ -336,14 +336,17 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
   const int per_row = w_gran == MPQ_PER_ROW;
   const bool w4 = w_storage_bits == 4;
   // (the score keeps one partial per 64 x 64 tile at most: its workspace holds no more)
-  if (const int waves = epi.yref ? 0 : skinny_waves(M, N, K))
+  const bool fast = fast_path(a_q, w_q, w4, M, N, K);
+  const int waves = epi.yref ? 0 : skinny_waves(M, N, K, fast && epi.amax);
+  const bool plain = !epi.yref && !epi.codes && !epi.act && !epi.amax;
+  const SplitPlan sp = plain && fast ? plan_split(M, N, K) : SplitPlan{};
+  const bool split = sp.split > 1 && ws && aligned16(ws) && ws_bytes >= (size_t)sp.split * (size_t)(M * N) * sizeof(int32_t);
+  if (waves)
     return launch_skinny(waves, w4, DmaArgs{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi,
                                             n_partials, 1, 0, false});
-  if (fast_path(a_q, w_q, w4, M, N, K)) {
+  if (fast) {
     DmaArgs d{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi, n_partials, 1, 0, false};
-    const bool plain = !epi.yref && !epi.codes && !epi.act && !epi.amax;
-    const SplitPlan sp = plain ? plan_split(M, N, K) : SplitPlan{};
-    if (sp.split > 1 && ws && aligned16(ws) && ws_bytes >= (size_t)sp.split * (size_t)(M * N) * sizeof(int32_t)) {
+    if (split) {
       int32_t* planes = reinterpret_cast<int32_t*>(ws);
       d.y_out = nullptr;
       d.acc_out = planes;
@@ -474,7 +477,7 @@ int qgemm_act_partials(const int8_t* a_q, const void* w_q, int w_storage_bits, i
                        float* absmax_out, float* part, int64_t room, int* parts, hipStream_t st) {
   EpiArgs epi{nullptr, nullptr, act, reinterpret_cast<unsigned*>(absmax_out), nullptr, 0, nullptr};
   *parts = 0;
-  const bool tiled = !skinny_waves(M, N, K) && fast_path(a_q, w_q, w_storage_bits == 4, M, N, K);
+  const bool tiled = fast_path(a_q, w_q, w_storage_bits == 4, M, N, K) && !skinny_waves(M, N, K, true);
   int64_t count = 0;
   if (tiled && max_partials(M, N) <= room) epi.amax_part = part;
   const int rc = run_qgemm(a_q, w_q, w_storage_bits, M, N, K, a_scale, w_scale, w_gran, y_out, nullptr, epi, &count, st);

@@ -788,7 +788,7 @@ int launch_dma_64(bool w4, bool long_k, bool two_stages, const DmaArgs& a);
 
 // Layers with few output tiles (qgemm_skinny.hip): how many waves split k, 0 where the layer is better
 // off with the tiled kernels.
-int skinny_waves(int64_t M, int64_t N, int64_t K);
+int skinny_waves(int64_t M, int64_t N, int64_t K, bool amax);
 int launch_skinny(int waves, bool w4, const DmaArgs& d);
 
 }  // namespace mpq

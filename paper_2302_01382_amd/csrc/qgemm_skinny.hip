@@ -143,9 +143,11 @@ __global__ __launch_bounds__(NW * 64) void qgemm_skinny(const int8_t* __restrict
 // packed int4.  Two tiles per CU (256 x 512): K = 256 3.2 | 5.0 / 4.1, 1024 4.6 | 6.2 / 7.3, 2304 7.1 | 8.4 / 8.3,
 // but 4608 11.4 | 12.6 / 10.1; from four tiles per CU on the tiled kernels win at every K (384 x 768: 6.1 / 4.1,
 // 9.2 / 6.6, 15.0 / 7.9).
-int skinny_waves(int64_t M, int64_t N, int64_t K) {
+// amax: with a running maximum, where the fast tiled kernels could take over, only up to one tile per CU: the atomics on its one address queue up (with ReLU and its
+// maximum 128 x 768 x 768 9.5 us against 7.4, 256 x 2304 x 512 14.3 against 10.4).
+int skinny_waves(int64_t M, int64_t N, int64_t K, bool amax) {
   const int64_t tm = (M + 15) / 16, tn = (N + 15) / 16;
-  if (tm > 2 * kNumCU || tn > 2 * kNumCU) return 0;
+  if (tm > 2 * kNumCU || tn > 2 * kNumCU || (amax && tm * tn > kNumCU)) return 0;
   if (tm * tn <= kNumCU) return K >= 2048 ? 8 : 4;
   return tm * tn <= 2 * kNumCU && K <= 2304 ? 4 : 0;
 }

@@ -96,3 +96,17 @@ def test_short_k_in_two_stages(mnk, wbits):
     y = np.maximum((host(acc).astype(np.float32) * sa) * sw, 0)
     np.testing.assert_array_equal(host(r), y)
     assert host(m)[0] == y.max()
+
+
+# with a running maximum up to one tile per CU in one launch, above that in 64 x 64 tiles
+@pytest.mark.parametrize("mnk", [(256, 256, 300), (256, 257, 300), (128, 768, 768), (130, 500, 272), (130, 500, 270)])
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_running_maximum_of_few_tiles(mnk, wbits):
+    M, N, K = mnk
+    a, w = rand_codes((M, K), 127, 82), rand_codes((N, K), 127 if wbits == 8 else 7, 83)
+    ws = w if wbits == 8 else oracle.pack4(w)
+    sa, sw = np.array([0.013], np.float32), np.array([0.002], np.float32)
+    want = np.maximum(((a.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32) * sa) * sw, 0)
+    y, m = mpq.qgemm_act(dev(a), dev(ws), dev(sa), dev(sw), mpq.ACT_RELU, wbits)
+    np.testing.assert_array_equal(host(y), want)
+    assert host(m)[0] == want.max()
