@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void sum_partials_k(const double* __restric
 // range) pair is a workgroup that writes its raw int32 accumulators to a plane of the workspace, and
 // one elementwise kernel adds the planes (integer sums: exact in any order, so the accumulators stay
 // bit-identical to the unsplit product) and applies the epilogue Y = (float(acc) * s_A) * s_W[n].
-// Layers of at most one or two 16 x 16 tiles per CU never come here (qgemm_skinny.hip).
+// Layers of at most one or two 16 x 16 tiles per CU come here with a long k only (split_beats_skinny).
 // Measured on the chip: the second kernel and the planes cost about 5 us, so the split pays only
 // where the unsplit grid is tiny; 1568 x 4608 x 512 (200 tiles of 64 x 64: 17 us) and 6272 x 2304 x 256
 // (14.6 us) lose 5-9 us with any split of either tile size, and stay unsplit.
@@ -263,6 +263,16 @@ static SplitPlan plan_split(int64_t M, int64_t N, int64_t K) {
   p.split = (int)((kt + per - 1) / per);            // no empty range
   if (p.split < 2) return SplitPlan{};
   return p;
+}
+
+// Layers that qgemm_skinny could take as well: with a workspace the split wins once k is long.  us, split | skinny
+// (M x N, int8 next to packed int4): 16 x 256 K = 8192 10.3 | 9.8 next to 10.8 | 8.1, 12288 10.4 | 13.2 next to
+// 10.7 | 10.7, 32768 13.5 | 30.7 next to 14.6 | 23.7; 128 x 512 K = 8192 11.8 | 10.2, 12288 12.0 | 13.9 next to 12.2 | 11.1,
+// 16384 12.8 | 17.8 next to 13.3 | 13.8; 16 x 4096, cut in four only, K = 12288 13.9 | 15.0, 32768 25.6 | 38.5 next to 28 | 25;
+// 1 x 1024, whose A is one row, packed int4 K = 16384 11.7 | 8.9, 32768 14.7 | 15.1.
+static bool split_beats_skinny(const SplitPlan& p, int64_t M, int64_t K, bool w4) {
+  if (w4) return K > (M == 1 ? 28672 : 13312) && p.split >= 8;
+  return K > 9216;
 }
 
 // acc = sum of `split` planes; ACC and / or Y from it.  VEC: four consecutive n per thread.
@@ -341,7 +351,7 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
   const bool plain = !epi.yref && !epi.codes && !epi.act && !epi.amax;
   const SplitPlan sp = plain && fast ? plan_split(M, N, K) : SplitPlan{};
   const bool split = sp.split > 1 && ws && aligned16(ws) && ws_bytes >= (size_t)sp.split * (size_t)(M * N) * sizeof(int32_t);
-  if (waves)
+  if (waves && !(split && split_beats_skinny(sp, M, K, w4)))
     return launch_skinny(waves, w4, DmaArgs{a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, st, epi,
                                             n_partials, 1, 0, false});
   if (fast) {

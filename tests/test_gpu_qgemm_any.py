@@ -98,6 +98,25 @@ def test_short_k_in_two_stages(mnk, wbits):
     assert host(m)[0] == y.max()
 
 
+# one 16 x 16 tile per CU at most: a long k (int8 above 9216, packed int4 above 13312 in eight ranges or more) is cut over
+# workgroups where there is a workspace, over the waves of a workgroup where there is none; on either side of the limits
+@pytest.mark.parametrize("mnk", [(5, 40, 9216), (5, 40, 9232), (49, 130, 12304), (16, 4096, 9248), (33, 72, 13312), (33, 72, 13344), (1, 60, 40000), (1, 60, 28672)])
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_long_k_of_few_tiles(mnk, wbits):
+    M, N, K = mnk
+    K += -K % 32 if wbits == 4 else 0
+    a, w = rand_codes((M, K), 127, 79), rand_codes((N, K), 127 if wbits == 8 else 7, 80)
+    ws = w if wbits == 8 else oracle.pack4(w)
+    sa = np.array([0.013], np.float32)
+    sw = (np.random.Generator(np.random.PCG64(81)).random(N).astype(np.float32) + 0.5) * np.float32(1e-3)
+    want = (a.astype(np.float64) @ w.astype(np.float64).T).astype(np.int64)
+    y_o = (want.astype(np.float32) * sa) * sw
+    for use in (True, False):
+        y, acc = mpq.qgemm(dev(a), dev(ws), dev(sa), dev(sw), wbits, mpq.PER_ROW, want_acc=True, use_workspace=use)
+        np.testing.assert_array_equal(host(acc), want)
+        np.testing.assert_array_equal(host(y), y_o)
+
+
 # with a running maximum up to one tile per CU in one launch, above that in 64 x 64 tiles
 @pytest.mark.parametrize("mnk", [(256, 256, 300), (256, 257, 300), (128, 768, 768), (130, 500, 272), (130, 500, 270)])
 @pytest.mark.parametrize("wbits", [8, 4])
