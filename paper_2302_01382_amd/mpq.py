@@ -165,8 +165,11 @@ def _stream() -> int:
         c = torch._C
         if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice"):
             torch.cuda.init()
+            in_bad_fork = getattr(c, "_cuda_isInBadFork", lambda: False)
 
             def _raw_stream_of_current_device():
+                if in_bad_fork():        # a child of a process that has used the GPU
+                    torch.cuda.init()    # raises, as a Stream object's construction does
                 return c._cuda_getCurrentRawStream(c._cuda_getDevice())
             _raw_stream = _raw_stream_of_current_device
         else:
