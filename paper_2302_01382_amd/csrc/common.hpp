@@ -95,6 +95,8 @@ inline dim3 wide_grid(int64_t want, int threads, unsigned y = 1) {
 // the limits are where one CU still beats the two launches, measured at each kernel.)
 constexpr int kOneBlock = 1024;
 
+constexpr int64_t kTiledFrom = 1ll << 19;
+
 // ---- device side ---------------------------------------------------------------------------
 #if defined(__HIPCC__)
 
@@ -227,8 +229,13 @@ __device__ __forceinline__ void store4(float* p, const float4& v) {
   *reinterpret_cast<f4_any*>(p) = f4_any{v.x, v.y, v.z, v.w};
 }
 
-// Visits every float4 of x4[0, n4) that the tile round-robin deals to this block: f(value, index).
-template <typename F>
+// Visits every float4 of x4[0, n4) that the tile round-robin deals to this block: f(value, index).  STREAM: loads
+// pass the caches by; in a tensor that starts anywhere neighbouring vectors share lines, and cached loads are faster.
+template <bool STREAM>
+__device__ __forceinline__ float4 load_vec(const float4* p) {
+  return STREAM ? load_stream(p) : load4(reinterpret_cast<const float*>(p));
+}
+template <bool STREAM = true, typename F>
 __device__ __forceinline__ void for_each_vec4_tiled(const float4* __restrict__ x4, int64_t n4, F&& f) {
   constexpr int64_t tile = (int64_t)kBlock * kTileVec;
   const int64_t ntiles = (n4 + tile - 1) / tile;
@@ -237,21 +244,21 @@ __device__ __forceinline__ void for_each_vec4_tiled(const float4* __restrict__ x
     if ((t + 1) * tile <= n4) {  // block-uniform
       float4 v[kTileVec];
 #pragma unroll
-      for (int u = 0; u < kTileVec; ++u) v[u] = load_stream(x4 + base + u * kBlock);
+      for (int u = 0; u < kTileVec; ++u) v[u] = load_vec<STREAM>(x4 + base + u * kBlock);
 #pragma unroll
       for (int u = 0; u < kTileVec; ++u) f(v[u], base + u * kBlock);
     } else {
 #pragma unroll
       for (int u = 0; u < kTileVec; ++u) {
         const int64_t i = base + u * kBlock;
-        if (i < n4) f(load_stream(x4 + i), i);
+        if (i < n4) f(load_vec<STREAM>(x4 + i), i);
       }
     }
   }
 }
 
 // Same walk over two tensors at once: f(a, b); two + two loads in flight.
-template <typename F>
+template <bool STREAM = true, typename F>
 __device__ __forceinline__ void for_each_vec4_pair_tiled(const float4* __restrict__ a4,
                                                          const float4* __restrict__ b4, int64_t n4, F&& f) {
   constexpr int U = 2;
@@ -260,23 +267,22 @@ __device__ __forceinline__ void for_each_vec4_pair_tiled(const float4* __restric
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t base = t * tile + threadIdx.x;
     if ((t + 1) * tile <= n4) {
-      const float4 a0 = load_stream(a4 + base), b0 = load_stream(b4 + base), a1 = load_stream(a4 + base + kBlock),
-                   b1 = load_stream(b4 + base + kBlock);
+      const float4 a0 = load_vec<STREAM>(a4 + base), b0 = load_vec<STREAM>(b4 + base), a1 = load_vec<STREAM>(a4 + base + kBlock),
+                   b1 = load_vec<STREAM>(b4 + base + kBlock);
       f(a0, b0);
       f(a1, b1);
     } else {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t i = base + u * kBlock;
-        if (i < n4) f(load_stream(a4 + i), load_stream(b4 + i));
+        if (i < n4) f(load_vec<STREAM>(a4 + i), load_vec<STREAM>(b4 + i));
       }
     }
   }
 }
 
-// The same over tensors that start anywhere, where neighbouring vectors share lines and cached loads beat
-// streaming ones, or that are too small to give every CU a tile: one vector per thread and trip, four trips'
-// loads in flight.  Grid: flat_grid(n, 4 * kBlock).
+// The same over tensors of up to kTiledFrom elements, too small to give every CU a tile: one vector per thread and
+// trip, four trips' loads in flight.  Grid: flat_grid(n, 4 * kBlock).
 template <typename F>
 __device__ __forceinline__ void for_each_vec4_strided(const float* __restrict__ x, int64_t n4, F&& f) {
   const int64_t step = (int64_t)gridDim.x * kBlock;

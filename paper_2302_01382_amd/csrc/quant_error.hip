@@ -26,8 +26,9 @@ constexpr int64_t kSeg = 16384;  // columns per wave item in the per-row kernels
 
 // ---- per tensor ----------------------------------------------------------------------------
 // partials: double [gridDim.x][NB]
-// PLAN: a tensor that a sweep plan can hold, summed as the batched kernels do (bit for bit)
-template <int NB, bool PLAN>
+// PLAN: a tensor that a sweep plan can hold, summed as the batched kernels do (bit for bit); any other in tiles or,
+// small ones, one vector a trip
+template <int NB, bool PLAN, bool TILED>
 __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, int64_t n,
                                                   const float* __restrict__ absmax, int b_lo,
                                                   double* __restrict__ partials) {
@@ -35,15 +36,18 @@ __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, i
   s.init(absmax[0], b_lo);
   s.clear();
   const int64_t n4 = n >> 2;
-  if (PLAN) for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
+  if (TILED) for_each_vec4_tiled<PLAN>(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { s.add4(v); });
   else for_each_vec4_strided(x, n4, [&](const float4 v) { s.add4(v); });
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
   if (blockIdx.x == 0 && j < n) s.add(x[j]);
-  __shared__ float sm[kBlock / kWave][NB];
+  using Sum = std::conditional_t<PLAN, float, double>;
+  __shared__ Sum sm[kBlock / kWave][NB];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const float w = wave_sum(s.total(b));
+    Sum w;
+    if constexpr (PLAN) w = wave_sum(s.total(b));
+    else w = wave_sum_rows(s.total(b));
     if (lane == 0) sm[wave][b] = w;
   }
   __syncthreads();
@@ -53,7 +57,8 @@ __global__ __launch_bounds__(kBlock) void qe_flat(const float* __restrict__ x, i
         ((double)sm[2][threadIdx.x] + (double)sm[3][threadIdx.x]);
 }
 
-// Up to kOneLimit / NB elements and kOneMost: one workgroup, one launch; a lane has an fp32 sum per element of a
+// Up to kOneLimit / NB elements and kOneMost (a quarter of it at any alignment, where two launches have chains of four
+// as well): one workgroup, one launch; a lane has an fp32 sum per element of a
 // vector, and double takes over from rows of sixteen lanes on.  Device time for b = 2..8, two launches against this: 64 x 64 5.7 / 4.6 us, 64 x 128
 // 6.0 / 5.3, 64 x 256 6.1 / 6.2 (and a launch, 4.3 us of the host's time, less); for one width 128 x 256 4.3 / 2.8,
 // 256 x 256 4.3 / 3.7, from 80000 elements on two launches are faster.
@@ -189,47 +194,63 @@ __global__ __launch_bounds__(kBlock) void qe_rows_sub(const float* __restrict__ 
   const float m = absmax[r];
   const float4* r4 = reinterpret_cast<const float4*>(x + r * cols);
   const int64_t e4 = cols >> 2;
-  float4 v[4];  // four vectors in flight per lane; those past the row's end are zeros, which add nothing
-  auto load = [&](int64_t i) { return PLAN ? load_stream(r4 + i) : load4(reinterpret_cast<const float*>(r4 + i)); };
-  auto fetch = [&](int64_t i0) {
-    if (i0 + 4 * LPR <= e4) {  // the same for all lanes of the wave
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = load(i0 + k * LPR + lr);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t i = i0 + k * LPR + lr;
-        v[k] = i < e4 ? load(i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      }
-    }
-  };
-  fetch(0);
-  const float last = lr < (int)(cols & 3) ? x[r * cols + (e4 << 2) + lr] : 0.0f;
   std::conditional_t<PLAN, Sweep<NB>, Sweep4<NB>> s;
-  if (NB == 1) {
-    s.init(m, b_lo);
+  auto constants = [&]() {
     s.clear();
-  } else {
+    s.m = m;
     // lane j < 7: inv of bit-width b_lo + j; lane 7 + j: scale of bit-width b_lo + j
     const int j = lr < 7 ? lr : lr - 7;
     float sc, inv;
     bit_constants(m, b_lo + (j < NB ? j : 0), sc, inv);
     const float mine = lr < 7 ? inv : sc;
-    s.m = m;
-    s.clear();
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       s.inv[b] = __shfl(mine, b, LPR);
       s.sc[b] = __shfl(mine, 7 + b, LPR);
     }
-  }
-  for (int64_t i0 = 0; i0 < e4; i0 += 4 * LPR) {
+  };
+  if constexpr (PLAN) {  // cols % 4 == 0
+    constants();
+    int64_t i = lr;
+    for (; i + 3 * LPR < e4; i += 4 * LPR) {
+      const float4 a = load_stream(r4 + i), b = load_stream(r4 + i + LPR), c = load_stream(r4 + i + 2 * LPR),
+                   d = load_stream(r4 + i + 3 * LPR);
+      s.add4(a); s.add4(b); s.add4(c); s.add4(d);
+    }
+    for (; i < e4; i += LPR) s.add4(load_stream(r4 + i));
+  } else {
+    // four vectors in flight per lane, the first ones in front of the constants, those that are left at the
+    // end of a row as well; vectors past the row's end are zeros, which add nothing
+    auto load = [&](int64_t i) { return load4(reinterpret_cast<const float*>(r4 + i)); };
+    auto fetch = [&](float4 (&v)[4], int64_t i0) {
+      if (i0 + 4 * LPR <= e4) {  // the same for all lanes of the wave
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (i0 + k * LPR < e4) s.add4(v[k]);
-    if (i0 + 4 * LPR < e4) fetch(i0 + 4 * LPR);
+        for (int k = 0; k < 4; ++k) v[k] = load(i0 + k * LPR + lr);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int64_t i = i0 + k * LPR + lr;
+          if (i0 + k * LPR < e4) v[k] = i < e4 ? load(i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);  // else not used
+        }
+      }
+    };
+    float4 v[4];
+    fetch(v, 0);
+    const float last = lr < (int)(cols & 3) ? x[r * cols + (e4 << 2) + lr] : 0.0f;
+    if (NB == 1) {
+      s.init(m, b_lo);
+      s.clear();
+    } else {
+      constants();
+    }
+    for (int64_t i0 = 0; i0 < e4; i0 += 4 * LPR) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k * LPR < e4) s.add4(v[k]);
+      if (i0 + 4 * LPR < e4) fetch(v, i0 + 4 * LPR);
+    }
+    s.add(last);
   }
-  s.add(last);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const float w = LPR == 16 ? row16_sum(s.total(b)) : wave_sum(s.total(b));
@@ -436,14 +457,14 @@ struct PairSum {
     add(a.x, b.x, 0); add(a.y, b.y, 1); add(a.z, b.z, 2); add(a.w, b.w, 3);
   }
 };
-template <bool ALIGNED>
+template <bool ALIGNED, bool TILED>
 __global__ __launch_bounds__(kBlock) void sse_pair_k(const float* __restrict__ y,
                                                      const float* __restrict__ yr, int64_t n,
                                                      double* __restrict__ partials) {
   PairSum s;
   const int64_t n4 = n >> 2;
-  if (ALIGNED)
-    for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
+  if (TILED)
+    for_each_vec4_pair_tiled<ALIGNED>(reinterpret_cast<const float4*>(y), reinterpret_cast<const float4*>(yr), n4,
                              [&](const float4 a, const float4 b) { s.add4(a, b); });
   else for_each_vec4_pair_strided(y, yr, n4, [&](const float4 a, const float4 b) { s.add4(a, b); });
   const int64_t j = (n4 << 2) + threadIdx.x;  // the last n % 4 elements
@@ -552,15 +573,17 @@ template <int NB>
 static void launch_qe(const QeGeom& g, const float* x, int64_t rows, int64_t cols, int gran,
                       const float* absmax, int b_lo, double* out, double* ws, hipStream_t st) {
   const int64_t n = rows * cols;
-  if (gran == MPQ_PER_TENSOR && n * NB <= kOneLimit && n <= kOneMost) {
+  if (gran == MPQ_PER_TENSOR && n * NB <= kOneLimit && n <= (aligned16(x) ? kOneMost : kOneMost / 4)) {
     qe_one<NB><<<1, kOneBlock, 0, st>>>(x, (int)n, absmax, b_lo, out);
   } else if (gran == MPQ_PER_TENSOR) {
     unsigned parts = g.gx;
     if (aligned16(x)) {
-      qe_flat<NB, true><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+      qe_flat<NB, true, true><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+    } else if (n > kTiledFrom) {
+      qe_flat<NB, false, true><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
     } else {
       parts = flat_grid(n, kBlock * 4, 4);
-      qe_flat<NB, false><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
+      qe_flat<NB, false, false><<<parts, kBlock, 0, st>>>(x, n, absmax, b_lo, ws);
     }
     qe_finish_tree<NB><<<1, kBlock, 0, st>>>(ws, (int64_t)parts, out);
   } else if (gran == MPQ_PER_ROW) {
@@ -723,9 +746,11 @@ extern "C" int mpq_sse_pair(const float* y, const float* y_ref, int64_t n, doubl
   }
   double* wsd = reinterpret_cast<double*>(ws);
   const bool aligned = aligned16(y) && aligned16(y_ref);
-  const unsigned grid = aligned ? flat_grid(n >> 2, kBlock * 2) : flat_grid(n, kBlock * 4);
-  if (aligned) sse_pair_k<true><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
-  else sse_pair_k<false><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  const bool tiled = aligned || n > kTiledFrom;
+  const unsigned grid = tiled ? flat_grid(n >> 2, kBlock * 2) : flat_grid(n, kBlock * 4);
+  if (aligned) sse_pair_k<true, true><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  else if (tiled) sse_pair_k<false, true><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
+  else sse_pair_k<false, false><<<grid, kBlock, 0, st>>>(y, y_ref, n, wsd);
   qe_finish_tree<1><<<1, kBlock, 0, st>>>(wsd, (int64_t)grid, sse_out);
   return launch_status();
 }
