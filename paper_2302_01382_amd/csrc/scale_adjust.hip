@@ -61,9 +61,23 @@ struct GradAcc4 {
   __device__ __forceinline__ float loss() const { return (k[0].s_loss + k[1].s_loss) + (k[2].s_loss + k[3].s_loss); }
 };
 
+// One for all of them: for rows of one vector per lane, where the products' own roundings count (a sum's first
+// product is rounded, the others enter it exactly: 1000 x 64 1.31e-8 of the sum of absolute values against 1.36e-8).
+template <bool HAS_G>
+struct GradAcc1 {
+  GradAcc k;
+  __device__ __forceinline__ void add(const TwoScales& t, float x, float g) { k.template add<HAS_G>(t, x, g); }
+  __device__ __forceinline__ void add4(const TwoScales& t, const float4& v, const float4& g) {
+    add(t, v.x, g.x); add(t, v.y, g.y); add(t, v.z, g.z); add(t, v.w, g.w);
+  }
+  __device__ __forceinline__ float code() const { return k.s_code; }
+  __device__ __forceinline__ float x() const { return k.s_x; }
+  __device__ __forceinline__ float loss() const { return k.s_loss; }
+};
+
 // ---- per tensor: one partial triple per workgroup ----------------------------------------------
-// TILED: tiles dealt round-robin, else (small or unaligned tensors) one vector a trip
-template <bool HAS_G, bool TILED>
+// TILED: tiles dealt round-robin, else (small tensors) one vector a trip
+template <bool HAS_G, bool TILED, bool STREAM>
 __global__ __launch_bounds__(kBlock) void sg_flat(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t n, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
@@ -73,10 +87,10 @@ __global__ __launch_bounds__(kBlock) void sg_flat(const float* __restrict__ x, c
   const int64_t n4 = n >> 2;
   if (TILED) {
     if (HAS_G)
-      for_each_vec4_pair_tiled(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
+      for_each_vec4_pair_tiled<STREAM>(reinterpret_cast<const float4*>(x), reinterpret_cast<const float4*>(g), n4,
                                [&](const float4 v, const float4 u) { a.add4(t, v, u); });
     else
-      for_each_vec4_tiled(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { a.add4(t, v, v); });
+      for_each_vec4_tiled<STREAM>(reinterpret_cast<const float4*>(x), n4, [&](const float4 v, int64_t) { a.add4(t, v, v); });
   } else {
     if (HAS_G) for_each_vec4_pair_strided(x, g, n4, [&](const float4 v, const float4 u) { a.add4(t, v, u); });
     else for_each_vec4_strided(x, n4, [&](const float4 v) { a.add4(t, v, v); });
@@ -128,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void sg_finish(const double* __restrict__ p
 // U 16-byte loads per tensor in flight per lane, the first ones in front of the scales: four where a row has
 // several trips for them (12288 x 768 9.8 -> 8.9 us, with a gradient 13.7 -> 12.5), one where the code's length
 // counts, as it is fetched cold (300 x 256 2.9 -> 2.4).
-template <bool HAS_G, int LPR, int U, bool STREAM>
+template <typename Acc, bool HAS_G, int LPR, int U, bool STREAM>
 __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, const float* __restrict__ g,
                                                   int64_t rows, int64_t cols, const float* __restrict__ inv,
                                                   const float* __restrict__ scale, int bits,
@@ -157,7 +171,7 @@ __global__ __launch_bounds__(kBlock) void sg_rows(const float* __restrict__ x, c
   const int64_t e = (cols & ~(int64_t)3) + lr;
   const float xe = tail ? xr[e] : 0.0f, ge = HAS_G && tail ? gr[e] : 0.0f;
   const TwoScales t(inv[r], scale[r], bits);
-  GradAcc4<HAS_G> a;
+  Acc a;
 #pragma unroll 1
   for (int64_t c0 = 0; c0 + 4 <= cols; c0 += U * kStep) {  // the same trips for every lane of the row
 #pragma unroll
@@ -210,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void fqs_flat(const float* __restrict__ x, 
   if (blockIdx.x == 0 && j < n) fqs_emit1(t, x[j], j, y, codes);
 }
 
-// LPR lanes per row (16 or 64); blockIdx.y: segments of seg columns (a multiple of 4)
+// LPR lanes per row (4, 16 or 64); blockIdx.y: segments of seg columns (a multiple of 4)
 template <int LPR>
 __global__ __launch_bounds__(kBlock) void fqs_rows(const float* __restrict__ x, int64_t rows, int64_t cols,
                                                    const float* __restrict__ inv, const float* __restrict__ scale,
@@ -227,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void fqs_rows(const float* __restrict__ x, 
     float4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (i + k * kStep + 4 <= end) v[k] = load_stream(x + i + k * kStep);
+      if (i + k * kStep + 4 <= end) v[k] = LPR == kWave ? load_stream(x + i + k * kStep) : load4(x + i + k * kStep);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (i + k * kStep + 4 <= end) fqs_emit4(t, v[k], i + k * kStep, y, codes);
@@ -278,6 +292,8 @@ extern "C" int mpq_fake_quant_scales(const float* x, int64_t rows, int64_t cols,
   hipStream_t st = (hipStream_t)stream;
   if (gran == MPQ_PER_TENSOR)
     fqs_flat<<<flat_grid((rows * cols) >> 2, kBlock * kTileVec), kBlock, 0, st>>>(x, rows * cols, inv, scale, bits, y_out, codes_out);
+  else if (cols <= 32)
+    fqs_rows<4><<<wide_grid((rows + 63) / 64, kBlock), kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, cols, y_out, codes_out);
   else if (cols <= kShortRow)
     fqs_rows<16><<<wide_grid((rows + 15) / 16, kBlock), kBlock, 0, st>>>(x, rows, cols, inv, scale, bits, cols, y_out, codes_out);
   else {
@@ -294,7 +310,7 @@ extern "C" int mpq_fake_quant_scales(const float* x, int64_t rows, int64_t cols,
 extern "C" size_t mpq_scale_grad_workspace_bytes(int64_t rows, int64_t cols, int gran) {
   if (check_sa(rows, cols, gran, 8) != MPQ_OK || gran != MPQ_PER_TENSOR) return 0;
   const int64_t n = rows * cols;
-  unsigned g = flat_grid(n, kBlock * 4);  // the grid of small and unaligned tensors
+  unsigned g = flat_grid(n, kBlock * 4);  // the grid of small tensors
   for (int v = 0; v < 2; ++v) {           // ... and for the largest grid any variant may use
     const unsigned c = sg_grid(n, v != 0);
     g = c > g ? c : g;
@@ -317,28 +333,27 @@ extern "C" int mpq_scale_grad(const float* x, int64_t rows, int64_t cols, int gr
     if (!ws || ws_bytes < mpq_scale_grad_workspace_bytes(rows, cols, gran)) return MPQ_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(ws) & 7u) return MPQ_ERR_ALIGN;
     double* partials = reinterpret_cast<double*>(ws);
-    // below 2^19 elements tiles give too few CUs a workgroup: 255000 4.7 us against 5.4, but 1000001 6.2 against 5.8
-    const bool tiled = aligned16(x) && (!g || aligned16(g)) && n > ((int64_t)1 << 19);
+    // below kTiledFrom tiles give too few CUs a workgroup: 255000 4.7 us against 5.4, but 1000001 6.2 against 5.8
+    const bool tiled = n > kTiledFrom, aligned = aligned16(x) && (!g || aligned16(g));
     const unsigned grid = tiled ? sg_grid(n, g != nullptr) : flat_grid(n, kBlock * 4);
-#define MPQ_SG(G_, T_) sg_flat<G_, T_><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials)
-    if (g) {
-      if (tiled) MPQ_SG(true, true);
-      else MPQ_SG(true, false);
-    } else {
-      if (tiled) MPQ_SG(false, true);
-      else MPQ_SG(false, false);
-    }
+#define MPQ_SG(G_) \
+  (!tiled ? sg_flat<G_, false, false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials) \
+   : aligned ? sg_flat<G_, true, true><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials) \
+             : sg_flat<G_, true, false><<<grid, kBlock, 0, st>>>(x, g, n, inv, scale, bits, partials))
+    if (g) MPQ_SG(true);
+    else MPQ_SG(false);
 #undef MPQ_SG
     sg_finish<<<1, kBlock, 0, st>>>(partials, (int64_t)grid, scale, dinv_out, dscale_out, loss_out);
   } else {
     const bool sixteen = sg_sixteen(rows, cols), short_code = cols <= (sixteen ? 256 : 768), stream = rows * cols > kStreamFrom;
     const unsigned grid = (unsigned)(sixteen ? (rows + 15) / 16 : (rows + 3) / 4);
-#define MPQ_SG(G_, LPR_, U_, S_) \
-  sg_rows<G_, LPR_, U_, S_><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out)
-#define MPQ_SG_U(G_, LPR_)                         \
-  if (stream) MPQ_SG(G_, LPR_, 4, true);           \
-  else if (short_code) MPQ_SG(G_, LPR_, 1, false); \
-  else MPQ_SG(G_, LPR_, 4, false)
+#define MPQ_SG(ACC_, G_, LPR_, U_, S_) \
+  sg_rows<ACC_<G_>, G_, LPR_, U_, S_><<<grid, kBlock, 0, st>>>(x, g, rows, cols, inv, scale, bits, dinv_out, dscale_out, loss_out)
+#define MPQ_SG_U(G_, LPR_)                                             \
+  if (stream) MPQ_SG(GradAcc4, G_, LPR_, 4, true);                     \
+  else if (cols < 4 * LPR_ + 4) MPQ_SG(GradAcc1, G_, LPR_, 1, false);  \
+  else if (short_code) MPQ_SG(GradAcc4, G_, LPR_, 1, false);           \
+  else MPQ_SG(GradAcc4, G_, LPR_, 4, false)
     if (sixteen) {
       if (g) { MPQ_SG_U(true, 16); }
       else { MPQ_SG_U(false, 16); }

@@ -65,7 +65,7 @@ def test_streaming_calls(shape, off, gran):
 @pytest.mark.parametrize("shape", [(1, 1), (5, 3), (67, 7), (33, 255), (20, 256), (9, 257), (70, 1030), (6, 4099), (2, 9001), (300, 64)])
 @pytest.mark.parametrize("off", [0, 3])
 def test_scale_adjustment(shape, off, gran):
-    """16 lanes (up to 256 columns) or a wave per row, pieces past the row's end, rows cut into segments."""
+    """4, 16 (up to 256 columns) lanes or a wave per row, pieces past the row's end, rows cut into segments."""
     x, g = data(shape, 96), data(shape, 97)
     m = oracle.absmax(x, gran)
     for bits in (3, 8):
@@ -178,7 +178,7 @@ def lane_sums(e):
 @pytest.mark.parametrize("n", [4096, 16384, 32768, 65536, 69632])
 @pytest.mark.parametrize("off", [0, 1])
 def test_small_tensors_are_summed_as_closely_as_larger_ones(n, off):
-    """One workgroup up to 65536 elements (one width) and 32768 (squared distance), any alignment: rms error over 24
+    """One workgroup up to 65536 elements (one width; 16384 unaligned) and 32768 (squared distance): rms error over 24
     inputs no larger than that of lane_sums, with 25 % for the spread of either estimate."""
     err = np.zeros((24, 4))
     for i in range(24):
@@ -232,8 +232,25 @@ def test_scale_gradients_are_summed_as_closely_as_by_64_lanes(shape):
 # lanes per row (4 up to 32 columns, 16 up to 256), rows per wave of a narrow tensor's columns (16, 64 and 128 columns),
 # one row chunk of column maxima (64 and 128 rows), long rows in segments of 1024 columns and of 16384
 @pytest.mark.parametrize("gran", [mpq.PER_ROW, mpq.PER_COL])
-@pytest.mark.parametrize("shape", [(70, 32), (70, 33), (300, 16), (300, 17), (64, 64), (65, 65), (128, 128), (129, 129), (130, 256), (70, 258),
+@pytest.mark.parametrize("shape", [(70, 31), (70, 32), (70, 33), (300, 16), (300, 17), (64, 64), (65, 65), (128, 128), (129, 129), (130, 256), (70, 258),
                                    (129, 3), (3, 70001), (2, 70002), (1, 5), (1100, 2050), (2060, 1030), (4000, 20), (1, 36866)])
 @pytest.mark.parametrize("off", [0, 1])
 def test_streaming_calls_where_the_layout_changes(shape, off, gran):
     test_streaming_calls(shape, off, gran)
+
+
+@pytest.mark.parametrize("shape", [(300, 16), (70, 31), (70, 32), (70, 33), (5000, 7)])
+def test_explicit_scales_of_short_rows(shape):
+    test_scale_adjustment(shape, 0, mpq.PER_ROW)
+    test_scale_adjustment(shape, 1, mpq.PER_ROW)
+
+
+# one vector a trip up to 2^19 elements, tiles above, streamed where the tensor is aligned
+@pytest.mark.parametrize("n", [2 ** 19, 2 ** 19 + 1, 2 ** 19 + 4098])
+def test_per_tensor_sums_where_the_layout_changes(n):
+    x, ref = data((1, n), 105), data((1, n), 106)
+    m = oracle.absmax(x) * np.float32(1.25)
+    for off in (0, 1, 3):
+        for widths in ((2, 8), (3, 3)):
+            np.testing.assert_allclose(host(mpq.quant_error(at(x, off), dev(m), *widths)), oracle.quant_error(x, m, *widths), rtol=1e-6)
+        assert host(mpq.sse_pair(at(x, off), at(ref, (off + 1) % 4)))[0] == pytest.approx(oracle.sse_pair(x, ref), rel=1e-6)
