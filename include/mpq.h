@@ -60,13 +60,14 @@ int mpq_last_hip_error(void);
 int mpq_version(void);
 /* Optional.  Configures, on the caller's current device, every kernel variant of the quantized-layer
  * calls and of mpq_hutchinson_quad_signs that needs more than the default amount of on-chip memory (a
- * per-kernel runtime attribute, not a stream operation).  Without it the first call that selects a variant does the same for
- * that variant; code that records the calls into a HIP graph calls mpq_init() before the capture
- * begins, or runs each call once eagerly first.  Thread safe, idempotent, allocates nothing. */
+ * per-kernel runtime attribute, not a stream operation).  Without it the first call that selects a
+ * variant does the same for that variant; code that records the calls into a HIP graph calls
+ * mpq_init() before the capture begins, or runs each call once eagerly first.  Thread safe,
+ * idempotent, allocates nothing. */
 int mpq_init(void);
 
 /* ---- Sec. 3.1, calibration step: m = max |x| --------------------------------------------
- * x          [rows x cols] fp32, any alignment (16-byte alignment enables 128-bit loads).
+ * x          [rows x cols] fp32, any alignment.
  * gran       PER_TENSOR -> absmax_out[1]; PER_ROW -> [rows]; PER_COL -> [cols].
  * accumulate 0: absmax_out is overwritten; 1: absmax_out = max(absmax_out, new), the running
  *            maximum over successive calibration batches (absmax_out must then hold valid
@@ -232,8 +233,8 @@ int mpq_noise_inject_sweep(const float* x, int64_t rows, int64_t cols, int gran,
  * aligned): partial int32 accumulators go to the workspace and are added by a second kernel --
  * integer sums, so acc_out and y_out are bit-identical to the unsplit product.  With ws == NULL (or
  * too small) the same results are computed without the split; layers of very few tiles (inference
- * batch 1) split K inside one kernel and do not touch the workspace; the query returns 0 for shapes
- * that are never cut. */
+ * batch 1) split a K of up to some ten thousand inside one kernel and do not touch the workspace; the
+ * query returns 0 for shapes that are never cut. */
 size_t mpq_qgemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int w_storage_bits);
 int mpq_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int64_t M, int64_t N,
               int64_t K, const float* a_scale, const float* w_scale, int w_gran, float* y_out,
@@ -298,9 +299,11 @@ size_t mpq_hutchinson_quad_workspace_bytes(int64_t M, int64_t K, int64_t P);
 int mpq_hutchinson_quad(const float* x, int64_t M, int64_t K, const float* v, int64_t P,
                         double* quad_out, void* ws, size_t ws_bytes, void* stream);
 /* The same quadratic forms for the sign probes mpq_rademacher(seed, stream_id, P, K) would store,
- * drawn inside the kernel: no probe matrix exists in memory.  Results equal those of
- * mpq_hutchinson_quad on that matrix up to the fp32 rounding of a different summation order over k.  Needs K % 16 == 0 and x 16-byte aligned
- * (MPQ_ERR_SHAPE otherwise: draw the matrix and use the call above).  Same workspace query. */
+ * drawn inside the kernel: no probe matrix exists in memory.  For finite x the results equal those of
+ * mpq_hutchinson_quad on that matrix up to the fp32 rounding of a different summation order over k
+ * (squares and the sum over 32 rows in fp32, everything above in double); an x that is not finite
+ * makes every form NaN here, where the call above may give +inf.  Needs K % 16 == 0 and x 16-byte
+ * aligned (MPQ_ERR_SHAPE otherwise: draw the matrix and use the call above).  Same workspace query. */
 int mpq_hutchinson_quad_signs(const float* x, int64_t M, int64_t K, uint64_t seed, uint64_t stream_id,
                               int64_t P, double* quad_out, void* ws, size_t ws_bytes, void* stream);
 /* The estimate itself (HOST function on the P quadratic forms read back from the device):
@@ -356,7 +359,8 @@ int mpq_scale_sgd_step(float* inv, float* scale, const double* dinv, const doubl
  *   l < n_layers - 1:  mpq_qgemm_act(..., act, h_l, running maximum into a_absmax[l + 1]),
  *   last layer:        mpq_qgemm_score(..., y_ref) -> sse_out[0],
  * i.e. the results of exactly those calls, in two launches per layer, issued from native code.
- * a_absmax[1..] is cleared first (one small kernel).
+ * a_absmax[1..] is cleared first (one small kernel).  The workspace is scratch from the first layer on
+ * (maxima of a layer's workgroups, then the score's partial sums).
  * The caller provides layer 0's a_codes, a_absmax[0] and a_scale[0] (the model's input does not
  * depend on the configuration).  mpq_stack_layer holds HOST arrays of DEVICE pointers.
  * Errors: as the calls above; every argument is checked before the first launch. */

@@ -31,7 +31,7 @@ __global__ void fill_u32_k(unsigned* p, unsigned v) { p[0] = v; }
 //
 // What bounds it: the latency of its loads (a workgroup waits a k tile's round trip, hidden by the
 // two register sets and by the other workgroups of the CU).  Against loading every byte by itself (us):
-// 2999 x 1155 x 1021 int8 148 -> 20, 16384 x 1001 x 1000 413 -> 63, 512 x 1001 x 512 102 -> 8.7,
+// 2999 x 1155 x 1021 int8 169 -> 18.8, 16384 x 1001 x 1000 413 -> 63, 512 x 1001 x 512 102 -> 8.7,
 // 6272 x 2302 x 256 packed int4 279 -> 20 (M x K x N); an aligned 6272 x 2304 x 256 takes 13.5 on the fast path.
 // =====================================================================================================
 constexpr int kAnyThreads = 256;  // 4 waves as 2 x 2

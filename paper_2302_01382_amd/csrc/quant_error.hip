@@ -11,9 +11,9 @@
 // gets into the inner loop (constants live in registers for the whole kernel, loads are 128-bit
 // and four deep).
 //
-// Reproducibility: per-lane fp32 partial sums (a lane sees at most ~4k elements), fixed-order
-// DPP wave reduction, then double precision across waves / blocks in a fixed order.  No float
-// atomics anywhere.
+// Reproducibility: per-lane fp32 partial sums (a lane adds at most ~4k elements one after the other; per column
+// rows * groups of 256 columns / 8192 of them, at least 8), fixed-order DPP wave reduction, then double
+// precision across waves / blocks in a fixed order.  No float atomics anywhere.
 #include "common.hpp"
 #include "sweep.hpp"
 

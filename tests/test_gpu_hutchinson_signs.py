@@ -15,7 +15,7 @@ def want(x, v):
 
 
 @pytest.mark.parametrize("mkp", [(1, 16, 1), (31, 48, 3), (32, 128, 32), (33, 144, 33), (65, 256, 64), (40, 272, 65),
-                                 (300, 1040, 5), (70, 2064, 130), (9000, 256, 4), (20000, 80, 7)])
+                                 (300, 1040, 5), (70, 2064, 130), (200, 4096, 3), (9000, 256, 4), (20000, 80, 7)])
 def test_layouts(mkp):
     M, K, P = mkp
     x = data((M, K), 110)
@@ -77,3 +77,10 @@ def test_replay_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(host(out), eager)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_values_that_are_not_finite_make_the_form_nan(bad):
+    x = data((70, 144), 114)
+    x[33, 20] = bad
+    assert np.all(np.isnan(host(mpq.hutchinson_quad_signs(dev(x), 5, 0, 35))))
