@@ -349,17 +349,17 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
                                         (unsigned long long)b * 128u;
         if (whole_blocks) {
           words[pb] = sign_block(sg, base);
-        } else {  // the 128 signs start at any multiple of 16 elements: cut out of two blocks
+        } else {  // the 128 signs start at any multiple of 16 elements: cut out of two blocks, in named values (an
+          // array of words went to scratch memory: 4798 x 192 7.8 us against 7.15)
           const U4 p0 = sign_block(sg, base), p1 = sign_block(sg, base + 128u);
-          unsigned w[8] = {p0.a, p0.b, p0.c, p0.d, p1.a, p1.b, p1.c, p1.d};
           const unsigned at = (unsigned)base & 127u;
-#pragma unroll
-          for (int i = 0; i < 7; ++i) w[i] = (at & 16u) ? (w[i] >> 16) | (w[i + 1] << 16) : w[i];
-#pragma unroll
-          for (int i = 0; i < 6; ++i) w[i] = (at & 32u) ? w[i + 1] : w[i];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) w[i] = (at & 64u) ? w[i + 2] : w[i];
-          words[pb] = U4{w[0], w[1], w[2], w[3]};
+          auto cut2 = [&](unsigned lo, unsigned hi) { return (at & 16u) ? (lo >> 16) | (hi << 16) : lo; };
+          const unsigned w0 = cut2(p0.a, p0.b), w1 = cut2(p0.b, p0.c), w2 = cut2(p0.c, p0.d), w3 = cut2(p0.d, p1.a),
+                         w4 = cut2(p1.a, p1.b), w5 = cut2(p1.b, p1.c), w6 = cut2(p1.c, p1.d);
+          const bool one = at & 32u, two = at & 64u;
+          const unsigned u0 = one ? w1 : w0, u1 = one ? w2 : w1, u2 = one ? w3 : w2, u3 = one ? w4 : w3, u4 = one ? w5 : w4,
+                         u5 = one ? w6 : w5;
+          words[pb] = two ? U4{u2, u3, u4, u5} : U4{u0, u1, u2, u3};
         }
       }
 #pragma unroll 1
