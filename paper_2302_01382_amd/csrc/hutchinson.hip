@@ -195,8 +195,8 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
 //
 // us with the finishing kernel, fp32 steps against this: 16384 x 4096 32 probes 77 -> 54 (5.0 TB/s), 64 probes
 // 110 -> 63; 16384 x 2048 42 -> 28; 70000 x 512 44 -> 31; 9000 x 2064 36 -> 33; 1000 x 4096 30 -> 19; 16384 x 64
-// 7.7 -> 7.0.  Below about 100 K elements both are launch and latency: 64 x 512 8.8 -> 7.7, 64 x 64 6.2 -> 6.3, and
-// 64 x 128, whose four tiles are one wave's, 6.3 -> 7.0.
+// 7.7 -> 7.0.  Below about 100 K elements both are launch and latency: 64 x 512 8.8 -> 7.3, 64 x 64 6.2 -> 5.2, 64 x 128
+// 6.3 -> 5.2, 89 x 144 6.75 -> 6.95.
 // =====================================================================================================
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
@@ -243,32 +243,34 @@ constexpr int kRing = 4;                 // tiles of a wave's ring
 constexpr int kTileBytes = 32 * 128;     // 32 rows x 32 floats
 // LDS of a workgroup of ks * groups waves: the rings, and the partial products of all but the first wave of a
 // group or, in their place, the last step's sums
-constexpr int signs_lds(int ks, int groups) {
+constexpr int signs_lds(int ks, int groups, int ring = kRing) {
   const int shares = (ks - 1) * groups * 16 * 64 * (int)sizeof(float), sums = groups * 2 * 32 * (int)sizeof(double);
-  return ks * groups * kRing * kTileBytes + (shares > sums ? shares : sums);
+  return ks * groups * ring * kTileBytes + (shares > sums ? shares : sums);
 }
 
 static __device__ __attribute__((aligned(16))) int g_zeros16[4];  // never written: rows and k past the edge
 
 // ks: waves that split k (1, 2, 4 or 8); the workgroup's ks * groups waves work on `groups` blocks of 32 rows
 // at a time
+// ONE: K <= 128, a single trip, a wave for each 32 k; its ring is one tile
 // part: the sums of squares of 32 rows are fp32, everything above them is double: with per_block float
 // [row blocks][PB * 32], one such sum each (what the workspace has room for up to kBlockSums of them), else
 // float [gridDim.x][2][PB * 32], the workgroup's share as the nearest float and what is left of it
-template <int PB>
+template <int PB, bool ONE>
 __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restrict__ X, int64_t M, int64_t K,
                                                           Signs sg, int ks, int groups, int iters, int per_block,
                                                           float* __restrict__ part) {
+  constexpr int RING = ONE ? 1 : kRing;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  float* red = reinterpret_cast<float*>(lds + ks * groups * kRing * kTileBytes);  // [(ks - 1) * groups][16][64]
+  float* red = reinterpret_cast<float*>(lds + ks * groups * RING * kTileBytes);  // [(ks - 1) * groups][16][64]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row = lane & 31, half = lane >> 5;
   const int group = wave / ks, kshare = wave % ks;
   const int64_t nblock = (K + 127) >> 7;                // 128-k blocks
-  const int64_t per = (nblock + ks - 1) / ks;           // of a wave: kshare, kshare + ks, ...; those past K read zeros
-  const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (unsigned)(wave * kRing * kTileBytes);
-  const char* my = lds + wave * kRing * kTileBytes;
+  const int64_t per = ONE ? 1 : (nblock + ks - 1) / ks;  // of a wave: kshare, kshare + ks, ...; those past K read zeros
+  const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (unsigned)(wave * RING * kTileBytes);
+  const char* my = lds + wave * RING * kTileBytes;
   const char* zero = reinterpret_cast<const char*>(g_zeros16);
 
   // Requests run kRing tiles ahead of the work, across row blocks.  Load i of a tile brings rows
@@ -287,14 +289,14 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
       int64_t m = rq_blk * 32 + 8 * i + (lane >> 3);
       if (m >= M) m = M - 1;
       const int c = (lane & 7) ^ ((4 * i + (lane >> 4)) & 7);
-      src[i] = reinterpret_cast<const char*>(X + m * K + (int64_t)kshare * 128 + 4 * c);
+      src[i] = reinterpret_cast<const char*>(X + m * K + (int64_t)kshare * (ONE ? 32 : 128) + 4 * c);
     }
   };
   start_block();
   const int64_t last_k = K - 32;  // K % 16 == 0 and a chunk of four is whole or absent
   auto request = [&](unsigned slot) {  // tile `slot` of the block
     if (rq_left == 0) return;
-    const int64_t k0 = ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
+    const int64_t k0 = ONE ? kshare * 32 : ((kshare + rq_b * ks) * 4 + (int)slot) * 32;
     const bool edge = k0 > last_k;  // wave-uniform
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
                    : "memory");
       src[i] += 128;
     }
-    if (slot == kRing - 1) {
+    if (slot == RING - 1) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) src[i] += (ks - 1) * 512;
       --rq_left;
@@ -319,8 +321,8 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
   };
   static_assert(kRing == 4, "tile t of a 128-k block lives in ring slot t");
   // (a wave whose only block is cut off by K requests and multiplies the tiles in front of K alone: there the
-  // kernel is latency from end to end: 64 x 64 7.5 -> 6.4 us with the finishing kernel's shorter reduction)
-  const int cut = rq_left == 1 && K < ((int64_t)kshare + 1) * 128 ? (int)((K - (int64_t)kshare * 128 + 31) >> 5) : 4;
+  // kernel is latency from end to end)
+  const int cut = ONE ? 1 : rq_left == 1 && K < ((int64_t)kshare + 1) * 128 ? (int)((K - (int64_t)kshare * 128 + 31) >> 5) : 4;
 #pragma unroll 1
   for (int t = 0; t < cut; ++t) request((unsigned)t);
   if (cut < 4) rq_left = 0;
@@ -341,7 +343,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[pb][v] = 0.0f;
-    for (int64_t b = kshare; b < per * ks; b += ks) {
+    for (int64_t b = ONE ? 0 : kshare, b_end = ONE ? 1 : per * ks; b < b_end; b += ks) {
       U4 words[PB];
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
@@ -361,6 +363,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
                          u5 = one ? w6 : w5;
           words[pb] = two ? U4{u2, u3, u4, u5} : U4{u0, u1, u2, u3};
         }
+        if (ONE) words[pb].a = (kshare & 2) ? ((kshare & 1) ? words[pb].d : words[pb].c) : (kshare & 1) ? words[pb].b : words[pb].a;
       }
 #pragma unroll 1
       for (int t = 0; t < cut; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
@@ -481,11 +484,21 @@ static int64_t hutch_grid(int64_t M, int pb) {
 // 16384 x 4096 in four and in eight waves per CU, 67 and 55 us -- and 1 us for adding the shares.
 struct SignsPlan {
   int ks = 1, groups = 1, iters = 1;
+  bool one = false;  // a tile of 32 k per wave
   int64_t grid = 1;
 };
 static SignsPlan plan_signs(int64_t M, int64_t K) {
   const int64_t nblk = (M + 31) >> 5, nb = (K + 127) >> 7;
   SignsPlan best;
+  // One block of k is latency from end to end, its four tiles one after the other in a wave: with a wave each 64 x 128
+  // 6.75 -> 5.25 us, 4000 x 128 (40 probes) 8.35 -> 6.65, 64 x 64 5.75 -> 5.2.  From two blocks on, one or two tiles
+  // per wave save nothing: 1000 x 192 7.05 | 7.15, 8192 x 256 9.1 | 10.1.
+  if (nb == 1 && nblk <= kNumCU) {
+    best.ks = (int)((K + 31) >> 5);
+    best.grid = nblk;
+    best.one = true;
+    return best;
+  }
   double least = 0.0;
   for (int ks = 1; ks <= kSW; ks *= 2)
     for (int groups = 1; groups * ks <= kSW; groups *= 2) {
@@ -511,7 +524,7 @@ static int signs_allow_lds() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   if (done[dev].load(std::memory_order_relaxed)) return MPQ_OK;
-  for (const void* k : {reinterpret_cast<const void*>(&hutch_signs_k<1>), reinterpret_cast<const void*>(&hutch_signs_k<2>)}) {
+  for (const void* k : {reinterpret_cast<const void*>(&hutch_signs_k<1, false>), reinterpret_cast<const void*>(&hutch_signs_k<2, false>)}) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, signs_lds(kSW, 1));
     if (e != hipSuccess) { set_last_hip_error((int)e); return MPQ_ERR_HIP; }
   }
@@ -567,9 +580,14 @@ static int run_hutchinson(const float* x, int64_t M, int64_t K, const float* v, 
       sums = per_block ? nblk : 2 * pl.grid;
       const Signs sg = {seed, stream_id, (unsigned long long)p0};
       const unsigned g = (unsigned)pl.grid;
-      const int threads = pl.ks * pl.groups * 64, lds = signs_lds(pl.ks, pl.groups);
-      if (pb == 1) hutch_signs_k<1><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, per_block, part);
-      else hutch_signs_k<2><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, per_block, part);
+      const int threads = pl.ks * pl.groups * 64, lds = signs_lds(pl.ks, pl.groups, pl.one ? 1 : kRing);
+#define MPQ_SIGNS(PB_, ONE_) \
+  hutch_signs_k<PB_, ONE_><<<g, threads, lds, st>>>(x, M, K, sg, pl.ks, pl.groups, pl.iters, per_block, part)
+      if (pl.one && pb == 1) MPQ_SIGNS(1, true);
+      else if (pl.one) MPQ_SIGNS(2, true);
+      else if (pb == 1) MPQ_SIGNS(1, false);
+      else MPQ_SIGNS(2, false);
+#undef MPQ_SIGNS
     } else {
       const unsigned g = (unsigned)hutch_grid(M, pb);
       sums = g;

@@ -25,6 +25,22 @@ def test_layouts(mkp):
     np.testing.assert_allclose(got, want(x, v), rtol=1e-5)
 
 
+# K <= 128: a wave per 32 k while there are at most as many row blocks as CUs, whole blocks per wave from 8193 rows on
+@pytest.mark.parametrize("P", [5, 40])
+@pytest.mark.parametrize("M", [1, 33, 8192, 8193])
+@pytest.mark.parametrize("K", [16, 32, 48, 80, 112, 128])
+def test_one_block_of_k(M, K, P):
+    x = data((M, K), 114)
+    v = host(mpq.rademacher(9, 1, P, K))
+    got = host(mpq.hutchinson_quad_signs(dev(x), 9, 1, P))
+    # exact products, so a row's s = sum of +-x is off by e <= 2^-24 (terms added) sum |x| (three parts per x, and one
+    # row can cancel: s << sum |x|), its square by 2 |s| e + e^2; squares and 32 of them in fp32: 33 roundings
+    e = 2.0 ** -24 * 3 * K * np.abs(x.astype(np.float64)).sum(1)
+    s = np.abs(x.astype(np.float64) @ v.astype(np.float64).T)
+    exact = want(x, v)
+    assert (np.abs(got - exact) <= (2 * s * e[:, None] + e[:, None] ** 2).sum(0) + 33 * 2.0 ** -24 * exact).all()
+
+
 # grid times row blocks per workgroup is 2048 at most, so these take two trips or more whatever the layout, the
 # last one partly past M: k in whole 128-k blocks and not, one probe block and two; a K long enough for 8 waves each
 @pytest.mark.parametrize("mkp", [(70001, 512, 33), (70001, 80, 5), (66000, 208, 64), (35003, 4096, 3)])
