@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kHW * 64, 4) void hutch_k(const float* __restrict__
 // us with the finishing kernel, fp32 steps against this: 16384 x 4096 32 probes 77 -> 54 (5.0 TB/s), 64 probes
 // 110 -> 63; 16384 x 2048 42 -> 28; 70000 x 512 44 -> 31; 9000 x 2064 36 -> 33; 1000 x 4096 30 -> 19; 16384 x 64
 // 7.7 -> 7.0.  Below about 100 K elements both are launch and latency: 64 x 512 8.8 -> 7.3, 64 x 64 6.2 -> 5.2, 64 x 128
-// 6.3 -> 5.2, 89 x 144 6.75 -> 6.95.
+// 6.3 -> 5.2, 89 x 144 6.75 -> 5.7, 4798 x 192 7.2 -> 6.1.
 // =====================================================================================================
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
@@ -252,7 +252,7 @@ static __device__ __attribute__((aligned(16))) int g_zeros16[4];  // never writt
 
 // ks: waves that split k (1, 2, 4 or 8); the workgroup's ks * groups waves work on `groups` blocks of 32 rows
 // at a time
-// ONE: K <= 128, a single trip, a wave for each 32 k; its ring is one tile
+// ONE: K <= 256, a single trip, a wave for each 32 k; its ring is one tile
 // part: the sums of squares of 32 rows are fp32, everything above them is double: with per_block float
 // [row blocks][PB * 32], one such sum each (what the workspace has room for up to kBlockSums of them), else
 // float [gridDim.x][2][PB * 32], the workgroup's share as the nearest float and what is left of it
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
     for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[pb][v] = 0.0f;
-    for (int64_t b = ONE ? 0 : kshare, b_end = ONE ? 1 : per * ks; b < b_end; b += ks) {
+    for (int64_t b = ONE ? kshare >> 2 : kshare, b_end = ONE ? b + 1 : per * ks; b < b_end; b += ks) {
       U4 words[PB];
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
@@ -363,7 +363,8 @@ __global__ __launch_bounds__(kSW * 64) void hutch_signs_k(const float* __restric
                          u5 = one ? w6 : w5;
           words[pb] = two ? U4{u2, u3, u4, u5} : U4{u0, u1, u2, u3};
         }
-        if (ONE) words[pb].a = (kshare & 2) ? ((kshare & 1) ? words[pb].d : words[pb].c) : (kshare & 1) ? words[pb].b : words[pb].a;
+        if (ONE)
+          words[pb].a = (kshare & 2) ? ((kshare & 1) ? words[pb].d : words[pb].c) : (kshare & 1) ? words[pb].b : words[pb].a;
       }
 #pragma unroll 1
       for (int t = 0; t < cut; ++t) {  // tile t of the block sits in ring slot t (rolled: the code is fetched cold)
@@ -490,10 +491,10 @@ struct SignsPlan {
 static SignsPlan plan_signs(int64_t M, int64_t K) {
   const int64_t nblk = (M + 31) >> 5, nb = (K + 127) >> 7;
   SignsPlan best;
-  // One block of k is latency from end to end, its four tiles one after the other in a wave: with a wave each 64 x 128
-  // 6.75 -> 5.25 us, 4000 x 128 (40 probes) 8.35 -> 6.65, 64 x 64 5.75 -> 5.2.  From two blocks on, one or two tiles
-  // per wave save nothing: 1000 x 192 7.05 | 7.15, 8192 x 256 9.1 | 10.1.
-  if (nb == 1 && nblk <= kNumCU) {
+  // Up to two blocks of k are latency from end to end, a block's four tiles one after the other in a wave: with a wave
+  // each 64 x 128 6.75 -> 5.25 us, 4000 x 128 (40 probes) 8.35 -> 6.65, 64 x 64 5.75 -> 5.2, 1000 x 192 7.0 -> 5.9,
+  // 8192 x 256 (40 probes) 9.05 -> 8.4, and the fp32 chains are shorter: 89 x 144 rms error 4.6e-8 -> 3.8e-8.
+  if (nb <= 2 && nblk <= kNumCU) {
     best.ks = (int)((K + 31) >> 5);
     best.grid = nblk;
     best.one = true;

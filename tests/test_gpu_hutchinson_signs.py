@@ -25,11 +25,11 @@ def test_layouts(mkp):
     np.testing.assert_allclose(got, want(x, v), rtol=1e-5)
 
 
-# K <= 128: a wave per 32 k while there are at most as many row blocks as CUs, whole blocks per wave from 8193 rows on
+# K <= 256: a wave per 32 k while there are at most as many row blocks as CUs, whole blocks per wave from 8193 rows on
 @pytest.mark.parametrize("P", [5, 40])
 @pytest.mark.parametrize("M", [1, 33, 8192, 8193])
-@pytest.mark.parametrize("K", [16, 32, 48, 80, 112, 128])
-def test_one_block_of_k(M, K, P):
+@pytest.mark.parametrize("K", [16, 32, 48, 80, 112, 128, 144, 208, 256, 272])
+def test_a_wave_per_tile_of_k(M, K, P):
     x = data((M, K), 114)
     v = host(mpq.rademacher(9, 1, P, K))
     got = host(mpq.hutchinson_quad_signs(dev(x), 9, 1, P))
