@@ -2,12 +2,13 @@
 // Alg. 1 / Alg. 2: acc[m][n] = sum_k A_q[m][k] * W_q[n][k] in int32 on the int8 matrix cores,
 // then Y = (float(acc) * s_A) * s_W[n].
 //
-// Both operands are K-contiguous, which is exactly what v_mfma_i32_32x32x32_i8 wants: lane l of
-// either operand holds 16 consecutive k-bytes of tile row l%32 (k-half l/32).
+// Both operands are K-contiguous, which is exactly what the int8 matrix instructions want: a lane of
+// either operand holds 16 consecutive k-bytes of a tile row.
 //
-// Two kernels: the fast path (qgemm_dma.hpp; 16-byte aligned operands, K a multiple of 16, or 32
+// Three kernels: the fast path (qgemm_dma.hpp and qgemm_quad.hpp; 16-byte aligned operands, K a multiple of 16, or 32
 // for packed int4) feeds a multi-stage LDS pipeline with direct global->LDS loads; qgemm_any right
-// below stages tiles through registers and handles any K and alignment.  Same arithmetic, same results.
+// below stages tiles through registers and handles any K and alignment; qgemm_skinny.hip takes layers of few
+// output tiles.  Same arithmetic, same results.
 //
 // Packed int4 weights are expanded on their way to the matrix core: a nibble n becomes the byte
 // n << 4 (= 16 n as int8, sign included), so the accumulator holds 16 * acc exactly and is shifted

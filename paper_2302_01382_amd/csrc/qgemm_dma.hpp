@@ -65,9 +65,6 @@ __device__ __forceinline__ float apply_act(float y, int act) {
   return y;
 }
 
-// four at once: one (uniform) branch on the kind of activation instead of four.  With the epilogue's scalars
-// in registers (below), 16384 x 1024 x 4096 with GELU and its maximum 139 -> 125 us, with ReLU 120 -> 108;
-// 12288 x 768 x 768 with ReLU 24.7 -> 21.2; 4096 x 1024 x 1024 16.3 -> 15.4.
 __device__ __forceinline__ float4 apply_act4(const float4& y, int act) {
   if (act == 1) return make_float4(fmaxf(y.x, 0.0f), fmaxf(y.y, 0.0f), fmaxf(y.z, 0.0f), fmaxf(y.w, 0.0f));
   if (act == 2) return make_float4(gelu_f(y.x), gelu_f(y.y), gelu_f(y.z), gelu_f(y.w));
@@ -135,22 +132,18 @@ __device__ __forceinline__ v4i fix_chunk16(const v4i& c, int row_bytes, int k) {
 //
 // A k tile is requested NSTAGE - 1 tiles ahead of the MFMAs that use it; a wave waits only for
 // its own share of the tile it needs next (s_waitcnt vmcnt) and then meets the others at the one
-// barrier per k tile.  The k loop is unrolled by NSTAGE so every LDS address is a compile-time
-// offset (the compiler then keeps ds_reads of one stage independent of the loads in flight into
-// the others).
+// barrier per k tile (two in qgemm_quad.hpp, which takes the 256 x 256 tile).
 //
-// What bounds this path (microbenchmarks on the same chip): a CU fills its LDS from L2 at about
-// 90 GB/s (one 1 KiB wave-load per ~27 clocks through its one address unit), so the 64 KiB k tile
-// of a 256 x 256 workgroup takes ~0.75 us to arrive against ~0.85-1.0 us of MFMA work on it;
-// and because a wave issues in order, a wave queueing at the address unit feeds no MFMAs -- a
-// plain stream of MFMAs with wave-loads between them, no waits and no barrier at all, reaches
-// about 70 % of the pure MFMA rate, which itself is ~82 % of the nominal peak under this load.
+// What bounds this path: a k tile costs a CU more than either of its halves alone.  On random operands the matrix
+// cores sustain 4.0-4.15 POP/s in steps of 16x16x64 (3.4-3.6 in steps of 32x32x32, which draw more power; constant
+// bytes 4.8 and 5.0), so a 128 x 128 x 128 tile is 0.26 us of matrix work on its CU; its 32 KiB come out of the L2 in
+// 0.26 us (8 ns per wave-load; 12.5 if a row's share were 64 bytes), its operand reads out of the LDS in 0.19 us, and it
+// takes 0.48 us at a clock that falls to 1.8 GHz.  Two to four stages, four or eight waves, k tiles of 128 or 256, two
+// barriers per tile instead of one: all within 10 % of each other (4096 x 1024 x 4096, 22.5-25 us).
 // =====================================================================================================
-#define MPQ_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define MPQ_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 static __device__ __attribute__((aligned(16))) int g_zero16[4];  // never written: zero fill for k tails
-
 
 // The direct-to-LDS load and its wait are written as inline assembly on purpose: when the
 // compiler sees the load it cannot tell which LDS bytes are in flight once more than a handful of
@@ -169,40 +162,80 @@ __device__ __forceinline__ void dma16(const char* src, unsigned lds_byte_off) {
   // (the compiler's hazard pass does not look inside inline assembly)
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_byte_off) : "memory");
 }
+// the same with a wave-uniform base in scalar registers and a 32-bit offset per lane
+__device__ __forceinline__ void dma16_base(const char* base, unsigned off, unsigned lds_byte_off) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_byte_off) : "memory");
+}
 template <int N_>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_) : "memory");
 }
+// This wave's LDS reads and writes are done, and so are everyone's.  (__syncthreads would also wait for the stores
+// of an epilogue.)
+__device__ __forceinline__ void lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void meet() {
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
-// KB: k bytes per stage (64, 128 or 256)
+// KB: k bytes per stage (128 or 256)
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool W4, int KB>
 struct DmaCfg {
   static constexpr int DBK = KB;
-  static constexpr int CPR = KB / 16;                 // 16-byte chunks per int8 tile row (4 | 8 | 16)
-  static constexpr int RPI = 64 / CPR;                // tile rows one wave-load covers (16 | 8 | 4)
+  static constexpr int CPR = KB / 16;                 // 16-byte chunks per int8 tile row (8 | 16)
+  static constexpr int RPI = 64 / CPR;                // tile rows one wave-load covers (8 | 4)
   // swizzle: slot = chunk ^ ((row >> SH) & (CPR-1)); 2^SH rows share 256 bytes (one sweep of the banks)
-  static constexpr int SH = CPR == 16 ? 0 : CPR == 8 ? 1 : 2;
-  static constexpr int PCPR = KB / 32;                // 16-byte chunks per packed-int4 tile row (2 | 4 | 8)
-  static constexpr int PRPI = 64 / PCPR;              // packed rows per wave-load (32 | 16 | 8)
-  static constexpr int PSH = PCPR == 8 ? 1 : PCPR == 4 ? 2 : 3;
+  static constexpr int SH = CPR == 16 ? 0 : 1;
+  static constexpr int PCPR = KB / 32;                // 16-byte chunks per packed-int4 tile row (4 | 8)
+  static constexpr int PRPI = 64 / PCPR;              // packed rows per wave-load (16 | 8)
+  static constexpr int PSH = PCPR == 8 ? 1 : 2;
   static constexpr int NW = WM * WN;
   static constexpr int NT = NW * 64;
   static constexpr int TM = BM / WM, TN = BN / WN;   // per-wave tile
-  static constexpr int FM = TM / 32, FN = TN / 32;   // 32x32 MFMA tiles per wave
+  static constexpr int FM = TM / 16, FN = TN / 16;   // 16x16 MFMA tiles per wave
   static constexpr int A_STAGE = BM * DBK;
   static constexpr int B_ROW = W4 ? DBK / 2 : DBK;   // bytes of one W tile row in LDS
   static constexpr int B_STAGE = BN * B_ROW;
   static constexpr int STAGE = A_STAGE + B_STAGE;
-  static constexpr int SCALE_OFF = NSTAGE * STAGE;    // two 1 KiB buffers of per-channel W scales
+  static constexpr int SCALE_OFF = NSTAGE * STAGE;    // 1 KiB of per-channel W scales, then the waves' sums
+  static constexpr int SUMS_OFF = SCALE_OFF + 1024;
   static constexpr int LDS_BYTES = SCALE_OFF + 2048;
   static constexpr int NLA = BM / RPI;                // wave-loads per A stage
   static constexpr int NLB = W4 ? BN / PRPI : BN / RPI;  // wave-loads per W stage
   static constexpr int LPW = (NLA + NLB) / NW;        // wave-loads per wave per stage
   static_assert(NLA % NW == 0 && NLB % NW == 0, "loads must divide evenly over the waves");
-  static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile is a multiple of 32 x 32");
-  static_assert(KB == 256 || KB == 128 || KB == 64, "k tile of 64, 128 or 256 bytes");
+  static_assert(TM % 16 == 0 && TN % 16 == 0, "wave tile is a multiple of 16 x 16");
+  static_assert(KB == 256 || KB == 128, "k tile of 128 or 256 bytes");
   static_assert((NSTAGE - 1) * LPW < 64, "vmcnt is a 6-bit counter");
 };
+
+// One matrix step into its own accumulator.  Inline assembly, because the compiler is free to give the builtin's
+// result another register than the accumulator it came from and does: the 32 accumulators of a wave then
+// wander through twice their registers and spill.  What its hazard pass would do is done here: two wait
+// states between a vector instruction that writes an operand and the matrix step (zero_acc, expand_half), and
+// acc_ready between the last matrix step and the first read of an accumulator.
+__device__ __forceinline__ void mma(v4i& acc, const v4i& w, const v4i& a) {
+  asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "v"(a));
+}
+template <int FM, int FN>
+__device__ __forceinline__ void zero_acc(v4i (&acc)[FM][FN]) {
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      acc[i][j] = v4i{0, 0, 0, 0};
+      asm volatile("" : "+v"(acc[i][j]));
+    }
+  asm volatile("s_nop 1" ::: "memory");
+}
+template <int FM, int FN>
+__device__ __forceinline__ void acc_ready(v4i (&acc)[FM][FN]) {
+  asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
 
 // compile-time loop: f(std::integral_constant<int, I>) for I = FIRST .. LAST - 1
 template <int FIRST, int LAST, class F>
@@ -213,200 +246,282 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// The k tile to be requested next: it runs NSTAGE k tiles ahead of the multiplication, across the output tiles of
+// the workgroup.  Everything here is wave-uniform.
+template <int KB, bool W4>
+struct Cursor {
+  const char* a;     // first row of its output tile, at its k
+  const char* b;     // the workgroup's first W row, at its k
+  const char* zero;  // chunks at or beyond `limit` come from here
+  int k, limit;      // limit: K; 0 once nothing is left (every further request fetches zeros)
+  int tile;
+
+  __device__ __forceinline__ void init(const char* a0, const char* b0, int k_len, int tile_) {
+    a = a0;
+    b = b0;
+    zero = reinterpret_cast<const char*>(g_zero16);
+    // once, in scalar registers: left to the compiler it is loaded in front of every request, and the wait for
+    // that load (lgkmcnt(0)) drains the LDS reads in flight
+    asm volatile("" : "+s"(zero));
+    k = 0;
+    limit = k_len;
+    tile = tile_;
+  }
+  // The k tile lies inside the row.  An output tile's k loop runs while it does and is followed by one that asks lane by
+  // lane (a branch per request in a single loop: 16384 x 4096 x 1024 66.0 us against 62.7, 4096 x 1024 x 1024 11.0 against 10.6)
+  __device__ __forceinline__ bool whole() const { return k + KB <= limit; }
+  // ... and so does the one after it
+  __device__ __forceinline__ bool whole_two(int tile_end) const {
+    return k + 2 * KB <= limit || (k + KB == limit && tile + 1 < tile_end);
+  }
+  // off: the lane's bytes from a (b); kl: its k within the tile
+  template <bool WHOLE, bool IS_A>
+  __device__ __forceinline__ void fetch(unsigned off, unsigned kl, unsigned lds_byte_off) const {
+    const char* base = IS_A ? a : b;
+    if (WHOLE) dma16_base(base, off, lds_byte_off);
+    else dma16(k + (int)kl < limit ? base + off : zero, lds_byte_off);
+  }
+  // true: at the first k tile of another output tile, whose rows are the caller's business
+  __device__ __forceinline__ bool advance(int tile_end) {
+    k += KB;
+    a += KB;
+    b += W4 ? KB / 2 : KB;
+    if (k < limit) return false;
+    if (limit == 0 || tile + 1 >= tile_end) {
+      limit = 0;
+      return false;
+    }
+    ++tile;
+    k = 0;
+    return true;
+  }
+};
+
 // What one wave fetches per stage.  Wave-load t of a wave covers tile rows first + t * STEP ..., and
 // because STEP is a multiple of the swizzle period every one of them has the lane fetch the same
-// logical chunk, so the plan is four registers: the lane's first row and chunk offset per operand.
-// Source addresses are formed at issue time (one 64-bit multiply-add per wave-load).
+// logical chunk.  The offsets do not change with k.
 template <class C, bool W4>
 struct DmaPlan {
-  static constexpr int NA = C::NLA / C::NW, NB_ = C::NLB / C::NW;
-  static constexpr int STEP_A = C::RPI * C::NW;
-  static constexpr int STEP_B = (W4 ? C::PRPI : C::RPI) * C::NW;
+  static constexpr int NA = C::NLA / C::NW, NB = C::NLB / C::NW;
+  static constexpr int BRPI = W4 ? C::PRPI : C::RPI;
+  static constexpr int STEP_A = C::RPI * C::NW, STEP_B = BRPI * C::NW;
   static_assert(((STEP_A >> C::SH) % C::CPR) == 0, "A swizzle must repeat from one wave-load to the next");
   static_assert(W4 ? ((STEP_B >> C::PSH) % C::PCPR) == 0 : ((STEP_B >> C::SH) % C::CPR) == 0,
                 "W swizzle must repeat from one wave-load to the next");
-  const char* A;
-  const char* W;
-  unsigned last_a, last_b;  // M - 1, N - 1: rows past the edge re-read the last row; never stored
-  unsigned K;
-  unsigned ra, rb;          // the lane's row of its first wave-load (global index)
-  int ka, kb;               // k of the lane's chunk within the tile (bytes of A / values of W)
-  unsigned wave_off;        // LDS offset of this wave's first wave-load within a stage region
+  unsigned off_a[NA], off_b[NB];  // bytes from the tile's first row at k = 0
+  unsigned ka, kb;                // k of the lane's chunk within the tile
+  unsigned lds_off;               // of the wave's first wave-load within a stage's operand
 
-  __device__ __forceinline__ void init(const int8_t* __restrict__ A_, const uint8_t* __restrict__ W_,
-                                       int64_t M, int64_t N, int64_t K_, int64_t m0, int64_t n0,
-                                       int wave_u, int lane) {
-    A = reinterpret_cast<const char*>(A_);
-    W = reinterpret_cast<const char*>(W_);
-    last_a = (unsigned)(M - 1);
-    last_b = (unsigned)(N - 1);
-    K = (unsigned)K_;
-    wave_off = (unsigned)wave_u * 1024u;
-    {
-      const int row = C::RPI * wave_u + lane / C::CPR;
-      ka = ((lane % C::CPR) ^ ((row >> C::SH) & (C::CPR - 1))) * 16;  // logical chunk this lane fetches
-      ra = (unsigned)m0 + (unsigned)row;
-    }
-    if (!W4) {
-      const int row = C::RPI * wave_u + lane / C::CPR;
-      kb = ((lane % C::CPR) ^ ((row >> C::SH) & (C::CPR - 1))) * 16;
-      rb = (unsigned)n0 + (unsigned)row;
-    } else {  // packed tile: a wave-load covers PRPI rows of KB/2 packed bytes; a chunk is 32 values
-      const int row = C::PRPI * wave_u + lane / C::PCPR;
-      kb = ((lane % C::PCPR) ^ ((row >> C::PSH) & (C::PCPR - 1))) * 32;
-      rb = (unsigned)n0 + (unsigned)row;
+  // last: last valid row, counted from the tile's first; rows past it re-read it and are never stored
+  __device__ __forceinline__ void rows_a(int wave, int lane, unsigned K, unsigned last) {
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      const unsigned row = (unsigned)(C::RPI * wave + lane / C::CPR + t * STEP_A);
+      off_a[t] = (row < last ? row : last) * K + ka;
     }
   }
-
-  // One k tile's requests of this wave, numbered 0 .. NA + NB_ - 1 (A first); chunks at or beyond
-  // k_limit are fetched from a block of zeros.
-  struct Tile {
-    const char* a0;
-    const char* b0;
-    bool va, vb;
-  };
-  __device__ __forceinline__ Tile tile(int k0, int k_limit) const {
-    Tile t;
-    t.va = k0 + ka < k_limit;
-    t.vb = k0 + kb < k_limit;
-    t.a0 = A + (unsigned)(k0 + ka);
-    t.b0 = W + (unsigned)(W4 ? (k0 + kb) >> 1 : k0 + kb);
-    return t;
-  }
-  template <int R>
-  __device__ __forceinline__ void request(const Tile& tl, unsigned lds_stage_off) const {
-    const char* zero = reinterpret_cast<const char*>(g_zero16);
-    if constexpr (R < NA) {
-      unsigned r = ra + (unsigned)(R * STEP_A);
-      r = r < last_a ? r : last_a;
-      const char* src = tl.va ? tl.a0 + (uint64_t)r * K : zero;
-      dma16(src, lds_stage_off + wave_off + (unsigned)(R * C::NW) * 1024u);
-    } else {
-      constexpr int T = R - NA;
-      const unsigned ldb = W4 ? K >> 1 : K;
-      unsigned r = rb + (unsigned)(T * STEP_B);
-      r = r < last_b ? r : last_b;
-      const char* src = tl.vb ? tl.b0 + (uint64_t)r * ldb : zero;
-      dma16(src, lds_stage_off + (unsigned)C::A_STAGE + wave_off + (unsigned)(T * C::NW) * 1024u);
+  __device__ __forceinline__ void init(int wave, int lane, unsigned K, unsigned last_b) {
+    lds_off = (unsigned)wave * 1024u;
+    const int row = C::RPI * wave + lane / C::CPR;
+    ka = (unsigned)(((lane % C::CPR) ^ ((row >> C::SH) & (C::CPR - 1))) * 16);
+    const int rb = BRPI * wave + (W4 ? lane / C::PCPR : lane / C::CPR);
+    kb = W4 ? (unsigned)(((lane % C::PCPR) ^ ((rb >> C::PSH) & (C::PCPR - 1))) * 32) : ka;  // a packed chunk is 32 values
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const unsigned r = (unsigned)(rb + t * STEP_B);
+      off_b[t] = (r < last_b ? r : last_b) * (W4 ? K >> 1 : K) + (W4 ? kb >> 1 : kb);
     }
   }
-  // all requests of the k tile starting at k0, back to back
-  __device__ __forceinline__ void issue(unsigned lds_stage_off, int k0, int k_limit) const {
-    const Tile tl = tile(k0, k_limit);
-    static_for<0, NA + NB_>([&](auto r_) { request<decltype(r_)::value>(tl, lds_stage_off); });
+  // request R of the cursor's k tile, numbered 0 .. NA + NB - 1 (A first), into the stage at LDS byte `stage`
+  template <int R, bool WHOLE>
+  __device__ __forceinline__ void request(const Cursor<C::DBK, W4>& c, unsigned stage) const {
+    if constexpr (R < NA) c.template fetch<WHOLE, true>(off_a[R], ka, stage + lds_off + (unsigned)(R * C::NW) * 1024u);
+    else c.template fetch<WHOLE, false>(off_b[R - NA], kb, stage + (unsigned)C::A_STAGE + lds_off + (unsigned)((R - NA) * C::NW) * 1024u);
   }
 };
 
 // LDS offsets (within a stage) of the first operand fragments of a lane, for k substep 0.  With
 // the XOR swizzle the offset for substep s is this value with a compile-time constant XORed into its
-// chunk bits, and rows 32 i further down add a multiple of the row pitch, which never reaches those bits.
+// chunk bits, and rows 16 i further down add a multiple of the row pitch, which never reaches those bits.
 //
-// Which 16 k-values a lane's operand holds in substep s is free as long as both operands agree (a
+// Which 16 k-values a lane's operand holds in substep s (64 k) is free as long as both operands agree (a
 // dot product does not care about the order of its terms).  int8 weights: the natural order, lane
-// half g of substep s holds k = 32 s + 16 g ..., i.e. 16-byte chunk 2 s + g of both rows.
+// quarter q of substep s holds k = 64 s + 16 q ..., i.e. 16-byte chunk 4 s + q of both rows.
 // Packed int4 weights: a 16-byte LDS chunk holds 32 k-values, and only whole chunks can be read without
 // bank conflicts (64-bit reads of half chunks leave half of the banks idle and collide two-fold on
-// the rest).  So a lane reads chunk 2 p + g of the W row ONCE per pair p of substeps and multiplies
-// its low 8 bytes (k = 64 p + 32 g ...) in substep 2 p, its high 8 bytes (k = 64 p + 32 g + 16 ...) in
-// substep 2 p + 1; the A operand follows: chunk 4 p + 2 g + h in substep 2 p + h.
+// the rest).  So a lane reads chunk 4 p + j of the W row ONCE per pair p of substeps and multiplies
+// its low 8 bytes (k = 128 p + 32 j ...) in substep 2 p, its high 8 bytes (k = 128 p + 32 j + 16 ...) in
+// substep 2 p + 1; the A operand follows: chunk 8 p + 2 j + h in substep 2 p + h.  Quarter q takes j = 0, 3, 1, 2:
+// the two quarters of either half wave then differ in bits 1 and 2 of their A chunk, which keeps the A reads free of
+// bank conflicts whichever 16 of the half wave's lanes are served together.
 template <class C, bool W4>
 struct FragBase {
   unsigned a, b;
   __device__ __forceinline__ void init(int wm, int wn, int lane) {
-    const int l31 = lane & 31, g = lane >> 5;
-    const int ra = wm * C::TM + l31;
-    const int ga = W4 ? g << 1 : g;
+    const int r = lane & 15, q = lane >> 4;
+    const int j = q == 0 ? 0 : q == 1 ? 3 : q - 1;  // 0 3 1 2
+    const int ra = wm * C::TM + r;
+    const int ga = W4 ? j << 1 : q;
     a = (unsigned)(ra * C::DBK + ((ga ^ ((ra >> C::SH) & (C::CPR - 1))) << 4));
-    const int rb = wn * C::TN + l31;
-    if (!W4) b = (unsigned)(C::A_STAGE + rb * C::DBK + ((g ^ ((rb >> C::SH) & (C::CPR - 1))) << 4));
-    else b = (unsigned)(C::A_STAGE + rb * (C::DBK / 2) + ((g ^ ((rb >> C::PSH) & (C::PCPR - 1))) << 4));
+    const int rb = wn * C::TN + r;
+    if (!W4) b = (unsigned)(C::A_STAGE + rb * C::DBK + ((q ^ ((rb >> C::SH) & (C::CPR - 1))) << 4));
+    else b = (unsigned)(C::A_STAGE + rb * (C::DBK / 2) + ((j ^ ((rb >> C::PSH) & (C::PCPR - 1))) << 4));
   }
 };
 
-// base ^ bits, computed where it is used: written as a plain expression the compiler would keep
-// one address register per (stage, substep, operand) alive across the whole k loop
-template <unsigned BITS>
-__device__ __forceinline__ unsigned xor_here(unsigned base) {
-  if (BITS == 0) return base;
-  unsigned r;
-  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(r) : "n"(BITS), "v"(base));
-  return r;
+// Half H of 32 packed nibbles (see FragBase) as a matrix operand
+template <int H>
+__device__ __forceinline__ v4i expand_half(const v4i& r) {
+  unsigned b0, b1, b2, b3;
+  expand8((unsigned)(H ? r.z : r.x), b0, b1);
+  expand8((unsigned)(H ? r.w : r.y), b2, b3);
+  v4i b = v4i{(int)b0, (int)b1, (int)b2, (int)b3};
+  asm volatile("s_nop 1" : "+v"(b));  // see mma
+  return b;
 }
 
-// W fragment as it sits in LDS: the MFMA operand itself (int8), or 32 packed nibbles that serve two
-// substeps and are expanded right before use (kept packed meanwhile: no more registers than int8
-// weights need, and the expansion never waits for a read issued a moment ago).
-struct BRaw { v4i v; };
-template <bool W4, int H>
-__device__ __forceinline__ v4i b_operand(const BRaw& r) {
-  if constexpr (!W4) {
-    return r.v;
-  } else {
-    unsigned b0, b1, b2, b3;
-    expand8((unsigned)(H ? r.v.z : r.v.x), b0, b1);
-    expand8((unsigned)(H ? r.v.w : r.v.y), b2, b3);
-    return v4i{(int)b0, (int)b1, (int)b2, (int)b3};
+// What a workgroup does with the accumulators of one output tile (see EpiArgs for EPI).  16x16 accumulator tile
+// (i, j): lane l holds m = l % 16 and the four consecutive n = 4 (l / 16) + 0..3: a store instruction writes 64
+// bytes of each of 16 rows.  (In 32x32 tiles it is 32 bytes of 32 rows: 67 MB stored by one workgroup per CU 14.5 us
+// against 11.5, 16.8 MB in 128 x 128 tiles 6.2 against 4.8, whole rows no better.)
+// scales: the tile's per-channel W scales in LDS (VEC).  sse, amax: the lane's running sums.
+template <class C, bool W4, bool VEC, int EPI, int ACT_KIND>
+__device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int64_t cur_m0, int64_t cur_n0, int wm, int wn, int lane,
+                                         const char* scales, int64_t M, int64_t N, float sa, float sw0,
+                                         const float* __restrict__ w_scale, int w_per_row, bool want_y, float q_inv, float q_max,
+                                         float* __restrict__ Y, int32_t* __restrict__ ACC, const EpiArgs& epi, float& sse,
+                                         float& amax) {
+  constexpr bool SCORE = EPI == 1, ACT = EPI >= 2, AMAX = EPI == 2, QOUT = EPI == 3;
+  int8_t* __restrict__ CODES = epi.codes;
+  const float* __restrict__ YREF = epi.yref;
+  const int nq = wn * C::TN + (lane >> 4) * 4;  // the lane's first n within the tile
+#pragma unroll
+  for (int i = 0; i < C::FM; ++i) {
+    const int64_t m = cur_m0 + wm * C::TM + i * 16 + (lane & 15);
+    if (m >= M) continue;
+    // Score: the loads of a group of G are in flight together (past the edge: the row's first columns).
+    constexpr int G = C::FN % 4 == 0 ? 4 : 2;
+    static_assert(C::FN % 2 == 0, "pairs of column tiles");
+#pragma unroll
+    for (int j0 = 0; j0 < C::FN; j0 += G) {
+      float4 yref[G];
+      if (SCORE && VEC) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int64_t n = cur_n0 + nq + (j0 + g) * 16;
+          yref[g] = *reinterpret_cast<const float4*>(YREF + m * N + (n < N ? n : 0));
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int j = j0 + g;
+        const int64_t n = cur_n0 + nq + j * 16;
+        if (n >= N) continue;
+        int a[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          a[e] = acc[i][j][e];
+          if (W4) a[e] >>= 4;  // exact: every product carried the factor 16
+        }
+        if (VEC) {  // N % 4 == 0 and 16-byte aligned outputs: the four n are all in range
+          if (EPI == 0 && ACC) *reinterpret_cast<v4i*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
+          if (want_y) {
+            const float4 sw = *reinterpret_cast<const float4*>(scales + (nq + j * 16) * 4);
+            float4 y = make_float4(((float)a[0] * sa) * sw.x, ((float)a[1] * sa) * sw.y,
+                                   ((float)a[2] * sa) * sw.z, ((float)a[3] * sa) * sw.w);
+            if (ACT) {
+              y = apply_act4(y, ACT_KIND);
+              if (AMAX) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
+            }
+            if (!QOUT && Y) *reinterpret_cast<float4*>(Y + m * N + n) = y;
+            if (QOUT && CODES) {  // four codes, lowest n in the lowest byte
+              const unsigned c0 = (unsigned)(int)code_f(y.x, q_inv, q_max) & 0xFFu;
+              const unsigned c1 = (unsigned)(int)code_f(y.y, q_inv, q_max) & 0xFFu;
+              const unsigned c2 = (unsigned)(int)code_f(y.z, q_inv, q_max) & 0xFFu;
+              const unsigned c3 = (unsigned)(int)code_f(y.w, q_inv, q_max);
+              *reinterpret_cast<unsigned*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
+            }
+            if (SCORE) {
+              const float4 r = yref[g];
+              float d = y.x - r.x;
+              sse = __builtin_fmaf(d, d, sse);
+              d = y.y - r.y;
+              sse = __builtin_fmaf(d, d, sse);
+              d = y.z - r.z;
+              sse = __builtin_fmaf(d, d, sse);
+              d = y.w - r.w;
+              sse = __builtin_fmaf(d, d, sse);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (n + e >= N) break;
+            if (EPI == 0 && ACC) ACC[m * N + n + e] = a[e];
+            if (want_y) {
+              float y = ((float)a[e] * sa) * (w_per_row ? w_scale[n + e] : sw0);
+              if (ACT) {
+                y = apply_act(y, ACT_KIND);
+                if (AMAX) amax = fmaxf(amax, fabsf(y));
+              }
+              if (!QOUT && Y) Y[m * N + n + e] = y;
+              if (QOUT && CODES) CODES[m * N + n + e] = (int8_t)(int)code_f(y, q_inv, q_max);
+              if (SCORE && YREF) {
+                const float d = y - YREF[m * N + n + e];
+                sse = __builtin_fmaf(d, d, sse);
+              }
+            }
+          }
+        }
+      }
+    }
   }
 }
 
-// A fragments of k-substep S (32 k-values) of the stage at byte offset stage_off
-template <class C, bool W4, int S>
-__device__ __forceinline__ void load_a_frags(const char* lds, unsigned stage_off, const FragBase<C, W4>& fr,
-                                             v4i (&fa)[C::FM]) {
-  // chunk bits: 2 S + g (int8 weights) or 4 (S / 2) + 2 g + S % 2 (packed weights); g is in fr.a
-  constexpr unsigned bits = W4 ? (unsigned)(((S >> 1) << 6) | ((S & 1) << 4)) : (unsigned)(S << 5);
-  const char* pa = lds + xor_here<bits>(fr.a + stage_off);
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i) fa[i] = *reinterpret_cast<const v4i*>(pa + i * 32 * C::DBK);
-}
-// LDS address of the lane's W fragments of k-substep S (packed rows: of the substep pair S / 2)
-template <class C, bool W4, int S>
-__device__ __forceinline__ const char* b_frag_ptr(const char* lds, unsigned stage_off, const FragBase<C, W4>& fr) {
-  return lds + xor_here<(unsigned)(W4 ? (S >> 1) << 5 : S << 5)>(fr.b + stage_off);
-}
-template <class C, bool W4>
-__device__ __forceinline__ void load_b_frag(const char* pb, int j, BRaw& fb) {
-  fb.v = *reinterpret_cast<const v4i*>(pb + j * 32 * (W4 ? C::DBK / 2 : C::DBK));
+// The kind of activation is chosen once per output tile: with a uniform branch per four values 4096 x 1024 x 1024 with
+// ReLU spends 2.3 us between its last matrix step and its last store, against 1.15 without an activation.
+template <class C, bool W4, bool VEC, int EPI>
+__device__ __forceinline__ void epilogue(const v4i (&acc)[C::FM][C::FN], int64_t cur_m0, int64_t cur_n0, int wm, int wn, int lane,
+                                         const char* scales, int64_t M, int64_t N, float sa, float sw0,
+                                         const float* __restrict__ w_scale, int w_per_row, bool want_y, float q_inv, float q_max,
+                                         float* __restrict__ Y, int32_t* __restrict__ ACC, const EpiArgs& epi, float& sse,
+                                         float& amax) {
+#define MPQ_EPI(K_)                                                                                                     \
+  epilogue_act<C, W4, VEC, EPI, K_>(acc, cur_m0, cur_n0, wm, wn, lane, scales, M, N, sa, sw0, w_scale, w_per_row, want_y, \
+                                    q_inv, q_max, Y, ACC, epi, sse, amax)
+  if (EPI >= 2 && epi.act == 2) MPQ_EPI(2);
+  else if (EPI >= 2 && epi.act == 1) MPQ_EPI(1);
+  else MPQ_EPI(0);
+#undef MPQ_EPI
 }
 
-// One k substep.  The operand reads of the FOLLOWING substep (S_NEXT of the stage at next_off) are
-// dealt in between the MFMAs: its A fragments first, into the other half of a double buffer; its
-// W fragment j into the registers of this substep's W fragment j as soon as the MFMAs that use
-// that one have been issued (packed weights: only after the second substep of a pair, whose
-// fragments serve both).  Every fragment is thus requested several MFMAs before its first
-// use, with 32 instead of 48 registers of fragments.  Left to itself the scheduler sinks every
-// read down to its first use, and a substep then starts by waiting out the LDS latency, hence
-// the pinning.
-// `request(r)` issues the wave's r-th global->LDS request of a k tile; NR of them are dealt out
-// over the substep (NR = 0: none).  A wave that issues its requests back to back sits in the
-// queue of the CU's one address unit (a 64 KiB k tile keeps it busy for about a thousand clocks)
-// and, issuing in order, feeds no MFMAs meanwhile.
-template <class C, bool W4, int S_NEXT, int NR, class Request>
-__device__ __forceinline__ void k_substep(v16i (&acc)[C::FM][C::FN], const v4i (&fa)[C::FM],
-                                          v4i (&fa_next)[C::FM], BRaw (&fb)[C::FN], const char* lds,
-                                          unsigned next_off, const FragBase<C, W4>& fr, Request&& request) {
-  constexpr int NM = C::FM * C::FN;
-  constexpr int H = (S_NEXT & 1) ^ 1;            // this substep's half of a packed fragment
-  constexpr bool RELOAD = !W4 || (S_NEXT & 1) == 0;  // the following substep starts a new pair
-  load_a_frags<C, W4, S_NEXT>(lds, next_off, fr, fa_next);
-  const char* pb = b_frag_ptr<C, W4, S_NEXT>(lds, next_off, fr);
-  __builtin_amdgcn_sched_barrier(0);
-  static_for<0, C::FN>([&](auto j_) {
-    constexpr int j = decltype(j_)::value;
-    const v4i b = b_operand<W4, H>(fb[j]);
-    static_for<0, C::FM>([&](auto i_) {
-      constexpr int i = decltype(i_)::value;
-      constexpr int q = j * C::FM + i;
-      static_for<q * NR / NM, (q + 1) * NR / NM>([&](auto r_) { request(r_); });
-      __builtin_amdgcn_sched_barrier(0);
-      // W fragment as the row operand: the lane then holds 4 consecutive n per register group,
-      // which the epilogue stores as one 16-byte piece of a Y row
-      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b, fa[i], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    if constexpr (RELOAD) load_b_frag<C, W4>(pb, j, fb[j]);
-    __builtin_amdgcn_sched_barrier(0);
-  });
+// The workgroup's share of the score or of the running maximum, once its last output tile is done.
+template <class C, int EPI>
+__device__ __forceinline__ void finish_sums(char* lds, int lane, int wave, float sse, float amax, const EpiArgs& epi) {
+  float* sm = reinterpret_cast<float*>(lds + C::SUMS_OFF);
+  if (EPI == 1 && epi.part) {  // one partial per workgroup, combined in a fixed order
+    const float w = wave_sum(sse);
+    if (lane == 0) sm[wave] = w;
+    lds_done();
+    meet();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int i = 0; i < C::NW; ++i) t += (double)sm[i];
+      epi.part[blockIdx.x] = t;
+    }
+  }
+  if (EPI == 2 && epi.amax) {  // one atomic per workgroup
+    const float w = wave_max(amax);
+    if (lane == 0) sm[wave] = w;
+    lds_done();
+    meet();
+    if (threadIdx.x == 0) {
+      float t = 0.0f;
+      for (int i = 0; i < C::NW; ++i) t = fmaxf(t, sm[i]);
+      if (epi.amax_part) epi.amax_part[blockIdx.x] = t;
+      else atomicMax(epi.amax, abs_key(t));
+    }
+  }
 }
 
 // A workgroup works off `chunk` output tiles that follow each other along M (same columns, so
@@ -416,10 +531,8 @@ __device__ __forceinline__ void k_substep(v16i (&acc)[C::FM][C::FN], const v4i (
 // fastest; `remap` regroups them so that the workgroups an XCD receives (ids congruent mod 8)
 // cover a contiguous id range and share its L2.
 // The k loop never drains between the tiles of a chunk: the requests issued during the last k
-// tiles of one output tile already fetch the first k tiles of the next one, and the epilogue's
-// stores overlap with those loads.  (k is padded to a multiple of NSTAGE tiles with zero tiles so
-// that a tile always starts in stage 0.)  Chunks stay short so that the hardware dispatcher, not a
-// fixed assignment, balances the load when other kernels hold some of the CUs.
+// tiles of one output tile already fetch the first k tiles of the next one.  Chunks stay short so that the
+// hardware dispatcher, not a fixed assignment, balances the load when other kernels hold some of the CUs.
 // MINW: waves the register allocation must leave room for on one SIMD.
 // EPI: 0 plain, 1 score, 2 activation and absmax of the output, 3 activation and int8 codes of the
 // output (see EpiArgs); variants of their own because the largest tile has no registers to spare
@@ -434,14 +547,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
                                                           int32_t* __restrict__ ACC, EpiArgs epi,
                                                           int tiles_n, int tiles_m, int chunk,
                                                           int remap, int k_per_split) {
-  constexpr bool SCORE = EPI == 1, ACT = EPI >= 2, AMAX = EPI == 2, QOUT = EPI == 3;
-  int8_t* __restrict__ CODES = epi.codes;
-  const float* __restrict__ YREF = epi.yref;
-  double* __restrict__ PART = epi.part;
+  constexpr bool QOUT = EPI == 3;
   using C = DmaCfg<BM, BN, WM, WN, NSTAGE, W4, KB>;
-  constexpr int DBK = KB;
-  constexpr int NSUB = DBK / 32;
-  static_assert(NSUB % 2 == 0, "fragment double buffer assumes an even number of k substeps");
+  using P = DmaPlan<C, W4>;
+  constexpr int NSUB = KB / 64;
+  static_assert(NSUB % 2 == 0, "operand registers alternate from one k substep to the next");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -459,235 +569,131 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
     Wv = reinterpret_cast<const char*>(Wv) + (W4 ? k_begin >> 1 : k_begin);
     ACC += (int64_t)blockIdx.y * M * N;
   }
-  const int KT = (k_len + DBK - 1) / DBK;
-  const int KTp = (KT + NSTAGE - 1) / NSTAGE * NSTAGE;
-
-  const uint8_t* Wb = reinterpret_cast<const uint8_t*>(Wv);
+  const int KT = (k_len + KB - 1) / KB;
   int tile = (wg / tiles_n) * chunk;  // row of tiles; < tiles_m: the grid is ceil(tiles_m / chunk) * tiles_n
   const int tile_end = tile + chunk < tiles_m ? tile + chunk : tiles_m;
-  int64_t m0 = (int64_t)tile * BM;
   const int64_t n0 = (int64_t)(wg % tiles_n) * BN;
-  DmaPlan<C, W4> plan;
-  plan.init(A, Wb, M, N, K, m0, n0, wave, lane);
-  int k_limit = k_len;  // 0 once there is no next tile: every further request fetches zeros
-  // Per-channel W scales of an output tile travel through LDS (one wave-load of 256 floats, issued
-  // by every wave ahead of the tile's first k tile, into the buffer `par` selects): the epilogue
-  // then needs no global loads between its stores and no registers to park the scales in.
   const bool want_y = EPI != 0 || Y != nullptr;
+
+  P plan;
+  plan.init(wave, lane, (unsigned)K, (unsigned)(N - 1 - n0 < BN ? N - 1 - n0 : BN));
+  const char* const b_first = reinterpret_cast<const char*>(Wv) + n0 * (W4 ? K >> 1 : K);
+  Cursor<KB, W4> cursor;
+  cursor.init(nullptr, b_first, k_len, tile);
+  auto start_rows = [&]() {
+    const int64_t m = (int64_t)cursor.tile * BM;
+    cursor.a = reinterpret_cast<const char*>(A) + m * K;
+    cursor.b = b_first;
+    plan.rows_a(wave, lane, (unsigned)K, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
+  };
+  start_rows();
+  // The per-channel W scales of the workgroup's columns travel through LDS (one wave-load of 256 floats, issued by
+  // every wave): the epilogue then needs no global loads between its stores.
+  const bool lds_scales = VEC && want_y && w_per_row;
+  if (lds_scales) {
+    const int64_t n = n0 + 4 * lane;
+    dma16((4 * lane < BN && n < N) ? reinterpret_cast<const char*>(w_scale + n) : cursor.zero, lds0 + C::SCALE_OFF);
+  }
+#pragma unroll
+  for (int p = 0; p < NSTAGE; ++p) {
+    if (cursor.whole()) static_for<0, C::LPW>([&](auto r_) { plan.template request<decltype(r_)::value, true>(cursor, lds0 + p * C::STAGE); });
+    else static_for<0, C::LPW>([&](auto r_) { plan.template request<decltype(r_)::value, false>(cursor, lds0 + p * C::STAGE); });
+    if (cursor.advance(tile_end)) start_rows();
+  }
+  // The scalars of the epilogue are loaded here, behind the requests, once, into scalar registers.  Loaded in the
+  // epilogue they may come as vector loads whose arrival the compiler waits for at every store (vmcnt(0), as it
+  // cannot tell on which path they were used first), and stores count in vmcnt as well: each 16-byte store of a
+  // wave then waits for the one before it to be acknowledged.
+  const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
+  const float sw0 = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y && !w_per_row ? w_scale[0] : 0.0f)));
   float q_inv = 0.0f, q_max = 0.0f;
   if (QOUT) {
     float q_scale;
     bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
-  // The scalars of the epilogue are loaded here, once, into scalar registers.  Loaded in the epilogue they
-  // may come as vector loads whose arrival the compiler waits for at every store (vmcnt(0), as it cannot
-  // tell on which path they were used first), and stores count in vmcnt as well: each 16-byte store of a
-  // wave then waits for the one before it to be acknowledged.
-  const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
-  const float sw0 = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y && !w_per_row ? w_scale[0] : 0.0f)));
-  const bool lds_scales = VEC && want_y && w_per_row;
-  if (VEC && want_y && !w_per_row) {  // one scale: both buffers hold it from the start (the first barrier is below)
+  if (VEC && want_y && !w_per_row) {
     float* sc = reinterpret_cast<float*>(lds + C::SCALE_OFF);
-    for (int i = threadIdx.x; i < 512; i += C::NT) sc[i] = sw0;
+    for (int i = threadIdx.x; i < 256; i += C::NT) sc[i] = sw0;
   }
-  unsigned par = 0;
-  auto issue_scales = [&](int64_t n_first, unsigned which) {
-    if (lds_scales) {  // wave-uniform
-      const int64_t n = n_first + 4 * lane;
-      const char* src = (4 * lane < BN && n < N) ? reinterpret_cast<const char*>(w_scale + n)
-                                                 : reinterpret_cast<const char*>(g_zero16);
-      dma16(src, lds0 + C::SCALE_OFF + which * 1024u);
-    }
-  };
 
-  // Software pipeline.  Every stage holds a k tile; k tile t + NSTAGE is requested into the stage of
-  // k tile t at the moment that stage has been read for the last time, which is BEFORE the MFMAs
-  // of the tile's last k substep are issued (their operands sit in registers by then).  The same
-  // point waits for k tile t + 1, passes the barrier and requests the first fragments of t + 1, so
-  // that barrier skew, the address arithmetic of the loads and the LDS latency all hide behind the
-  // matrix pipe working off the queued MFMAs.
-  issue_scales(n0, par);  // older than every k tile request: the counted waits below cover it
-#pragma unroll
-  for (int p = 0; p < NSTAGE; ++p) plan.issue(lds0 + p * C::STAGE, p * DBK, k_limit);
-  wait_vmcnt<(NSTAGE - 1) * C::LPW>();  // this wave's share of k tile 0 has landed
-  __syncthreads();                      // ... and everyone else's
-  v4i fa[2][C::FM];
-  BRaw fb[C::FN];
+  // Operand registers of two k substeps (64 k each): one set is multiplied while the other is read from LDS.
+  // Packed weights are read once per pair of substeps and expanded, both halves, during the first of them.
+  v4i fa[2][C::FM], fb[2][C::FN], raw[W4 ? C::FN : 1];
   FragBase<C, W4> fr;
   fr.init(wm, wn, lane);
-  load_a_frags<C, W4, 0>(lds, 0u, fr, fa[0]);
-  {
-    const char* pb = b_frag_ptr<C, W4, 0>(lds, 0u, fr);
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) load_b_frag<C, W4>(pb, j, fb[j]);
-  }
-  float sse = 0.0f;    // this lane's share of sum (Y - YREF)^2 over the chunk
-  float amax = 0.0f;   // this lane's largest |Y| after the activation
-  bool drain = false;  // true for the first wait after an epilogue: stores are in flight, and
-                       // loads and stores do not retire in order with respect to each other
+  auto lds_at = [&](unsigned off) { return *reinterpret_cast<const v4i*>(lds + off); };
+  // reads of substep S of the stage at `stage`, numbered so that the first matrix step's operands come first
+  auto read = [&](auto s_, auto n_, unsigned stage) {
+    constexpr int S = decltype(s_)::value, n = decltype(n_)::value;
+    // chunk bits: 4 S + q (int8 weights) or 8 (S / 2) + 2 j + S % 2 (packed weights); q and j are in fr
+    constexpr unsigned xa = W4 ? (unsigned)(((S >> 1) << 7) | ((S & 1) << 4)) : (unsigned)(S << 6);
+    constexpr unsigned xb = W4 ? (unsigned)((S >> 1) << 6) : (unsigned)(S << 6);
+    if constexpr (n < C::FM) fa[S & 1][n] = lds_at(((fr.a + stage) ^ xa) + (unsigned)(n * 16 * C::DBK));
+    else if constexpr (W4) raw[n - C::FM] = lds_at(((fr.b + stage) ^ xb) + (unsigned)((n - C::FM) * 16 * C::B_ROW));
+    else fb[S & 1][n - C::FM] = lds_at(((fr.b + stage) ^ xb) + (unsigned)((n - C::FM) * 16 * C::B_ROW));
+  };
+
+  wait_vmcnt<(NSTAGE - 1) * C::LPW>();  // this wave's share of k tile 0 has landed
+  float sse = 0.0f;   // this lane's share of sum (Y - YREF)^2 over the chunk
+  float amax = 0.0f;  // this lane's largest |Y| after the activation
+  unsigned cur = 0;   // stage of the k tile being multiplied
+  int landed = 0;     // k tiles of this output tile known to be in LDS already
 
   while (true) {
-    v16i acc[C::FM][C::FN];
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-    const int next = tile + 1;
-    const int64_t cur_m0 = m0, cur_n0 = n0;  // m0 moves on to the next tile before the epilogue
-
-    for (int kt = 0; kt < KTp; kt += NSTAGE) {
-      const bool tail = kt + NSTAGE >= KTp;  // requests from here on belong to the next output tile
-      if (tail) {
-        if (next < tile_end) {
-          m0 = (int64_t)next * BM;
-          plan.init(A, Wb, M, N, K, m0, n0, wave, lane);
-        } else {
-          k_limit = 0;
+    // Everyone's share of the first k tile is there.  (Its operands are read here and not carried over from the loop
+    // before: they would hold registers that the epilogue needs.)
+    lds_done();
+    meet();
+    static_for<0, C::FM + C::FN>([&](auto n_) { read(std::integral_constant<int, 0>{}, n_, cur); });
+    v4i acc[C::FM][C::FN];
+    zero_acc(acc);
+    auto step = [&](auto whole_, int t) {
+      unsigned nxt = cur + C::STAGE;
+      nxt = nxt == NSTAGE * C::STAGE ? 0u : nxt;
+      static_for<0, NSUB>([&](auto sub_) {
+        constexpr int S = decltype(sub_)::value;
+        constexpr bool LAST = S == NSUB - 1;
+        constexpr int S1 = LAST ? 0 : S + 1;  // whose operands are read meanwhile, two per matrix step
+        constexpr int NR = C::FM + (W4 && (S1 & 1) ? 0 : C::FN), NM = C::FM * C::FN, NQ = LAST ? C::LPW : 0;
+        // The stage has been read for the last time and the next k tile has landed: its first operands are read and
+        // the stage is filled again while this substep, whose operands are in registers, is multiplied.
+        if constexpr (LAST) {
+          lds_done();
+          if (t + 1 >= landed) wait_vmcnt<(NSTAGE - 2) * C::LPW>();
+          meet();
         }
-      }
-      static_for<0, NSTAGE>([&](auto u_) {
-        constexpr int u = decltype(u_)::value;
-        static_for<0, NSUB>([&](auto sub_) {
-          constexpr int sub = decltype(sub_)::value;
-          if constexpr (sub + 1 < NSUB) {
-            k_substep<C, W4, sub + 1, 0>(acc, fa[sub & 1], fa[(sub + 1) & 1], fb, lds, (unsigned)(u * C::STAGE), fr,
-                                         [](auto) {});
-          } else {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave has read the stage for the last time
-            if (drain) wait_vmcnt<0>();                          // its share of the next k tile has landed
-            else wait_vmcnt<(NSTAGE - 2) * C::LPW>();
-            drain = false;
-            __syncthreads();
-            const int k_next = tail ? u * DBK : (kt + u + NSTAGE) * DBK;
-            if (u == 0 && tail && next < tile_end) issue_scales(n0, par ^ 1u);
-            const auto tl = plan.tile(k_next, k_limit);
-            // the stage just given up is refilled while the last substep's MFMAs, whose operands
-            // are in registers, run; the next stage's first fragments are read alongside
-            k_substep<C, W4, 0, C::LPW>(acc, fa[sub & 1], fa[0], fb, lds, (unsigned)(((u + 1) % NSTAGE) * C::STAGE), fr,
-                                        [&](auto r_) { plan.template request<decltype(r_)::value>(tl, lds0 + u * C::STAGE); });
-          }
+        if constexpr (W4 && (S & 1) == 0) fb[0][0] = expand_half<0>(raw[0]);
+        static_for<0, NM>([&](auto m_) {
+          constexpr int m = decltype(m_)::value, j = m / C::FM, i = m % C::FM;
+          // W fragment as the row operand: the lane then holds 4 consecutive n, which the epilogue stores as one
+          // 16-byte piece of a Y row
+          mma(acc[i][j], fb[S & 1][j], fa[S & 1][i]);
+          __builtin_amdgcn_sched_barrier(0);
+          static_for<2 * m < NR ? 2 * m : NR, 2 * m + 2 < NR ? 2 * m + 2 : NR>(
+              [&](auto n_) { read(std::integral_constant<int, S1>{}, n_, LAST ? nxt : cur); });
+          static_for<m * NQ / NM, (m + 1) * NQ / NM>([&](auto r_) { plan.template request<decltype(r_)::value, decltype(whole_)::value>(cursor, lds0 + cur); });
+          if constexpr (W4 && (S & 1) == 0 && i == 0) fb[1][j] = expand_half<1>(raw[j]);
+          if constexpr (W4 && (S & 1) == 0 && i == C::FM - 1 && j + 1 < C::FN) fb[0][j + 1] = expand_half<0>(raw[j + 1]);
+          __builtin_amdgcn_sched_barrier(0);
         });
       });
-    }
-
-    // epilogue.  32x32 accumulator tile (i, j): lane l holds m = l % 32 and, in registers
-    // 4g .. 4g+3, the four consecutive n = 8g + 4 (l / 32) + 0..3.
-    const char* scales = lds + C::SCALE_OFF + par * 1024u;
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-      const int64_t m = cur_m0 + wm * C::TM + i * 32 + (lane & 31);
-      if (m >= M) continue;
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j) {
-        // Score: the loads of four groups in flight together (past the edge: the row's first columns), where
-        // the accumulators leave registers for them (the 256 x 256 tile spills: 113 -> 121 us on
-        // 16384 x 1024 x 4096; 12288 x 768 x 768 in 192 x 192 tiles 21.4 -> 18.7).
-        constexpr bool AHEAD = SCORE && VEC && C::FM * C::FN <= 6;
-        float4 yref[4];
-        if (AHEAD) {
-#pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const int64_t n = cur_n0 + wn * C::TN + j * 32 + g4 * 8 + (lane >> 5) * 4;
-            yref[g4] = *reinterpret_cast<const float4*>(YREF + m * N + (n < N ? n : 0));
-          }
-        }
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int64_t n = cur_n0 + wn * C::TN + j * 32 + g4 * 8 + (lane >> 5) * 4;
-          if (n >= N) continue;
-          int a[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            a[e] = acc[i][j][g4 * 4 + e];
-            if (W4) a[e] >>= 4;  // exact: every product carried the factor 16
-          }
-          if (VEC) {  // N % 4 == 0 and 16-byte aligned outputs: the four n are all in range
-            if (EPI == 0 && ACC) *reinterpret_cast<v4i*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
-            if (want_y) {
-              const float4 sw = *reinterpret_cast<const float4*>(scales + (wn * C::TN + j * 32 + g4 * 8 + (lane >> 5) * 4) * 4);
-              float4 y = make_float4(((float)a[0] * sa) * sw.x, ((float)a[1] * sa) * sw.y,
-                                     ((float)a[2] * sa) * sw.z, ((float)a[3] * sa) * sw.w);
-              if (ACT) {
-                y = apply_act4(y, epi.act);
-                if (AMAX) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
-              }
-              if (!QOUT && Y) *reinterpret_cast<float4*>(Y + m * N + n) = y;
-              if (QOUT && CODES) {  // four codes, lowest n in the lowest byte
-                const unsigned c0 = (unsigned)(int)code_f(y.x, q_inv, q_max) & 0xFFu;
-                const unsigned c1 = (unsigned)(int)code_f(y.y, q_inv, q_max) & 0xFFu;
-                const unsigned c2 = (unsigned)(int)code_f(y.z, q_inv, q_max) & 0xFFu;
-                const unsigned c3 = (unsigned)(int)code_f(y.w, q_inv, q_max);
-                *reinterpret_cast<unsigned*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-              }
-              if (SCORE) {
-                const float4 r = AHEAD ? yref[g4] : *reinterpret_cast<const float4*>(YREF + m * N + n);
-                float d = y.x - r.x;
-                sse = __builtin_fmaf(d, d, sse);
-                d = y.y - r.y;
-                sse = __builtin_fmaf(d, d, sse);
-                d = y.z - r.z;
-                sse = __builtin_fmaf(d, d, sse);
-                d = y.w - r.w;
-                sse = __builtin_fmaf(d, d, sse);
-              }
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (n + e >= N) break;
-              if (EPI == 0 && ACC) ACC[m * N + n + e] = a[e];
-              if (want_y) {
-                float y = ((float)a[e] * sa) * (w_per_row ? w_scale[n + e] : sw0);
-                if (ACT) {
-                  y = apply_act(y, epi.act);
-                  if (AMAX) amax = fmaxf(amax, fabsf(y));
-                }
-                if (!QOUT && Y) Y[m * N + n + e] = y;
-                if (QOUT && CODES) CODES[m * N + n + e] = (int8_t)(int)code_f(y, q_inv, q_max);
-                if (SCORE && YREF) {
-                  const float d = y - YREF[m * N + n + e];
-                  sse = __builtin_fmaf(d, d, sse);
-                }
-              }
-            }
-          }
-        }
-      }
-    }
-    if (next >= tile_end) break;  // block-uniform
-    tile = next;
-    par ^= 1u;
-    drain = true;
+      if (cursor.advance(tile_end)) start_rows();
+      cur = nxt;
+    };
+    int t = 0;
+    for (; t < KT && cursor.whole(); ++t) step(std::true_type{}, t);
+    for (; t < KT; ++t) step(std::false_type{}, t);
+    // The next output tile's first NSTAGE k tiles land here, ahead of the stores: no wait of its first barriers
+    // then has to wait for a store (both count in vmcnt).
+    wait_vmcnt<0>();
+    landed = NSTAGE;
+    acc_ready(acc);
+    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane, lds + C::SCALE_OFF, M, N, sa, sw0, w_scale, w_per_row,
+                              want_y, q_inv, q_max, Y, ACC, epi, sse, amax);
+    if (++tile >= tile_end) break;  // block-uniform
   }
-  wait_vmcnt<0>();  // the zero-fill requests past the last tile land before the LDS is given back
-  if (SCORE && PART) {  // one partial per workgroup, combined in a fixed order
-    const float w = wave_sum(sse);
-    __syncthreads();  // nobody reads a stage or a scale buffer any more
-    float* sm = reinterpret_cast<float*>(lds);
-    if (lane == 0) sm[wave] = w;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int i = 0; i < C::NW; ++i) t += (double)sm[i];
-      PART[blockIdx.x] = t;
-    }
-  }
-  if (AMAX && epi.amax) {  // one atomic per workgroup
-    const float w = wave_max(amax);
-    __syncthreads();
-    float* sm = reinterpret_cast<float*>(lds);
-    if (lane == 0) sm[wave] = w;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float t = 0.0f;
-      for (int i = 0; i < C::NW; ++i) t = fmaxf(t, sm[i]);
-      if (epi.amax_part) epi.amax_part[blockIdx.x] = t;
-      else atomicMax(epi.amax, abs_key(t));
-    }
-  }
+  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi);
 }
 
 // Dynamic LDS above 64 KiB has to be allowed once per kernel and device (hipFuncSetAttribute, not a
@@ -705,6 +711,40 @@ inline int allow_lds(const void* kern, int bytes, std::atomic<unsigned>* done, i
   return MPQ_OK;
 }
 
+// How a call is launched with a tile size: kernel variant (EPI * 2 + VEC), grid and chunk length.
+struct LaunchShape {
+  int which = 0;
+  int64_t tm = 0, tn = 0, grid = 0;
+  int chunk = 1, remap = 0;
+};
+inline int launch_shape(int bm, int bn, int lds_bytes, int64_t M, int64_t N, const float* w_scale, int per_row, const float* y_out,
+                        const int32_t* acc_out, const EpiArgs& epi, int split, LaunchShape& s) {
+  // float4 / int4 stores need every 4-group of n inside the row and 16-byte aligned
+  const bool vec = (N & 3) == 0 && (!y_out || aligned16(y_out)) && (!acc_out || aligned16(acc_out)) &&
+                   (!((y_out || epi.yref || epi.amax || epi.codes) && per_row) || aligned16(w_scale)) &&
+                   (!epi.yref || aligned16(epi.yref)) && (!epi.codes || (reinterpret_cast<uintptr_t>(epi.codes) & 3u) == 0);
+  const int mode = epi.yref ? 1 : epi.codes ? 3 : (epi.act || epi.amax) ? 2 : 0;
+  s.which = mode * 2 + (vec ? 1 : 0);
+  s.tm = (M + bm - 1) / bm;
+  s.tn = (N + bn - 1) / bn;
+  if (s.tm * s.tn > 0x7FFFFFFF || s.tn > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
+  // Chunk length: the chip holds `slots` workgroups at a time (what the LDS allows per CU), so a
+  // launch costs about ceil(grid / slots) * chunk tile times; take the length up to 4 that makes
+  // this smallest, the longer one on a tie (more tile boundaries without a drain).
+  int per_cu = (160 * 1024) / lds_bytes;
+  if (per_cu > 4) per_cu = 4;
+  if (per_cu < 1) per_cu = 1;
+  const int64_t slots = kNumCU * per_cu;
+  int64_t best = 0;
+  for (int c = 1; c <= 4; ++c) {
+    const int64_t g = ((s.tm + c - 1) / c) * s.tn;
+    const int64_t cost = ((g * split + slots - 1) / slots) * c;
+    if (c == 1 || cost <= best) { best = cost; s.chunk = c; s.grid = g; }
+  }
+  s.remap = (s.grid % 8 == 0 && s.grid >= 16) ? 1 : 0;
+  return MPQ_OK;
+}
+
 // prepare_only: configure every kernel variant of this instantiation and launch nothing (mpq_init).
 // split > 1: workgroup rows y = 0 .. split - 1 each take k_per_split of k (a multiple of the k tile)
 // and write raw accumulators to plane y of acc_out (plain epilogue only).
@@ -714,7 +754,6 @@ static int launch_dma(const int8_t* a_q, const void* w_q, int64_t M, int64_t N, 
                       int32_t* acc_out, hipStream_t st, EpiArgs epi = kNoEpi,
                       int64_t* n_partials = nullptr, int split = 1, int k_per_split = 0,
                       bool prepare_only = false) {
-  const float* y_ref = epi.yref;
   using C = DmaCfg<BM, BN, WM, WN, NSTAGE, W4, KB>;
   using Kern = void (*)(const int8_t*, const void*, int64_t, int64_t, int64_t, const float*, const float*, int,
                         float*, int32_t*, EpiArgs, int, int, int, int, int);
@@ -731,36 +770,14 @@ static int launch_dma(const int8_t* a_q, const void* w_q, int64_t M, int64_t N, 
     }
     return MPQ_OK;
   }
-  // float4 / int4 stores need every 4-group of n inside the row and 16-byte aligned
-  const bool vec = (N & 3) == 0 && (!y_out || aligned16(y_out)) && (!acc_out || aligned16(acc_out)) &&
-                   (!((y_out || y_ref || epi.amax || epi.codes) && per_row) || aligned16(w_scale)) &&
-                   (!y_ref || aligned16(y_ref)) && (!epi.codes || (reinterpret_cast<uintptr_t>(epi.codes) & 3u) == 0);
-  const int mode = y_ref ? 1 : epi.codes ? 3 : (epi.act || epi.amax) ? 2 : 0;
-  const int which = mode * 2 + (vec ? 1 : 0);
-  const Kern kern = kerns[which];
-  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-  if (tm * tn > 0x7FFFFFFF || tn > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-  const int rc = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_BYTES, done, which);
-  if (rc != MPQ_OK) return rc;
-  // Chunk length: the chip holds `slots` workgroups at a time (what the LDS allows per CU), so a
-  // launch costs about ceil(grid / slots) * chunk tile times; take the length up to 4 that makes
-  // this smallest, the longer one on a tie (more tile boundaries without a drain).
-  int per_cu = (160 * 1024) / C::LDS_BYTES;
-  if (per_cu > 4) per_cu = 4;
-  if (per_cu < 1) per_cu = 1;
-  const int64_t slots = kNumCU * per_cu;
-  int chunk = 1;
-  int64_t best = 0, grid = 0;
-  for (int c = 1; c <= 4; ++c) {
-    const int64_t g = ((tm + c - 1) / c) * tn;
-    const int64_t cost = ((g * split + slots - 1) / slots) * c;
-    if (c == 1 || cost <= best) { best = cost; chunk = c; grid = g; }
-  }
-  const int remap = (grid % 8 == 0 && grid >= 16) ? 1 : 0;
   if (split <= 1) { split = 1; k_per_split = (int)K; }
-  kern<<<dim3((unsigned)grid, (unsigned)split), C::NT, C::LDS_BYTES, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out,
-                                                                    acc_out, epi, (int)tn, (int)tm, chunk, remap, k_per_split);
-  if (n_partials) *n_partials = grid;
+  LaunchShape s;
+  int rc = launch_shape(BM, BN, C::LDS_BYTES, M, N, w_scale, per_row, y_out, acc_out, epi, split, s);
+  if (rc == MPQ_OK) rc = allow_lds(reinterpret_cast<const void*>(kerns[s.which]), C::LDS_BYTES, done, s.which);
+  if (rc != MPQ_OK) return rc;
+  kerns[s.which]<<<dim3((unsigned)s.grid, (unsigned)split), C::NT, C::LDS_BYTES, st>>>(
+      a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, epi, (int)s.tn, (int)s.tm, s.chunk, s.remap, k_per_split);
+  if (n_partials) *n_partials = s.grid;
   return launch_status();
 }
 
