@@ -363,7 +363,7 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
       d.acc_out = planes;
       d.split = sp.split;
       d.k_per_split = sp.k_per_split;
-      const int rc = launch_dma_64(w4, false, false, d);
+      const int rc = launch_dma_64(w4, w4 ? 2 : 3, 128, d);
       if (rc != MPQ_OK) return rc;
       const int64_t MN = M * N;
       const bool vec = (N & 3) == 0 && (!y_out || aligned16(y_out)) && (!acc_out || aligned16(acc_out)) &&
@@ -374,29 +374,11 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
       else splitk_reduce<false><<<blocks, kBlock, 0, st>>>(planes, sp.split, MN, N, a_scale, w_scale, per_row, y_out, acc_out);
       return launch_status();
     }
-    // tile choice (from sweeps over the configured shapes): 256 x 256 when that gives at least
-    // three CUs in four a tile; else 192 x 192 (six waves) when it covers the problem in exactly
-    // one round with at least three CUs in four busy and next to no padding (the BERT-base
-    // widths: 768 = 4 x 192 gives 12288 x 768 exactly 256 tiles where 256 x 256 gives 144);
-    // else 128 x 128 when it gives at least half of the CUs a tile, else 64 x 64.
-    // 128 x 128 runs three stages (one workgroup per CU) when there is at most one tile per CU
-    // anyway or k is long, two stages (two workgroups per CU) otherwise.
-    // k is padded to a multiple of the stages, so a k of two or four tiles takes two of them: with three,
-    // four tiles are multiplied as six.  Three | two stages, us (M x K x N): 4096 x 512 x 1024 10.9 | 9.5,
-    // 1000 x 512 x 512 4.9 | 4.3, 1000 x 256 x 512 4.1 | 3.7, 2048 x 1024 x 512 (k tiles of 256) 7.1 | 5.9; eight
-    // tiles padded to nine are better off in three (24 layers of 4096 x 1024 x 1024 454 | 476).
-    auto two = [&](int kb) { const int64_t kt = (K + kb - 1) / kb; return kt == 2 || kt == 4; };
-    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const int64_t t192 = tiles(192, 192);
-    if (N > 128 && tiles(256, 256) >= kNumCU * 3 / 4) return launch_dma_256(w4, d);
-    if (N % 192 == 0 && t192 <= kNumCU && t192 >= kNumCU * 3 / 4 && t192 * 192 * 192 <= M * N + M * N / 32)
-      return launch_dma_192(w4, K >= 1024, d);
-    if (N > 64 && tiles(128, 128) >= kNumCU / 2)
-      return launch_dma_128(w4, K >= 2048 || (tiles(128, 128) <= kNumCU && !two(128)), d);
-    // k tiles of 256 bytes where the grid is at most one workgroup per CU anyway (the longer stages
-    // leave room for one workgroup per CU only) and k is long enough to have several of them
-    const bool long_k = K >= 1024 && tiles(64, 64) <= kNumCU;
-    return launch_dma_64(w4, long_k, two(long_k ? 256 : 128), d);
+    const FastTile t = fast_tile(M, N, K, w4, kNumCU);
+    if (t.side == 256) return launch_dma_256(w4, d);
+    if (t.side == 192) return launch_dma_192(w4, d);
+    if (t.side == 128) return launch_dma_128(w4, t.stages, d);
+    return launch_dma_64(w4, t.stages, t.kb, d);
   }
   const int ts = any_tile(M, N, K, kNumCU);
   const int64_t gx = (N + ts - 1) / ts, gy = (M + ts - 1) / ts;
@@ -426,12 +408,12 @@ extern "C" int mpq_init(void) {
   const DmaArgs d{nullptr, nullptr, 0, 0, 0, nullptr, nullptr, 0, nullptr, nullptr, nullptr, kNoEpi, nullptr, 1, 0, true};
   for (int w4 = 0; w4 < 2; ++w4) {
     int rc = launch_dma_256(w4 != 0, d);
-    if (rc == MPQ_OK) rc = launch_dma_192(w4 != 0, true, d);
-    if (rc == MPQ_OK) rc = launch_dma_192(w4 != 0, false, d);
-    if (rc == MPQ_OK) rc = launch_dma_128(w4 != 0, true, d);
-    if (rc == MPQ_OK) rc = launch_dma_128(w4 != 0, false, d);
-    for (int v = 0; v < 4; ++v)
-      if (rc == MPQ_OK) rc = launch_dma_64(w4 != 0, (v & 1) != 0, (v & 2) != 0, d);
+    if (rc == MPQ_OK) rc = launch_dma_192(w4 != 0, d);
+    for (int stages = 2; stages <= 3; ++stages) {
+      if (rc == MPQ_OK) rc = launch_dma_128(w4 != 0, stages, d);
+      for (int kb = 128; kb <= 256; kb += 128)
+        if (rc == MPQ_OK) rc = launch_dma_64(w4 != 0, stages, kb, d);
+    }
     if (rc != MPQ_OK) return rc;
   }
   return prepare_hutchinson();

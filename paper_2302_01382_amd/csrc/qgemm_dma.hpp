@@ -13,6 +13,10 @@ namespace mpq {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+// the same in memory at any address an element may have
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32_any __attribute__((aligned(1)));
 
 // What an epilogue may do beyond Y = (float(acc) * s_A) * s_W[n]:
 //  - score: accumulate sum (Y - yref)^2, one double partial per workgroup in `part`;
@@ -165,6 +169,24 @@ __device__ __forceinline__ void dma16(const char* src, unsigned lds_byte_off) {
 // the same with a wave-uniform base in scalar registers and a 32-bit offset per lane
 __device__ __forceinline__ void dma16_base(const char* base, unsigned off, unsigned lds_byte_off) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_byte_off) : "memory");
+}
+// one 4-byte value per lane, at +4 l
+__device__ __forceinline__ void dma4(const float* src, unsigned lds_byte_off) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_byte_off) : "memory");
+}
+// The per-channel W scales of a workgroup's columns travel through LDS: the epilogue then needs no global loads between
+// its stores.  Every wave fetches them, so that its own wait covers them.  Columns past the edge: any scale.
+template <bool VEC>
+__device__ __forceinline__ void request_scales(const float* w_scale, int64_t n0, int64_t N, int bn, int lane, unsigned lds_byte_off) {
+  if (VEC) {  // N % 4 == 0, w_scale 16-byte aligned
+    const int64_t n = n0 + 4 * lane;
+    dma16(reinterpret_cast<const char*>(w_scale + (n < N ? n : 0)), lds_byte_off);
+  } else {
+    for (int i = 0; i < bn; i += 64) {
+      const int64_t n = n0 + i + lane;
+      dma4(w_scale + (n < N ? n : 0), lds_byte_off + (unsigned)i * 4u);
+    }
+  }
 }
 template <int N_>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -384,32 +406,36 @@ __device__ __forceinline__ v4i expand_half(const v4i& r) {
 // (i, j): lane l holds m = l % 16 and the four consecutive n = 4 (l / 16) + 0..3: a store instruction writes 64
 // bytes of each of 16 rows.  (In 32x32 tiles it is 32 bytes of 32 rows: 67 MB stored by one workgroup per CU 14.5 us
 // against 11.5, 16.8 MB in 128 x 128 tiles 6.2 against 4.8, whole rows no better.)
-// scales: the tile's per-channel W scales in LDS (VEC).  sse, amax: the lane's running sums.
+// scales: the tile's per-channel W scales in LDS.  sse, amax: the lane's running sums.
+// Rows of N % 4 != 0 values, stored one by one before: 6846 x 1152 x 3139 121 -> 49 us, 2999 x 1152 x 1021 20.8 -> 9.7.
 template <class C, bool W4, bool VEC, int EPI, int ACT_KIND>
 __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int64_t cur_m0, int64_t cur_n0, int wm, int wn, int lane,
-                                         const char* scales, int64_t M, int64_t N, float sa, float sw0,
-                                         const float* __restrict__ w_scale, int w_per_row, bool want_y, float q_inv, float q_max,
+                                         const char* scales, int64_t M, int64_t N, float sa, bool want_y, float q_inv, float q_max,
                                          float* __restrict__ Y, int32_t* __restrict__ ACC, const EpiArgs& epi, float& sse,
                                          float& amax) {
   constexpr bool SCORE = EPI == 1, ACT = EPI >= 2, AMAX = EPI == 2, QOUT = EPI == 3;
   int8_t* __restrict__ CODES = epi.codes;
   const float* __restrict__ YREF = epi.yref;
+  // A group of four n that lies inside the row travels in one access whatever its alignment
+  using F4 = std::conditional_t<VEC, v4f, f4_any>;
+  using I4 = std::conditional_t<VEC, v4i, v4i_any>;
+  using C4 = std::conditional_t<VEC, unsigned, u32_any>;
   const int nq = wn * C::TN + (lane >> 4) * 4;  // the lane's first n within the tile
 #pragma unroll
   for (int i = 0; i < C::FM; ++i) {
     const int64_t m = cur_m0 + wm * C::TM + i * 16 + (lane & 15);
     if (m >= M) continue;
-    // Score: the loads of a group of G are in flight together (past the edge: the row's first columns).
+    // Score: the loads of a group of G are in flight together (past the edge: others of the row).
     constexpr int G = C::FN % 4 == 0 ? 4 : 2;
     static_assert(C::FN % 2 == 0, "pairs of column tiles");
 #pragma unroll
     for (int j0 = 0; j0 < C::FN; j0 += G) {
-      float4 yref[G];
-      if (SCORE && VEC) {
+      v4f yref[G];
+      if (SCORE && (VEC || N >= 4)) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           const int64_t n = cur_n0 + nq + (j0 + g) * 16;
-          yref[g] = *reinterpret_cast<const float4*>(YREF + m * N + (n < N ? n : 0));
+          yref[g] = *reinterpret_cast<const F4*>(YREF + m * N + (n + 4 <= N ? n : 0));
         }
       }
 #pragma unroll
@@ -423,26 +449,26 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
           a[e] = acc[i][j][e];
           if (W4) a[e] >>= 4;  // exact: every product carried the factor 16
         }
-        if (VEC) {  // N % 4 == 0 and 16-byte aligned outputs: the four n are all in range
-          if (EPI == 0 && ACC) *reinterpret_cast<v4i*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
+        const float4 sw = *reinterpret_cast<const float4*>(scales + (nq + j * 16) * 4);
+        if (VEC || n + 4 <= N) {  // VEC: N % 4 == 0 and 16-byte aligned outputs
+          if (EPI == 0 && ACC) *reinterpret_cast<I4*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
           if (want_y) {
-            const float4 sw = *reinterpret_cast<const float4*>(scales + (nq + j * 16) * 4);
             float4 y = make_float4(((float)a[0] * sa) * sw.x, ((float)a[1] * sa) * sw.y,
                                    ((float)a[2] * sa) * sw.z, ((float)a[3] * sa) * sw.w);
             if (ACT) {
               y = apply_act4(y, ACT_KIND);
               if (AMAX) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
             }
-            if (!QOUT && Y) *reinterpret_cast<float4*>(Y + m * N + n) = y;
+            if (!QOUT && Y) *reinterpret_cast<F4*>(Y + m * N + n) = v4f{y.x, y.y, y.z, y.w};
             if (QOUT && CODES) {  // four codes, lowest n in the lowest byte
               const unsigned c0 = (unsigned)(int)code_f(y.x, q_inv, q_max) & 0xFFu;
               const unsigned c1 = (unsigned)(int)code_f(y.y, q_inv, q_max) & 0xFFu;
               const unsigned c2 = (unsigned)(int)code_f(y.z, q_inv, q_max) & 0xFFu;
               const unsigned c3 = (unsigned)(int)code_f(y.w, q_inv, q_max);
-              *reinterpret_cast<unsigned*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
+              *reinterpret_cast<C4*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
             }
             if (SCORE) {
-              const float4 r = yref[g];
+              const v4f r = yref[g];
               float d = y.x - r.x;
               sse = __builtin_fmaf(d, d, sse);
               d = y.y - r.y;
@@ -453,13 +479,14 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
               sse = __builtin_fmaf(d, d, sse);
             }
           }
-        } else {
+        } else {  // the last group of a row that it does not fill
+          const float s4[4] = {sw.x, sw.y, sw.z, sw.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             if (n + e >= N) break;
             if (EPI == 0 && ACC) ACC[m * N + n + e] = a[e];
             if (want_y) {
-              float y = ((float)a[e] * sa) * (w_per_row ? w_scale[n + e] : sw0);
+              float y = ((float)a[e] * sa) * s4[e];
               if (ACT) {
                 y = apply_act(y, ACT_KIND);
                 if (AMAX) amax = fmaxf(amax, fabsf(y));
@@ -482,13 +509,11 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
 // ReLU spends 2.3 us between its last matrix step and its last store, against 1.15 without an activation.
 template <class C, bool W4, bool VEC, int EPI>
 __device__ __forceinline__ void epilogue(const v4i (&acc)[C::FM][C::FN], int64_t cur_m0, int64_t cur_n0, int wm, int wn, int lane,
-                                         const char* scales, int64_t M, int64_t N, float sa, float sw0,
-                                         const float* __restrict__ w_scale, int w_per_row, bool want_y, float q_inv, float q_max,
+                                         const char* scales, int64_t M, int64_t N, float sa, bool want_y, float q_inv, float q_max,
                                          float* __restrict__ Y, int32_t* __restrict__ ACC, const EpiArgs& epi, float& sse,
                                          float& amax) {
 #define MPQ_EPI(K_)                                                                                                     \
-  epilogue_act<C, W4, VEC, EPI, K_>(acc, cur_m0, cur_n0, wm, wn, lane, scales, M, N, sa, sw0, w_scale, w_per_row, want_y, \
-                                    q_inv, q_max, Y, ACC, epi, sse, amax)
+  epilogue_act<C, W4, VEC, EPI, K_>(acc, cur_m0, cur_n0, wm, wn, lane, scales, M, N, sa, want_y, q_inv, q_max, Y, ACC, epi, sse, amax)
   if (EPI >= 2 && epi.act == 2) MPQ_EPI(2);
   else if (EPI >= 2 && epi.act == 1) MPQ_EPI(1);
   else MPQ_EPI(0);
@@ -580,25 +605,22 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
   const char* const b_first = reinterpret_cast<const char*>(Wv) + n0 * (W4 ? K >> 1 : K);
   Cursor<KB, W4> cursor;
   cursor.init(nullptr, b_first, k_len, tile);
-  auto start_rows = [&]() {
+  // The lane's offsets are the same in every output tile but one that reaches past M, which is the workgroup's last.
+  // (Formed for each tile they were known before the k loop and spilled over it by the 256 tile, and to load a spilled
+  // register waits for all stores in flight: with the epilogue's addresses, below, 16384 x 1024 x 4096 95.2 -> 91.3 us.)
+  auto start_rows = [&](bool first) {
     const int64_t m = (int64_t)cursor.tile * BM;
     cursor.a = reinterpret_cast<const char*>(A) + m * K;
     cursor.b = b_first;
-    plan.rows_a(wave, lane, (unsigned)K, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
+    if (first || m + BM > M) plan.rows_a(wave, lane, (unsigned)K, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
   };
-  start_rows();
-  // The per-channel W scales of the workgroup's columns travel through LDS (one wave-load of 256 floats, issued by
-  // every wave): the epilogue then needs no global loads between its stores.
-  const bool lds_scales = VEC && want_y && w_per_row;
-  if (lds_scales) {
-    const int64_t n = n0 + 4 * lane;
-    dma16((4 * lane < BN && n < N) ? reinterpret_cast<const char*>(w_scale + n) : cursor.zero, lds0 + C::SCALE_OFF);
-  }
+  start_rows(true);
+  if (want_y && w_per_row) request_scales<VEC>(w_scale, n0, N, BN, lane, lds0 + C::SCALE_OFF);
 #pragma unroll
   for (int p = 0; p < NSTAGE; ++p) {
     if (cursor.whole()) static_for<0, C::LPW>([&](auto r_) { plan.template request<decltype(r_)::value, true>(cursor, lds0 + p * C::STAGE); });
     else static_for<0, C::LPW>([&](auto r_) { plan.template request<decltype(r_)::value, false>(cursor, lds0 + p * C::STAGE); });
-    if (cursor.advance(tile_end)) start_rows();
+    if (cursor.advance(tile_end)) start_rows(false);
   }
   // The scalars of the epilogue are loaded here, behind the requests, once, into scalar registers.  Loaded in the
   // epilogue they may come as vector loads whose arrival the compiler waits for at every store (vmcnt(0), as it
@@ -612,7 +634,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
     bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
-  if (VEC && want_y && !w_per_row) {
+  if (want_y && !w_per_row) {
     float* sc = reinterpret_cast<float*>(lds + C::SCALE_OFF);
     for (int i = threadIdx.x; i < 256; i += C::NT) sc[i] = sw0;
   }
@@ -678,7 +700,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
           __builtin_amdgcn_sched_barrier(0);
         });
       });
-      if (cursor.advance(tile_end)) start_rows();
+      if (cursor.advance(tile_end)) start_rows(false);
       cur = nxt;
     };
     int t = 0;
@@ -689,8 +711,10 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
     wait_vmcnt<0>();
     landed = NSTAGE;
     acc_ready(acc);
-    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane, lds + C::SCALE_OFF, M, N, sa, sw0, w_scale, w_per_row,
-                              want_y, q_inv, q_max, Y, ACC, epi, sse, amax);
+    int lane_here = lane;  // its addresses are formed here: known before the k loop they would be spilled over it
+    asm volatile("" : "+v"(lane_here));
+    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane_here, lds + C::SCALE_OFF, M, N, sa, want_y, q_inv, q_max,
+                              Y, ACC, epi, sse, amax);
     if (++tile >= tile_end) break;  // block-uniform
   }
   finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi);
@@ -799,9 +823,9 @@ struct DmaArgs {
   bool prepare_only;  // configure the kernels of this tile size, launch nothing
 };
 int launch_dma_256(bool w4, const DmaArgs& a);
-int launch_dma_192(bool w4, bool three_stages, const DmaArgs& a);
-int launch_dma_128(bool w4, bool three_stages, const DmaArgs& a);
-int launch_dma_64(bool w4, bool long_k, bool two_stages, const DmaArgs& a);
+int launch_dma_192(bool w4, const DmaArgs& a);
+int launch_dma_128(bool w4, int stages, const DmaArgs& a);
+int launch_dma_64(bool w4, int stages, int kb, const DmaArgs& a);
 
 // Layers with few output tiles (qgemm_skinny.hip): how many waves split k, 0 where the layer is better
 // off with the tiled kernels.

@@ -16,12 +16,13 @@
 //
 // (The other tiles keep their waves' operands of 64 k in registers twice over; here the accumulators take half of them.)
 //
-// What bounds it: 16384 x 4096 x 1024 (one output tile per CU) is 1.43 us per k tile, at 2.0 GHz and 2900 clocks for
-// 2048 clocks of matrix steps; without its requests 1.05, without its LDS reads 1.33, without barriers and waits 1.33,
-// matrix steps alone 1.17: the loads into the LDS, and the power they take, are what is left over it, and where in the
-// k tile they are issued makes no difference (spread, bunched, the two waves of a SIMD apart: 62-66 us).  With a
-// barrier per k tile, a whole stage freed at once and 32 x 32 matrix steps 68.4 us -> 61.9; 16384 x 1024 x 4096 with
-// GELU and its maximum 121 -> 109, 16384 x 4096 x 1024 with the score, packed weights, 70.4 -> 63.1.
+// What bounds it: with int8 weights a k tile takes a CU 1.36 us (16384 x 4096 x 1024, one output tile per CU), of which
+// the matrix steps alone are 1.05-1.17; at 2.0 GHz 2900 clocks passed for 2048 of matrix steps when it took 1.43.  Then,
+// without its requests it took 1.05, without its LDS reads 1.33, without barriers and waits 1.33: the loads into the
+// LDS, and the power they take, are what is left, and where in the k tile they are issued makes no difference (spread,
+// bunched, the two waves of a SIMD apart).  An output tile costs 12-13 us besides: its 256 KiB at the memory's rate.
+// Against a barrier per k tile, a whole stage freed at once and 32x32 matrix steps: 16384 x 4096 x 1024 67.8 -> 57.9 us
+// (packed weights 71.2 -> 60.5), 4096 x 4096 x 4096 67.5 -> 58.2, 16384 x 1024 x 4096 100.4 -> 91.3 (99.0 -> 87.3).
 #pragma once
 
 #include "qgemm_dma.hpp"
@@ -113,13 +114,13 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
   const char* const b_first = reinterpret_cast<const char*>(Wv) + n0 * (W4 ? K >> 1 : K);
   Cursor<128, W4> cursor;
   cursor.init(nullptr, b_first, (int)K, tile);
-  auto start_rows = [&]() {
+  auto start_rows = [&](bool first) {  // see qgemm_dma
     const int64_t m = (int64_t)cursor.tile * BM;
     cursor.a = reinterpret_cast<const char*>(A) + m * K;
     cursor.b = b_first;
-    plan.rows_a(wave, lane, Ku, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
+    if (first || m + BM > M) plan.rows_a(wave, lane, Ku, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
   };
-  start_rows();
+  start_rows(true);
   // request r (A loads first) of half h of the cursor's k tile into the stage at LDS offset `stage`
   auto request = [&](auto whole_, auto h_, auto r_, unsigned stage) {
     constexpr bool WHOLE = decltype(whole_)::value;
@@ -133,10 +134,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
                                    lds0 + stage + plan.lds_b + (unsigned)((h * P::TNH + x * P::BRPI) * C::B_ROW));
     }
   };
-  if (VEC && want_y && w_per_row) {  // the per-channel W scales of the workgroup's columns
-    const int64_t n = n0 + 4 * lane;
-    dma16((4 * lane < BN && n < N) ? reinterpret_cast<const char*>(w_scale + n) : cursor.zero, lds0 + C::SCALE_OFF);
-  }
+  if (want_y && w_per_row) request_scales<VEC>(w_scale, n0, N, BN, lane, lds0 + C::SCALE_OFF);
 #pragma unroll 1
   for (int p = 0; p < NSTAGE; ++p) {
     auto both = [&](auto whole_) {
@@ -145,7 +143,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     };
     if (cursor.whole()) both(std::true_type{});
     else both(std::false_type{});
-    if (cursor.advance(tile_end)) start_rows();
+    if (cursor.advance(tile_end)) start_rows(false);
   }
   // the epilogue's scalars: behind the requests, into scalar registers (see qgemm_dma)
   const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
@@ -156,7 +154,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
-  if (VEC && want_y && !w_per_row) {
+  if (want_y && !w_per_row) {
     float* sc = reinterpret_cast<float*>(lds + C::SCALE_OFF);
     for (int i = threadIdx.x; i < 256; i += C::NT) sc[i] = sw0;
   }
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
       quarter(I1{}, I0{}, Own{}, std::integral_constant<int, BK * HN>{},
               [&](auto n_) { read_b(n_, I0{}, Other{}, bn, bn ^ 64u); }, std::integral_constant<int, P::NB>{},
               [&](auto r_) { request(whole_, I1{}, std::integral_constant<int, decltype(r_)::value + P::NA>{}, cur); });
-      if (cursor.advance(tile_end)) start_rows();
+      if (cursor.advance(tile_end)) start_rows(false);
       cur = nxt;
     };
     int t = 0;
@@ -260,8 +258,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     wait_vmcnt<0>();
     landed = NSTAGE;
     acc_ready(acc);
-    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane, lds + C::SCALE_OFF, M, N, sa, sw0, w_scale, w_per_row,
-                              want_y, q_inv, q_max, Y, ACC, epi, sse, amax);
+    int lane_here = lane;  // see qgemm_dma
+    asm volatile("" : "+v"(lane_here));
+    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane_here, lds + C::SCALE_OFF, M, N, sa, want_y, q_inv, q_max,
+                              Y, ACC, epi, sse, amax);
     if (++tile >= tile_end) break;  // block-uniform
   }
   finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi);

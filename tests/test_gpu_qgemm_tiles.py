@@ -13,7 +13,7 @@ from paper_2302_01382_amd import mpq
 pytestmark = pytest.mark.gpu
 
 # M x N: 256, 192, 128 and 64 tiles; one and several output tiles per workgroup
-TILES = [(12300, 1024), (256 * 97 - 3, 1020), (12288, 768), (4093, 1024), (1000, 512), (333, 102)]
+TILES = [(16381, 1024), (32700, 1021), (12288, 768), (4093, 1022), (1000, 512), (333, 102)]
 
 
 def _unpack(p):
