@@ -19,14 +19,15 @@ inline unsigned blocks_z(int64_t want, int threads) {
   return (unsigned)((want + x - 1) / x);
 }
 
-// Side of the output tile of qgemm_any: 128 once such tiles fill the chip twice and k is long enough that the loop
-// and not the output counts, else 64.  us, 128 against 64: 4000 x 2000 x 1500 33.0 / 41.0, 16384 x 1000 x 1001
-// 62.6 / 74.3, but 4000 x 1000 x 1500 (256 tiles of 128) 27.0 / 23.6 and 12288 x 1000 x 200 32.9 / 20.7 (M x K x N).
+// Side of the output tile of qgemm_any: 128 (eight waves) once such tiles reach half of the CUs and k is long enough
+// that the loop and not the output counts, else 64.  us, 128 against 64: 2999 x 1155 x 1021 15.8 / 17.7, 16384 x 1001 x 1000
+// 54 / 62, 16384 x 501 x 100 (128 tiles of 128) 8.2 / 8.5, but 1200 x 1201 x 1200 (100) 12.0 / 10.8 and 1000 x 77 x 3000 6.9 /
+// 6.6 (M x K x N).
 // The grid's y counts the row tiles: more than kMaxGridY of 64 rows take 128 whatever the speed (the
 // argument check admits what 128 can cover).
 inline int any_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
   if ((M + 63) / 64 > kMaxGridY) return 128;
-  return K >= 512 && ((N + 127) / 128) * ((M + 127) / 128) >= 2 * num_cu ? 128 : 64;
+  return K >= 256 && ((N + 127) / 128) * ((M + 127) / 128) >= num_cu / 2 ? 128 : 64;
 }
 
 // The tile of the fast kernels of mpq_qgemm: side of the square output tile, LDS stages, k bytes per stage.

@@ -23,19 +23,17 @@ __global__ void fill_u32_k(unsigned* p, unsigned v) { p[0] = v; }
 // Any K, any alignment: tiles staged through registers.
 //
 // Rows of a tensor with K % 16 != 0 start at any byte, so a tile cannot travel by global->LDS loads of
-// 16 aligned bytes.  gfx950 takes 16-byte global loads at any byte address, so a thread fetches its
-// chunks with those (load_chunk16), two k tiles ahead of their use in two register sets, and writes
-// them to a double-buffered LDS tile; one barrier per k tile of 128 bytes.  The last chunk of a row
-// is loaded so that it ENDS at the row's end (never past it: the last row may be the end of the
-// allocation) and is shifted into place when it is written to LDS.  Rows shorter than 16 bytes are
-// read byte by byte.
+// 16 aligned bytes.  A thread fetches its chunks of 16 bytes into registers (AnyStage), up to three k tiles of 128
+// ahead, and writes them to a double-buffered LDS tile; one barrier per k tile.  The loads of k tiles behind the last one
+// are issued as well, at the row's last bytes: nothing outside the row's dwords is ever read.
 //
-// What bounds it: the latency of its loads (a workgroup waits a k tile's round trip, hidden by the
-// two register sets and by the other workgroups of the CU).  Against loading every byte by itself (us):
-// 2999 x 1155 x 1021 int8 169 -> 18.8, 16384 x 1001 x 1000 413 -> 63, 512 x 1001 x 512 102 -> 8.7,
-// 6272 x 2302 x 256 packed int4 279 -> 20 (M x K x N); an aligned 6272 x 2304 x 256 takes 13.5 on the fast path.
+// What bounds it: a k tile's chain of loads, stores, barrier, reads and matrix steps, which the other workgroups of the CU
+// hide in part, and the output (stored value by value it was as long as eight k tiles).  us, before the chunks were loaded
+// as dwords, the output stored in 16 bytes and the 128 tile given eight waves -> now (M x K x N): 2999 x 1155 x 1021
+// 19.9 -> 15.5, 16384 x 1001 x 1000 59.5 -> 55, 512 x 1001 x 512 8.7 -> 6.9, 4000 x 2002 x 1500 42 -> 34, 6272 x 2302 x 256
+// packed 18.7 -> 16.5, 3000 x 1156 x 1000 16.3 -> 12.6; an aligned 2999 x 1152 x 1021 takes 9.7 on the fast path.  Chunks
+// written between the matrix steps instead of in front of the barrier: 15.8 -> 17.0.
 // =====================================================================================================
-constexpr int kAnyThreads = 256;  // 4 waves as 2 x 2
 constexpr int kAnyBK = 128;       // k values per tile
 
 // byte offset of 16-byte chunk `ch` (0..7) of tile row `row` in a [rows][128 B] LDS tile; the XOR makes
@@ -44,10 +42,19 @@ __device__ __forceinline__ int lds_off(int row, int ch) { return row * kAnyBK + 
 
 // One thread's share of an operand tile: CN chunks of 16 bytes, chunk j of tile row row0 + j * STEP.
 // CPR: chunks per tile row (8, or 4 of a packed-int4 tile, whose 16 bytes are 32 values).
-template <int CN, int CPR>
+// A load of 16 bytes per lane runs at 7.5 ns per KiB and CU at any address that is a multiple of 4 and at 17-22 at one
+// that is not (measured out of the L2), so the dwords that hold the row's bytes are loaded and shifted into place on
+// their way to the LDS.  The dword a chunk lacks at its end comes from the next lane, the last chunk's from the next
+// k tile.  Nothing is read but dwords that hold a byte of the row.
+// KIND: rows that start at a multiple of 4 (nothing to shift), at any byte, or of less than 16 bytes, which are read byte
+// by byte and have a single k tile.
+enum RowKind { kRowsDword, kRowsByte, kRowsShort };
+template <int NT, int ROWS, int CPR, RowKind KIND>
 struct AnyStage {
-  static constexpr int STEP = kAnyThreads / CPR;
-  const uint8_t* p[CN];  // start of the row
+  static constexpr bool SHORT = KIND == kRowsShort;
+  static constexpr int STEP = NT / CPR, CN = ROWS / STEP;
+  const uint8_t* p[CN];  // start of the dword that the row starts in (SHORT: of the row)
+  int sh[CN];            // bytes of that dword in front of the row
   int kb;                // byte offset of the thread's chunk within a tile row
   int row_bytes;
 
@@ -59,164 +66,192 @@ struct AnyStage {
       int64_t r = r0 + (int)threadIdx.x / CPR + j * STEP;
       if (r >= nrows) r = nrows - 1;  // rows past the edge re-read the last row; never stored
       p[j] = reinterpret_cast<const uint8_t*>(base) + r * row_bytes_;
+      sh[j] = KIND == kRowsByte ? (int)(reinterpret_cast<uintptr_t>(p[j]) & 3u) : 0;
+      p[j] -= sh[j];
     }
   }
+  // the last place, counted from p, that 16 bytes of the row's dwords start at
+  __device__ __forceinline__ int last(int j) const { return ((sh[j] + row_bytes + 3) & ~3) - 16; }
   // k0: first byte of the tile within the row
   __device__ __forceinline__ void load(v4i (&c)[CN], int k0) const {
 #pragma unroll
-    for (int j = 0; j < CN; ++j) c[j] = load_chunk16(p[j], row_bytes, k0 + kb);
+    for (int j = 0; j < CN; ++j) {
+      if (SHORT) {
+        c[j] = load_chunk16(p[j], row_bytes, k0 + kb);
+      } else {
+        const int k = k0 + kb, l = last(j);
+        c[j] = *reinterpret_cast<const v4i_any*>(p[j] + (k < l ? k : l));
+      }
+    }
   }
-  __device__ __forceinline__ v4i fixed(const v4i& c, int k0) const { return fix_chunk16(c, row_bytes, k0 + kb); }
-  __device__ __forceinline__ bool edge(int k0) const { return k0 + CPR * 16 > row_bytes; }  // workgroup-uniform
+  // the tile, or with rows at any byte the one after it, reaches the row's end (workgroup-uniform)
+  __device__ __forceinline__ bool edge(int k0) const { return k0 + (KIND == kRowsByte ? 2 : 1) * CPR * 16 > row_bytes; }
+  // dwords that a load at the row's end was moved back by, zeros behind the end
+  __device__ __forceinline__ static v4i moved(v4i c, int back) {
+    if (back >= 16) return v4i{0, 0, 0, 0};
+    if (back >= 8) c = v4i{c.z, c.w, 0, 0};
+    if (back == 4 || back == 12) c = v4i{c.y, c.z, c.w, 0};
+    return c;
+  }
+  // chunk j of the tile at k0, as it goes into the LDS; next: the chunks of the tile after it
+  template <bool EDGE>
+  __device__ __forceinline__ v4i place(const v4i (&cur)[CN], const v4i (&next)[CN], int j, int k0) const {
+    const int k = k0 + kb;
+    if constexpr (SHORT) return fix_chunk16(cur[j], row_bytes, k);
+    v4i c = cur[j];
+    const int l = last(j);
+    if (EDGE && k > l) c = moved(c, k - l);
+    if constexpr (KIND == kRowsDword) return c;
+    int follow = next[j].x;
+    if (EDGE && k + CPR * 16 > l) follow = moved(next[j], k + CPR * 16 - l).x;
+    // the dword behind the chunk: the first of the next lane's; of the last lane of a row the first of the next tile
+    const int lane = (int)threadIdx.x % CPR, w = lane == 0 ? follow : c.x;
+    int behind;
+    if constexpr (CPR == 4) {
+      behind = __builtin_amdgcn_update_dpp(0, w, 0x39, 0xF, 0xF, true);  // quad_perm 1 2 3 0
+    } else {
+      const int up = __builtin_amdgcn_update_dpp(0, w, 0x101, 0xF, 0xF, true);    // row_shl 1: from the lane above
+      const int down = __builtin_amdgcn_update_dpp(0, w, 0x117, 0xF, 0xF, true);  // row_shr 7: from seven lanes below
+      behind = lane == CPR - 1 ? down : up;
+    }
+    c = v4i{(int)__builtin_amdgcn_alignbyte((unsigned)c.y, (unsigned)c.x, (unsigned)sh[j]),
+            (int)__builtin_amdgcn_alignbyte((unsigned)c.z, (unsigned)c.y, (unsigned)sh[j]),
+            (int)__builtin_amdgcn_alignbyte((unsigned)c.w, (unsigned)c.z, (unsigned)sh[j]),
+            (int)__builtin_amdgcn_alignbyte((unsigned)behind, (unsigned)c.w, (unsigned)sh[j])};
+    if (EDGE) {  // bytes behind the row's end may be the next row's
+      auto keep = [](int v, int valid) { return valid >= 4 ? v : valid <= 0 ? 0 : v & (int)((1u << (8 * valid)) - 1u); };
+      const int valid = row_bytes - k;
+      c = v4i{keep(c.x, valid), keep(c.y, valid - 4), keep(c.z, valid - 8), keep(c.w, valid - 12)};
+    }
+    return c;
+  }
 };
 
-template <int CN>
-__device__ __forceinline__ void store8(int8_t* lds, const AnyStage<CN, 8>& st, const v4i (&c)[CN], int k0) {
+template <bool EDGE, class S>
+__device__ __forceinline__ void store8(int8_t* lds, const S& st, const v4i (&c)[S::CN], const v4i (&next)[S::CN], int k0) {
   const int row = (int)threadIdx.x >> 3, ch = (int)threadIdx.x & 7;
-  if (st.edge(k0)) {
 #pragma unroll
-    for (int j = 0; j < CN; ++j) *reinterpret_cast<v4i*>(lds + lds_off(row + j * 32, ch)) = st.fixed(c[j], k0);
-  } else {
-#pragma unroll
-    for (int j = 0; j < CN; ++j) *reinterpret_cast<v4i*>(lds + lds_off(row + j * 32, ch)) = c[j];
-  }
+  for (int j = 0; j < S::CN; ++j)
+    *reinterpret_cast<v4i*>(lds + lds_off(row + j * S::STEP, ch)) = st.template place<EDGE>(c, next, j, k0);
 }
 
-template <int CN>
-__device__ __forceinline__ void store4(int8_t* lds, const AnyStage<CN, 4>& st, const v4i (&c)[CN], int k0) {
+template <bool EDGE, class S>
+__device__ __forceinline__ void store4(int8_t* lds, const S& st, const v4i (&c)[S::CN], const v4i (&next)[S::CN], int k0) {
   const int row = (int)threadIdx.x >> 2, quarter = (int)threadIdx.x & 3;
 #pragma unroll
-  for (int j = 0; j < CN; ++j) {
-    const v4i v = st.edge(k0) ? st.fixed(c[j], k0) : c[j];
+  for (int j = 0; j < S::CN; ++j) {
+    const v4i v = st.template place<EDGE>(c, next, j, k0);
     unsigned b[8];
     expand8((unsigned)v.x, b[0], b[1]);
     expand8((unsigned)v.y, b[2], b[3]);
     expand8((unsigned)v.z, b[4], b[5]);
     expand8((unsigned)v.w, b[6], b[7]);
-    const int r = row + j * 64;
+    const int r = row + j * S::STEP;
     *reinterpret_cast<v4i*>(lds + lds_off(r, 2 * quarter)) = v4i{(int)b[0], (int)b[1], (int)b[2], (int)b[3]};
     *reinterpret_cast<v4i*>(lds + lds_off(r, 2 * quarter + 1)) = v4i{(int)b[4], (int)b[5], (int)b[6], (int)b[7]};
   }
 }
 
 // grid: x = N tiles (fast index, so neighbouring workgroups share the A row panel), y = M tiles.
-// TS: side of the output tile (64 or 128); a wave owns (TS / 2) x (TS / 2) of it.
-template <int TS, bool W4>
-__global__ __launch_bounds__(kAnyThreads, TS == 64 ? 4 : 2) void qgemm_any(
+// TS: side of the output tile: 64 with four waves as 2 x 2, 128 with eight as 2 x 4.  EPI: as qgemm_dma.
+template <int TS>
+struct AnyCfg {
+  static constexpr int NT = TS == 64 ? 256 : 512, NW = NT / 64, WN = NW / 2;
+  static constexpr int TM = TS / 2, TN = TS / WN;   // a wave's tile
+  static constexpr int FM = TM / 16, FN = TN / 16;  // in 16 x 16 matrix tiles
+  static constexpr int SUMS_OFF = 0;
+};
+template <int TS, bool W4, RowKind KIND, int EPI>
+__global__ __launch_bounds__(AnyCfg<TS>::NT, TS == 64 ? 3 : 2) void qgemm_any(
     const int8_t* __restrict__ A, const void* __restrict__ Wv, int64_t M, int64_t N, int64_t K,
     const float* __restrict__ a_scale, const float* __restrict__ w_scale, int w_per_row, float* __restrict__ Y,
     int32_t* __restrict__ ACC, EpiArgs epi) {
-  constexpr int F = TS / 64;  // 32 x 32 matrix tiles per wave and side
-  constexpr int CA = TS / 32, CB = W4 ? TS / 64 : TS / 32;
-  const float* __restrict__ YREF = epi.yref;
-  double* __restrict__ PART = epi.part;
+  using C = AnyCfg<TS>;
+  using SA = AnyStage<C::NT, TS, 8, KIND>;
+  using SB = AnyStage<C::NT, TS, W4 ? 4 : 8, KIND>;
+  constexpr bool SHORT = KIND == kRowsShort;
   __shared__ __attribute__((aligned(16))) int8_t lds_a[2][TS * kAnyBK];
   __shared__ __attribute__((aligned(16))) int8_t lds_b[2][TS * kAnyBK];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  __shared__ __attribute__((aligned(16))) float scales[TS];
+  __shared__ float sums[C::NW];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wm = wave / C::WN, wn = wave % C::WN;
   const int64_t m0 = (int64_t)blockIdx.y * TS, n0 = (int64_t)blockIdx.x * TS;
 
-  v16i acc[F][F];
-#pragma unroll
-  for (int i = 0; i < F; ++i)
-#pragma unroll
-    for (int j = 0; j < F; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-
-  AnyStage<CA, 8> sa_;
-  AnyStage<CB, W4 ? 4 : 8> sb_;
+  SA sa_;
+  SB sb_;
   sa_.init(A, M, K, m0);
   sb_.init(Wv, N, W4 ? K >> 1 : K, n0);
   constexpr int BKB = W4 ? kAnyBK / 2 : kAnyBK;  // bytes of k per W tile row in memory
-  v4i ra[2][CA], rb[2][CB];
-  const int KT = (int)((K + kAnyBK - 1) / kAnyBK);
-  sa_.load(ra[0], 0);
-  sb_.load(rb[0], 0);
-  if (KT > 1) {
-    sa_.load(ra[1], kAnyBK);
-    sb_.load(rb[1], BKB);
+  constexpr int NS = SHORT ? 1 : 3;
+  v4i ra[NS][SA::CN], rb[NS][SB::CN];  // k tiles t, t + 1 and t + 2; tile KT, behind the last one, ends it
+  const int KT = SHORT ? 1 : (int)((K + kAnyBK - 1) / kAnyBK);
+#pragma unroll
+  for (int u = 0; u < NS; ++u) {
+    sa_.load(ra[u], u * kAnyBK);
+    sb_.load(rb[u], u * BKB);
   }
-  for (int kt = 0; kt < KT; kt += 2) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = kt + u;
-      if (t >= KT) break;  // workgroup-uniform
-      // buffer u was last read in step t - 2; every wave has passed the barrier of step t - 1 since
-      store8<CA>(lds_a[u], sa_, ra[u], t * kAnyBK);
-      if constexpr (W4) store4<CB>(lds_b[u], sb_, rb[u], t * BKB);
-      else store8<CB>(lds_b[u], sb_, rb[u], t * BKB);
-      if (t + 2 < KT) {
-        sa_.load(ra[u], (t + 2) * kAnyBK);
-        sb_.load(rb[u], (t + 2) * BKB);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int s = 0; s < kAnyBK / 32; ++s) {
-        const int ch = 2 * s + (lane >> 5);
-        v4i fa[F], fb[F];
-#pragma unroll
-        for (int i = 0; i < F; ++i)
-          fa[i] = *reinterpret_cast<const v4i*>(lds_a[u] + lds_off(wm * (TS / 2) + i * 32 + (lane & 31), ch));
-#pragma unroll
-        for (int j = 0; j < F; ++j)
-          fb[j] = *reinterpret_cast<const v4i*>(lds_b[u] + lds_off(wn * (TS / 2) + j * 32 + (lane & 31), ch));
-#pragma unroll
-        for (int i = 0; i < F; ++i)
-#pragma unroll
-          for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-      }
-    }
+  const bool want_y = EPI != 0 || Y != nullptr;
+  const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
+  if (want_y && (int)threadIdx.x < TS) {
+    const int64_t n = n0 + (int)threadIdx.x;
+    scales[threadIdx.x] = w_scale[w_per_row && n < N ? n : 0];
   }
-
-  // epilogue: lane holds column l%32 and rows 8*(v/4) + 4*(l/32) + v%4 of each 32x32 tile
-  const bool want_y = Y || YREF || epi.amax || epi.codes;
-  const float sa = want_y ? a_scale[0] : 0.0f;
-  float sse = 0.0f;  // this lane's share of sum (Y - YREF)^2
-  float amax = 0.0f;
-  float q_scale = 0.0f, q_inv = 0.0f, q_max = 0.0f;
-  if (epi.codes) {
+  float q_inv = 0.0f, q_max = 0.0f;
+  if (EPI == 3) {
+    float q_scale;
     bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
+  v4i acc[C::FM][C::FN];
+  zero_acc(acc);
+  for (int kt = 0; kt < KT; kt += NS) {
 #pragma unroll
-  for (int j = 0; j < F; ++j) {
-    const int64_t n = n0 + wn * (TS / 2) + j * 32 + (lane & 31);
-    if (n >= N) continue;
-    const float sw = want_y ? w_scale[w_per_row ? n : 0] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < F; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t m = m0 + wm * (TS / 2) + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        if (m >= M) continue;
-        int a = acc[i][j][v];
-        if (W4) a >>= 4;  // exact: every product carried the factor 16
-        if (ACC) ACC[m * N + n] = a;
-        const float y = apply_act(((float)a * sa) * sw, epi.act);
-        amax = fmaxf(amax, fabsf(y));
-        if (Y) Y[m * N + n] = y;
-        if (epi.codes) epi.codes[m * N + n] = (int8_t)(int)code_f(y, q_inv, q_max);
-        if (YREF) {
-          const float d = y - YREF[m * N + n];
-          sse = __builtin_fmaf(d, d, sse);
-        }
+    for (int u = 0; u < NS; ++u) {
+      const int t = kt + u, next = (u + 1) % NS;
+      if (t >= KT) break;  // workgroup-uniform
+      // this buffer was last read in step t - 2; every wave has passed the barrier of step t - 1 since
+      int8_t* la = lds_a[t & 1];
+      int8_t* lb = lds_b[t & 1];
+      auto store = [&](auto edge) {
+        constexpr bool EDGE = decltype(edge)::value;
+        store8<EDGE>(la, sa_, ra[u], ra[next], t * kAnyBK);
+        if constexpr (W4) store4<EDGE>(lb, sb_, rb[u], rb[next], t * BKB);
+        else store8<EDGE>(lb, sb_, rb[u], rb[next], t * BKB);
+      };
+      if (!SHORT && sa_.edge(t * kAnyBK)) store(std::true_type{});  // (both operands end in the same k tile)
+      else store(std::false_type{});
+      if (!SHORT) {  // past the row's end, where loads stay at its last bytes, as well: under a condition the compiler would
+        // take it as not issued and wait for the tile before it
+        sa_.load(ra[u], (t + NS) * kAnyBK);
+        sb_.load(rb[u], (t + NS) * BKB);
       }
+      __syncthreads();
+      v4i fa[2][C::FM], fb[2][C::FN];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {  // 64 k each
+        const int ch = 4 * s + (lane >> 4);
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+          fb[s][j] = *reinterpret_cast<const v4i*>(lb + lds_off(wn * C::TN + j * 16 + (lane & 15), ch));
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+          fa[s][i] = *reinterpret_cast<const v4i*>(la + lds_off(wm * C::TM + i * 16 + (lane & 15), ch));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+          for (int i = 0; i < C::FM; ++i) mma(acc[i][j], fb[s][j], fa[s][i]);
     }
   }
-  if (PART) {  // one partial per workgroup, combined in a fixed order
-    const float w = wave_sum(sse);
-    __syncthreads();  // the tiles in LDS are not needed any more
-    float* sm = reinterpret_cast<float*>(lds_a[0]);
-    if (lane == 0) sm[wave] = w;
-    __syncthreads();
-    if (threadIdx.x == 0)
-      PART[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = ((double)sm[0] + (double)sm[1]) + ((double)sm[2] + (double)sm[3]);
-  }
-  if (epi.amax) {
-    const float w = wave_max(amax);
-    if (lane == 0) atomicMax(epi.amax, abs_key(w));
-  }
+  acc_ready(acc);
+  float sse = 0.0f, amax = 0.0f;
+  epilogue<C, W4, false, EPI>(acc, m0, n0, wm, wn, lane, reinterpret_cast<const char*>(scales), M, N, sa, want_y, q_inv, q_max, Y,
+                              ACC, epi, sse, amax);
+  finish_sums<C, EPI>(reinterpret_cast<char*>(sums), lane, wave, sse, amax, epi, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // sum of `count` per-workgroup partials, one workgroup, fixed order
@@ -383,15 +418,31 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
   const int ts = any_tile(M, N, K, kNumCU);
   const int64_t gx = (N + ts - 1) / ts, gy = (M + ts - 1) / ts;
   const dim3 grid((unsigned)gx, (unsigned)gy);
-#define MPQ_ANY(TS_, W4_) \
-  qgemm_any<TS_, W4_><<<grid, kAnyThreads, 0, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, acc_out, epi)
+  const int64_t w_row = w4 ? K >> 1 : K;
+  const bool dword = ((K | w_row | (int64_t)reinterpret_cast<uintptr_t>(a_q) | (int64_t)reinterpret_cast<uintptr_t>(w_q)) & 3) == 0;
+  const RowKind kind = w_row < 16 ? kRowsShort : dword ? kRowsDword : kRowsByte;
+  const int mode = epi.yref ? 1 : epi.codes ? 3 : (epi.act || epi.amax) ? 2 : 0;
+#define MPQ_ANY(TS_, W4_, KIND_, EPI_)                                                                                    \
+  qgemm_any<TS_, W4_, KIND_, EPI_><<<grid, AnyCfg<TS_>::NT, 0, st>>>(a_q, w_q, M, N, K, a_scale, w_scale, per_row, y_out, \
+                                                                     acc_out, epi)
+#define MPQ_ANY_EPI(TS_, W4_, KIND_)               \
+  (mode == 1   ? (void)MPQ_ANY(TS_, W4_, KIND_, 1) \
+   : mode == 2 ? (void)MPQ_ANY(TS_, W4_, KIND_, 2) \
+   : mode == 3 ? (void)MPQ_ANY(TS_, W4_, KIND_, 3) \
+               : (void)MPQ_ANY(TS_, W4_, KIND_, 0))
+#define MPQ_ANY_KIND(TS_, W4_)                                      \
+  (kind == kRowsShort   ? MPQ_ANY_EPI(TS_, W4_, kRowsShort)         \
+   : kind == kRowsDword ? MPQ_ANY_EPI(TS_, W4_, kRowsDword)         \
+                        : MPQ_ANY_EPI(TS_, W4_, kRowsByte))
   if (ts == 128) {
-    if (w4) MPQ_ANY(128, true);
-    else MPQ_ANY(128, false);
+    if (w4) MPQ_ANY_KIND(128, true);
+    else MPQ_ANY_KIND(128, false);
   } else {
-    if (w4) MPQ_ANY(64, true);
-    else MPQ_ANY(64, false);
+    if (w4) MPQ_ANY_KIND(64, true);
+    else MPQ_ANY_KIND(64, false);
   }
+#undef MPQ_ANY_KIND
+#undef MPQ_ANY_EPI
 #undef MPQ_ANY
   if (n_partials) *n_partials = gx * gy;
   return launch_status();

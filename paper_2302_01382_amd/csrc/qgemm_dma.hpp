@@ -520,9 +520,10 @@ __device__ __forceinline__ void epilogue(const v4i (&acc)[C::FM][C::FN], int64_t
 #undef MPQ_EPI
 }
 
-// The workgroup's share of the score or of the running maximum, once its last output tile is done.
+// The workgroup's share of the score or of the running maximum, once its last output tile is done.  index: its number.
 template <class C, int EPI>
-__device__ __forceinline__ void finish_sums(char* lds, int lane, int wave, float sse, float amax, const EpiArgs& epi) {
+__device__ __forceinline__ void finish_sums(char* lds, int lane, int wave, float sse, float amax, const EpiArgs& epi,
+                                            int64_t index) {
   float* sm = reinterpret_cast<float*>(lds + C::SUMS_OFF);
   if (EPI == 1 && epi.part) {  // one partial per workgroup, combined in a fixed order
     const float w = wave_sum(sse);
@@ -532,7 +533,7 @@ __device__ __forceinline__ void finish_sums(char* lds, int lane, int wave, float
     if (threadIdx.x == 0) {
       double t = 0.0;
       for (int i = 0; i < C::NW; ++i) t += (double)sm[i];
-      epi.part[blockIdx.x] = t;
+      epi.part[index] = t;
     }
   }
   if (EPI == 2 && epi.amax) {  // one atomic per workgroup
@@ -543,7 +544,7 @@ __device__ __forceinline__ void finish_sums(char* lds, int lane, int wave, float
     if (threadIdx.x == 0) {
       float t = 0.0f;
       for (int i = 0; i < C::NW; ++i) t = fmaxf(t, sm[i]);
-      if (epi.amax_part) epi.amax_part[blockIdx.x] = t;
+      if (epi.amax_part) epi.amax_part[index] = t;
       else atomicMax(epi.amax, abs_key(t));
     }
   }
@@ -717,7 +718,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
                               Y, ACC, epi, sse, amax);
     if (++tile >= tile_end) break;  // block-uniform
   }
-  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi);
+  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi, blockIdx.x);
 }
 
 // Dynamic LDS above 64 KiB has to be allowed once per kernel and device (hipFuncSetAttribute, not a

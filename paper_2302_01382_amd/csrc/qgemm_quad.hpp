@@ -264,7 +264,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
                               Y, ACC, epi, sse, amax);
     if (++tile >= tile_end) break;  // block-uniform
   }
-  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi);
+  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi, blockIdx.x);
 }
 
 // prepare_only: configure every kernel variant of this instantiation and launch nothing (mpq_init).

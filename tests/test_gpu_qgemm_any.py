@@ -46,6 +46,31 @@ def test_the_128_tile(K, wbits):
     np.testing.assert_array_equal(host(acc).astype(np.int64).sum(0), a.astype(np.int64).sum(0) @ w.astype(np.int64).T)
 
 
+# rows that start at a multiple of 4 and at every other byte, ending in every byte of a dword, in the last lane's
+# chunk and in the first of a k tile; both tiles, every epilogue against the plain float64 product
+@pytest.mark.parametrize("mn", [(700, 131), (1500, 1500)])
+@pytest.mark.parametrize("K", [256, 257, 258, 259, 260, 371, 383, 385, 512, 515])
+@pytest.mark.parametrize("wbits,by", [(8, 0), (8, 2), (8, 3), (4, 0), (4, 1)])
+def test_rows_at_any_byte(mn, K, wbits, by):
+    import torch
+    (M, N), K = mn, K + (K & 1 if wbits == 4 else 0)
+    a, w = rand_codes((M, K), 127, 76), rand_codes((N, K), 127 if wbits == 8 else 7, 77)
+    qa, qw = misaligned(a, by), misaligned(w if wbits == 8 else oracle.pack4(w), by)
+    acc = dev(a).double() @ dev(w).double().t().contiguous()
+    sa, sw = torch.full((1,), 0.01, device="cuda"), torch.rand(N, device="cuda") + 0.5
+    y = (acc.float() * sa) * sw
+    got, acc_k = mpq.qgemm(qa, qw, sa, sw, wbits, mpq.PER_ROW, want_acc=True)
+    assert torch.equal(acc_k.double(), acc) and torch.equal(got, y)
+    relu, top = mpq.qgemm_act(qa, qw, sa, sw, mpq.ACT_RELU, wbits, mpq.PER_ROW)
+    assert torch.equal(relu, y.clamp(min=0)) and float(top) == float(y.max().clamp(min=0))
+    codes = mpq.qgemm_act_codes(qa, qw, sa, sw, mpq.ACT_RELU, top, 8, wbits, mpq.PER_ROW)
+    assert torch.equal(codes, mpq.fake_quant(relu, top, 8, want_y=False, want_codes=True)[1])
+    ref = y + torch.rand_like(y)
+    sse, _ = mpq.qgemm_score(qa, qw, sa, sw, ref, wbits, mpq.PER_ROW)
+    want = float((y.double() - ref.double()).square().sum())
+    assert abs(float(sse) - want) <= 4e-6 * want  # a lane's 32 squares one after the other, its wave in 6 steps: 38 * 2^-24, twice
+
+
 # one 16 x 16 tile per CU at most, 4 waves (K < 2048) and 8; two per CU; K around the step of 128, fewer
 # steps than waves, more steps than one round of loads; ragged M and N; any alignment
 @pytest.mark.parametrize("mnk", [(1, 1, 128), (7, 250, 96), (16, 16, 129), (49, 512, 640), (64, 256, 256), (33, 31, 2047),
