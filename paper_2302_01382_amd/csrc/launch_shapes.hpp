@@ -32,49 +32,27 @@ inline int any_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
 
 // The tile of the fast kernels of mpq_qgemm: side of the square output tile, LDS stages, k bytes per stage.
 //
-// A tile costs its CU a fixed part (first loads, epilogue) and one per k tile of 128; a grid costs between its
-// exact number of rounds and the whole rounds it starts (workgroups share CUs, and a chip that is not full
-// clocks higher).  The three numbers per side, us, were fitted to 148 layers (64 <= M <= 100352, 64 <= N <= 4096,
-// 64 <= K <= 4608, int8 and packed int4 weights, each timed with every tile): the side of least cost is on average
-// 2.0 % slower than the best, where the thresholds this replaced (256 from 192 tiles on, 192 where it is exactly one
-// round, 128 from 128 tiles on) were at 4.3 %.  us, before -> now: 4096 x 512 x 512 7.1 -> 6.0, 2048 x 1024 x 1024
-// 8.8 -> 7.2, 12288 x 3072 x 768 59 -> 51, 3000 x 3000 x 512 16.3 -> 13.8 (M x N x K).
-// Stages: two where the grid shares CUs or k is short, three where a workgroup has its CU to itself and k is
-// long (1568 x 512 x 4608: 13.2 | 11.7), and then, with the 64 tile, k tiles of 256 (11.4); packed weights, whose k tiles are
-// a quarter shorter, take two of those (16384 x 128 x 4096: 19.5 in three of 128 | 18.0).  With a short k in many
-// rounds the stores of two workgroups of a CU are in each other's way once the weights are packed: three stages
-// (16384 x 4096 x 128: 62 | 51; int8 55 | 60).
+// 256 when such tiles reach three CUs in four; else 192 when it covers the problem in exactly one round with next to no
+// padding (the BERT-base widths: 768 = 4 x 192 gives 12288 x 768 exactly 256 tiles); else 128 when those reach three CUs
+// in four, else 64 (with half of the CUs for the 128 tile, us, 128 | 64: 4096 x 512 x 512 7.1 | 5.9, 2048 x 1024 x 1024 8.6 |
+// 7.2, M x N x K).  Lines drawn where operands lie in the caches move when they come from memory, as the operands of a
+// run's layers do: 12288 x 3072 x 768 in 192 tiles 51 us against 59 in 256 with warm operands, 68 against 65 with cold
+// ones, 100352 x 256 x 256 in 128 tiles 23 against 26 and 42 against 32; these lines hold for cold operands.
+// Stages: three, the deeper prefetch, where k is long (cold, 3 | 2: 6272 x 256 x 2304 14.0 | 16.4, 12288 x 768 x 3072 39.6 |
+// 43.9), two where it is short or workgroups share the CU.  With a long k and a CU each the 64 tile takes k tiles
+// of 256 (1568 x 512 x 4608 11.4 | 11.7 us).
 struct FastTile {
   int side, stages, kb;
 };
-inline FastTile fast_tile(int64_t M, int64_t N, int64_t K, bool w4, int num_cu) {
-  struct Cost {
-    int side;
-    double tile, k_tile, whole;  // us per tile, us per k tile of 128, share of the rounds that counts as whole
-  };
-  const Cost costs[4] = {{256, 13.4, 1.34, 0.6}, {192, 7.4, 1.08, 0.9}, {128, 2.9, 0.58, 0.6}, {64, 1.1, 0.20, 0.8}};
-  const int64_t kt = (K + 127) / 128;
-  int side = 64;
-  int64_t count = 0;
-  double least = 0.0;
-  for (const Cost& c : costs) {
-    const int64_t n = ((M + c.side - 1) / c.side) * ((N + c.side - 1) / c.side);
-    const double exact = n > num_cu ? (double)n / num_cu : 1.0, whole = (double)((n + num_cu - 1) / num_cu);
-    const double cost = ((1.0 - c.whole) * exact + c.whole * whole) * (c.tile + c.k_tile * (double)kt);
-    if (count == 0 || cost < least) {
-      least = cost;
-      side = c.side;
-      count = n;
-    }
-  }
-  if (side == 256 || side == 192) return {side, 2, 128};
-  if (side == 128) {
-    const bool alone = K > 2048 || (count <= num_cu && K > 512) || (w4 && count >= 6 * num_cu && K <= 512);
-    return {128, alone ? 3 : 2, 128};
-  }
-  if (K <= 2304) return {64, 2, 128};
-  if (w4) return {64, 2, 256};
-  return {64, 3, count <= num_cu ? 256 : 128};
+inline FastTile fast_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
+  auto tiles = [&](int64_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
+  const int64_t most = num_cu * 3 / 4, t192 = tiles(192), t128 = tiles(128);
+  if (N > 128 && tiles(256) >= most) return {256, 2, 128};
+  if (N % 192 == 0 && t192 <= num_cu && t192 >= most && t192 * 192 * 192 <= M * N + M * N / 32)
+    return {192, K >= 1024 ? 3 : 2, 128};
+  if (N > 64 && t128 >= most) return {128, K >= 2048 || (t128 <= num_cu && K > 512) ? 3 : 2, 128};
+  if (K < 1024) return {64, 2, 128};
+  return {64, 3, K >= 2048 && tiles(64) <= num_cu ? 256 : 128};
 }
 
 }  // namespace mpq

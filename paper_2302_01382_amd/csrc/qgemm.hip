@@ -398,7 +398,7 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
       d.acc_out = planes;
       d.split = sp.split;
       d.k_per_split = sp.k_per_split;
-      const int rc = launch_dma_64(w4, w4 ? 2 : 3, 128, d);
+      const int rc = launch_dma_64(w4, 3, 128, d);
       if (rc != MPQ_OK) return rc;
       const int64_t MN = M * N;
       const bool vec = (N & 3) == 0 && (!y_out || aligned16(y_out)) && (!acc_out || aligned16(acc_out)) &&
@@ -409,9 +409,9 @@ static int run_qgemm(const int8_t* a_q, const void* w_q, int w_storage_bits, int
       else splitk_reduce<false><<<blocks, kBlock, 0, st>>>(planes, sp.split, MN, N, a_scale, w_scale, per_row, y_out, acc_out);
       return launch_status();
     }
-    const FastTile t = fast_tile(M, N, K, w4, kNumCU);
+    const FastTile t = fast_tile(M, N, K, kNumCU);
     if (t.side == 256) return launch_dma_256(w4, d);
-    if (t.side == 192) return launch_dma_192(w4, d);
+    if (t.side == 192) return launch_dma_192(w4, t.stages, d);
     if (t.side == 128) return launch_dma_128(w4, t.stages, d);
     return launch_dma_64(w4, t.stages, t.kb, d);
   }
@@ -459,8 +459,8 @@ extern "C" int mpq_init(void) {
   const DmaArgs d{nullptr, nullptr, 0, 0, 0, nullptr, nullptr, 0, nullptr, nullptr, nullptr, kNoEpi, nullptr, 1, 0, true};
   for (int w4 = 0; w4 < 2; ++w4) {
     int rc = launch_dma_256(w4 != 0, d);
-    if (rc == MPQ_OK) rc = launch_dma_192(w4 != 0, d);
     for (int stages = 2; stages <= 3; ++stages) {
+      if (rc == MPQ_OK) rc = launch_dma_192(w4 != 0, stages, d);
       if (rc == MPQ_OK) rc = launch_dma_128(w4 != 0, stages, d);
       for (int kb = 128; kb <= 256; kb += 128)
         if (rc == MPQ_OK) rc = launch_dma_64(w4 != 0, stages, kb, d);

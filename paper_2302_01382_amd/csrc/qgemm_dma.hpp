@@ -824,7 +824,7 @@ struct DmaArgs {
   bool prepare_only;  // configure the kernels of this tile size, launch nothing
 };
 int launch_dma_256(bool w4, const DmaArgs& a);
-int launch_dma_192(bool w4, const DmaArgs& a);
+int launch_dma_192(bool w4, int stages, const DmaArgs& a);
 int launch_dma_128(bool w4, int stages, const DmaArgs& a);
 int launch_dma_64(bool w4, int stages, int kb, const DmaArgs& a);
 

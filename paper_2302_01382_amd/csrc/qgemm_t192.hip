@@ -4,9 +4,11 @@
 
 namespace mpq {
 
-#define MPQ_GO(W4) launch_dma<192, 192, 2, 3, 2, W4>(a.a_q, a.w_q, a.M, a.N, a.K, a.a_scale, a.w_scale, a.per_row, a.y_out, a.acc_out, a.st, a.epi, a.n_partials, a.split, a.k_per_split, a.prepare_only)
-// (three stages, one workgroup per CU either way: 12288 x 768 x 768 16.3 us against 15.8, K = 3072 33.0 against 32.9)
-int launch_dma_192(bool w4, const DmaArgs& a) { return w4 ? MPQ_GO(true) : MPQ_GO(false); }
+#define MPQ_GO(NS, W4) launch_dma<192, 192, 2, 3, NS, W4>(a.a_q, a.w_q, a.M, a.N, a.K, a.a_scale, a.w_scale, a.per_row, a.y_out, a.acc_out, a.st, a.epi, a.n_partials, a.split, a.k_per_split, a.prepare_only)
+int launch_dma_192(bool w4, int stages, const DmaArgs& a) {
+  if (stages == 3) return w4 ? MPQ_GO(3, true) : MPQ_GO(3, false);
+  return w4 ? MPQ_GO(2, true) : MPQ_GO(2, false);
+}
 #undef MPQ_GO
 
 }  // namespace mpq

@@ -8,9 +8,9 @@ namespace mpq {
 // What fast_tile and the split along k ask for.  k tiles of 256 bytes: with four matrix steps per wave and k substep
 // this tile is bound by the latency of its barrier and of the loads behind it, paid once per k tile.
 int launch_dma_64(bool w4, int stages, int kb, const DmaArgs& a) {
-  if (w4) return kb == 256 ? MPQ_GO(2, true, 256) : MPQ_GO(2, true, 128);
-  if (kb == 256) return MPQ_GO(3, false, 256);
-  return stages == 3 ? MPQ_GO(3, false, 128) : MPQ_GO(2, false, 128);
+  if (kb == 256) return w4 ? MPQ_GO(3, true, 256) : MPQ_GO(3, false, 256);
+  if (stages == 3) return w4 ? MPQ_GO(3, true, 128) : MPQ_GO(3, false, 128);
+  return w4 ? MPQ_GO(2, true, 128) : MPQ_GO(2, false, 128);
 }
 #undef MPQ_GO
 
