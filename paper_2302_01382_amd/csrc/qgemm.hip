@@ -251,7 +251,7 @@ __global__ __launch_bounds__(AnyCfg<TS>::NT, TS == 64 ? 3 : 2) void qgemm_any(
   float sse = 0.0f, amax = 0.0f;
   epilogue<C, W4, false, EPI>(acc, m0, n0, wm, wn, lane, reinterpret_cast<const char*>(scales), M, N, sa, want_y, q_inv, q_max, Y,
                               ACC, epi, sse, amax);
-  finish_sums<C, EPI>(reinterpret_cast<char*>(sums), lane, wave, sse, amax, epi, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+  finish_sums<C, EPI>(reinterpret_cast<char*>(sums), wave, sse, amax, epi, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // sum of `count` per-workgroup partials, one workgroup, fixed order

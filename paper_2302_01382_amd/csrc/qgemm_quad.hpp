@@ -118,7 +118,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     const int64_t m = (int64_t)cursor.tile * BM;
     cursor.a = reinterpret_cast<const char*>(A) + m * K;
     cursor.b = b_first;
-    if (first || m + BM > M) plan.rows_a(wave, lane, Ku, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
+    if (first || m + BM > M) plan.rows_a(wave, first ? lane : lane_again(), Ku, (unsigned)(M - 1 - m < BM ? M - 1 - m : BM));
   };
   start_rows(true);
   // request r (A loads first) of half h of the cursor's k tile into the stage at LDS offset `stage`
@@ -258,13 +258,11 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     wait_vmcnt<0>();
     landed = NSTAGE;
     acc_ready(acc);
-    int lane_here = lane;  // see qgemm_dma
-    asm volatile("" : "+v"(lane_here));
-    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane_here, lds + C::SCALE_OFF, M, N, sa, want_y, q_inv, q_max,
+    epilogue<C, W4, VEC, EPI>(acc, (int64_t)tile * BM, n0, wm, wn, lane_again(), lds + C::SCALE_OFF, M, N, sa, want_y, q_inv, q_max,
                               Y, ACC, epi, sse, amax);
     if (++tile >= tile_end) break;  // block-uniform
   }
-  finish_sums<C, EPI>(lds, lane, wave, sse, amax, epi, blockIdx.x);
+  finish_sums<C, EPI>(lds, wave, sse, amax, epi, blockIdx.x);
 }
 
 // prepare_only: configure every kernel variant of this instantiation and launch nothing (mpq_init).
