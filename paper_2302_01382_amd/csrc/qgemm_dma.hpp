@@ -174,6 +174,14 @@ __device__ __forceinline__ void dma16_base(const char* base, unsigned off, unsig
 __device__ __forceinline__ void dma4(const float* src, unsigned lds_byte_off) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_byte_off) : "memory");
 }
+// One value that is the same for the whole launch and that no kernel in flight writes, by a scalar load wherever it stands.
+// Behind an LDS request, which may write anything as far as the compiler knows, an ordinary load becomes a vector
+// load, and to wait for that one is to wait for every request in flight: the whole prefetch, where the first barrier needs
+// its first k tile (operands in memory, M x K x N, us, ordinary | scalar: 4096 x 1024 x 1024 12.8 | 12.3, 1000 x 2048 x 1000
+// 9.8 | 9.3).
+__device__ __forceinline__ float load_scalar(const float* p) {
+  return *(const __attribute__((address_space(4))) float*)(uintptr_t)p;
+}
 // The per-channel W scales of a workgroup's columns travel through LDS: the epilogue then needs no global loads between
 // its stores.  Every wave fetches them, so that its own wait covers them.  Columns past the edge: any scale.
 template <bool VEC>
@@ -634,16 +642,15 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void qgemm_dma(const int8_t* __
     else static_for<0, C::LPW>([&](auto r_) { plan.template request<decltype(r_)::value, false>(cursor, lds0 + p * C::STAGE); });
     if (cursor.advance(tile_end)) start_rows(false);
   }
-  // The scalars of the epilogue are loaded here, behind the requests, once, into scalar registers.  Loaded in the
-  // epilogue they may come as vector loads whose arrival the compiler waits for at every store (vmcnt(0), as it
-  // cannot tell on which path they were used first), and stores count in vmcnt as well: each 16-byte store of a
-  // wave then waits for the one before it to be acknowledged.
-  const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
-  const float sw0 = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y && !w_per_row ? w_scale[0] : 0.0f)));
+  // The scalars of the epilogue are loaded here, behind the requests, once, into scalar registers.  (Loaded in the
+  // epilogue they may come as vector loads whose arrival the compiler waits for at every store, vmcnt(0), as it
+  // cannot tell on which path they were used first, and stores count in vmcnt as well: each 16-byte store of a
+  // wave then waits for the one before it to be acknowledged.)
+  const float sa = want_y ? load_scalar(a_scale) : 0.0f, sw0 = want_y && !w_per_row ? load_scalar(w_scale) : 0.0f;
   float q_inv = 0.0f, q_max = 0.0f;
   if (QOUT) {
     float q_scale;
-    bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
+    bit_constants(load_scalar(epi.q_absmax), epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
   if (want_y && !w_per_row) {

@@ -146,12 +146,11 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void qgemm_quad(const int8_t* __re
     if (cursor.advance(tile_end)) start_rows(false);
   }
   // the epilogue's scalars: behind the requests, into scalar registers (see qgemm_dma)
-  const float sa = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y ? a_scale[0] : 0.0f)));
-  const float sw0 = f_from_bits(__builtin_amdgcn_readfirstlane(bits_from_f(want_y && !w_per_row ? w_scale[0] : 0.0f)));
+  const float sa = want_y ? load_scalar(a_scale) : 0.0f, sw0 = want_y && !w_per_row ? load_scalar(w_scale) : 0.0f;
   float q_inv = 0.0f, q_max = 0.0f;
   if (QOUT) {
     float q_scale;
-    bit_constants(epi.q_absmax[0], epi.q_bits, q_scale, q_inv);
+    bit_constants(load_scalar(epi.q_absmax), epi.q_bits, q_scale, q_inv);
     q_max = (float)((1 << (epi.q_bits - 1)) - 1);
   }
   if (want_y && !w_per_row) {

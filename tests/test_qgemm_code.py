@@ -58,3 +58,23 @@ def test_no_register_of_a_fast_kernel_is_spilled(code_objects):
             if count or scratch:
                 spilled.append((name, count, scratch))
     assert kernels >= 4 * 16 and not spilled, spilled
+
+
+def test_the_first_barrier_waits_for_the_first_k_tile_only(code_objects):
+    """The kernels request NSTAGE k tiles and wait for the first with a counted vmcnt: a vmcnt(0) between the requests and
+    the first barrier, as the compiler puts behind an ordinary load, waits for all of them."""
+    kernels, full = 0, []
+    for path in code_objects:
+        text = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn", "--no-leading-addr", path],
+                              stdout=subprocess.PIPE, text=True, check=True).stdout
+        for part in re.split(r"^(?=\S*<\S+>:$)", text, flags=re.M):
+            name = re.match(r"\S*<(\S+)>:$", part, re.M)
+            if not name or not re.search("qgemm_(dma|quad)", name.group(1)):
+                continue
+            kernels += 1
+            start = part[part.index("global_load_lds_"):]
+            waits = re.findall(r"vmcnt\((\d+)\)", start[:start.index("s_barrier")])
+            assert waits, name.group(1)  # the counted one
+            if "0" in waits:
+                full.append(name.group(1))
+    assert kernels >= 4 * 16 and not full, full
