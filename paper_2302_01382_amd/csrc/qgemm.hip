@@ -30,9 +30,12 @@ __global__ void fill_u32_k(unsigned* p, unsigned v) { p[0] = v; }
 // What bounds it: a k tile's chain of loads, stores, barrier, reads and matrix steps, which the other workgroups of the CU
 // hide in part, and the output (stored value by value it was as long as eight k tiles).  us, before the chunks were loaded
 // as dwords, the output stored in 16 bytes and the 128 tile given eight waves -> now (M x K x N): 2999 x 1155 x 1021
-// 19.9 -> 15.5, 16384 x 1001 x 1000 59.5 -> 55, 512 x 1001 x 512 8.7 -> 6.9, 4000 x 2002 x 1500 42 -> 34, 6272 x 2302 x 256
+// 19.9 -> 14.7, 16384 x 1001 x 1000 59.5 -> 55, 512 x 1001 x 512 8.7 -> 6.9, 4000 x 2002 x 1500 42 -> 34, 6272 x 2302 x 256
 // packed 18.7 -> 16.5, 3000 x 1156 x 1000 16.3 -> 12.6; an aligned 2999 x 1152 x 1021 takes 9.7 on the fast path.  Chunks
 // written between the matrix steps instead of in front of the barrier: 15.8 -> 17.0.
+// The 64 tile keeps within 128 registers, four workgroups per CU: with 136 (int8 weights, rows at any byte: an address and a
+// shift per chunk) there were three, and 2000 x 250 x 2000, 1024 tiles, took two rounds: 10.9 us against 9.2, 4096 x 33 x 1000
+// 8.9 against 7.3, 1900 x 130 x 2048 10.7 against 8.9.
 // =====================================================================================================
 constexpr int kAnyBK = 128;       // k values per tile
 
@@ -53,35 +56,36 @@ template <int NT, int ROWS, int CPR, RowKind KIND>
 struct AnyStage {
   static constexpr bool SHORT = KIND == kRowsShort;
   static constexpr int STEP = NT / CPR, CN = ROWS / STEP;
-  const uint8_t* p[CN];  // start of the dword that the row starts in (SHORT: of the row)
-  int sh[CN];            // bytes of that dword in front of the row
-  int kb;                // byte offset of the thread's chunk within a tile row
+  static_assert(STEP % 4 == 0, "the rows of a thread start at the same byte of their dwords");
+  const uint8_t* base;  // the dword that the tile's first row starts in (workgroup-uniform)
+  unsigned off[CN];     // of the dwords that the thread's rows start in (SHORT: of the rows), counted from it
+  unsigned front;       // bytes of those dwords in front of the row
+  int last;             // the last place, counted from them, that 16 bytes of a row's dwords start at
+  int kb;               // byte offset of the thread's chunk within a tile row
   int row_bytes;
 
-  __device__ __forceinline__ void init(const void* base, int64_t nrows, int64_t row_bytes_, int64_t r0) {
+  __device__ __forceinline__ void init(const void* all, int64_t nrows, int64_t row_bytes_, int64_t r0) {
     row_bytes = (int)row_bytes_;
     kb = ((int)threadIdx.x % CPR) * 16;
+    base = reinterpret_cast<const uint8_t*>(all) + r0 * row_bytes_;
+    const unsigned skew = KIND == kRowsByte ? (unsigned)reinterpret_cast<uintptr_t>(base) & 3u : 0u;
+    base -= skew;
+    const unsigned edge_row = (unsigned)(nrows - 1 - r0 < ROWS ? nrows - 1 - r0 : ROWS);
+    // rows past the edge re-read the thread's first row, or the last one if that is past it as well; never stored
+    const unsigned r = threadIdx.x / CPR, first = r < edge_row ? r : edge_row;
+    const unsigned at = first * (unsigned)row_bytes_ + skew;
+    front = KIND == kRowsByte ? at & 3u : 0u;
+    last = (((int)front + row_bytes + 3) & ~3) - 16;
 #pragma unroll
-    for (int j = 0; j < CN; ++j) {
-      int64_t r = r0 + (int)threadIdx.x / CPR + j * STEP;
-      if (r >= nrows) r = nrows - 1;  // rows past the edge re-read the last row; never stored
-      p[j] = reinterpret_cast<const uint8_t*>(base) + r * row_bytes_;
-      sh[j] = KIND == kRowsByte ? (int)(reinterpret_cast<uintptr_t>(p[j]) & 3u) : 0;
-      p[j] -= sh[j];
-    }
+    for (int j = 0; j < CN; ++j) off[j] = at - front + (r + j * STEP <= edge_row ? (unsigned)(j * STEP) * (unsigned)row_bytes_ : 0u);
   }
-  // the last place, counted from p, that 16 bytes of the row's dwords start at
-  __device__ __forceinline__ int last(int j) const { return ((sh[j] + row_bytes + 3) & ~3) - 16; }
   // k0: first byte of the tile within the row
   __device__ __forceinline__ void load(v4i (&c)[CN], int k0) const {
+    const int k = k0 + kb;
 #pragma unroll
     for (int j = 0; j < CN; ++j) {
-      if (SHORT) {
-        c[j] = load_chunk16(p[j], row_bytes, k0 + kb);
-      } else {
-        const int k = k0 + kb, l = last(j);
-        c[j] = *reinterpret_cast<const v4i_any*>(p[j] + (k < l ? k : l));
-      }
+      if (SHORT) c[j] = load_chunk16(base + off[j], row_bytes, k);
+      else c[j] = *reinterpret_cast<const v4i_any*>(base + (off[j] + (unsigned)(k < last ? k : last)));
     }
   }
   // the tile, or with rows at any byte the one after it, reaches the row's end (workgroup-uniform)
@@ -99,11 +103,10 @@ struct AnyStage {
     const int k = k0 + kb;
     if constexpr (SHORT) return fix_chunk16(cur[j], row_bytes, k);
     v4i c = cur[j];
-    const int l = last(j);
-    if (EDGE && k > l) c = moved(c, k - l);
+    if (EDGE && k > last) c = moved(c, k - last);
     if constexpr (KIND == kRowsDword) return c;
     int follow = next[j].x;
-    if (EDGE && k + CPR * 16 > l) follow = moved(next[j], k + CPR * 16 - l).x;
+    if (EDGE && k + CPR * 16 > last) follow = moved(next[j], k + CPR * 16 - last).x;
     // the dword behind the chunk: the first of the next lane's; of the last lane of a row the first of the next tile
     const int lane = (int)threadIdx.x % CPR, w = lane == 0 ? follow : c.x;
     int behind;
@@ -114,10 +117,10 @@ struct AnyStage {
       const int down = __builtin_amdgcn_update_dpp(0, w, 0x117, 0xF, 0xF, true);  // row_shr 7: from seven lanes below
       behind = lane == CPR - 1 ? down : up;
     }
-    c = v4i{(int)__builtin_amdgcn_alignbyte((unsigned)c.y, (unsigned)c.x, (unsigned)sh[j]),
-            (int)__builtin_amdgcn_alignbyte((unsigned)c.z, (unsigned)c.y, (unsigned)sh[j]),
-            (int)__builtin_amdgcn_alignbyte((unsigned)c.w, (unsigned)c.z, (unsigned)sh[j]),
-            (int)__builtin_amdgcn_alignbyte((unsigned)behind, (unsigned)c.w, (unsigned)sh[j])};
+    c = v4i{(int)__builtin_amdgcn_alignbyte((unsigned)c.y, (unsigned)c.x, front),
+            (int)__builtin_amdgcn_alignbyte((unsigned)c.z, (unsigned)c.y, front),
+            (int)__builtin_amdgcn_alignbyte((unsigned)c.w, (unsigned)c.z, front),
+            (int)__builtin_amdgcn_alignbyte((unsigned)behind, (unsigned)c.w, front)};
     if (EDGE) {  // bytes behind the row's end may be the next row's
       auto keep = [](int v, int valid) { return valid >= 4 ? v : valid <= 0 ? 0 : v & (int)((1u << (8 * valid)) - 1u); };
       const int valid = row_bytes - k;
@@ -162,7 +165,7 @@ struct AnyCfg {
   static constexpr int SUMS_OFF = 0;
 };
 template <int TS, bool W4, RowKind KIND, int EPI>
-__global__ __launch_bounds__(AnyCfg<TS>::NT, TS == 64 ? 3 : 2) void qgemm_any(
+__global__ __launch_bounds__(AnyCfg<TS>::NT, TS == 64 ? 4 : 2) void qgemm_any(
     const int8_t* __restrict__ A, const void* __restrict__ Wv, int64_t M, int64_t N, int64_t K,
     const float* __restrict__ a_scale, const float* __restrict__ w_scale, int w_per_row, float* __restrict__ Y,
     int32_t* __restrict__ ACC, EpiArgs epi) {

@@ -1,4 +1,4 @@
-"""What the fast kernels of the quantized layer were compiled to, read from the library that was built here: properties that
+"""What the kernels of the quantized layer were compiled to, read from the library that was built here: properties that
 no result shows and that a change of the source loses easily."""
 import os
 import re
@@ -20,7 +20,7 @@ def _tool(name):
 
 @pytest.fixture(scope="module")
 def code_objects(tmp_path_factory):
-    """The gfx950 code objects with fast kernels, one per translation unit, as files."""
+    """The gfx950 code objects of the library, one per translation unit, as (contents, file)."""
     if not _tool("llvm-readelf") or not _tool("llvm-objdump"):
         pytest.skip("no LLVM tools")
     with open(build.LIB, "rb") as f:
@@ -33,38 +33,48 @@ def code_objects(tmp_path_factory):
             target = data[pos + 24:pos + 24 + name]
             pos += 24 + name
             elf = data[at + offset:at + offset + size]
-            if b"gfx950" in target and (b"qgemm_dma" in elf or b"qgemm_quad" in elf):
+            if b"gfx950" in target:
                 path = tmp_path_factory.mktemp("code") / ("%d.elf" % len(out))
                 path.write_bytes(elf)
-                out.append(str(path))
+                out.append((elf, str(path)))
         at = data.find(MAGIC, at + 1)
-    assert len(out) == 4  # the tiles of 256, 192, 128 and 64
     return out
+
+
+def _metadata(code_objects, kernel):
+    """(name, its metadata) of every kernel whose name contains `kernel`."""
+    for elf, path in code_objects:
+        if kernel.encode() not in elf:
+            continue
+        notes = subprocess.run([_tool("llvm-readelf"), "--notes", path], stdout=subprocess.PIPE, text=True, check=True).stdout
+        for part in notes.split("- .agpr_count:")[1:]:
+            name = re.search(r"^\s+\.name:\s+(\S+)", part, re.M).group(1)
+            if kernel in name:
+                yield name, {k: int(v) for k, v in re.findall(r"^\s+\.(\w+):\s+(\d+)$", part, re.M)}
 
 
 def test_no_register_of_a_fast_kernel_is_spilled(code_objects):
     """A reload waits for every load and store in flight (s_waitcnt vmcnt(0)): at the head of an output tile for the
     stores of the one before it, in the k loop for the prefetch."""
-    kernels, spilled = 0, []
-    for path in code_objects:
-        notes = subprocess.run([_tool("llvm-readelf"), "--notes", path], stdout=subprocess.PIPE, text=True, check=True).stdout
-        for part in notes.split("- .agpr_count:")[1:]:
-            name = re.search(r"^\s+\.name:\s+(\S+)", part, re.M).group(1)
-            if "qgemm" not in name:
-                continue
-            kernels += 1
-            count = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", part).group(1))
-            scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", part).group(1))
-            if count or scratch:
-                spilled.append((name, count, scratch))
-    assert kernels >= 4 * 16 and not spilled, spilled
+    kernels = list(_metadata(code_objects, "qgemm_"))
+    spilled = [n for n, m in kernels if m["vgpr_spill_count"] or m["private_segment_fixed_size"]]
+    assert len(kernels) >= 4 * 16 + 48 and not spilled, spilled
+
+
+def test_four_workgroups_of_the_any_alignment_kernel_share_a_cu(code_objects):
+    """Its 64 tile: four waves a workgroup, a SIMD's 512 registers over four of them."""
+    kernels = list(_metadata(code_objects, "qgemm_anyILi64E"))
+    over = [(n, m["vgpr_count"]) for n, m in kernels if m["vgpr_count"] > 128 or 4 * m["group_segment_fixed_size"] > 160 * 1024]
+    assert len(kernels) == 24 and not over, over
 
 
 def test_the_first_barrier_waits_for_the_first_k_tile_only(code_objects):
     """The kernels request NSTAGE k tiles and wait for the first with a counted vmcnt: a vmcnt(0) between the requests and
     the first barrier, as the compiler puts behind an ordinary load, waits for all of them."""
     kernels, full = 0, []
-    for path in code_objects:
+    for elf, path in code_objects:
+        if b"qgemm_dma" not in elf and b"qgemm_quad" not in elf:
+            continue
         text = subprocess.run([_tool("llvm-objdump"), "-d", "--no-show-raw-insn", "--no-leading-addr", path],
                               stdout=subprocess.PIPE, text=True, check=True).stdout
         for part in re.split(r"^(?=\S*<\S+>:$)", text, flags=re.M):
