@@ -49,6 +49,16 @@ int main() {
       {12288, 768, 1152, 192}, {4093, 1022, 32, 128}, {4093, 1022, 1152, 128}, {1000, 512, 32, 64}, {333, 102, 1152, 64}};
   for (auto& c : sides)
     if (fast_tile(c.M, c.N, c.K, 256).side != c.side) { std::printf("side %d for %lld x %lld x %lld\n", fast_tile(c.M, c.N, c.K, 256).side, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
+  // between half and three quarters of the CUs of 128 tiles the side depends on k; a short k has three stages where a
+  // workgroup has its CU, or half of one, to itself
+  const struct { int64_t M, N, K; int side, stages; } lines[] = {
+      {1408, 2048, 1024, 64, 3}, {1408, 2048, 2560, 128, 3}, {1408, 2048, 3584, 128, 3}, {2944, 1024, 4096, 128, 3}, {2048, 1024, 4096, 64, 3},
+      {24000, 128, 512, 64, 2}, {24000, 128, 1024, 128, 3}, {768, 1024, 512, 64, 2}, {768, 1024, 528, 64, 3}, {768, 1024, 896, 64, 3},
+      {900, 1500, 512, 64, 2}, {900, 1500, 768, 64, 3}, {1408, 1664, 768, 64, 2}};
+  for (auto& c : lines) {
+    const FastTile t = fast_tile(c.M, c.N, c.K, 256);
+    if (t.side != c.side || t.stages != c.stages) { std::printf("%d, %d stages for %lld x %lld x %lld\n", t.side, t.stages, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
+  }
   if (!bad) std::puts("shapes ok");
   return bad;
 }
