@@ -449,6 +449,7 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
 #pragma unroll
     for (int j0 = 0; j0 < C::FN; j0 += G) {
       v4f yref[G];
+      float part = 0.0f;  // the group's squares, summed before they join the lane's running sum: short chains
       if (SCORE && (VEC || N >= 4)) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -488,13 +489,13 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
             if (SCORE) {
               const v4f r = yref[g];
               float d = y.x - r.x;
-              sse = __builtin_fmaf(d, d, sse);
+              part = __builtin_fmaf(d, d, part);
               d = y.y - r.y;
-              sse = __builtin_fmaf(d, d, sse);
+              part = __builtin_fmaf(d, d, part);
               d = y.z - r.z;
-              sse = __builtin_fmaf(d, d, sse);
+              part = __builtin_fmaf(d, d, part);
               d = y.w - r.w;
-              sse = __builtin_fmaf(d, d, sse);
+              part = __builtin_fmaf(d, d, part);
             }
           }
         } else {  // the last group of a row that it does not fill
@@ -513,12 +514,13 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
               if (QOUT && CODES) CODES[m * N + n + e] = (int8_t)(int)code_f(y, q_inv, q_max);
               if (SCORE && YREF) {
                 const float d = y - YREF[m * N + n + e];
-                sse = __builtin_fmaf(d, d, sse);
+                part = __builtin_fmaf(d, d, part);
               }
             }
           }
         }
       }
+      if (SCORE) sse += part;
     }
   }
 }

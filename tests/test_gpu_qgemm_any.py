@@ -68,7 +68,7 @@ def test_rows_at_any_byte(mn, K, wbits, by):
     ref = y + torch.rand_like(y)
     sse, _ = mpq.qgemm_score(qa, qw, sa, sw, ref, wbits, mpq.PER_ROW)
     want = float((y.double() - ref.double()).square().sum())
-    assert abs(float(sse) - want) <= 4e-6 * want  # a lane's 32 squares one after the other, its wave in 6 steps: 38 * 2^-24, twice
+    assert abs(float(sse) - want) <= 4e-6 * want  # a lane's squares by eights, at most four times, its wave in 6 steps, the difference: (8 + 4 + 6 + 2) * 2^-24 = 1.2e-6
 
 
 # one 16 x 16 tile per CU at most, 4 waves (K < 2048) and 8; two per CU; K around the step of 128, fewer
@@ -154,3 +154,18 @@ def test_running_maximum_of_few_tiles(mnk, wbits):
     y, m = mpq.qgemm_act(dev(a), dev(ws), dev(sa), dev(sw), mpq.ACT_RELU, wbits)
     np.testing.assert_array_equal(host(y), want)
     assert host(m)[0] == want.max()
+
+
+@pytest.mark.parametrize("M,N", [(1024, 1024), (2048, 1024)])
+def test_score_of_equal_differences(M, N):
+    """All squares equal, so that the roundings of a running sum pull one way: a chain of n of them is off by up to (n + 1) / 2
+    * 2^-24 of its sum.  A lane of either tile adds them up by eights, four times at most: 4.5 + 2.5 = 7; doubling along the
+    wave is exact.  1.9405739: one chain of 32 is off by 8.5, of 16 by nothing."""
+    import torch
+    a, w = torch.zeros((M, 257), dtype=torch.int8, device="cuda"), torch.zeros((N, 257), dtype=torch.int8, device="cuda")
+    one = torch.ones(1, device="cuda")
+    for d in (1.9405739, 1.382529, 1.8926064, 1.1, 1.7):
+        ref = torch.full((M, N), -d, device="cuda")
+        want = M * N * float(np.float32(d)) ** 2
+        sse, _ = mpq.qgemm_score(a, w, one, one, ref)
+        assert abs(float(sse) - want) <= 7 * 2.0 ** -24 * want, (d, (float(sse) / want - 1) * 2 ** 24)
