@@ -420,6 +420,21 @@ __device__ __forceinline__ v4i expand_half(const v4i& r) {
   return b;
 }
 
+// A group of four n that lies inside the row travels in one access whatever its alignment.  (A type that came
+// through a template argument would have lost its own alignment.)
+template <bool VEC>
+struct Four {  // N % 4 == 0 and 16-byte aligned outputs
+  typedef v4f F;
+  typedef v4i I;
+  typedef unsigned C;
+};
+template <>
+struct Four<false> {
+  typedef f4_any F;
+  typedef v4i_any I;
+  typedef u32_any C;
+};
+
 // What a workgroup does with the accumulators of one output tile (see EpiArgs for EPI).  16x16 accumulator tile
 // (i, j): lane l holds m = l % 16 and the four consecutive n = 4 (l / 16) + 0..3: a store instruction writes 64
 // bytes of each of 16 rows.  (In 32x32 tiles it is 32 bytes of 32 rows: 67 MB stored by one workgroup per CU 14.5 us
@@ -434,10 +449,11 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
   constexpr bool SCORE = EPI == 1, ACT = EPI >= 2, AMAX = EPI == 2, QOUT = EPI == 3;
   int8_t* __restrict__ CODES = epi.codes;
   const float* __restrict__ YREF = epi.yref;
-  // A group of four n that lies inside the row travels in one access whatever its alignment
-  using F4 = std::conditional_t<VEC, v4f, f4_any>;
-  using I4 = std::conditional_t<VEC, v4i, v4i_any>;
-  using C4 = std::conditional_t<VEC, unsigned, u32_any>;
+  using F4 = typename Four<VEC>::F;
+  using I4 = typename Four<VEC>::I;
+  using C4 = typename Four<VEC>::C;
+  static_assert(alignof(F4) == (VEC ? 16 : 4) && alignof(I4) == (VEC ? 16 : 4) && alignof(C4) == (VEC ? 4 : 1),
+                "no access promises more than the address has");
   const int nq = wn * C::TN + (lane >> 4) * 4;  // the lane's first n within the tile
 #pragma unroll
   for (int i = 0; i < C::FM; ++i) {
