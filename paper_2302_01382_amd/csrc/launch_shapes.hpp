@@ -67,4 +67,22 @@ inline FastTile fast_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
   return {64, 3, K >= 2048 && t64 <= num_cu ? 256 : 128};
 }
 
+// Output tiles that a workgroup of the fast kernels works off, along M: the chip holds `slots` workgroups at a time (what
+// the LDS allows per CU), so a launch costs about ceil(grid / slots) * chunk tile times; the length up to 4 that makes
+// this smallest, the longer one on a tie (more tile boundaries without a drain).
+inline int chunk_tiles(int64_t tm, int64_t tn, int split, int lds_bytes, int num_cu) {
+  int per_cu = (160 * 1024) / lds_bytes;
+  if (per_cu > 4) per_cu = 4;
+  if (per_cu < 1) per_cu = 1;
+  const int64_t slots = (int64_t)num_cu * per_cu;
+  int chunk = 1;
+  int64_t best = 0;
+  for (int c = 1; c <= 4; ++c) {
+    const int64_t grid = (tm + c - 1) / c * tn;
+    const int64_t cost = (grid * split + slots - 1) / slots * c;
+    if (c == 1 || cost <= best) { best = cost; chunk = c; }
+  }
+  return chunk;
+}
+
 }  // namespace mpq

@@ -787,19 +787,8 @@ inline int launch_shape(int bm, int bn, int lds_bytes, int64_t M, int64_t N, con
   s.tm = (M + bm - 1) / bm;
   s.tn = (N + bn - 1) / bn;
   if (s.tm * s.tn > 0x7FFFFFFF || s.tn > 0x7FFFFFFF) return MPQ_ERR_SHAPE;
-  // Chunk length: the chip holds `slots` workgroups at a time (what the LDS allows per CU), so a
-  // launch costs about ceil(grid / slots) * chunk tile times; take the length up to 4 that makes
-  // this smallest, the longer one on a tie (more tile boundaries without a drain).
-  int per_cu = (160 * 1024) / lds_bytes;
-  if (per_cu > 4) per_cu = 4;
-  if (per_cu < 1) per_cu = 1;
-  const int64_t slots = kNumCU * per_cu;
-  int64_t best = 0;
-  for (int c = 1; c <= 4; ++c) {
-    const int64_t g = ((s.tm + c - 1) / c) * s.tn;
-    const int64_t cost = ((g * split + slots - 1) / slots) * c;
-    if (c == 1 || cost <= best) { best = cost; s.chunk = c; s.grid = g; }
-  }
+  s.chunk = chunk_tiles(s.tm, s.tn, split, lds_bytes, kNumCU);
+  s.grid = (s.tm + s.chunk - 1) / s.chunk * s.tn;
   s.remap = (s.grid % 8 == 0 && s.grid >= 16) ? 1 : 0;
   return MPQ_OK;
 }

@@ -334,7 +334,7 @@ def test_qgemm_large_tiles_on_sampled_rows(mnk, wbits):
     # cheap global invariant instead: column sums of acc equal (sum of A rows) . W
     colsum = a.astype(np.int64).sum(0) @ w.astype(np.int64).T
     np.testing.assert_array_equal(host(acc).astype(np.int64).sum(0), colsum)
-    # per-channel scales or an output that are only 4-byte aligned take the scalar epilogue: same bits
+    # per-channel scales or an output that are only 4-byte aligned take the epilogue whose accesses are: same bits
     y_s, _ = mpq.qgemm(dev(a), dev(ws), dev(sa), dev_misaligned(sw), wbits, mpq.PER_ROW)
     np.testing.assert_array_equal(host(y_s), host(y))
     y_buf = dev_misaligned(np.zeros((M, N), np.float32))

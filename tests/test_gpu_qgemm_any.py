@@ -102,8 +102,8 @@ def test_layers_of_few_tiles(mnk, wbits, by):
     np.testing.assert_array_equal(host(buf), y_o)
 
 
-# a k of two and of four k tiles takes two LDS stages: 64 x 64 tiles with k tiles of 128 and of 256 bytes, 128 x 128
-# tiles; last tile whole and ragged; the counts on either side take three
+# k tiles around the number of LDS stages, last tile whole and ragged: 64 x 64 tiles in two stages (up to a k of 512, or with
+# more than two tiles per CU) and in three
 @pytest.mark.parametrize("mnk", [(1000, 520, 256), (1000, 520, 224), (1000, 520, 512), (1000, 520, 416), (1000, 520, 128), (1000, 520, 384),
                                  (1000, 520, 640), (1001, 530, 1024), (1001, 530, 1008), (2100, 1030, 256), (2100, 1030, 512),
                                  (2100, 1030, 448)])

@@ -49,6 +49,18 @@ int main() {
       {12288, 768, 1152, 192}, {4093, 1022, 32, 128}, {4093, 1022, 1152, 128}, {1000, 512, 32, 64}, {333, 102, 1152, 64}};
   for (auto& c : sides)
     if (fast_tile(c.M, c.N, c.K, 256).side != c.side) { std::printf("side %d for %lld x %lld x %lld\n", fast_tile(c.M, c.N, c.K, 256).side, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
+  // ... and the output tiles per workgroup: one for the sizes above but the second, several for the tall ones (W in 8 and 4 bits)
+  const struct { int64_t M, N, K; int more8, more4; } chunks[] = {
+      {16381, 1024, 128, 0, 0}, {32700, 1021, 128, 1, 1}, {12288, 768, 128, 0, 0}, {4093, 1022, 128, 0, 0}, {1000, 512, 128, 0, 0},
+      {140001, 128, 32, 1, 1}, {140001, 101, 416, 1, 1}, {70001, 128, 2176, 1, 1}, {200001, 100, 160, 1, 1}, {140001, 61, 32, 1, 1},
+      {140001, 61, 160, 1, 1}, {70001, 61, 1152, 1, 1}};
+  for (auto& c : chunks)
+    for (int w = 8; w >= 4; w -= 4) {
+      const FastTile t = fast_tile(c.M, c.N, c.K, 256);
+      const int lds = t.stages * t.side * (t.kb + t.kb * w / 8) + 2048;
+      const int chunk = chunk_tiles((c.M + t.side - 1) / t.side, (c.N + t.side - 1) / t.side, 1, lds, 256);
+      if (chunk < 1 || chunk > 4 || (chunk > 1) != (w == 8 ? c.more8 : c.more4)) { std::printf("chunk %d of %d tiles for %lld x %lld x %lld\n", chunk, t.side, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
+    }
   // between half and three quarters of the CUs of 128 tiles the side depends on k; a short k has three stages where a
   // workgroup has its CU, or half of one, to itself
   const struct { int64_t M, N, K; int side, stages; } lines[] = {
