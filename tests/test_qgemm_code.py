@@ -88,3 +88,46 @@ def test_the_first_barrier_waits_for_the_first_k_tile_only(code_objects):
             if "0" in waits:
                 full.append(name.group(1))
     assert kernels >= 4 * 16 and not full, full
+
+
+def _instructions(path):
+    """(kernel, its instructions as (address, text, address of the branch's target or None)) of a code object."""
+    text = subprocess.run([_tool("llvm-objdump"), "-d", path], stdout=subprocess.PIPE, text=True, check=True).stdout
+    for part in re.split(r"^(?=[0-9a-f]+ <\S+>:$)", text, flags=re.M):
+        head = re.match(r"([0-9a-f]+) <(\S+)>:$", part, re.M)
+        if not head:
+            continue
+        found = re.findall(r"^\t(.+?)\s*// ([0-9A-F]+):[0-9A-F ]+(?:<\S+?\+0x([0-9a-f]+)>|<\S+>)?$", part, re.M)
+        yield head.group(2), [(int(at, 16), op, int(head.group(1), 16) + int(to, 16) if to else None) for op, at, to in found]
+
+
+def test_the_last_output_tile_is_stored_without_waiting_for_requests(code_objects):
+    """Behind a workgroup's last k tile only zeros are still on their way into the LDS: there is a way from the last matrix
+    step to the epilogue's first access of memory without a vmcnt(0)."""
+    kernels, waiting = 0, []
+    for elf, path in code_objects:
+        if b"qgemm_dma" not in elf:
+            continue
+        for name, code in _instructions(path):
+            if not re.search("qgemm_dma", name):
+                continue
+            kernels += 1
+            index = {at: i for i, (at, _, _) in enumerate(code)}
+            todo, seen, free = [max(i for i, c in enumerate(code) if c[1].startswith("v_mfma"))], set(), False
+            while todo and not free:
+                i = todo.pop()
+                if i in seen or i >= len(code):
+                    continue
+                seen.add(i)
+                _, op, to = code[i]
+                if re.match("global_(store|load_dword)", op):
+                    free = True
+                if re.match(r"s_waitcnt vmcnt\(0\)", op) or op.startswith("s_endpgm"):
+                    continue
+                if to is not None:
+                    todo.append(index[to])
+                if not op.startswith("s_branch"):
+                    todo.append(i + 1)
+            if not free:
+                waiting.append(name)
+    assert kernels >= 3 * 16 and not waiting, waiting
