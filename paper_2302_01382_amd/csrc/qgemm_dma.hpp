@@ -455,88 +455,100 @@ __device__ __forceinline__ void epilogue_act(const v4i (&acc)[C::FM][C::FN], int
   static_assert(alignof(F4) == (VEC ? 16 : 4) && alignof(I4) == (VEC ? 16 : 4) && alignof(C4) == (VEC ? 4 : 1),
                 "no access promises more than the address has");
   const int nq = wn * C::TN + (lane >> 4) * 4;  // the lane's first n within the tile
+  // Score: the loads of four accumulator tiles are in flight together, two rows of them where a row has two (past the edge:
+  // others of the matrix).  us, two in flight | four, operands from memory, M x K x N: 6301 x 128 x 60
+  // 6.8 | 6.3, 5272 x 288 x 72 7.5 | 7.1, 15489 x 160 x 192 10.6 | 10.1, 4737 x 724 x 51 10.3 | 9.7.  (In the aligned
+  // 64 tile the compiler moves two of them behind the first row's arithmetic; held in front of it all are 1-2 % slower.)
+  constexpr int G = C::FN % 4 == 0 ? 4 : 2, GI = 4 / G;
+  static_assert(C::FN % 2 == 0 && C::FM % GI == 0, "groups of four accumulator tiles");
 #pragma unroll
-  for (int i = 0; i < C::FM; ++i) {
-    const int64_t m = cur_m0 + wm * C::TM + i * 16 + (lane & 15);
-    if (m >= M) continue;
-    // Score: the loads of a group of G are in flight together (past the edge: others of the row).
-    constexpr int G = C::FN % 4 == 0 ? 4 : 2;
-    static_assert(C::FN % 2 == 0, "pairs of column tiles");
+  for (int i0 = 0; i0 < C::FM; i0 += GI) {
 #pragma unroll
     for (int j0 = 0; j0 < C::FN; j0 += G) {
-      v4f yref[G];
-      float part = 0.0f;  // the group's squares, summed before they join the lane's running sum: short chains
+      v4f yref[GI][G];
       if (SCORE && (VEC || N >= 4)) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int64_t n = cur_n0 + nq + (j0 + g) * 16;
-          yref[g] = *reinterpret_cast<const F4*>(YREF + m * N + (n + 4 <= N ? n : 0));
+        for (int h = 0; h < GI; ++h) {
+          const int64_t m = cur_m0 + wm * C::TM + (i0 + h) * 16 + (lane & 15);
+          const float* row = YREF + (m < M ? m : cur_m0) * N;
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int64_t n = cur_n0 + nq + (j0 + g) * 16;
+            yref[h][g] = *reinterpret_cast<const F4*>(row + (n + 4 <= N ? n : 0));
+          }
         }
       }
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int j = j0 + g;
-        const int64_t n = cur_n0 + nq + j * 16;
-        if (n >= N) continue;
-        int a[4];
+      for (int h = 0; h < GI; ++h) {
+        const int i = i0 + h;
+        const int64_t m = cur_m0 + wm * C::TM + i * 16 + (lane & 15);
+        if (m >= M) continue;
+        float part = 0.0f;  // the row's squares of the group, summed before they join the lane's running sum: short chains
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          a[e] = acc[i][j][e];
-          if (W4) a[e] >>= 4;  // exact: every product carried the factor 16
-        }
-        const float4 sw = *reinterpret_cast<const float4*>(scales + (nq + j * 16) * 4);
-        if (VEC || n + 4 <= N) {  // VEC: N % 4 == 0 and 16-byte aligned outputs
-          if (EPI == 0 && ACC) *reinterpret_cast<I4*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
-          if (want_y) {
-            float4 y = make_float4(((float)a[0] * sa) * sw.x, ((float)a[1] * sa) * sw.y,
-                                   ((float)a[2] * sa) * sw.z, ((float)a[3] * sa) * sw.w);
-            if (ACT) {
-              y = apply_act4(y, ACT_KIND);
-              if (AMAX) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
-            }
-            if (!QOUT && Y) *reinterpret_cast<F4*>(Y + m * N + n) = v4f{y.x, y.y, y.z, y.w};
-            if (QOUT && CODES) {  // four codes, lowest n in the lowest byte
-              const unsigned c0 = (unsigned)(int)code_f(y.x, q_inv, q_max) & 0xFFu;
-              const unsigned c1 = (unsigned)(int)code_f(y.y, q_inv, q_max) & 0xFFu;
-              const unsigned c2 = (unsigned)(int)code_f(y.z, q_inv, q_max) & 0xFFu;
-              const unsigned c3 = (unsigned)(int)code_f(y.w, q_inv, q_max);
-              *reinterpret_cast<C4*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-            }
-            if (SCORE) {
-              const v4f r = yref[g];
-              float d = y.x - r.x;
-              part = __builtin_fmaf(d, d, part);
-              d = y.y - r.y;
-              part = __builtin_fmaf(d, d, part);
-              d = y.z - r.z;
-              part = __builtin_fmaf(d, d, part);
-              d = y.w - r.w;
-              part = __builtin_fmaf(d, d, part);
-            }
-          }
-        } else {  // the last group of a row that it does not fill
-          const float s4[4] = {sw.x, sw.y, sw.z, sw.w};
+        for (int g = 0; g < G; ++g) {
+          const int j = j0 + g;
+          const int64_t n = cur_n0 + nq + j * 16;
+          if (n >= N) continue;
+          int a[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            if (n + e >= N) break;
-            if (EPI == 0 && ACC) ACC[m * N + n + e] = a[e];
+            a[e] = acc[i][j][e];
+            if (W4) a[e] >>= 4;  // exact: every product carried the factor 16
+          }
+          const float4 sw = *reinterpret_cast<const float4*>(scales + (nq + j * 16) * 4);
+          if (VEC || n + 4 <= N) {  // VEC: N % 4 == 0 and 16-byte aligned outputs
+            if (EPI == 0 && ACC) *reinterpret_cast<I4*>(ACC + m * N + n) = v4i{a[0], a[1], a[2], a[3]};
             if (want_y) {
-              float y = ((float)a[e] * sa) * s4[e];
+              float4 y = make_float4(((float)a[0] * sa) * sw.x, ((float)a[1] * sa) * sw.y,
+                                     ((float)a[2] * sa) * sw.z, ((float)a[3] * sa) * sw.w);
               if (ACT) {
-                y = apply_act(y, ACT_KIND);
-                if (AMAX) amax = fmaxf(amax, fabsf(y));
+                y = apply_act4(y, ACT_KIND);
+                if (AMAX) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
               }
-              if (!QOUT && Y) Y[m * N + n + e] = y;
-              if (QOUT && CODES) CODES[m * N + n + e] = (int8_t)(int)code_f(y, q_inv, q_max);
-              if (SCORE && YREF) {
-                const float d = y - YREF[m * N + n + e];
+              if (!QOUT && Y) *reinterpret_cast<F4*>(Y + m * N + n) = v4f{y.x, y.y, y.z, y.w};
+              if (QOUT && CODES) {  // four codes, lowest n in the lowest byte
+                const unsigned c0 = (unsigned)(int)code_f(y.x, q_inv, q_max) & 0xFFu;
+                const unsigned c1 = (unsigned)(int)code_f(y.y, q_inv, q_max) & 0xFFu;
+                const unsigned c2 = (unsigned)(int)code_f(y.z, q_inv, q_max) & 0xFFu;
+                const unsigned c3 = (unsigned)(int)code_f(y.w, q_inv, q_max);
+                *reinterpret_cast<C4*>(CODES + m * N + n) = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
+              }
+              if (SCORE) {
+                const v4f r = yref[h][g];
+                float d = y.x - r.x;
+                part = __builtin_fmaf(d, d, part);
+                d = y.y - r.y;
+                part = __builtin_fmaf(d, d, part);
+                d = y.z - r.z;
+                part = __builtin_fmaf(d, d, part);
+                d = y.w - r.w;
                 part = __builtin_fmaf(d, d, part);
               }
             }
+          } else {  // the last group of a row that it does not fill
+            const float s4[4] = {sw.x, sw.y, sw.z, sw.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if (n + e >= N) break;
+              if (EPI == 0 && ACC) ACC[m * N + n + e] = a[e];
+              if (want_y) {
+                float y = ((float)a[e] * sa) * s4[e];
+                if (ACT) {
+                  y = apply_act(y, ACT_KIND);
+                  if (AMAX) amax = fmaxf(amax, fabsf(y));
+                }
+                if (!QOUT && Y) Y[m * N + n + e] = y;
+                if (QOUT && CODES) CODES[m * N + n + e] = (int8_t)(int)code_f(y, q_inv, q_max);
+                if (SCORE && YREF) {
+                  const float d = y - YREF[m * N + n + e];
+                  part = __builtin_fmaf(d, d, part);
+                }
+              }
+            }
           }
         }
+        if (SCORE) sse += part;
       }
-      if (SCORE) sse += part;
     }
   }
 }

@@ -131,3 +131,26 @@ def test_the_last_output_tile_is_stored_without_waiting_for_requests(code_object
             if not free:
                 waiting.append(name)
     assert kernels >= 3 * 16 and not waiting, waiting
+
+
+def test_the_score_has_four_loads_of_the_reference_in_flight(code_objects):
+    """The epilogue that scores reads the reference output from memory: 16 bytes of four accumulator tiles at a time."""
+    kernels, few = 0, []
+    for elf, path in code_objects:
+        if b"qgemm_dma" not in elf and b"qgemm_quad" not in elf:
+            continue
+        for name, code in _instructions(path):
+            tile = re.search(r"qgemm_(?:dmaILi(\d+)|quad)\w+?Lb\dELb(\d)E(?:Li\d+ELi\d+E)?Li1EEEvPKa", name)
+            if not tile or tile.groups() == ("64", "1"):  # (there the compiler moves two behind the first row's arithmetic)
+                continue
+            kernels += 1
+            most = now = 0
+            for _, op, _ in code:
+                if op.startswith("global_load_dwordx4"):
+                    now += 1
+                    most = max(most, now)
+                elif "vmcnt" in op:
+                    now = 0
+            if most < 4:
+                few.append((name, most))
+    assert kernels >= 2 * 2 * 6 and not few, few
