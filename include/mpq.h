@@ -420,8 +420,8 @@ int mpq_latency_estimate(const double* layer_us, int n_layers, int n_widths, con
 int mpq_model_size_bytes(const int64_t* parameters, const int* bits, int n_layers, double* bytes_out);
 
 /* ---- measurement aid (not part of the method) --------------------------------------------------
- * Launches a kernel that does nothing but issue int8 matrix-core instructions (one workgroup of
- * eight waves per CU, 16 x iters instructions per wave) on operand registers filled once from
+ * Launches a kernel that does nothing but issue the int8 matrix instructions of the GEMM kernels (16x16x64; one
+ * workgroup of eight waves per CU, 32 x iters instructions per wave) on operand registers filled once from
  * `operands` (device, 16-byte aligned, at least mpq_diag_mfma_operand_bytes() bytes).  Timing it
  * gives the matrix rate this chip sustains for operands of that kind: the clock under matrix load
  * depends on how much the operand bits toggle.  ops_out (host, nullable) receives the number of

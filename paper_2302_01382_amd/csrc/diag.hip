@@ -1,10 +1,9 @@
 // diag.hip -- measurement aids, not part of the method.
-// (1) The rate at which this chip issues
-// v_mfma_i32_32x32x32_i8 when nothing else happens (operands sit in registers, no memory traffic
-// inside the loop).  The sustained clock under matrix load depends on how much the operand bits
-// toggle, so the "matrix peak" a GEMM can be held against is this measured rate on operands like
-// its own, not the nominal 5 POP/s: on MI355X about 4.9 POP/s for constant bytes and about
-// 3.3 POP/s for uniformly random int8.
+// (1) The rate at which this chip issues v_mfma_i32_16x16x64_i8, the matrix step of the GEMM kernels, when nothing
+// else happens (operands sit in registers, no memory traffic inside the loop).  The sustained clock under matrix
+// load depends on how much the operand bits toggle, so the "matrix peak" a GEMM can be held against is this
+// measured rate on operands like its own, not the nominal 5 POP/s: on MI355X about 4.4 POP/s for constant bytes
+// and about 3.6 POP/s for uniformly random int8 (steps of 32x32x32, which draw more power on random bytes: 4.9 and 3.3).
 // (2) The rate at which it works off the arithmetic of the error sweep (sweep.hpp, b = 2..8) when the
 // elements sit in registers: the vector-ALU ceiling of that kernel, measured instead of derived.
 #include "common.hpp"
@@ -13,11 +12,10 @@
 namespace mpq {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kBurnWaves = 8;  // per workgroup, one workgroup per CU: two waves per SIMD, like the GEMM
 
-// every lane reads 8 x 16 bytes of operands once, then 16 matrix steps per iteration on them
+// every lane reads 8 x 16 bytes of operands once, then 32 matrix steps per iteration on them, 16 of them independent
 __global__ __launch_bounds__(kBurnWaves * 64) void mfma_burn(const v4i* __restrict__ src, int iters,
                                                              int* __restrict__ sink) {
   const size_t base = ((size_t)blockIdx.x * (kBurnWaves * 64) + threadIdx.x) * 8;
@@ -27,23 +25,21 @@ __global__ __launch_bounds__(kBurnWaves * 64) void mfma_burn(const v4i* __restri
     a[i] = src[base + i];
     b[i] = src[base + 4 + i];
   }
-  v16i acc[4];
+  v4i acc[16];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][v] = 0;
+  for (int i = 0; i < 16; ++i) acc[i] = v4i{0, 0, 0, 0};
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], b[(i + j) & 3], acc[i], 0, 0, 0);
+      for (int i = 0; i < 16; ++i)
+        acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i & 3], b[((i >> 2) + (i & 3) + h) & 3], acc[i], 0, 0, 0);
   }
   int s = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 16; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s += acc[i][v];
+    for (int v = 0; v < 4; ++v) s += acc[i][v];
   if (s == 0x7fffffff) sink[0] = s;  // keeps the loop alive; practically never taken
 }
 
@@ -86,7 +82,7 @@ extern "C" int mpq_diag_mfma_rate(const void* operands, size_t operand_bytes, in
   if (!aligned16(operands)) return MPQ_ERR_ALIGN;
   if (iters <= 0 || iters > (1 << 20)) return MPQ_ERR_SHAPE;
   mfma_burn<<<kNumCU, kBurnWaves * 64, 0, (hipStream_t)stream>>>(reinterpret_cast<const v4i*>(operands), iters, sink);
-  if (ops_out) *ops_out = (double)kNumCU * kBurnWaves * (double)iters * 16.0 * 2.0 * 32 * 32 * 32;
+  if (ops_out) *ops_out = (double)kNumCU * kBurnWaves * (double)iters * 32.0 * 2.0 * 16 * 16 * 64;
   return launch_status();
 }
 

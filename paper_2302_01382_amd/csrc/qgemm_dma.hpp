@@ -12,7 +12,6 @@
 namespace mpq {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 // the same in memory at any address an element may have
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -134,13 +133,13 @@ __device__ __forceinline__ v4i fix_chunk16(const v4i& c, int row_bytes, int k) {
 // 16 addresses are distinct modulo 256 B.  The MFMA operand reads apply the same XOR.  Chunks
 // beyond K are fetched from a 16-byte block of zeros.
 //
-// A k tile is requested NSTAGE - 1 tiles ahead of the MFMAs that use it; a wave waits only for
-// its own share of the tile it needs next (s_waitcnt vmcnt) and then meets the others at the one
-// barrier per k tile (two in qgemm_quad.hpp, which takes the 256 x 256 tile).
+// A k tile is requested NSTAGE tiles ahead of the MFMAs that use it, once the stage it goes to has been read for the last
+// time; a wave waits only for its own share of the tile it needs next (s_waitcnt vmcnt) and then meets the others at the
+// one barrier per k tile (two in qgemm_quad.hpp, which takes the 256 x 256 tile).
 //
 // What bounds this path: a k tile costs a CU more than either of its halves alone.  On random operands the matrix
-// cores sustain 4.0-4.15 POP/s in steps of 16x16x64 (3.4-3.6 in steps of 32x32x32, which draw more power; constant
-// bytes 4.8 and 5.0), so a 128 x 128 x 128 tile is 0.26 us of matrix work on its CU; its 32 KiB come out of the L2 in
+// cores sustain 3.6 POP/s in steps of 16x16x64 (3.3 in steps of 32x32x32, which draw more power; constant
+// bytes 4.4 and 4.9), so a 128 x 128 x 128 tile is 0.30 us of matrix work on its CU; its 32 KiB come out of the L2 in
 // 0.26 us (8 ns per wave-load; 12.5 if a row's share were 64 bytes), its operand reads out of the LDS in 0.19 us, and it
 // takes 0.48 us at a clock that falls to 1.8 GHz.  Two to four stages, four or eight waves, k tiles of 128 or 256, two
 // barriers per tile instead of one: all within 10 % of each other (4096 x 1024 x 4096, 22.5-25 us).

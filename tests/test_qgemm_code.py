@@ -154,3 +154,16 @@ def test_the_score_has_four_loads_of_the_reference_in_flight(code_objects):
             if most < 4:
                 few.append((name, most))
     assert kernels >= 2 * 2 * 6 and not few, few
+
+
+def test_the_measured_matrix_rate_is_that_of_the_kernels_own_steps(code_objects):
+    """mpq_diag_mfma_rate is what a GEMM is held against: it issues the matrix instruction that the GEMM kernels issue."""
+    steps = {}
+    for elf, path in code_objects:
+        if b"mfma_burn" not in elf and b"qgemm_" not in elf:
+            continue
+        for name, code in _instructions(path):
+            kind = re.search("mfma_burn|qgemm_(?:dma|quad|any)", name)
+            if kind:
+                steps.setdefault(kind.group(0), set()).update(op.split()[0] for _, op, _ in code if op.startswith("v_mfma"))
+    assert len(steps) == 4 and set.union(*steps.values()) == steps["qgemm_quad"] == steps["mfma_burn"], steps
