@@ -530,8 +530,8 @@ def _timed_calls(torch, calls, reps):
 # HBM traffic per launch of mpq_qgemm on cfg5.ffn2 (16384 x 4096 x 1024), bytes, from the counter runs
 # summarised in profiles/cfg5_ffn2_qgemm_hbm_traffic.txt: (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000) KiB
 TRAFFIC_BYTES_PER_LAUNCH_GEMM = {
-    ("cfg5.ffn2", 8): (49275.3 * 2.0 + 67481.8) * 1024.0,
-    ("cfg5.ffn2", 4): (41118.6 * 2.0 + 66957.9) * 1024.0,
+    ("cfg5.ffn2", 8): (49288.7 * 2.0 + 66472.4) * 1024.0,
+    ("cfg5.ffn2", 4): (41112.5 * 2.0 + 68386.2) * 1024.0,
 }
 
 # HBM traffic per launch of the batched sweep kernels over configuration 4, bytes, from the rocprofv3
