@@ -50,7 +50,9 @@ inline int any_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
 // 43.9), two where it is short or workgroups share the CU.  64 tiles, warm / cold, 3 | 2: 768 x 1024 x 384 4.5 / 5.3 | 4.4 / 5.6,
 // x 768 5.2 / 6.5 | 5.2 / 7.8; two per CU 900 x 1500 x 512 5.8 / 7.1 | 5.6 / 7.3, x 768 6.3 / 8.1 | 6.3 / 8.8; more 1408 x 1664 x 768
 // 8.5 / 10.8 | 8.2 / 10.6.  With a long k and a CU each the 64 tile takes k tiles of 256 (768 x 1024 x 2048 7.4 / 9.4 against
-// 7.3 / 10.2 us).
+// 7.3 / 10.2 us); up to a workgroup per two CUs a medium k does as well where it pads no half of one (warm / cold, 256 | 128, with
+// the score: 48 x 2304 x 1440 8.6 / 10.3 | 8.9 / 11.0, 512 x 1024 x 1792 9.8 / 11.7 | 9.7 / 12.2; by kind and size a K of 1152 or 1280
+// 0-7 % slower in 256, and with a CU each 900 x 1024 x 1440 6.9 / 7.9 | 6.6 / 8.6).
 struct FastTile {
   int side, stages, kb;
 };
@@ -64,7 +66,8 @@ inline FastTile fast_tile(int64_t M, int64_t N, int64_t K, int num_cu) {
   const bool long_k = K >= (N <= 128 ? 1024 : 2560) && t128 >= num_cu / 2 && t64 > 2 * num_cu;
   if (N > 64 && (t128 >= most || long_k)) return {128, K >= 2048 || (t128 <= num_cu && K > 512) ? 3 : 2, 128};
   if (K < 1024) return {64, K > 512 && t64 <= 2 * num_cu ? 3 : 2, 128};
-  return {64, 3, K >= 2048 && t64 <= num_cu ? 256 : 128};
+  const bool wide_k = K >= 2048 ? t64 <= num_cu : K > 1280 && (K + 127) / 128 % 2 == 0 && t64 <= num_cu / 2;
+  return {64, 3, wide_k ? 256 : 128};
 }
 
 // Output tiles that a workgroup of the fast kernels works off, along M: the chip holds `slots` workgroups at a time (what

@@ -71,6 +71,12 @@ int main() {
     const FastTile t = fast_tile(c.M, c.N, c.K, 256);
     if (t.side != c.side || t.stages != c.stages) { std::printf("%d, %d stages for %lld x %lld x %lld\n", t.side, t.stages, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
   }
+  // k tiles of 256 in the 64 tile: a long k with a CU per workgroup, a medium one that pads no half of them with two CUs
+  const struct { int64_t M, N, K; int kb; } wide[] = {
+      {48, 2304, 1280, 128}, {48, 2304, 1296, 128}, {48, 2304, 1440, 256}, {48, 2304, 1600, 128}, {512, 1024, 1792, 256},
+      {520, 1024, 1792, 128}, {48, 2304, 2032, 256}, {768, 1024, 2032, 128}, {768, 1024, 2048, 256}, {1025, 1024, 2048, 128}};
+  for (auto& c : wide)
+    if (fast_tile(c.M, c.N, c.K, 256).kb != c.kb) { std::printf("k tiles of %d for %lld x %lld x %lld\n", fast_tile(c.M, c.N, c.K, 256).kb, (long long)c.M, (long long)c.N, (long long)c.K); bad = 1; }
   if (!bad) std::puts("shapes ok");
   return bad;
 }
