@@ -20,7 +20,8 @@
 // the matrix steps alone are 1.05-1.17; at 2.0 GHz 2900 clocks passed for 2048 of matrix steps when it took 1.43.  Then,
 // without its requests it took 1.05, without its LDS reads 1.33, without barriers and waits 1.33: the loads into the
 // LDS, and the power they take, are what is left, and where in the k tile they are issued makes no difference (spread,
-// bunched, the two waves of a SIMD apart).  An output tile costs 12-13 us besides: its 256 KiB at the memory's rate.
+// bunched, the two waves of a SIMD apart).  A further output tile costs 10 us besides (the same
+// k tiles as four output tiles per workgroup, 16384 x 1024 x 4096, 91.0 us against 61.6): its 256 KiB at the memory's rate.
 // Against a barrier per k tile, a whole stage freed at once and 32x32 matrix steps: 16384 x 4096 x 1024 67.8 -> 57.9 us
 // (packed weights 71.2 -> 60.5), 4096 x 4096 x 4096 67.5 -> 58.2, 16384 x 1024 x 4096 100.4 -> 91.3 (99.0 -> 87.3).
 #pragma once
